@@ -205,10 +205,29 @@ static Dims make_dims(const arckv_problem *p, int t) {
   return d;
 }
 
-// Capacity of the assignment's candidate pool, per cached key of a pair (about 1
-// candidate per key at the 32K workload; a key whose list does not fit keeps its
-// first-pass decision and is counted as undecided).
-constexpr int64_t kPoolPerKey = 8;
+// Candidates per cached key, on average, that the assignment's pool can hold.
+// The pool and every list of the later passes live in E^T's place, which is
+// dead once the contraction has left its partials, so the pool is sized by
+// what E^T leaves free: per key 4 + 8 bytes for each candidate, and
+// kPassDEntryBytes for each entry of the float64 pass (one per key and one
+// per kPassDSplit candidates); 36 for the smallest E^T row (256 fp16 values).
+// A key whose list does not fit is decided in float64 over all t anchors,
+// n t float64 exponentials where a pooled candidate costs n fp32 products: on
+// 32K-token caches a pair with 320K-750K candidates (10-23 per key; keys whose
+// similarities all sit within the first pass's absolute error list whole
+// anchor tiles) overflowed a pool of 8 per key, and the float64 pass took
+// 294-1107 ms of a 256-pair call instead of 7.
+constexpr int64_t kPoolPerKeyMax = 256;
+constexpr int64_t kPassDEntryBytes = 36;   // dkey, dn, doff, dgrp, dgn, dr, ditem (4 each), dsim (8)
+
+static int64_t pool_per_key(const Dims &d) {
+  // 64 bytes per key are left for the entries' rounding and alignment
+  const int64_t room = d.np_ * d.esz - kPassDEntryBytes - 64;
+  const int64_t k = room * kPassDSplit / (12 * kPassDSplit + kPassDEntryBytes);
+  const int64_t cap = ((1ll << 30) / d.Tp) > 8 ? (1ll << 30) / d.Tp : 8;   // pool offsets are int32
+  const int64_t m = k < kPoolPerKeyMax ? k : kPoolPerKeyMax;
+  return m < cap ? m : cap;
+}
 
 struct Bump {
   int64_t off = 0;
@@ -260,6 +279,23 @@ static Plan make_plan(const Dims &d, int64_t P) {
   const int64_t phase0 = c.off;
   Bump m = c;
   pl.Et = m.take(P * d.Tp * d.np_ * d.esz);
+  // the lists of the passes after the contraction, in E^T's place
+  {
+    Bump l;
+    l.off = pl.Et;
+    const int64_t ppk = pool_per_key(d), dcap = pass_d_capacity(d.Tp, ppk);
+    pl.psim = l.take(P * ppk * d.Tp * 8);
+    pl.dsim = l.take(P * dcap * 8);
+    pl.pool = l.take(P * ppk * d.Tp * 4);
+    pl.dkey = l.take(P * dcap * 4);
+    pl.dn = l.take(P * dcap * 4);
+    pl.doff = l.take(P * dcap * 4);
+    pl.dgrp = l.take(P * dcap * 4);
+    pl.dgn = l.take(P * dcap * 4);
+    pl.dr = l.take(P * dcap * 4);
+    pl.ditem = l.take(P * (dcap + 2) * 4);
+    if (l.off > m.off) m.off = l.off;   // never with the rule of pool_per_key; keeps the plan safe
+  }
   pl.U = m.take(P * d.tp * d.np_ * d.esz);
   pl.Ua = m.take(P * d.tp * d.np_ * 4);       // precise anchor profiles (fp32)
   pl.anorm = m.take(P * d.tp * 8);
@@ -272,19 +308,8 @@ static Plan make_plan(const Dims &d, int64_t P) {
   pl.foff = m.take(P * d.Tp * 4);
   pl.fn = m.take(P * d.Tp * 4);
   pl.pcnt = m.take(P * 4);
-  pl.pool = m.take(P * kPoolPerKey * d.Tp * 4);   // candidate pool: kPoolPerKey entries per key on average
-  pl.psim = m.take(P * kPoolPerKey * d.Tp * 8);
   pl.dcnt = m.take(P * 4);
-  const int64_t dcap = pass_d_capacity(d.Tp, kPoolPerKey);
-  pl.dkey = m.take(P * dcap * 4);
-  pl.dn = m.take(P * dcap * 4);
-  pl.doff = m.take(P * dcap * 4);
   pl.goff = m.take(P * (d.Tp / 64 + 2) * 4);   // pass C work items per group of 64 queued keys
-  pl.dgrp = m.take(P * dcap * 4);
-  pl.dgn = m.take(P * dcap * 4);
-  pl.dsim = m.take(P * dcap * 8);
-  pl.dr = m.take(P * dcap * 4);
-  pl.ditem = m.take(P * (dcap + 2) * 4);
   pl.offsets = m.take(P * (int64_t)(d.t + 1) * 4);
   pl.cursor = m.take(P * (int64_t)d.t * 4);
   pl.perm = m.take(P * (int64_t)d.T * 4);
@@ -421,14 +446,15 @@ static arckv_status run_merge_chunk(const Ctx &c, int b0, int P, const void *K, 
   void *pn = c.chunk<char>(c.pl.pn);
   uint64_t *part1 = c.chunk<uint64_t>(c.pl.part1), *part2 = c.chunk<uint64_t>(c.pl.part2);
   uint32_t *part3 = c.chunk<uint32_t>(c.pl.part3);
+  const int64_t ppk = pool_per_key(d);
   AssignLists L{c.chunk<int32_t>(c.pl.fcnt), c.chunk<int32_t>(c.pl.fkey),  c.chunk<int32_t>(c.pl.foff),
                 c.chunk<int32_t>(c.pl.fn),   c.chunk<int32_t>(c.pl.pcnt),  c.chunk<int32_t>(c.pl.pool),
-                c.chunk<double>(c.pl.psim),  kPoolPerKey * d.Tp,           c.chunk<int32_t>(c.pl.dcnt),
+                c.chunk<double>(c.pl.psim),  ppk * d.Tp,                   c.chunk<int32_t>(c.pl.dcnt),
                 c.chunk<int32_t>(c.pl.dkey), c.chunk<int32_t>(c.pl.dn),    c.chunk<int32_t>(c.pl.doff),
                 c.pers<int32_t>(c.pl.astats) + (size_t)b0 * kAssignStats, d.Tp,
                 c.chunk<int32_t>(c.pl.goff), d.Tp / 64 + 2,
                 c.chunk<int32_t>(c.pl.dgrp), c.chunk<int32_t>(c.pl.dgn), c.chunk<double>(c.pl.dsim),
-                c.chunk<int32_t>(c.pl.dr),   c.chunk<int32_t>(c.pl.ditem), pass_d_capacity(d.Tp, kPoolPerKey)};
+                c.chunk<int32_t>(c.pl.dr),   c.chunk<int32_t>(c.pl.ditem), pass_d_capacity(d.Tp, ppk)};
   const float *zm = zmax + b0;
   int32_t *kap = kappa + (size_t)b0 * d.T;
   const float *phib = phi + (size_t)b0 * d.T;

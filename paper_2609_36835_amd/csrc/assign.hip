@@ -426,7 +426,7 @@ __global__ void __launch_bounds__(256) k_assign_finalize(
     return;
   }
   const int off = atomicAdd(&L.pcnt[b], nc);
-  if ((int64_t)off + nc > L.pcap) {   // pool full (near-equal profiles): decided in float64 over all t anchors
+  if (off < 0 || (int64_t)off + nc > L.pcap) {   // pool full (near-equal profiles): decided in float64 over all t anchors
     push_d(L, b, j, -1, t);
     return;
   }
@@ -750,33 +750,57 @@ __global__ void __launch_bounds__(256) k_refine_plan(AssignLists L, int cap_c) {
   if (tid == 0) goff[G] = carry;
 }
 
-// Pass C decision, one thread per queued key, once every chunk of its
+// Pass C decision, one wave per queued key, once every chunk of its
 // candidates has its similarity: the best one (equal ones to the lower r)
 // becomes the key's anchor for now, the candidates within the bound of it
-// survive, compacted in place at the front of the key's pool segment, and a
-// key with more than one survivor goes to pass D.
+// survive, compacted in place and in order at the front of the key's pool
+// segment, and a key with more than one survivor goes to pass D.  A wave and
+// not a thread: a key with whole anchor tiles has up to t candidates, which
+// one thread read one dependent load at a time (77 us against 8 for 8 pairs of
+// T = 15,001, t = 1500).
 template <typename E>
 __global__ void __launch_bounds__(256) k_assign_decide(const E *__restrict__ K, const float *__restrict__ zmerge,
                                                        const AssignPair *__restrict__ pn, int T, double s,
                                                        int32_t *__restrict__ kappa, AssignLists L) {
   constexpr bool BF = sizeof(E) == 2;
-  const int b = blockIdx.y;
+  const int b = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int F = L.fcnt[b];
   const AssignPair pp = pn[b];
   const double zm = (double)zmerge[b];
   int32_t *pool = L.pool + (size_t)b * L.pcap;
   const double *psim = L.psim + (size_t)b * L.pcap;
-  for (int f = blockIdx.x * 256 + threadIdx.x; f < F; f += gridDim.x * 256) {
+  for (int f = blockIdx.x * 4 + wave; f < F; f += gridDim.x * 4) {   // uniform over the wave
     const size_t q = (size_t)b * L.cap + f;
     const int j = L.fkey[q], o = L.foff[q], m = L.fn[q];
     if (m <= 0) continue;
-    int best = 0;
-    for (int c = 1; c < m; ++c)
-      if (psim[o + c] > psim[o + best] || (psim[o + c] == psim[o + best] && pool[o + c] < pool[o + best]))
-        best = c;
+    double bs = -INFINITY;
+    int br = 0x7FFFFFFF;
+    for (int c = lane; c < m; c += 64) {
+      const double v = psim[o + c];
+      const int r = pool[o + c];
+      if (v > bs || (v == bs && r < br)) {
+        bs = v;
+        br = r;
+      }
+    }
+#pragma unroll
+    for (int w = 32; w >= 1; w >>= 1) {
+      const double ov = __shfl_xor(bs, w, 64);
+      const int orr = __shfl_xor(br, w, 64);
+      if (ov > bs || (ov == bs && orr < br)) {
+        bs = ov;
+        br = orr;
+      }
+    }
+    if (br == 0x7FFFFFFF) {   // no comparable similarity (non-finite input): the first candidate stands
+      if (lane == 0) kappa[(size_t)b * T + j] = pool[o];
+      continue;
+    }
     double eta;
     if constexpr (BF) {
-      const double kn = row_norm(K + ((size_t)b * T + j) * kHeadDim);
+      const E *kr = K + ((size_t)b * T + j) * kHeadDim + 2 * lane;   // the row's norm, two elements per lane
+      const double k0 = (double)(float)kr[0], k1 = (double)(float)kr[1];
+      const double kn = sqrt(wave_sum(fma(k0, k0, k1 * k1))) * (1.0 + 1e-12);
       const double g = gamma_m(kSliceTerms) * s * pp.qmax, Z = fabs(zm) * 1.4426950408889634;
       const double ek = g * kn + exp32_err(s * pp.qmax * kn * 1.4426950408889634 * 1.001, Z);
       const double ea = g * pp.amax + exp32_err(s * pp.qmax * pp.amax * 1.4426950408889634 * 1.001, Z);
@@ -784,14 +808,20 @@ __global__ void __launch_bounds__(256) k_assign_decide(const E *__restrict__ K, 
     } else {
       eta = 3.0 * kU32 + gamma_m(4) + 1e-12;
     }
-    const double bs = psim[o + best];
     const double thc = bs * (1.0 - eta) / (1.0 + eta) - 1e-300;
-    kappa[(size_t)b * T + j] = pool[o + best];
-    // writes trail reads: this thread alone owns the key's pool segment
+    if (lane == 0) kappa[(size_t)b * T + j] = br;
+    // writes trail reads: this wave alone owns the key's pool segment, and a
+    // round's 64 candidates are read before its survivors are written
     int ns = 0;
-    for (int c = 0; c < m; ++c)
-      if (psim[o + c] >= thc) pool[o + ns++] = pool[o + c];
-    if (ns > 1) push_d(L, b, j, o, ns);
+    for (int c0 = 0; c0 < m; c0 += 64) {
+      const int c = c0 + lane;
+      const bool keep = c < m && psim[o + c] >= thc;
+      const int r = keep ? pool[o + c] : 0;
+      const uint64_t mask = __ballot(keep);
+      if (keep) pool[o + ns + __popcll(mask & ((1ull << lane) - 1ull))] = r;
+      ns += __popcll(mask);
+    }
+    if (ns > 1 && lane == 0) push_d(L, b, j, o, ns);
   }
 }
 
@@ -1136,7 +1166,7 @@ hipError_t launch_assign_refine(int dtype, const void *Q, const void *K, const f
   if (T - t <= 0) return hipSuccess;
   const bool bf = dtype == ARCKV_BF16;
   hipLaunchKernelGGL(k_refine_plan, dim3(P), dim3(256), 0, s, L, 8 * kRefineCpw);
-  const dim3 g(kRefineBlocks, P), gd(8, P);
+  const dim3 g(kRefineBlocks, P), gd(64, P);
   if (bf) {
     hipLaunchKernelGGL(k_assign_refine<bf16>, g, dim3(512), 0, s, (const bf16 *)Q, (const bf16 *)K, zmerge, Ua,
                        anorm, T, n, tp, np_, (double)scale, L);

@@ -378,3 +378,29 @@ def test_merge_many_groups(t):
     K64 = np64(Kb)[0]
     ref = oracle.merge_keys(K64, np64(phi)[0], kap, S, oracle.LAMBDA_M)
     np.testing.assert_allclose(np64(Ck)[0], ref, rtol=0, atol=2e-5 * np.abs(K64).max())
+
+
+@pytest.mark.parametrize("n,pooled", [(256, False), (1024, True)])
+def test_every_anchor_a_candidate(n, pooled):
+    """One key 30 logits above the rest leaves every other profile below fp16's
+    range, so each key lists all t anchors: 100 candidates per key fit the pool
+    that E^T's rows of 1024 values leave room for (149 per key), and overflow
+    the one of 256-value rows (31), whose last keys go to the float64 pass with
+    all anchors.  Either way kappa is the float64 argmax."""
+    rng = np.random.default_rng(n)
+    T, t = 700, 100
+    s = 1.0 / math.sqrt(128)
+    K = rng.standard_normal((T, 128)).astype(np.float32)
+    V = rng.standard_normal((T, 128)).astype(np.float32)
+    Q = rng.standard_normal((n, 128)).astype(np.float32)
+    Q[0] *= 4.0
+    K[5] = Q[0] * (34.0 / (s * float(Q[0] @ Q[0])))
+    S = np.sort(rng.choice(T, t, replace=False))
+    Kb, Vb, Qb = (torch.from_numpy(x).to(torch.bfloat16) for x in (K, V, Q))
+    kap, st = gpu_assignment(Kb[None].cuda().contiguous(), Vb[None].cuda().contiguous(),
+                             Qb[None].cuda().contiguous(), torch.from_numpy(S.astype(np.int32))[None].cuda(), s)
+    K64, Q64 = np64(Kb), np64(Qb)
+    ref, _, _ = oracle.profiles_assign_phi(Q64, K64, S, s)
+    assert st[2] > 8 * 768 and st[3] == 0, st
+    assert (st[6] == st[0]) == pooled, st     # keys refined from the pool, all of the flagged ones or not
+    certify_flips(kap, ref, Q64, K64, S, s)
