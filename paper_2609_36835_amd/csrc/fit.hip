@@ -12,13 +12,10 @@
 //                                     earlier panel to it (hi / lo planes of
 //                                     L s_r, three products, about 2^-22
 //                                     relative)
-//                      k_chol_diag    factor a 64 x 64 diagonal block and
-//                                     invert it (1024 threads, four entries
-//                                     of a row each, one barrier per column)
-//                      k_chol_panel   L_ik = A_ik L_kk^-T inside the panel's
-//                                     256 x 256 diagonal block (fp32 MFMA
-//                                     with the inverse)
-//                      k_chol_upd     A -= L L^T inside that block (fp32 MFMA)
+//                      k_chol_diag256 factor the panel's 256 x 256 diagonal
+//                                     block in LDS (16-column steps, fp32
+//                                     MFMA) and invert its 64 x 64 diagonal
+//                                     blocks
 //                      k_chol_strip16 the rows below it: the same panel steps
 //                                     and updates on a 128 x 256 strip held in
 //                                     LDS as hi / lo planes (fp16 MFMA), then
@@ -211,276 +208,186 @@ __global__ void __launch_bounds__(256) k_nonfinite(const float *__restrict__ a, 
   if (__any(any) && (threadIdx.x & 63) == 0) atomicOr(&bad[b], 1);
 }
 
-// Factor the 64 x 64 diagonal block k in place and write L_kk^-1 to
-// dinv[b][k] (one workgroup of 256 threads per pair).  Thread (r, cls) with
-// r = tid / 4, cls = tid % 4 keeps A[r][4j + cls] (j < 16) in registers.
-// Threads of k_chol_diag: 64 rows x kDiagCls column classes, each thread
-// holding kDiagPer entries of its row (four waves per SIMD hide each other's
-// latency along the per-column dependence chain).
-constexpr int kDiagCls = 16, kDiagPer = kNB / kDiagCls, kDiagThreads = kNB * kDiagCls;
+// ------------------------------------------------- the panel's diagonal block
+// 16 x 16 fp32 tiles in LDS and in registers share one layout: element (r, c)
+// at float 64 (c / 4) + 4 r + c % 4, so lane l = 16 g + r holds columns
+// 4 g .. 4 g + 3 of row r as four consecutive floats (one conflict-free 16-byte
+// access per lane).  tile_mac(acc, X, Y) adds X Y^T: with the MFMA's operands
+// given as (Y, X) its output lands in this layout again, so a result feeds the
+// next product without leaving the registers.
+__device__ inline f32x4 tile_mac(f32x4 acc, f32x4 x, f32x4 y) {
+#pragma unroll
+  for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(y[s], x[s], acc, 0, 0, 0);
+  return acc;
+}
 
-// Right-looking over the 64 columns c with one barrier per column: column c,
-// updated through column c - 1 but not yet scaled, sits in LDS (its owners
-// publish it right after their own update of step c - 1), so every thread
-// reads the pivot, takes d = sqrt and 1 / d itself, scales the entries it
-// needs, L[x][c] = A'[x][c] / d, and subtracts L[r][c] L[q][c] from its
-// entries.  The inverse X = L^-1 is an elimination on the identity in the
-// same loop: row c of X is row c of the updated identity times 1 / d,
-// published at step c, and rows below subtract L[r][c] X[c][q] one step
-// later, when that row is visible.  Both recurrences accumulate in column
-// order with the same products and fused multiply-adds as a plain
-// column-by-column factorisation and row-by-row substitution.  A failed pivot
-// records info = column + 1 and leaves the block and dinv unwritten.
-__global__ void __launch_bounds__(kDiagThreads) k_chol_diag(float *__restrict__ Gw, int64_t ld, int k,
-                                                   int32_t *__restrict__ info, float *__restrict__ dinv) {
-  __shared__ float sA[kNB * kSD];   // column c: A updated through column c - 1, unscaled
-  __shared__ float sX[kNB * kSD];   // L^-1, one row per column step
-  __shared__ float sd[kNB], sdg[kNB];   // 1 / L[c][c] and L[c][c]
-  const int b = blockIdx.x, tid = threadIdx.x;
+// Lane N of each row of 16 lanes, broadcast over that row.
+template <int N>
+__device__ __forceinline__ float row_bcast(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + N, 0xf, 0xf, false));
+}
+
+// a[C + 1 ..] -= l L_qC for the columns q = C + 1 .. 15 (lane q's a[C] is L_qC).
+template <int C, int... Q>
+__device__ __forceinline__ void factor16_update(float (&a)[16], float l, std::integer_sequence<int, Q...>) {
+  ((a[C + 1 + Q] = fmaf(-l, row_bcast<C + 1 + Q>(a[C]), a[C + 1 + Q])), ...);
+}
+
+// Columns C .. 15 of a 16 x 16 factorisation in one wave: lane r of every row
+// of 16 lanes holds row r of A in a[] (the four rows of lanes repeat the
+// work); y holds columns 4 g .. 4 g + 3 of row r of the identity and becomes
+// row r of L^-1 before its scaling by 1 / L_rr.  a[c] becomes L_rc for r > c;
+// entries above the diagonal are never read by another lane.  piv and inv
+// collect row r's pivot and 1 / L_rr.
+template <int C>
+__device__ __forceinline__ void factor16(float (&a)[16], f32x4 &y, float &piv, float &inv, int r) {
+  if constexpr (C < 16) {
+    const float p = row_bcast<C>(a[C]);
+    // 1 / sqrt(p): the hardware estimate and one Newton step (about one unit
+    // in the last place); pivots near its underflow are scaled by 2^64 first
+    const bool small = p < 0x1p-96f;
+    const float q = small ? p * 0x1p64f : p;
+    const float r0 = __builtin_amdgcn_rsqf(q);
+    const float r1 = fmaf(0.5f * r0, fmaf(-(q * r0), r0, 1.0f), r0);
+    const float rs = small ? r1 * 0x1p32f : r1;
+    piv = r == C ? p : piv;
+    inv = r == C ? rs : inv;
+    a[C] *= rs;
+    const float l = r > C ? a[C] : 0.0f;
+    const float lx = l * rs;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) y[v] = fmaf(-lx, row_bcast<C>(y[v]), y[v]);
+    factor16_update<C>(a, l, std::make_integer_sequence<int, 15 - C>{});
+    factor16<C + 1>(a, y, piv, inv, r);
+  }
+}
+
+// The 256 x 256 diagonal block at K0 in one workgroup per pair: L in place and
+// the inverses of its four 64 x 64 diagonal blocks to dinv.  The block is held
+// in LDS as its 136 lower 16 x 16 tiles; wave i owns tile row i.  Step k
+// (16 columns): wave k factors tile (k, k) and inverts it, while the waves
+// below form what columns 0 .. k - 1 subtract from column k + 1
+// (left-looking); then L_ik = A_ik L_kk^-T from registers, and the last
+// product of column k + 1, L_ik L_k+1,k^T, from the rows just written.  Two
+// barriers per step.  nk = ceil((t - K0) / 16) steps, at most 16: the padding
+// is an identity already.  A failed pivot records info = column + 1.
+//
+// Bound by the chain of its 256 pivots (16 factorisations of one wave, about
+// 0.9 us each) with the fp32 MFMA products of the trailing tiles under it.
+// One launch in place of ten (four 64-column factorisations of 35 us, whose
+// 1024 threads each took every column's square root and division, and three
+// panel and three update launches on single blocks): 197 -> 64 us
+// per block at 8 pairs.
+constexpr size_t kDiag256Lds = (size_t)136 * 256 * sizeof(float) + 16;
+
+__global__ void __launch_bounds__(1024) k_chol_diag256(float *__restrict__ Gw, int64_t ld, int K0, int nk,
+                                                       int32_t *__restrict__ info, float *__restrict__ dinv) {
+  extern __shared__ __attribute__((aligned(16))) float diag_smem[];
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 15, g = lane >> 4;
   if (info[b] != 0) return;   // uniform over the workgroup
-  const int r = tid / kDiagCls, cls = tid % kDiagCls;
-  float *D = Gw + (size_t)b * ld * ld + (size_t)k * kNB * ld + (size_t)k * kNB;
-  for (int e = tid; e < kNB * kNB / 4; e += kDiagThreads) {
-    const int rr = e >> 4, c4 = (e & 15) * 4;
-    const f32x4 v = *reinterpret_cast<const f32x4 *>(D + (size_t)rr * ld + c4);
+  int32_t *fail = reinterpret_cast<int32_t *>(diag_smem + 136 * 256);
+  auto tile = [&](int i, int m) { return diag_smem + (i * (i + 1) / 2 + m) * 256; };
+  auto get = [&](int i, int m) { return *reinterpret_cast<const f32x4 *>(tile(i, m) + 4 * lane); };
+  auto put = [&](int i, int m, f32x4 v) { *reinterpret_cast<f32x4 *>(tile(i, m) + 4 * lane) = v; };
+  float *D = Gw + (size_t)b * ld * ld + (size_t)K0 * ld + K0;
+  float *grow = D + (size_t)(16 * wave + r) * ld + 4 * g;   // this lane's part of tile row `wave`
+  const f32x4 eye = {4 * g == r ? 1.0f : 0.0f, 4 * g + 1 == r ? 1.0f : 0.0f, 4 * g + 2 == r ? 1.0f : 0.0f,
+                     4 * g + 3 == r ? 1.0f : 0.0f};
+  {
+    f32x4 v[16];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) sA[rr * kSD + c4 + q] = v[q];
+    for (int m = 0; m < 16; ++m)
+      if (m <= wave) v[m] = *reinterpret_cast<const f32x4 *>(grow + 16 * m);
+#pragma unroll
+    for (int m = 0; m < 16; ++m)
+      if (m <= wave) put(wave, m, v[m]);
   }
+  if (wave >= nk) put(wave, wave, eye);
+  if (tid == 0) *fail = 0;
   __syncthreads();
-  // Each thread reads only its own entries, and column 0 needs no update.
-  float a[kDiagPer], y[kDiagPer];
-#pragma unroll
-  for (int j = 0; j < kDiagPer; ++j) {
-    const int q = kDiagCls * j + cls;
-    a[j] = sA[r * kSD + q];
-    y[j] = q == r ? 1.0f : 0.0f;
-  }
-  int fail = 0;
-  float plrc = 0.0f;   // L[r][c - 1]
-#pragma unroll 1
-  for (int c = 0; c < kNB; ++c) {
-    const float piv = sA[c * kSD + c];
-    const float arc = sA[r * kSD + c];
-    float col[kDiagPer], xp[kDiagPer];
-#pragma unroll
-    for (int j = 0; j < kDiagPer; ++j) col[j] = sA[(kDiagCls * j + cls) * kSD + c];
-    if (c > 0) {
-#pragma unroll
-      for (int j = 0; j < kDiagPer; ++j) xp[j] = sX[(c - 1) * kSD + kDiagCls * j + cls];
-    }
-    if (!(piv > 0.0f) || !isfinite(piv)) {   // uniform: every thread read the same pivot
-      fail = c + 1;
-      break;
-    }
-    const float d = sqrtf(piv), inv = 1.0f / d;
-    if (c > 0 && r >= c) {
-#pragma unroll
-      for (int j = 0; j < kDiagPer; ++j) y[j] = fmaf(-plrc, xp[j], y[j]);
-    }
-    if (r == c) {
-#pragma unroll
-      for (int j = 0; j < kDiagPer; ++j) sX[c * kSD + kDiagCls * j + cls] = y[j] * inv;
-    }
-    const float lrc = arc * inv;
-    if (r > c) {
-#pragma unroll
-      for (int j = 0; j < kDiagPer; ++j) a[j] = fmaf(-lrc, col[j] * inv, a[j]);
-    }
-    plrc = lrc;
-    if (c + 1 < kNB && cls == (c + 1) % kDiagCls) {
-      const int jn = (c + 1) / kDiagCls;
-      float v = a[0];
-#pragma unroll
-      for (int j = 1; j < kDiagPer; ++j) v = j == jn ? a[j] : v;
-      sA[r * kSD + c + 1] = v;
-    }
-    if (tid == 0) {
-      sd[c] = inv;
-      sdg[c] = d;
-    }
-    __syncthreads();
-  }
-  if (fail) {
-    if (tid == 0) info[b] = k * kNB + fail;
-    return;
-  }
-  float *Xi = dinv + ((size_t)b * (ld / kNB) + k) * kNB * kNB;
-  for (int e = tid; e < kNB * kNB; e += kDiagThreads) {
-    const int rr = e >> 6, q = e & 63;
-    if (q < rr) D[(size_t)rr * ld + q] = sA[rr * kSD + q] * sd[q];
-    else if (q == rr) D[(size_t)rr * ld + q] = sdg[q];
-    Xi[e] = sX[rr * kSD + q];
-  }
-}
-
-// Panel: L_ik = A_ik L_kk^-T for the rows below diagonal block k up to row
-// r_end, as an fp32 MFMA product with the inverse from k_chol_diag.  A
-// workgroup takes 128 rows (4 waves x 32 rows x 64 columns).
-__global__ void __launch_bounds__(256) k_chol_panel(float *__restrict__ Gw, int64_t ld, int k, int64_t r_end,
-                                                    const float *__restrict__ dinv,
-                                                    const int32_t *__restrict__ info) {
-  __shared__ float sLi[kNB * kSD], sA[128 * kSD];
-  const int b = blockIdx.y;
-  if (info[b] != 0) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, col = lane & 31;
-  const int64_t rb = (int64_t)(k + 1) * kNB + 128 * (int64_t)blockIdx.x;
-  float *G = Gw + (size_t)b * ld * ld;
-  const float *Li = dinv + ((size_t)b * (ld / kNB) + k) * kNB * kNB;
-  for (int e = tid; e < kNB * kNB / 4; e += 256) {
-    const int r = e / 16, c4 = (e % 16) * 4;
-    const f32x4 v = *reinterpret_cast<const f32x4 *>(Li + r * kNB + c4);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) sLi[r * kSD + c4 + q] = v[q];
-  }
-  for (int e = tid; e < 128 * kNB / 4; e += 256) {
-    const int r = e / 16, c4 = (e % 16) * 4;
-    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-    if (rb + r < r_end) v = *reinterpret_cast<const f32x4 *>(G + (size_t)(rb + r) * ld + (size_t)k * kNB + c4);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) sA[r * kSD + c4 + q] = v[q];
-  }
-  __syncthreads();
-  f32x16 acc0 = zero16(), acc1 = zero16();
-#pragma unroll
-  for (int ks = 0; ks < kNB / 2; ++ks) {
-    const float fa = sA[(32 * wave + col) * kSD + 2 * ks + h];
-    acc0 = Mfma<float>::mma(fa, sLi[col * kSD + 2 * ks + h], acc0);
-    acc1 = Mfma<float>::mma(fa, sLi[(32 + col) * kSD + 2 * ks + h], acc1);
-  }
-#pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int64_t r = rb + 32 * wave + acc_row(v, lane);
-    if (r < r_end) {
-      G[(size_t)r * ld + (size_t)k * kNB + col] = acc0[v];
-      G[(size_t)r * ld + (size_t)k * kNB + 32 + col] = acc1[v];
-    }
-  }
-}
-
-// Trailing update of the blocked factorisation on fp32 MFMA:
-//   G[r][c] -= sum_{q in [q0, q0+kw)} L[r][q] L[c][q]
-// for r in [r_lo, r_hi), c in [r_lo, c_hi), c <= r (up to the 64-wide diagonal
-// block), with 128 x 128 output tiles (4 waves of 64 x 64).  Only tiles on or
-// below the diagonal are launched: row tile ti holds column tiles
-// tj < min(ti + 1, n_ct); workgroups are remapped so each XCD owns a
-// contiguous range of (pair, tile).  The L operands are the finished panel
-// columns [q0, q0+kw), streamed through LDS in slabs of 32.
-__device__ inline void chol_upd_tile(int64_t idx, int n_ct, int &ti, int &tj) {
-  const int64_t tri = (int64_t)n_ct * (n_ct + 1) / 2;
-  if (idx < tri) {
-    int m = (int)((sqrt(8.0 * (double)idx + 1.0) - 1.0) * 0.5);
-    while ((int64_t)m * (m + 1) / 2 > idx) --m;
-    while ((int64_t)(m + 1) * (m + 2) / 2 <= idx) ++m;
-    ti = m;
-    tj = (int)(idx - (int64_t)m * (m + 1) / 2);
-  } else {
-    const int64_t r = idx - tri;
-    ti = n_ct + (int)(r / n_ct);
-    tj = (int)(r % n_ct);
-  }
-}
-
-__host__ __device__ inline int64_t chol_upd_tiles(int n_rt, int n_ct) {
-  return (int64_t)n_ct * (n_ct + 1) / 2 + (int64_t)(n_rt - n_ct) * n_ct;
-}
-
-__global__ void __launch_bounds__(256) k_chol_upd(float *__restrict__ Gw, int64_t ld, int r_lo, int r_hi, int c_hi,
-                                                  int q0, int kw, int n_rt, int n_ct,
-                                                  const int32_t *__restrict__ info) {
-  // LDS rows of 33 floats: the 4-byte fragment reads of 32 consecutive rows
-  // then fall in 32 distinct banks.  Two buffers; the next slab is fetched into
-  // registers while the current one is consumed.
-  constexpr int TB = 128, BKc = 32, SLc = BKc + 1, CHc = TB * BKc / 4 / 256;
-  __shared__ float sA[2][TB * SLc], sB[2][TB * SLc];
-  const int64_t per = chol_upd_tiles(n_rt, n_ct);
-  const int64_t tile = xcd_remap(blockIdx.x, gridDim.x);
-  const int b = (int)(tile / per);
-  if (info[b] != 0) return;
-  int ti, tj;
-  chol_upd_tile(tile % per, n_ct, ti, tj);
-  const int rb = r_lo + TB * ti, cb = r_lo + TB * tj;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1, h = lane >> 5, col = lane & 31;
-  float *G = Gw + (size_t)b * ld * ld;
-  f32x4 ra[CHc], rbv[CHc];
-  auto fetch = [&](int kq) {
-#pragma unroll
-    for (int c = 0; c < CHc; ++c) {
-      const int e = tid + 256 * c, r = e / (BKc / 4), c4 = (e % (BKc / 4)) * 4;
-      const int row_a = rb + r, row_b = cb + r;
-      ra[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-      rbv[c] = ra[c];
-      if (row_a < r_hi) ra[c] = *reinterpret_cast<const f32x4 *>(G + (size_t)row_a * ld + q0 + kq + c4);
-      if (row_b < c_hi) rbv[c] = *reinterpret_cast<const f32x4 *>(G + (size_t)row_b * ld + q0 + kq + c4);
-    }
-  };
-  auto stash = [&](int bf) {
-#pragma unroll
-    for (int c = 0; c < CHc; ++c) {
-      const int e = tid + 256 * c, r = e / (BKc / 4), c4 = (e % (BKc / 4)) * 4;
+  const bool live = wave < nk;
+  f32x4 cc = get(wave, 0), cn = cc;   // this row's tile of column k, and of column k + 1 without L_ik's product
+  for (int k = 0; k < nk; ++k) {   // uniform over the workgroup
+    if (wave == k) {
+      put(k, k, cc);
+      float a[16];
+      __builtin_amdgcn_wave_barrier();
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        sA[bf][r * SLc + c4 + q] = ra[c][q];
-        sB[bf][r * SLc + c4 + q] = rbv[c][q];
+        const f32x4 v = *reinterpret_cast<const f32x4 *>(tile(k, k) + 64 * q + 4 * r);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a[4 * q + e] = v[e];
       }
-    }
-  };
-  f32x16 acc[2][2];
+      __builtin_amdgcn_wave_barrier();
+      f32x4 y = eye;
+      float piv = 0.0f, inv = 0.0f;
+      factor16<0>(a, y, piv, inv, r);
+      const uint64_t bad = __ballot(!(piv > 0.0f) || !isfinite(piv)) & 0xffffull;
+      if (bad != 0 && lane == 0) *fail = K0 + 16 * k + __ffsll((unsigned long long)bad);
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+      for (int v = 0; v < 4; ++v) y[v] *= inv;
+      put(k, k, y);   // the tile's inverse, which the panel and the block inverses read
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = zero16();
-  fetch(0);
-  stash(0);
-  __syncthreads();
-  int bf = 0;
-  for (int kq = 0; kq < kw; kq += BKc) {
-    const bool more = kq + BKc < kw;
-    if (more) fetch(kq + BKc);
-#pragma unroll
-    for (int ks = 0; ks < BKc / 2; ++ks) {
-      float fa[2], fb[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        fa[i] = sA[bf][(wm * 64 + 32 * i + col) * SLc + 2 * ks + h];
-        fb[i] = sB[bf][(wn * 64 + 32 * i + col) * SLc + 2 * ks + h];
+      for (int v = 0; v < 4; ++v) {
+        const float l = g == 0 ? a[v] : g == 1 ? a[4 + v] : g == 2 ? a[8 + v] : a[12 + v];
+        const int c = 4 * g + v;
+        if (c <= r) grow[16 * k + v] = c == r ? piv * inv : l;
       }
+    } else if (wave > k && live && k + 1 < nk) {
+      f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+      int m = 0;
+      for (; m + 1 < k; m += 2) {
+        s0 = tile_mac(s0, get(wave, m), get(k + 1, m));
+        s1 = tile_mac(s1, get(wave, m + 1), get(k + 1, m + 1));
+      }
+      if (m < k) s0 = tile_mac(s0, get(wave, m), get(k + 1, m));
+      cn = get(wave, k + 1);
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = Mfma<float>::mma(fa[i], fb[j], acc[i][j]);
+      for (int v = 0; v < 4; ++v) cn[v] -= s0[v] + s1[v];
     }
-    if (more) stash(bf ^ 1);
     __syncthreads();
-    bf ^= 1;
+    if (*fail) break;   // uniform: every thread reads it between two barriers
+    f32x4 lik = {0.f, 0.f, 0.f, 0.f};
+    if (wave > k && live) {
+      lik = tile_mac(lik, cc, get(k, k));
+      put(wave, k, lik);
+      *reinterpret_cast<f32x4 *>(grow + 16 * k) = lik;
+    }
+    __syncthreads();
+    if (wave > k && live && k + 1 < nk) {
+      const f32x4 u = tile_mac(f32x4{0.f, 0.f, 0.f, 0.f}, lik, get(k + 1, k));
+#pragma unroll
+      for (int v = 0; v < 4; ++v) cc[v] = cn[v] - u[v];
+    }
   }
-  // Read-modify-write of the tile: every old value is loaded (unconditionally,
-  // from a clamped in-range address) before any store, so the loads pipeline
-  // instead of paying one memory round trip each.
-  const int64_t lm = ld - 1;
-  float old[2][2][16];
+  if (*fail) {
+    if (tid == 0) info[b] = *fail;
+    return;
+  }
+  // inverse of the 64 x 64 diagonal block q, tile column j per wave: with
+  // X = L^-1, X_ij = -X_ii sum_m L_im X_mj, kept transposed (xt = X_mj^T)
+  const int q = wave >> 2, j = wave & 3, q4 = 4 * q;
+  float *Xi = dinv + ((size_t)b * (ld / kNB) + K0 / kNB + q) * kNB * kNB;
+  f32x4 xt[4];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < 4; ++i) {
+    f32x4 x = {0.f, 0.f, 0.f, 0.f};
+    if (i == j) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int64_t c = cb + wn * 64 + 32 * j + col, cc = c < lm ? c : lm;
+      for (int v = 0; v < 4; ++v) x[v] = tile(q4 + j, q4 + j)[64 * (r >> 2) + 4 * (4 * g + v) + (r & 3)];
+    } else if (i > j) {
+      f32x4 st = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int64_t r = rb + wm * 64 + 32 * i + acc_row(v, lane), rr = r < lm ? r : lm;
-        old[i][j][v] = __builtin_nontemporal_load(&G[rr * ld + cc]);
-      }
+      for (int m = 0; m < i; ++m)
+        if (m >= j) st = tile_mac(st, xt[m], get(q4 + i, q4 + m));
+      x = tile_mac(x, st, get(q4 + i, q4 + i));
+#pragma unroll
+      for (int v = 0; v < 4; ++v) x[v] = -x[v];
     }
+    xt[i] = x;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int c = cb + wn * 64 + 32 * j + col;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int r = rb + wm * 64 + 32 * i + acc_row(v, lane);
-        if (r < r_hi && c < c_hi && c <= r + 63) G[(size_t)r * ld + c] = old[i][j][v] - acc[i][j][v];
-      }
-    }
+    for (int v = 0; v < 4; ++v) Xi[(16 * i + 4 * g + v) * kNB + 16 * j + r] = x[v];
+  }
 }
 
 // Left-looking update of the column panel K0 .. K0 + 255:
@@ -1732,9 +1639,9 @@ hipError_t launch_cholesky_factor(float *Gw, const float *Gc, int B, int t, int6
   // contraction applies every earlier panel to it (rows K0 .. ld, K = 3 K0 over
   // the fp16 hi / lo planes of L), so each trailing entry is read and written
   // once per factorisation instead of once per outer panel.  Inside the panel,
-  // 64-wide diagonal factor + panel-solve steps on its 256 x 256 diagonal block,
-  // then the fused strip kernel on the rows below, which also writes their
-  // planes for the later panels' contractions.
+  // its 256 x 256 diagonal block in one workgroup per pair, then the fused
+  // strip kernel on the rows below, which also writes their planes for the
+  // later panels' contractions.
   // lsplit layout (B (4 ld^2 + 8 ld) bytes): planes [B][2][ld][ld] fp16 (hi,
   // lo), then shifts [B][ld] int32, then inverse scales [B][ld] fp32.
   constexpr int kOuter = 256;
@@ -1746,6 +1653,9 @@ hipError_t launch_cholesky_factor(float *Gw, const float *Gc, int B, int t, int6
   const hipError_t ea = hipFuncSetAttribute((const void *)k_chol_strip16, hipFuncAttributeMaxDynamicSharedMemorySize,
                                             (int)kStrip16Lds);
   if (ea != hipSuccess) return ea;
+  const hipError_t ed = hipFuncSetAttribute((const void *)k_chol_diag256, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                            (int)kDiag256Lds);
+  if (ed != hipSuccess) return ed;
   for (int K0 = 0; K0 < ld; K0 += kOuter) {
     const int K1 = (int)(K0 + kOuter < ld ? K0 + kOuter : ld);
     if (K0 > 0) {
@@ -1759,20 +1669,9 @@ hipError_t launch_cholesky_factor(float *Gw, const float *Gc, int B, int t, int6
           g, reinterpret_cast<const bf16 *>(Ar), reinterpret_cast<const bf16 *>(Ar), e, s);
       if (err != hipSuccess) return err;
     }
-    // the 256 x 256 diagonal block: 64-wide steps restricted to its rows
-    for (int c = K0; c < K1; c += kNB) {
-      const int k = c / kNB;
-      hipLaunchKernelGGL(k_chol_diag, dim3(B), dim3(kDiagThreads), 0, s, Gw, ld, k, st.info, dinv);
-      const int rem = (K1 - c) / kNB - 1;   // row blocks of the diagonal block below block k
-      if (rem > 0)
-        hipLaunchKernelGGL(k_chol_panel, dim3((rem + 1) / 2, B), dim3(256), 0, s, Gw, ld, k, (int64_t)K1, dinv,
-                           st.info);
-      if (c + kNB < K1) {
-        const int r_lo = c + kNB, n_rt = (K1 - r_lo + 127) / 128, n_ct = (K1 - r_lo + 127) / 128;
-        hipLaunchKernelGGL(k_chol_upd, dim3((unsigned)(chol_upd_tiles(n_rt, n_ct) * B)), dim3(256), 0, s, Gw, ld,
-                           r_lo, K1, K1, c, kNB, n_rt, n_ct, st.info);
-      }
-    }
+    // the 256 x 256 diagonal block
+    const int nk = t - K0 < kOuter ? (t - K0 + 15) / 16 : 16;
+    hipLaunchKernelGGL(k_chol_diag256, dim3(B), dim3(1024), kDiag256Lds, s, Gw, ld, K0, nk > 0 ? nk : 0, st.info, dinv);
     // the rows below: all four steps, written back once, with their planes
     if (K1 < ld)
       hipLaunchKernelGGL(k_chol_strip16, dim3((unsigned)((ld - K1) / kStripRows), B), dim3(512), kStrip16Lds, s, Gw,
