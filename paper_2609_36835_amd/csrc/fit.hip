@@ -224,13 +224,13 @@ __device__ inline f32x4 tile_mac(f32x4 acc, f32x4 x, f32x4 y) {
 // Lane N of each row of 16 lanes, broadcast over that row.
 template <int N>
 __device__ __forceinline__ float row_bcast(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + N, 0xf, 0xf, false));
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x150 + N, 0xf, 0xf, true));
 }
 
-// a[C + 1 ..] -= l L_qC for the columns q = C + 1 .. 15 (lane q's a[C] is L_qC).
+// a[C + 1 ..] += nl L_qC for the columns q = C + 1 .. 15 (lane q's a[C] is L_qC).
 template <int C, int... Q>
-__device__ __forceinline__ void factor16_update(float (&a)[16], float l, std::integer_sequence<int, Q...>) {
-  ((a[C + 1 + Q] = fmaf(-l, row_bcast<C + 1 + Q>(a[C]), a[C + 1 + Q])), ...);
+__device__ __forceinline__ void factor16_update(float (&a)[16], float nl, std::integer_sequence<int, Q...>) {
+  ((a[C + 1 + Q] = fmaf(row_bcast<C + 1 + Q>(a[C]), nl, a[C + 1 + Q])), ...);
 }
 
 // Columns C .. 15 of a 16 x 16 factorisation in one wave: lane r of every row
@@ -253,11 +253,11 @@ __device__ __forceinline__ void factor16(float (&a)[16], f32x4 &y, float &piv, f
     piv = r == C ? p : piv;
     inv = r == C ? rs : inv;
     a[C] *= rs;
-    const float l = r > C ? a[C] : 0.0f;
-    const float lx = l * rs;
+    const float nl = r > C ? -a[C] : 0.0f;
+    factor16_update<C>(a, nl, std::make_integer_sequence<int, 15 - C>{});
+    const float nx = nl * rs;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) y[v] = fmaf(-lx, row_bcast<C>(y[v]), y[v]);
-    factor16_update<C>(a, l, std::make_integer_sequence<int, 15 - C>{});
+    for (int v = 0; v < 4; ++v) y[v] = fmaf(row_bcast<C>(y[v]), nx, y[v]);
     factor16<C + 1>(a, y, piv, inv, r);
   }
 }
@@ -276,7 +276,7 @@ __device__ __forceinline__ void factor16(float (&a)[16], f32x4 &y, float &piv, f
 // 0.9 us each) with the fp32 MFMA products of the trailing tiles under it.
 // One launch in place of ten (four 64-column factorisations of 35 us, whose
 // 1024 threads each took every column's square root and division, and three
-// panel and three update launches on single blocks): 197 -> 64 us
+// panel and three update launches on single blocks): 197 -> 45 us
 // per block at 8 pairs.
 constexpr size_t kDiag256Lds = (size_t)136 * 256 * sizeof(float) + 16;
 
@@ -321,17 +321,23 @@ __global__ void __launch_bounds__(1024) k_chol_diag256(float *__restrict__ Gw, i
       __builtin_amdgcn_wave_barrier();
       f32x4 y = eye;
       float piv = 0.0f, inv = 0.0f;
+      __builtin_amdgcn_s_setprio(3);   // the step's critical chain
       factor16<0>(a, y, piv, inv, r);
+      __builtin_amdgcn_s_setprio(0);
       const uint64_t bad = __ballot(!(piv > 0.0f) || !isfinite(piv)) & 0xffffull;
       if (bad != 0 && lane == 0) *fail = K0 + 16 * k + __ffsll((unsigned long long)bad);
 #pragma unroll
       for (int v = 0; v < 4; ++v) y[v] *= inv;
       put(k, k, y);   // the tile's inverse, which the panel and the block inverses read
+      // this lane's columns of L (bit masks: a select over the array elements
+      // would index the array in scratch memory)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const float l = g == 0 ? a[v] : g == 1 ? a[4 + v] : g == 2 ? a[8 + v] : a[12 + v];
+        int l = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) l |= __float_as_int(a[4 * q + v]) & (g == q ? -1 : 0);
         const int c = 4 * g + v;
-        if (c <= r) grow[16 * k + v] = c == r ? piv * inv : l;
+        if (c <= r) grow[16 * k + v] = c == r ? piv * inv : __int_as_float(l);
       }
     } else if (wave > k && live && k + 1 < nk) {
       f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
