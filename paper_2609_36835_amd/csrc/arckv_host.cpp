@@ -87,8 +87,6 @@ hipError_t launch_cholesky(float *Gw, const float *Gc, int B, int t, int64_t ld,
                            FitState st, float *dinv, void *lsplit, const int32_t *bad, int32_t *cnt,
                            hipStream_t s);
 hipError_t launch_nonfinite(const float *a, int B, int64_t per, int32_t *bad, hipStream_t s);
-hipError_t launch_trsv(const float *Gw, const float *dinv, int B, int64_t ld, const double *rhs, double *sw,
-                       double *y, double *x, double *acc, const int32_t *info, hipStream_t s);
 hipError_t launch_cholesky_factor(float *Gw, const float *Gc, int B, int t, int64_t ld, float delta0, int max_esc,
                                   FitState st, float *dinv, void *lsplit, hipStream_t s);
 hipError_t launch_nnls(const float *Gc, float *Gw, const double *h, const float *LT, const float *z, const float *m,

@@ -20,6 +20,8 @@
 //                                     and updates on a 128 x 256 strip held in
 //                                     LDS as hi / lo planes (fp16 MFMA), then
 //                                     L and its planes written back
+//                      k_chol_inv256  the inverses of the 256 x 256 diagonal
+//                                     blocks, for the solves
 //                    a failed pivot records info = column + 1 for that pair
 //   escalation       pairs that failed are refactored by the same kernels with
 //                    delta raised tenfold (from 1e-7 when zero), at most
@@ -664,88 +666,216 @@ __global__ void __launch_bounds__(256) k_chol_scales(const float *__restrict__ G
   inv[(size_t)b * ld + r] = ldexpf(1.0f, -sh);
 }
 
-// --------------------------------------------------------------- one right-hand side
-// One-rhs triangular solves, float64 vectors, right-looking over 64-row
-// blocks with one launch per block j, so that every block row below (forward)
-// or above (backward) is updated by its own workgroup:
-//   forward  L y = rhs:   y_j = D_j s_j,   s_i -= L_ij y_j      (i > j)
-//   backward L^T x = y:   x_j = D_j^T y_j, y_i -= L_ji^T x_j    (i < j)
-// D_j is the inverse of diagonal block j from the factorisation.  Each
-// workgroup recomputes the block solution (a 64 x 64 product) and updates its
-// target block; workgroup 0 also writes the solution (and adds it to `acc` on
-// the backward pass when given).  Forward step 0 reads the rhs, later steps the
-// work vector s; the backward pass updates y in place.
-template <bool FWD>
-__global__ void __launch_bounds__(256) k_trsv_step(const float *__restrict__ Gw, const float *__restrict__ dinv,
-                                                   int64_t ld, int j, const double *__restrict__ rhs,
-                                                   double *__restrict__ work, double *__restrict__ out,
-                                                   double *__restrict__ acc, const int32_t *__restrict__ info) {
-  __shared__ double sv[kNB], sol[kNB], red[4][kNB];
-  const int b = blockIdx.y, g = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (info[b] != 0) return;
-  const int nb = (int)(ld / kNB);
-  const int i = FWD ? j + 1 + g : g;                       // target block
-  const bool has_target = FWD ? i < nb : i < j;
-  const float *L = Gw + (size_t)b * ld * ld;
-  const float *D = dinv + ((size_t)b * nb + j) * kNB * kNB;
-  const double *src = (FWD && j == 0) ? rhs + (size_t)b * ld : work + (size_t)b * ld;
-  if (tid < kNB) sv[tid] = src[(size_t)j * kNB + tid];
+// ------------------------------------------------- inverses of the 256-wide diagonal blocks
+// D_K = L_KK^-1, 256 x 256 lower triangular in fp32, for the triangular solves,
+// which then take ld / 256 steps.  It is kept in the unused diagonal block of
+// the planes of L (the contractions read rows below a panel only): of row r,
+// columns 0 .. 127 in the hi plane's 512 bytes at (K0 + r, K0) and columns
+// 128 .. 255 in the lo plane's.  The four 64 x 64 diagonal blocks are stored
+// with their zeros above the diagonal, the other upper entries are not stored.
+struct DiagInv {
+  const float *hi, *lo;   // row 0 of either half
+  int64_t ldf;            // floats between rows
+  __device__ __forceinline__ const float *at(int r, int c) const {   // four columns from c, c a multiple of 4
+    return (c < 128 ? hi + c : lo + (c - 128)) + (size_t)r * ldf;
+  }
+};
+
+__device__ inline DiagInv diag_inv(const void *lsplit, int64_t ld, int b, int64_t K0) {
+  const f16 *p = reinterpret_cast<const f16 *>(lsplit) + (size_t)b * 2 * ld * ld + (size_t)K0 * ld + K0;
+  return {reinterpret_cast<const float *>(p), reinterpret_cast<const float *>(p + (size_t)ld * ld), ld / 2};
+}
+
+// One workgroup per (block, pair), after the factorisation: the lower 16 x 16
+// tiles of L and the inverses of its diagonal tiles (from dinv) in LDS; wave j
+// solves tile column j of X = L^-1 by substitution, X_ij = -X_ii sum_m L_im
+// X_mj, its tiles transposed in registers.  Columns are independent, so no
+// barrier; column 0's 135 tile products on fp32 MFMA bound it.
+__global__ void __launch_bounds__(1024) k_chol_inv256(const float *__restrict__ Gw, int64_t ld,
+                                                      const float *__restrict__ dinv, void *__restrict__ lsplit,
+                                                      const int32_t *__restrict__ info) {
+  extern __shared__ __attribute__((aligned(16))) float diag_smem[];
+  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 15, g = lane >> 4;
+  if (info[b] != 0) return;   // uniform over the workgroup
+  const int64_t K0 = (int64_t)blockIdx.x * 256;
+  auto tile = [&](int i, int m) { return diag_smem + (i * (i + 1) / 2 + m) * 256; };
+  auto get = [&](int i, int m) { return *reinterpret_cast<const f32x4 *>(tile(i, m) + 4 * lane); };
+  const float *grow = Gw + (size_t)b * ld * ld + (size_t)(K0 + 16 * wave + r) * ld + K0 + 4 * g;
+  const float *drow = dinv + ((size_t)b * (ld / kNB) + K0 / kNB + (wave >> 2)) * kNB * kNB +
+                      (16 * (wave & 3) + r) * kNB + 16 * (wave & 3) + 4 * g;
+  {
+    f32x4 v[16];
+#pragma unroll
+    for (int m = 0; m < 16; ++m)
+      if (m <= wave) v[m] = *reinterpret_cast<const f32x4 *>(m < wave ? grow + 16 * m : drow);
+#pragma unroll
+    for (int m = 0; m < 16; ++m)
+      if (m <= wave) *reinterpret_cast<f32x4 *>(tile(wave, m) + 4 * lane) = v[m];
+  }
   __syncthreads();
-  if constexpr (FWD) {
-    // row-major tiles: four lanes per row, each over 16 contiguous columns
-    // (16-byte loads); a lane's partial is the sum the column-quarter took in
-    // the transposed form, and the quarters meet in the same order
-    const int rr = tid >> 2, qs = tid & 3;
-    auto rowdot = [&](const float *row, const double *vec) {
-      double pr = 0.0;
+  const int j = wave;
+  float *out = const_cast<float *>(diag_inv(lsplit, ld, b, K0).at(0, j < 8 ? 0 : 128)) + 16 * (j & 7) + r;
+  const int64_t ldf = ld / 2;
+  f32x4 xt[16];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const f32x4 v = *reinterpret_cast<const f32x4 *>(row + 16 * qs + 4 * c);
+  for (int i = 0; i < 16; ++i) {
+    f32x4 x = {0.f, 0.f, 0.f, 0.f};
+    if (i == j) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) pr += (double)v[q] * vec[16 * qs + 4 * c + q];
-      }
-      const double p1 = __shfl_down(pr, 1, 4), p2 = __shfl_down(pr, 2, 4), p3 = __shfl_down(pr, 3, 4);
-      return ((pr + p1) + p2) + p3;   // valid in the row's first lane
-    };
-    const double sr = rowdot(D + rr * kNB, sv);
-    if (qs == 0) sol[rr] = sr;
-    __syncthreads();
-    if (g == 0 && tid < kNB) out[(size_t)b * ld + (size_t)j * kNB + tid] = sol[tid];
-    if (!has_target) return;
-    const double ur = rowdot(L + ((size_t)i * kNB + rr) * ld + (size_t)j * kNB, sol);
-    if (qs == 0) {
-      const size_t e = (size_t)b * ld + (size_t)i * kNB + rr;
-      const double base = j == 0 ? rhs[e] : work[e];
-      work[e] = base - ur;
+      for (int v = 0; v < 4; ++v) x[v] = tile(j, j)[64 * (r >> 2) + 4 * (4 * g + v) + (r & 3)];
+    } else if (i > j) {
+      f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+#pragma unroll
+      for (int m = 0; m < i; ++m)
+        if (m >= j) {
+          if (m & 1) s1 = tile_mac(s1, xt[m], get(i, m));
+          else s0 = tile_mac(s0, xt[m], get(i, m));
+        }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) s0[v] = -(s0[v] + s1[v]);
+      x = tile_mac(x, s0, get(i, i));
     }
-    return;
-  }
-  double part = 0.0;
+    xt[i] = x;
+    if (i >= (j & ~3)) {   // with the zero tiles above the diagonal inside the 64 x 64 block
 #pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    const int q = 16 * wave + e;
-    part += (double)D[q * kNB + lane] * sv[q];
+      for (int v = 0; v < 4; ++v) out[(size_t)(16 * i + 4 * g + v) * ldf] = x[v];
+    }
   }
-  red[wave][lane] = part;
-  __syncthreads();
-  if (tid < kNB) sol[tid] = red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid];
-  __syncthreads();
-  if (g == 0 && tid < kNB) {
-    out[(size_t)b * ld + (size_t)j * kNB + tid] = sol[tid];
-    if (!FWD && acc) acc[(size_t)b * ld + (size_t)j * kNB + tid] += sol[tid];
-  }
-  if (!has_target) return;
-  part = 0.0;
+}
+
+// --------------------------------------------------------------- one right-hand side
+// One-rhs triangular solves, float64 vectors, right-looking over 256-row
+// blocks K with one launch per block:
+//   forward  L y = rhs:   y_K = D_K s_K,     s_i -= L_iK y_K      (rows i below)
+//   backward L^T x = y:   x_K = D_K^T y_K,   y_i -= L_Ki^T x_K    (columns i before)
+// Every workgroup forms the block solution (a 256 x 256 triangular product)
+// and updates `per` chunks of 64 targets; workgroup 0 also writes the solution
+// (and adds it to `acc` on the backward pass when given).  Forward step 0
+// reads the rhs, later steps the work vector s; the backward pass updates y in
+// place.  Bound by the launches and the two dependent reads of one: 64-row
+// blocks took four times the launches at 4.3 us each, these 7.9 us: 725 -> 332 us for
+// the six passes of 8 pairs at t = 1638; 64 pairs at t = 3277: 22.2 -> 20.5 ms
+// per 256 pairs for the mass fit's solve stage with its residuals.
+template <bool FWD>
+__global__ void __launch_bounds__(1024) k_trsv256(const float *__restrict__ Gw, const void *__restrict__ lsplit,
+                                                  int64_t ld, int K, int per, const double *__restrict__ rhs,
+                                                  double *__restrict__ work, double *__restrict__ out,
+                                                  double *__restrict__ acc, const int32_t *__restrict__ info) {
+  __shared__ double sv[256], sol[256], red[16][256];
+  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (info[b] != 0) return;
+  const int64_t K0 = (int64_t)K * 256;
+  const int nch = (int)(FWD ? (ld - K0 - 256) / 64 : K0 / 64);   // chunks of 64 targets
+  const int ch0 = blockIdx.x * per, ch1 = min(ch0 + per, nch);
+  const float *L = Gw + (size_t)b * ld * ld;
+  const DiagInv D = diag_inv(lsplit, ld, b, K0);
+  const double *src = (FWD && K == 0 ? rhs : work) + (size_t)b * ld;
+  if (tid < 256) sv[tid] = src[K0 + tid];
+  // the chunk's part of L, loaded ahead of its use: forward 16 lanes per
+  // target row, backward 16 lanes per row of the block
+  const int q = tid & 15, rg = tid >> 4;
+  f32x4 lv[4];
+  auto load_l = [&](int ch) {
 #pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    const int q = 16 * wave + e;
-    part += (double)L[((size_t)j * kNB + q) * ld + (size_t)i * kNB + lane] * sol[q];
+    for (int u = 0; u < 4; ++u)
+      lv[u] = *reinterpret_cast<const f32x4 *>(FWD ? L + (size_t)(K0 + 256 + 64 * ch + rg) * ld + K0 + 4 * (q + 16 * u)
+                                                   : L + (size_t)(K0 + rg + 64 * u) * ld + 64 * ch + 4 * q);
+  };
+  if constexpr (FWD) {
+    // y_K: four lanes per row, interleaved over its 16-byte groups up to the diagonal
+    const int r = tid >> 2, p = tid & 3;
+    f32x4 d[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+      if (4 * (p + 4 * u) <= r) d[u] = *reinterpret_cast<const f32x4 *>(D.at(r, 4 * (p + 4 * u)));
+    if (ch0 < ch1) load_l(ch0);
+    __syncthreads();
+    double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+      if (4 * (p + 4 * u) <= r) {
+        const double *v = sv + 4 * (p + 4 * u);
+        s0 = fma((double)d[u][0], v[0], s0);
+        s1 = fma((double)d[u][1], v[1], s1);
+        s0 = fma((double)d[u][2], v[2], s0);
+        s1 = fma((double)d[u][3], v[3], s1);
+      }
+    double s = s0 + s1;
+    s += __shfl_xor(s, 1, 64);
+    s += __shfl_xor(s, 2, 64);
+    if (p == 0) sol[r] = s;
+  } else {
+    // x_K: a lane per four columns, a wave per 16 rows r = wave (mod 16)
+    f32x4 d[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+      if (16 * u + wave >= 4 * lane) d[u] = *reinterpret_cast<const f32x4 *>(D.at(16 * u + wave, 4 * lane));
+    if (ch0 < ch1) load_l(ch0);
+    __syncthreads();
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+      if (16 * u + wave >= 4 * lane) {
+        const double v = sv[16 * u + wave];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[e] = fma((double)d[u][e], v, s[e]);
+      }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) red[wave][4 * lane + e] = s[e];
+    __syncthreads();
+    if (tid < 256) {
+      double x = 0.0;
+#pragma unroll
+      for (int w = 0; w < 16; ++w) x += red[w][tid];
+      sol[tid] = x;
+    }
   }
-  red[wave][lane] = part;     // red is free: every thread read it before the last barrier
   __syncthreads();
-  if (tid < kNB) {
-    const size_t e = (size_t)b * ld + (size_t)i * kNB + tid;
-    work[e] = work[e] - (red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid]);
+  if (blockIdx.x == 0 && tid < 256) {
+    out[(size_t)b * ld + K0 + tid] = sol[tid];
+    if (!FWD && acc) acc[(size_t)b * ld + K0 + tid] += sol[tid];
+  }
+  for (int ch = ch0; ch < ch1; ++ch) {   // uniform over the workgroup
+    if constexpr (FWD) {
+      double s = 0.0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s = fma((double)lv[u][e], sol[4 * (q + 16 * u) + e], s);
+      if (ch + 1 < ch1) load_l(ch + 1);
+#pragma unroll
+      for (int m = 8; m >= 1; m >>= 1) s += __shfl_xor(s, m, 64);
+      if (q == 0) {
+        const size_t e = (size_t)b * ld + K0 + 256 + 64 * ch + rg;
+        work[e] = (K == 0 ? rhs[e] : work[e]) - s;
+      }
+    } else {
+      double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const double v = sol[rg + 64 * u];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[e] = fma((double)lv[u][e], v, s[e]);
+      }
+      if (ch + 1 < ch1) load_l(ch + 1);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        s[e] += __shfl_xor(s[e], 16, 64);
+        s[e] += __shfl_xor(s[e], 32, 64);
+      }
+      __syncthreads();   // the previous use of red is over
+      if (lane < 16) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) red[wave][4 * lane + e] = s[e];
+      }
+      __syncthreads();
+      if (tid < 64) {
+        double x = 0.0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) x += red[w][tid];
+        work[(size_t)b * ld + 64 * ch + tid] -= x;
+      }
+    }
   }
 }
 
@@ -1595,7 +1725,7 @@ __global__ void k_nnls_finish(const int32_t *__restrict__ state, int B, int32_t 
 
 // ------------------------------------------------------------------ launchers
 hipError_t launch_fill_i32(int32_t *p, int64_t count, int32_t v, hipStream_t s);
-hipError_t launch_trsv(const float *Gw, const float *dinv, int B, int64_t ld, const double *rhs, double *sw,
+hipError_t launch_trsv(const float *Gw, const void *lsplit, int B, int64_t ld, const double *rhs, double *sw,
                        double *y, double *x, double *acc, const int32_t *info, hipStream_t s);
 hipError_t launch_cholesky_factor(float *Gw, const float *Gc, int B, int t, int64_t ld, float delta0, int max_esc,
                                   FitState st, float *dinv, void *lsplit, hipStream_t s);
@@ -1683,6 +1813,11 @@ hipError_t launch_cholesky_factor(float *Gw, const float *Gc, int B, int t, int6
       hipLaunchKernelGGL(k_chol_strip16, dim3((unsigned)((ld - K1) / kStripRows), B), dim3(512), kStrip16Lds, s, Gw,
                          ld, K0, dinv, Lp, shift, st.info);
   }
+  const hipError_t ei = hipFuncSetAttribute((const void *)k_chol_inv256, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                            (int)kDiag256Lds);
+  if (ei != hipSuccess) return ei;
+  hipLaunchKernelGGL(k_chol_inv256, dim3((unsigned)(ld / kOuter), B), dim3(1024), kDiag256Lds, s, Gw, ld, dinv,
+                     lsplit, st.info);
   (void)Gc;
   (void)delta0;
   (void)max_esc;
@@ -1690,19 +1825,29 @@ hipError_t launch_cholesky_factor(float *Gw, const float *Gc, int B, int t, int6
 }
 
 // Forward L y = rhs then backward L^T x = y; sw and y are work vectors
-// [B][ld]; x receives the solution, acc (optional) accumulates it.
-hipError_t launch_trsv(const float *Gw, const float *dinv, int B, int64_t ld, const double *rhs, double *sw,
+// [B][ld]; x receives the solution, acc (optional) accumulates it.  A
+// workgroup takes one chunk of 64 targets while few pairs leave CUs idle, and
+// up to four (256 rows, as much of L as of D_K) once the launch holds more
+// than kTrsvGroups of them, so that D_K is not re-read for every 64 rows.
+constexpr int kTrsvGroups = 512;
+hipError_t launch_trsv(const float *Gw, const void *lsplit, int B, int64_t ld, const double *rhs, double *sw,
                        double *y, double *x, double *acc, const int32_t *info, hipStream_t s) {
-  const int nb = (int)(ld / kNB);
-  for (int j = 0; j < nb; ++j) {
-    const int ng = nb - 1 - j > 0 ? nb - 1 - j : 1;
-    hipLaunchKernelGGL(k_trsv_step<true>, dim3(ng, B), dim3(256), 0, s, Gw, dinv, ld, j, rhs, sw, y,
+  const int nblk = (int)(ld / 256);
+  auto groups = [&](int nch, int &per) {
+    per = (int)((int64_t)nch * B / kTrsvGroups);
+    per = per < 1 ? 1 : per > 4 ? 4 : per;
+    return nch > 0 ? (nch + per - 1) / per : 1;
+  };
+  int per = 1;
+  for (int K = 0; K < nblk; ++K) {
+    const int ng = groups(4 * (nblk - 1 - K), per);
+    hipLaunchKernelGGL(k_trsv256<true>, dim3(ng, B), dim3(1024), 0, s, Gw, lsplit, ld, K, per, rhs, sw, y,
                        (double *)nullptr, info);
   }
-  for (int j = nb - 1; j >= 0; --j) {
-    const int ng = j > 0 ? j : 1;
-    hipLaunchKernelGGL(k_trsv_step<false>, dim3(ng, B), dim3(256), 0, s, Gw, dinv, ld, j, (const double *)nullptr,
-                       y, x, acc, info);
+  for (int K = nblk - 1; K >= 0; --K) {
+    const int ng = groups(4 * K, per);
+    hipLaunchKernelGGL(k_trsv256<false>, dim3(ng, B), dim3(1024), 0, s, Gw, lsplit, ld, K, per,
+                       (const double *)nullptr, y, x, acc, info);
   }
   return hipGetLastError();
 }
@@ -1730,12 +1875,12 @@ hipError_t launch_mass_solve(float *Gw, const float *Gc, float *dinv, void *lspl
   const dim3 gb((B + 255) / 256);
   if ((e = launch_fill_i32(ms.div, B, 0, s)) != hipSuccess) return e;
   for (int round = 0;; ++round) {
-    if ((e = launch_trsv(Gw, dinv, B, tp, ms.h, ms.sw, ms.y, ms.w, nullptr, st.info, s)) != hipSuccess) return e;
+    if ((e = launch_trsv(Gw, lsplit, B, tp, ms.h, ms.sw, ms.y, ms.w, nullptr, st.info, s)) != hipSuccess) return e;
     for (int it = 0; it < refine_steps; ++it) {
       if ((e = launch_mass_residual(ms.LT, ms.z, ms.m, ms.w, st.lam, B, n, t, tp, np_, ms.u, ms.res, st.info, s,
                                       nullptr, nullptr, nullptr, nullptr)) != hipSuccess)
         return e;
-      if ((e = launch_trsv(Gw, dinv, B, tp, ms.res, ms.sw, ms.y, ms.x, ms.w, st.info, s)) != hipSuccess) return e;
+      if ((e = launch_trsv(Gw, lsplit, B, tp, ms.res, ms.sw, ms.y, ms.x, ms.w, st.info, s)) != hipSuccess) return e;
       hipLaunchKernelGGL(k_refine_watch, dim3(B), dim3(256), 0, s, ms.w, ms.x, tp, it, ms.rprev, ms.div, st,
                          max_esc);
     }
@@ -1784,7 +1929,7 @@ hipError_t launch_nnls(const float *Gc, float *Gw, const double *h, const float 
       // residual of the full ridged system against the data, h - (G + lam I) x
       hipLaunchKernelGGL(k_nnls_gather_vec, gf, dim3(256), 0, s, rs == 0 ? h : res, tp, nw.idx, nw.nf, st.info, ldf,
                          nw.rf);
-      if ((e = launch_trsv(Gw, dinv, B, ldf, nw.rf, sw, yw, nw.xf, nullptr, st.info, s)) != hipSuccess) return e;
+      if ((e = launch_trsv(Gw, lsplit, B, ldf, nw.rf, sw, yw, nw.xf, nullptr, st.info, s)) != hipSuccess) return e;
       hipLaunchKernelGGL(k_nnls_scatter, gv, dim3(256), 0, s, nw.xf, ldf, nw.pos, tp, st.info, rs > 0 ? 1 : 0, x);
       // x vanishes off F, so Phi_C x sums over the free keys; the residual is
       // needed on the free keys for a correction, on the bound keys (the dual)
