@@ -99,11 +99,8 @@ hipError_t launch_phat(int dtype, const float *LT, const float *beta_ws, int B, 
                        int64_t np_, void *out, void *outm, hipStream_t s);
 hipError_t launch_transpose128(int dtype, const float *in, int B, int rows, int64_t in_pair, int64_t rows_pad,
                                void *out, int64_t out_pair, hipStream_t s);
-hipError_t launch_trsm(bool fwd, const float *Gw, const float *dinv, int B, int64_t ld, const float *R, float *X,
+hipError_t launch_trsm(bool fwd, const float *Gw, const void *lsplit, int B, int64_t ld, float *R, float *X, float *xt,
                        const int32_t *info, hipStream_t s);
-hipError_t launch_trsm_fwd_blocked(const float *Gw, const float *dinv, const void *lsplit, int B, int64_t ld,
-                                   const float *R, float *Y, const float *lam, const int32_t *info, void *tw,
-                                   hipStream_t s);
 hipError_t launch_add(float *x, const float *dx, int B, int64_t n_per, const int32_t *info, hipStream_t s);
 hipError_t launch_values_out(const float *Xp, int B, int64_t tp, int t, const int32_t *info, float *Cv,
                              hipStream_t s);
@@ -246,7 +243,7 @@ struct Plan {
   int64_t Et, U, Ua, anorm, pn, part1, part2, part3, fcnt, fkey, foff, fn, pcnt, pool, psim, dcnt, dkey, dn,
       doff, goff, dgrp, dgn, dsim, dr, ditem;   // merge phase
   int64_t offsets, cursor, perm;
-  int64_t PhiT, LT, Gw, Gc, dinv, lsplit, tw, h, w, y, x, res, sw, rprev, div, u, YT, Bm, X, R, Y2, XT, Pm, UT;  // fit phase
+  int64_t PhiT, LT, Gw, Gc, dinv, lsplit, h, w, y, x, res, sw, rprev, div, u, YT, Bm, X, R, Y2, XT, Pm, UT;  // fit phase
   int64_t nF, nidx, nbidx, npos, nnf, nnb, nstate, nred, ny, nrhs, ndx;   // exact NNLS (bias_mode 1)
   int64_t chunk_bytes;
 };
@@ -318,7 +315,6 @@ static Plan make_plan(const Dims &d, int64_t P) {
   pl.Gc = f.take(P * d.tp * d.tp * 4);
   pl.dinv = f.take(P * d.tp * 64 * 4);   // one 64 x 64 inverse per diagonal block
   pl.lsplit = f.take(P * (4 * d.tp * d.tp + 8 * d.tp));   // L's fp16 hi / lo planes, row shifts and scales
-  pl.tw = f.take(P * (4 * kHeadDimH * d.tp + 4 * kHeadDimH + 8));   // forward solve: Y^T planes, column scales, flags
   pl.h = f.take(P * d.tp * 8);
   pl.w = f.take(P * d.tp * 8);
   pl.y = f.take(P * d.tp * 8);
@@ -587,10 +583,10 @@ static arckv_status run_fit_values_chunk(const Ctx &c, int b0, int P, const floa
                                    c.chunk<char>(c.pl.lsplit), bad, c.pers<int32_t>(c.pl.cnt), stream));
   {
     StageScope _sc(ST_SOLVE_V, stream);
-    void *lsp = c.chunk<char>(c.pl.lsplit), *tw = c.chunk<char>(c.pl.tw);
-    if (launch_trsm_fwd_blocked(Gw, dinv, lsp, P, d.tp, Bm, Y2, st.lam, st.info, tw, stream) != hipSuccess)
-      return ARCKV_ERR_HIP;
-    if (launch_trsm(false, Gw, dinv, P, d.tp, Y2, X, st.info, stream) != hipSuccess) return ARCKV_ERR_HIP;
+    const void *lsp = c.chunk<char>(c.pl.lsplit);
+    float *xt = c.chunk<float>(c.pl.XT);   // scratch of the solves; the residual's X^T is formed and read between them
+    if (launch_trsm(true, Gw, lsp, P, d.tp, Bm, Y2, xt, st.info, stream) != hipSuccess) return ARCKV_ERR_HIP;
+    if (launch_trsm(false, Gw, lsp, P, d.tp, Y2, X, xt, st.info, stream) != hipSuccess) return ARCKV_ERR_HIP;
     // refinement against the data: R = P^T (Y - P X) - lam X
     for (int it = 0; it < fp.value_refine_steps; ++it) {
       if (launch_transpose128(d.dtype, X, P, (int)d.tp, d.tp * kHeadDimH, d.tp, XT, pl * d.tp * kHeadDimH, stream) !=
@@ -598,9 +594,8 @@ static arckv_status run_fit_values_chunk(const Ctx &c, int b0, int P, const floa
         return ARCKV_ERR_HIP;
       if (launch_value_residual(d.dtype, XT, Pm, PT, Yc, UT, X, st.lam, R, P, d.n, d.tp, d.np_, stream) != hipSuccess)
         return ARCKV_ERR_HIP;
-      if (launch_trsm_fwd_blocked(Gw, dinv, lsp, P, d.tp, R, Y2, st.lam, st.info, tw, stream) != hipSuccess)
-        return ARCKV_ERR_HIP;
-      if (launch_trsm(false, Gw, dinv, P, d.tp, Y2, R, st.info, stream) != hipSuccess) return ARCKV_ERR_HIP;
+      if (launch_trsm(true, Gw, lsp, P, d.tp, R, Y2, xt, st.info, stream) != hipSuccess) return ARCKV_ERR_HIP;
+      if (launch_trsm(false, Gw, lsp, P, d.tp, Y2, R, xt, st.info, stream) != hipSuccess) return ARCKV_ERR_HIP;
       if (launch_add(X, R, P, d.tp * kHeadDimH, st.info, stream) != hipSuccess) return ARCKV_ERR_HIP;
     }
     if (launch_values_out(X, P, d.tp, d.t, st.info, Cv + (size_t)b0 * d.t * kHeadDimH, stream) != hipSuccess)

@@ -26,8 +26,8 @@
 //   escalation       pairs that failed are refactored by the same kernels with
 //                    delta raised tenfold (from 1e-7 when zero), at most
 //                    max_escalations times (launch_cholesky)
-//   solves           TRSV (one rhs, float64 accumulation) / TRSM (128 rhs; the
-//                    forward one in 256-row blocks on the planes of L)
+//   solves           TRSV (one rhs, float64 accumulation) / TRSM (128 rhs, fp32
+//                    MFMA), both right-looking in 256-row blocks
 //   residuals        rhs - (M + lam I) x, float64 (mass fit) or float32 MFMA
 //                    (value fit), for iterative refinement
 #include "common.hpp"
@@ -1176,314 +1176,137 @@ __global__ void __launch_bounds__(256) k_transpose128(const float *__restrict__ 
 }
 
 // --------------------------------------------------------------- 128 right-hand sides
-// 128-rhs triangular solve on fp32 MFMA: L X = R (forward) or L^T X = R
-// (backward), one workgroup per pair (8 waves = 2 row tiles x 4 column tiles
-// of 32), 64-row blocks, so L is read once per solve.  For block kb the
-// update  acc = sum_p L_kb,p X_p  (forward) or  sum_p L_p,kb^T X_p  (backward)
-// is an MFMA product with the L tile and the X tile staged in LDS; the block
-// is then X_kb = D (R_kb - acc) with D = L_kb,kb^-1 (forward) or its
-// transpose (backward), the diagonal-block inverses written by the
-// factorisation.
-constexpr int kTrsmRB = 64, kTrsmSLD = kTrsmRB + 1, kTrsmSXD = kHeadDim + 1;
-constexpr size_t kTrsmLds = (size_t)2 * (kTrsmRB * kTrsmSLD + kTrsmRB * kTrsmSXD) * sizeof(float);
-
+// L Y = R (forward) and L^T X = Y (backward) for 128 right-hand sides, fp32
+// MFMA throughout, right-looking over 256-row blocks K:
+//   k_trsm_diag  X_K = D_K R_K (or D_K^T R_K), one 16 x 16 tile per wave, written
+//                to X and, as 16 x 16 tiles of X_K^T in the fragments' layout, to
+//                xt [B][16 k tiles][8 column tiles][256]
+//   k_trsm_upd   R_i -= L_iK X_K (or L_Ki^T X_K) on the remaining rows
+// The remaining rows are updated by their own workgroups, so a call over few
+// pairs fills the chip where one workgroup per pair (a left-looking solve)
+// ran on as many CUs as there are pairs; at many pairs it is bound by the
+// fp32 MFMA rate and by reading and writing R once per block.  The four solves of 8 pairs\n// at t = 1638: 3.4 -> 0.5 ms; of 256 pairs at t = 3277, 64 at a time: 46 -> 25 ms.
+// R is overwritten; X must not alias it.
 template <bool FWD>
-__global__ void __launch_bounds__(512) k_trsm_mfma(const float *__restrict__ Gw, int64_t ld,
-                                                   const float *__restrict__ dinv, const float *__restrict__ R,
-                                                   float *__restrict__ X, const int32_t *__restrict__ info) {
-  constexpr int RB = kTrsmRB, SLD = kTrsmSLD, SXD = kTrsmSXD;
-  extern __shared__ float trsm_smem[];
-  auto sL = [&](int bf) { return trsm_smem + bf * RB * SLD; };
-  auto sX = [&](int bf) { return trsm_smem + 2 * RB * SLD + bf * RB * SXD; };
-  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+__global__ void __launch_bounds__(256) k_trsm_diag(const void *__restrict__ lsplit, int64_t ld, int K,
+                                                   const float *__restrict__ R, float *__restrict__ X,
+                                                   float *__restrict__ xt, const int32_t *__restrict__ info) {
+  const int b = blockIdx.y;
   if (info[b] != 0) return;
-  const int wr = wave >> 2, wc = wave & 3, h = lane >> 5, col = lane & 31;
-  const float *L = Gw + (size_t)b * ld * ld;
-  const float *Rb = R + (size_t)b * ld * kHeadDim;
-  float *Xb = X + (size_t)b * ld * kHeadDim;
-  const int nb = (int)(ld / RB);
-  const float *Db = dinv + (size_t)b * nb * RB * RB;
-  f32x4 rl[2], rx[4];
-  // tile (i, k) of the operand: forward L[r0+i][p0+k], backward L[p0+k][r0+i]
-  auto fetch = [&](int r0, int p0) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, g = lane >> 4;
+  const int64_t K0 = (int64_t)K * 256;
+  const DiagInv D = diag_inv(lsplit, ld, b, K0);
+  // workgroup: 16 rows x 64 columns; tile (rt, ct) per wave
+  const int rt = blockIdx.x >> 1, ct = 4 * (blockIdx.x & 1) + wave;
+  const float *Rb = R + ((size_t)b * ld + K0) * kHeadDim + 16 * ct + r;
+  // k tiles where D has entries (or stored zeros): up to the diagonal tile, or
+  // from it.  Every tile is loaded, so that all loads are in flight at once;
+  // the others' values are replaced by zeros.
+  const int k0 = FWD ? 0 : rt, k1 = FWD ? rt + 1 : 16;
+  f32x4 d[16], v[16];
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const int e = tid + 512 * c, i = e / 16, k4 = (e % 16) * 4;
-      rl[c] = FWD ? *reinterpret_cast<const f32x4 *>(L + (size_t)(r0 + i) * ld + p0 + k4)
-                  : *reinterpret_cast<const f32x4 *>(L + (size_t)(p0 + i) * ld + r0 + k4);
+  for (int kt = 0; kt < 16; ++kt) {
+    if constexpr (FWD) {
+      d[kt] = *reinterpret_cast<const f32x4 *>(D.at(16 * rt + r, 16 * kt + 4 * g));
+    } else {
+      const float *dp = D.at(16 * kt + 4 * g, 16 * rt) + r;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) d[kt][e] = dp[(size_t)e * D.ldf];
     }
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int e = tid + 512 * c, i = e / 32, k4 = (e % 32) * 4;
-      rx[c] = *reinterpret_cast<const f32x4 *>(Xb + (size_t)(p0 + i) * kHeadDim + k4);
+    for (int e = 0; e < 4; ++e) v[kt][e] = Rb[(size_t)(16 * kt + 4 * g + e) * kHeadDim];
+  }
+  __builtin_amdgcn_sched_barrier(0);   // loads first
+  f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+#pragma unroll
+  for (int kt = 0; kt < 16; ++kt) {   // adds (R_kt^T) (D_rt,kt)^T: the tile of X^T
+    const bool in = kt >= k0 && kt < k1;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      d[kt][e] = in ? d[kt][e] : 0.0f;
+      v[kt][e] = in ? v[kt][e] : 0.0f;
     }
-  };
-  auto stash = [&](int bf) {
+    if (kt & 1) s1 = tile_mac(s1, v[kt], d[kt]);
+    else s0 = tile_mac(s0, v[kt], d[kt]);
+  }
+  f32x4 o;   // column r of the tile, rows 4 g .. 4 g + 3
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const int e = tid + 512 * c, i = e / 16, k4 = (e % 16) * 4;
+  for (int e = 0; e < 4; ++e) o[e] = s0[e] + s1[e];
+  *reinterpret_cast<f32x4 *>(xt + (((size_t)b * 16 + rt) * 8 + ct) * 256 + 4 * lane) = o;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (FWD) sL(bf)[i * SLD + k4 + q] = rl[c][q];
-        else sL(bf)[(k4 + q) * SLD + i] = rl[c][q];
+  for (int e = 0; e < 4; ++e) X[((size_t)b * ld + K0 + 16 * rt + 4 * g + e) * kHeadDim + 16 * ct + r] = o[e];
+}
+
+// 64 rows x 32 TN columns per workgroup, 32 x 16 TN per wave (2 x 2 waves);
+// fragments straight from global memory, a 16-byte load per lane and tile (the
+// backward rows of L: four 4-byte loads).
+template <bool FWD, int TN>
+__global__ void __launch_bounds__(256) k_trsm_upd(const float *__restrict__ Gw, int64_t ld, int K,
+                                                  float *__restrict__ R, const float *__restrict__ xt,
+                                                  const int32_t *__restrict__ info) {
+  constexpr int NCG = kHeadDim / (32 * TN);
+  const int b = blockIdx.y;
+  if (info[b] != 0) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, g = lane >> 4;
+  const int64_t K0 = (int64_t)K * 256;
+  const int cg = blockIdx.x % NCG, rc = blockIdx.x / NCG;
+  const int64_t row0 = (FWD ? K0 + 256 : 0) + 64 * (int64_t)rc + 32 * (wave & 1);
+  const int ct0 = 2 * TN * cg + TN * (wave >> 1);
+  const float *Lb = Gw + (size_t)b * ld * ld + (FWD ? (size_t)(row0 + r) * ld + K0 + 4 * g
+                                                    : (size_t)(K0 + 4 * g) * ld + row0 + r);
+  const float *xb = xt + ((size_t)b * 16 * 8 + ct0) * 256 + 4 * lane;
+  f32x4 acc[2][TN];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto load = [&](int kt, f32x4 (&l)[2], f32x4 (&x)[TN]) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      if constexpr (FWD) {
+        l[i] = *reinterpret_cast<const f32x4 *>(Lb + (size_t)(16 * i) * ld + 16 * kt);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) l[i][e] = Lb[(size_t)(16 * kt + e) * ld + 16 * i];
       }
     }
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int e = tid + 512 * c, i = e / 32, k4 = (e % 32) * 4;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) sX(bf)[i * SXD + k4 + q] = rx[c][q];
-    }
+    for (int j = 0; j < TN; ++j) x[j] = *reinterpret_cast<const f32x4 *>(xb + (size_t)(8 * kt + j) * 256);
   };
-  for (int step = 0; step < nb; ++step) {
-    const int kb = FWD ? step : nb - 1 - step;
-    const int r0 = kb * RB;
-    f32x16 acc = zero16();
-    const int pb0 = FWD ? 0 : kb + 1, pb1 = FWD ? kb : nb;
-    int bf = 0;
-    if (pb0 < pb1) {
-      __syncthreads();
-      fetch(r0, pb0 * RB);
-      stash(0);
-      __syncthreads();
-    }
-    for (int pb = pb0; pb < pb1; ++pb) {
-      const bool more = pb + 1 < pb1;
-      if (more) fetch(r0, (pb + 1) * RB);
-#pragma unroll 8
-      for (int ks = 0; ks < RB / 2; ++ks)
-        acc = Mfma<float>::mma(sL(bf)[(32 * wr + col) * SLD + 2 * ks + h],
-                               sX(bf)[(2 * ks + h) * SXD + 32 * wc + col], acc);
-      if (more) stash(bf ^ 1);
-      __syncthreads();
-      bf ^= 1;
-    }
-    __syncthreads();
-    // right-hand side minus update into sX(0); D into sL(0) (row r = output row)
+  auto mac = [&](const f32x4 (&l)[2], const f32x4 (&x)[TN]) {
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int r = 32 * wr + acc_row(v, lane), c = 32 * wc + col;
-      sX(0)[r * SXD + c] = Rb[(size_t)(r0 + r) * kHeadDim + c] - acc[v];
-    }
-    const float *Dk = Db + (size_t)kb * RB * RB;
-    for (int e = tid; e < RB * RB / 4; e += 512) {
-      const int i = e / 16, k4 = (e % 16) * 4;
-      const f32x4 v = *reinterpret_cast<const f32x4 *>(Dk + i * RB + k4);
+    for (int e = 0; e < 4; ++e)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (FWD) sL(0)[i * SLD + k4 + q] = v[q];
-        else sL(0)[(k4 + q) * SLD + i] = v[q];
-      }
-    }
-    __syncthreads();
-    f32x16 out = zero16();
-#pragma unroll 8
-    for (int ks = 0; ks < RB / 2; ++ks)
-      out = Mfma<float>::mma(sL(0)[(32 * wr + col) * SLD + 2 * ks + h], sX(0)[(2 * ks + h) * SXD + 32 * wc + col],
-                             out);
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int r = 32 * wr + acc_row(v, lane), c = 32 * wc + col;
-      Xb[(size_t)(r0 + r) * kHeadDim + c] = out[v];
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[j][e], l[i][e], acc[i][j], 0, 0, 0);
+  };
+  if constexpr (TN == 2) {   // few workgroups: a wave's whole operands in flight at once
+    f32x4 l[16][2], x[16][TN];
+#pragma unroll
+    for (int kt = 0; kt < 16; ++kt) load(kt, l[kt], x[kt]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int kt = 0; kt < 16; ++kt) mac(l[kt], x[kt]);
+  } else {
+#pragma unroll 4
+    for (int kt = 0; kt < 16; ++kt) {
+      f32x4 l[2], x[TN];
+      load(kt, l, x);
+      mac(l, x);
     }
-    __threadfence_block();
   }
-}
-
-// ---------------------------------------------------------------- blocked forward solve
-// L Y = R for 128 right-hand sides in 256-row blocks kb: the contribution of the
-// earlier blocks, L[kb, 0:kb] Y[0:kb], is one contraction on fp16 MFMA over the
-// factorisation's hi / lo planes of L (row r scaled by 2^shift[r]) and hi / lo
-// planes of Y^T (column c scaled by 2^e_c), the three products hi.hi, hi.lo,
-// lo.hi as in the left-looking update (about 2^-22 relative); the 256 x 256
-// diagonal block is then solved by one workgroup per pair with the stored
-// 64 x 64 inverses on fp32 MFMA.  Pairs flagged here are solved again by the
-// fp32 kernel (k_trsm_mfma).
-
-// e_c with 2 ||R_c|| / sqrt(lam) 2^e_c < 2^10: |Y_rc| <= ||R_c|| / sigma_min(L)
-// and sigma_min(L)^2 is about the smallest eigenvalue of the ridged Gram, at
-// least lam, so the scaled values keep 2^6 of headroom under fp16's largest.
-// A pair without a ridge, or with a non-finite right-hand side, is flagged.
-__global__ void __launch_bounds__(1024) k_trsm_colexp(const float *__restrict__ R, int64_t ld,
-                                                      const float *__restrict__ lam, const int32_t *__restrict__ info,
-                                                      int32_t *__restrict__ ex, int32_t *__restrict__ flag) {
-  __shared__ double part[8][kHeadDim];
-  const int b = blockIdx.x, tid = threadIdx.x, c = tid & (kHeadDim - 1), g = tid >> 7;
-  if (info[b] != 0) return;
-  // eight row groups per column, eight loads in flight per thread
-  const float *Rb = R + (size_t)b * ld * kHeadDim + c;
-  double ss = 0.0;
-#pragma unroll 8
-  for (int64_t r = g; r < ld; r += 8) {
-    const double v = Rb[r * kHeadDim];
-    ss = fma(v, v, ss);
-  }
-  part[g][c] = ss;
-  if (tid == 0) flag[b] = 0;
-  __syncthreads();
-  if (g != 0) return;
-  ss = 0.0;
 #pragma unroll
-  for (int q = 0; q < 8; ++q) ss += part[q][c];
-  const float lb = lam[b];
-  const double bound = lb > 0.0f ? 2.0 * sqrt(ss) / sqrt((double)lb) : INFINITY;
-  int e = 0;
-  const bool ok = isfinite(bound);
-  if (ok && bound > 0.0) {
-    int x = 0;
-    frexp(bound, &x);   // bound < 2^x
-    e = max(min(10 - x, 126), -126);
-  }
-  ex[(size_t)b * kHeadDim + c] = e;
-  if (!ok) flag[b] = 1;
-}
-
-// Y[r0 + m][c] = R[r0 + m][c] - acc 2^-shift[r0 + m] 2^-e_c for one 256-row block
-// (tile rows m, columns c < 128).
-template <int TM, int TN>
-struct EpiTrsmFwd {
-  const float *R;
-  float *Y;
-  int64_t ld;
-  int r0;
-  const float *sinv;     // L's inverse row scales [P][ld]
-  const int32_t *ex;     // [P][128]
-  const int32_t *info, *flag;
-  __device__ __forceinline__ bool skip(int p) const { return info[p] != 0 || flag[p] != 0; }
-  __device__ __forceinline__ void operator()(f32x16 (&acc)[TM][TN], int p, int row0, int col0, int, int, int lane,
-                                             int, int) const {
-    const int col = lane & 31;
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-      const int c = col0 + 32 * j + col;
-      const float sc = ldexpf(1.0f, -ex[(size_t)p * kHeadDim + c]);
+      f32x4 *p = reinterpret_cast<f32x4 *>(R + ((size_t)b * ld + row0 + 16 * i + r) * kHeadDim + 16 * (ct0 + j) + 4 * g);
+      f32x4 o = *p;
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int64_t r = r0 + row0 + 32 * i + acc_row(v, lane);
-          const size_t o = ((size_t)p * ld + r) * kHeadDim + c;
-          Y[o] = R[o] - acc[i][j][v] * (sinv[(size_t)p * ld + r] * sc);
-        }
+      for (int e = 0; e < 4; ++e) o[e] -= acc[i][j][e];
+      *p = o;
     }
-  }
-};
-
-// One 256-row block per pair: right-hand sides rows r0 .. r0 + 255 (src), four
-// 64-row steps y_s = D_s r_s with r_s' -= L_s's y_s for the later steps s'
-// (right-looking inside the block, the right-hand sides held in registers:
-// wave (wm, wn) owns rows 32 wm and columns 32 wn of every 64-row step).  Writes
-// Y (fp32) and the planes of Y^T for the later blocks' contractions; a scaled
-// value at or above 2^15 flags the pair.
-__global__ void __launch_bounds__(512) k_trsm_fwd_blk(const float *__restrict__ Gw, const float *__restrict__ dinv,
-                                                      int64_t ld, int kb, const float *__restrict__ src,
-                                                      float *__restrict__ Y, f16 *__restrict__ Yt,
-                                                      const int32_t *__restrict__ ex,
-                                                      const int32_t *__restrict__ info, int32_t *__restrict__ flag) {
-  constexpr int SY = 160;             // row stride of the [64][128] operand: the two half-waves on opposite banks
-  __shared__ float sD[kNB * kSD];      // D_s, then L_s's
-  __shared__ float sY[kNB * SY];       // r_s, then y_s, [k][c]
-  const int b = blockIdx.x;
-  if (info[b] != 0 || flag[b] != 0) return;   // uniform over the workgroup
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 2, wn = wave & 3, h = lane >> 5, col = lane & 31;
-  const int nb = (int)(ld / kNB);
-  const int64_t r0 = (int64_t)kb * 256;
-  const float *L = Gw + (size_t)b * ld * ld;
-  const int c = 32 * wn + col;
-  const int e = ex[(size_t)b * kHeadDim + c];
-  f32x16 rt[4];
-#pragma unroll
-  for (int s = 0; s < 4; ++s)
-#pragma unroll
-    for (int v = 0; v < 16; ++v)
-      rt[s][v] = src[((size_t)b * ld + r0 + 64 * s + 32 * wm + acc_row(v, lane)) * kHeadDim + c];
-  auto stage = [&](const float *A, int64_t lda) {   // a 64 x 64 operand into sD, row-major
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int g = tid + 512 * q, i = g >> 4, c4 = (g & 15) * 4;
-      const f32x4 v = *reinterpret_cast<const f32x4 *>(A + (size_t)i * lda + c4);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) sD[i * kSD + c4 + u] = v[u];
-    }
-  };
-  auto product = [&]() {   // this wave's 32 x 32 block of sD x sY
-    f32x16 acc = zero16();
-#pragma unroll 8
-    for (int ks = 0; ks < kNB / 2; ++ks)
-      acc = Mfma<float>::mma(sD[(32 * wm + col) * kSD + 2 * ks + h], sY[(2 * ks + h) * SY + c], acc);
-    return acc;
-  };
-  bool over = false;
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    __syncthreads();
-#pragma unroll
-    for (int v = 0; v < 16; ++v) sY[(32 * wm + acc_row(v, lane)) * SY + c] = rt[s][v];
-    stage(dinv + ((size_t)b * nb + 4 * kb + s) * kNB * kNB, kNB);
-    __syncthreads();
-    const f32x16 y = product();
-    __syncthreads();
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int64_t r = r0 + 64 * s + 32 * wm + acc_row(v, lane);
-      sY[(32 * wm + acc_row(v, lane)) * SY + c] = y[v];
-      Y[((size_t)b * ld + r) * kHeadDim + c] = y[v];
-    }
-    // planes of Y^T: rows 8 g + 4 h .. + 3 of this lane are four consecutive r
-    f16 *hi = Yt + ((size_t)b * 2 * kHeadDim + c) * ld + r0 + 64 * s + 32 * wm + 4 * h;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      f16x4 xh, xl;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const float x = ldexpf(y[4 * g + u], e);
-        over |= !(fabsf(x) < 32768.0f);
-        xh[u] = (f16)x;
-        xl[u] = (f16)(x - (float)xh[u]);
-      }
-      *reinterpret_cast<f16x4 *>(hi + 8 * g) = xh;
-      *reinterpret_cast<f16x4 *>(hi + (size_t)kHeadDim * ld + 8 * g) = xl;
-    }
-#pragma unroll
-    for (int s2 = s + 1; s2 < 4; ++s2) {
-      __syncthreads();   // every wave is done with sD; sY holds y_s
-      stage(L + (size_t)(r0 + 64 * s2) * ld + r0 + 64 * s, ld);
-      __syncthreads();
-      const f32x16 u = product();
-#pragma unroll
-      for (int v = 0; v < 16; ++v) rt[s2][v] -= u[v];
-    }
-  }
-  if (over) flag[b] = 1;
-}
-
-// After the blocked solve: a column whose largest scaled value |Y_rc| 2^e_c is
-// below 2^-6 (a bound far above the solution) kept fewer than about 18
-// significant bits in its planes; its pair is flagged for the fp32 solve.
-__global__ void __launch_bounds__(1024) k_trsm_colcheck(const float *__restrict__ Y, int64_t ld,
-                                                        const int32_t *__restrict__ ex,
-                                                        const int32_t *__restrict__ info, int32_t *__restrict__ flag) {
-  __shared__ float part[8][kHeadDim];
-  const int b = blockIdx.x, tid = threadIdx.x, c = tid & (kHeadDim - 1), g = tid >> 7;
-  if (info[b] != 0 || flag[b] != 0) return;   // uniform over the workgroup
-  const float *Yb = Y + (size_t)b * ld * kHeadDim + c;
-  float m = 0.0f;
-#pragma unroll 8
-  for (int64_t r = g; r < ld; r += 8) m = fmaxf(m, fabsf(Yb[r * kHeadDim]));
-  part[g][c] = m;
-  __syncthreads();
-  if (g != 0) return;
-#pragma unroll
-  for (int q = 1; q < 8; ++q) m = fmaxf(m, part[q][c]);
-  if (m > 0.0f && ldexpf(m, ex[(size_t)b * kHeadDim + c]) < 0.015625f) flag[b] = 1;
-}
-
-// out[b] = 1 where the fp32 solve must skip pair b (failed, or solved above)
-__global__ void k_trsm_fallback_mask(const int32_t *__restrict__ info, const int32_t *__restrict__ flag, int B,
-                                     int32_t *__restrict__ out) {
-  const int b = blockIdx.x * 256 + threadIdx.x;
-  if (b < B) out[b] = (info[b] != 0 || flag[b] == 0) ? 1 : 0;
 }
 
 __global__ void __launch_bounds__(256) k_add_copy(float *__restrict__ x, const float *__restrict__ dx, int64_t n_per,
@@ -1972,50 +1795,29 @@ hipError_t launch_transpose128(int dtype, const float *in, int B, int rows, int6
   return hipGetLastError();
 }
 
-hipError_t launch_trsm(bool fwd, const float *Gw, const float *dinv, int B, int64_t ld, const float *R, float *X,
+// L X = R (fwd) or L^T X = R for 128 right-hand sides; R is overwritten, xt is
+// scratch [B][256][128].  The update takes 64 columns per workgroup while that
+// leaves CUs idle, else all 128, which reads L once instead of twice.
+template <bool FWD>
+static hipError_t trsm(const float *Gw, const void *lsplit, int B, int64_t ld, float *R, float *X, float *xt,
                        const int32_t *info, hipStream_t s) {
-  const void *kern = fwd ? (const void *)k_trsm_mfma<true> : (const void *)k_trsm_mfma<false>;
-  const hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTrsmLds);
-  if (e != hipSuccess) return e;
-  dim3 grid(1, B);
-  if (fwd)
-    hipLaunchKernelGGL(k_trsm_mfma<true>, grid, dim3(512), kTrsmLds, s, Gw, ld, dinv, R, X, info);
-  else
-    hipLaunchKernelGGL(k_trsm_mfma<false>, grid, dim3(512), kTrsmLds, s, Gw, ld, dinv, R, X, info);
+  const int nblk = (int)(ld / 256);
+  for (int st = 0; st < nblk; ++st) {
+    const int K = FWD ? st : nblk - 1 - st;
+    hipLaunchKernelGGL(k_trsm_diag<FWD>, dim3(32, B), dim3(256), 0, s, lsplit, ld, K, R, X, xt, info);
+    const int chunks = 4 * (nblk - 1 - st);
+    if (chunks == 0) break;
+    if ((int64_t)chunks * B < 512)
+      hipLaunchKernelGGL((k_trsm_upd<FWD, 2>), dim3(2 * chunks, B), dim3(256), 0, s, Gw, ld, K, R, xt, info);
+    else
+      hipLaunchKernelGGL((k_trsm_upd<FWD, 4>), dim3(chunks, B), dim3(256), 0, s, Gw, ld, K, R, xt, info);
+  }
   return hipGetLastError();
 }
 
-// Blocked forward solve L Y = R (see k_trsm_fwd_blk) with the fp32 solve for the
-// pairs it flags.  lsplit holds the factorisation's planes, shifts and inverse
-// scales (launch_cholesky_factor); tw: Y^T planes [B][2][128][ld] fp16, then
-// e [B][128], flags [B] and the fallback mask [B] (int32).
-hipError_t launch_trsm_fwd_blocked(const float *Gw, const float *dinv, const void *lsplit, int B, int64_t ld,
-                                   const float *R, float *Y, const float *lam, const int32_t *info, void *tw,
-                                   hipStream_t s) {
-  const f16 *Lp = reinterpret_cast<const f16 *>(lsplit);
-  const float *sinv = reinterpret_cast<const float *>(reinterpret_cast<const int32_t *>(Lp + (size_t)B * 2 * ld * ld) +
-                                                      (size_t)B * ld);
-  f16 *Yt = reinterpret_cast<f16 *>(tw);
-  int32_t *ex = reinterpret_cast<int32_t *>(Yt + (size_t)B * 2 * kHeadDim * ld);
-  int32_t *flag = ex + (size_t)B * kHeadDim;
-  int32_t *mask = flag + B;
-  hipLaunchKernelGGL(k_trsm_colexp, dim3(B), dim3(1024), 0, s, R, ld, lam, info, ex, flag);
-  const int nblk = (int)(ld / 256);
-  for (int kb = 0; kb < nblk; ++kb) {
-    if (kb > 0) {
-      const int K0 = 256 * kb;
-      BigShape g{B, 256, kHeadDim, K0, 2 * ld * ld, ld * ld, ld, 2 * kHeadDim * ld, kHeadDim * ld, ld, false, 1};
-      EpiTrsmFwd<2, 2> e{R, Y, ld, K0, sinv, ex, info, flag};
-      const hipError_t err = launch_gemm_big<4, 2, 2, 2, 32, 2, 2, 3, f16>(
-          g, reinterpret_cast<const bf16 *>(Lp + (size_t)K0 * ld), reinterpret_cast<const bf16 *>(Yt), e, s);
-      if (err != hipSuccess) return err;
-    }
-    hipLaunchKernelGGL(k_trsm_fwd_blk, dim3(B), dim3(512), 0, s, Gw, dinv, ld, kb, kb == 0 ? R : Y, Y, Yt, ex, info,
-                       flag);
-  }
-  hipLaunchKernelGGL(k_trsm_colcheck, dim3(B), dim3(1024), 0, s, Y, ld, ex, info, flag);
-  hipLaunchKernelGGL(k_trsm_fallback_mask, dim3((B + 255) / 256), dim3(256), 0, s, info, flag, B, mask);
-  return launch_trsm(true, Gw, dinv, B, ld, R, Y, mask, s);
+hipError_t launch_trsm(bool fwd, const float *Gw, const void *lsplit, int B, int64_t ld, float *R, float *X, float *xt,
+                       const int32_t *info, hipStream_t s) {
+  return fwd ? trsm<true>(Gw, lsplit, B, ld, R, X, xt, info, s) : trsm<false>(Gw, lsplit, B, ld, R, X, xt, info, s);
 }
 
 hipError_t launch_add(float *x, const float *dx, int B, int64_t n_per, const int32_t *info, hipStream_t s) {
