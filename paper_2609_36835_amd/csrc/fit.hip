@@ -886,56 +886,65 @@ __global__ void __launch_bounds__(1024) k_trsv256(const float *__restrict__ Gw, 
 // (list [P][tp], count [P]): the exact non-negative fit sums only over its free
 // keys (w = 0 elsewhere) and needs each residual only on one side of its
 // partition.  Without a list every key r < t takes part.
-// Stage 1: u_i = m_i - sum_{r<t} Phi[i][r] w_r.  256 queries per workgroup,
-// four per lane (16-byte loads of the L^T rows); wave s sums the compact keys
-// r = s (mod 4) with two accumulator sets, and the four partial sums meet in LDS.
-__global__ void __launch_bounds__(256) k_mass_resid_rows(const float *__restrict__ LT, const float *__restrict__ z,
+// Stage 1: u_i = m_i - sum_{r<t} Phi[i][r] w_r.  64 queries per workgroup, four
+// per lane (16-byte loads of the L^T rows, 256-byte runs); the 32 groups of 16
+// lanes take the compact keys r = group (mod 32), four of them in flight, and
+// their partial sums meet in LDS.  256 queries per workgroup of four waves left
+// a call over few pairs with long serial sums on half of the CUs:
+// 143 -> 48 us a call for 8
+// pairs at n = 4096, t = 1638.
+__global__ void __launch_bounds__(512) k_mass_resid_rows(const float *__restrict__ LT, const float *__restrict__ z,
                                                          const float *__restrict__ m, const double *__restrict__ w,
                                                          int n, int t, int64_t tp, int64_t np_,
                                                          double *__restrict__ u, const int32_t *__restrict__ info,
                                                          const int32_t *__restrict__ list,
                                                          const int32_t *__restrict__ count) {
-  __shared__ double red[4][256];
-  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int NG = 32;
+  __shared__ double red[8][64];
+  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, q = tid & 15, grp = tid >> 4;
   if (info[b] != 0) return;
-  const int i0 = blockIdx.x * 256 + 4 * lane;
-  double a0[4] = {0.0, 0.0, 0.0, 0.0}, a1[4] = {0.0, 0.0, 0.0, 0.0};
-  if (i0 < n) {
-    const float *L = LT + (size_t)b * tp * np_ + i0;   // L^T rows are zero beyond n
-    const double *wb = w + (size_t)b * tp;
-    float zi[4];
+  const int i0 = blockIdx.x * 64 + 4 * q;
+  const float *L = LT + (size_t)b * tp * np_ + i0;   // L^T rows are zero beyond n
+  const double *wb = w + (size_t)b * tp;
+  const int32_t *lb = list ? list + (size_t)b * tp : nullptr;
+  const int c = list ? count[b] : t;
+  float zi[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) zi[k] = i0 + k < n ? z[(size_t)b * n + i0 + k] : 0.0f;
-    auto term = [&](int r, double (&a)[4]) {
-      const f32x4 v = *reinterpret_cast<const f32x4 *>(L + (size_t)r * np_);
-      const double wr = wb[r];
+  for (int k = 0; k < 4; ++k) zi[k] = i0 + k < n ? z[(size_t)b * n + i0 + k] : 0.0f;
+  double a[4] = {0.0, 0.0, 0.0, 0.0};
+  auto term = [&](f32x4 v, double wr) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) a[k] += (double)expf(v[k] - zi[k]) * wr;
-    };
-    if (list) {
-      const int32_t *lb = list + (size_t)b * tp;
-      const int c = count[b];
-      int k = wave;
-      for (; k + 4 < c; k += 8) {
-        term(lb[k], a0);
-        term(lb[k + 4], a1);
-      }
-      if (k < c) term(lb[k], a0);
-    } else {
-      int r = wave;
-      for (; r + 4 < t; r += 8) {
-        term(r, a0);
-        term(r + 4, a1);
-      }
-      if (r < t) term(r, a0);
+    for (int k = 0; k < 4; ++k) a[k] += (double)expf(v[k] - zi[k]) * wr;
+  };
+  int k = grp;
+  for (; k + 3 * NG < c; k += 4 * NG) {
+    f32x4 v[4];
+    double wr[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = lb ? lb[k + e * NG] : k + e * NG;
+      v[e] = *reinterpret_cast<const f32x4 *>(L + (size_t)r * np_);
+      wr[e] = wb[r];
     }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) term(v[e], wr[e]);
+  }
+  for (; k < c; k += NG) {
+    const int r = lb ? lb[k] : k;
+    term(*reinterpret_cast<const f32x4 *>(L + (size_t)r * np_), wb[r]);
   }
 #pragma unroll
-  for (int k = 0; k < 4; ++k) red[wave][4 * lane + k] = a0[k] + a1[k];
+  for (int e = 0; e < 4; ++e) {   // the wave's four groups
+    a[e] += __shfl_xor(a[e], 16, 64);
+    a[e] += __shfl_xor(a[e], 32, 64);
+    if (lane < 16) red[wave][4 * lane + e] = a[e];
+  }
   __syncthreads();
-  const int i = blockIdx.x * 256 + tid;
-  if (i < np_) {
-    const double acc = red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid];
+  if (tid < 64) {
+    const int i = blockIdx.x * 64 + tid;
+    double acc = 0.0;
+#pragma unroll
+    for (int wv = 0; wv < 8; ++wv) acc += red[wv][tid];
     u[(size_t)b * np_ + i] = i < n ? (double)m[(size_t)b * n + i] - acc : 0.0;
   }
 }
@@ -1679,7 +1688,7 @@ hipError_t launch_mass_residual(const float *LT, const float *z, const float *m,
                                 int B, int n, int t, int64_t tp, int64_t np_, double *u, double *res,
                                 const int32_t *info, hipStream_t s, const int32_t *row_list,
                                 const int32_t *row_count, const int32_t *col_list, const int32_t *col_count) {
-  hipLaunchKernelGGL(k_mass_resid_rows, dim3((unsigned)(np_ / 256), B), dim3(256), 0, s, LT, z, m, w, n, t, tp, np_,
+  hipLaunchKernelGGL(k_mass_resid_rows, dim3((unsigned)(np_ / 64), B), dim3(512), 0, s, LT, z, m, w, n, t, tp, np_,
                      u, info, row_list, row_count);
   hipLaunchKernelGGL(k_mass_resid_cols, dim3((unsigned)(tp / (4 * kResKeys)), B), dim3(256), 0, s, LT, z, u, w, lam,
                      n, t, tp, np_, res, info, col_list, col_count);
