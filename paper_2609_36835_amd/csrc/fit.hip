@@ -401,10 +401,9 @@ __global__ void __launch_bounds__(1024) k_chol_diag256(float *__restrict__ Gw, i
 // Left-looking update of the column panel K0 .. K0 + 255:
 // G[K0 + r][K0 + c] -= acc s_r s_c for the tile's entries with c <= r + 63
 // (the lower triangle, up to whole diagonal 64-blocks), s the rows' inverse
-// scales 2^-shift (k_chol_scales; 256 x 256 tiles, 512 threads); per row
-// block of the wave, every old value is loaded before any store so the loads
-// pipeline.
-template <int TM, int TN>
+// scales 2^-shift (k_chol_scales; BM x BN tiles); per row block of the wave,
+// every old value is loaded before any store so the loads pipeline.
+template <int TM, int TN, int BM, int BN>
 struct EpiCholUpd {
   float *G;
   int64_t ld;
@@ -416,15 +415,15 @@ struct EpiCholUpd {
   __device__ __forceinline__ void operator()(f32x16 (&acc)[TM][TN], int p, int row0, int col0, int mt, int nt,
                                              int lane, int, int) const {
     if (info[p] != 0) return;   // uniform over the workgroup
-    // the tile's 256 row and 256 column scales, staged in LDS (the operand
-    // stages are free: the caller synchronised the workgroup before the epilogue)
+    // the tile's row and column scales, staged in LDS (the operand stages are
+    // free: the caller synchronised the workgroup before the epilogue)
     extern __shared__ __attribute__((aligned(1024))) char big_smem[];
     float *ssc = reinterpret_cast<float *>(big_smem);
     const float *sp = rs + (size_t)p * rs_pair;
-    for (int x = threadIdx.x; x < 512; x += blockDim.x) ssc[x] = sp[(x < 256 ? mt : nt) * 256 + (x & 255)];
+    for (int x = threadIdx.x; x < BM + BN; x += blockDim.x) ssc[x] = sp[x < BM ? mt * BM + x : nt * BN + x - BM];
     __syncthreads();
     float *Gp = G + (size_t)p * ld * ld + (size_t)K0 * ld + K0;
-    const int col = lane & 31, rl = row0 - mt * 256, cl = col0 - nt * 256;
+    const int col = lane & 31, rl = row0 - mt * BM, cl = col0 - nt * BN;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
       float old[TN][16];
@@ -437,7 +436,7 @@ struct EpiCholUpd {
         }
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
-        const float scj = ssc[256 + cl + 32 * j + col];
+        const float scj = ssc[BM + cl + 32 * j + col];
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int r = row0 + 32 * i + acc_row(v, lane), c = col0 + 32 * j + col;
@@ -1632,9 +1631,19 @@ hipError_t launch_cholesky_factor(float *Gw, const float *Gc, int B, int t, int6
       // plane is read once), 256 x 256 tiles down the panel
       const f16 *Ar = Lp + (size_t)K0 * ld;
       BigShape g{B, (int)(ld - K0), kOuter, K0, 2 * ld * ld, ld * ld, ld, 2 * ld * ld, ld * ld, ld, false, 4};
-      EpiCholUpd<2, 4> e{Gw, ld, K0, st.info, sinv + K0, ld};
-      const hipError_t err = launch_gemm_big<4, 2, 2, 4, 32, 2, 2, 2, f16>(
-          g, reinterpret_cast<const bf16 *>(Ar), reinterpret_cast<const bf16 *>(Ar), e, s);
+      const bf16 *Ab = reinterpret_cast<const bf16 *>(Ar);
+      hipError_t err;
+      // 64 x 64 tiles while 256 x 256 ones would leave most CUs without any:
+      // then each slab of a tile waits for its loads, and a tile's time is its
+      // number of slabs, so many small tiles finish sooner (67 -> 19 us a
+      // call at 8 pairs, ld = 1792)
+      if ((int64_t)B * (ld - K0) / 256 < kFewTiles) {
+        EpiCholUpd<1, 1, 64, 64> e{Gw, ld, K0, st.info, sinv + K0, ld};
+        err = launch_gemm_big<2, 2, 1, 1, 32, 2, 2, 4, f16>(g, Ab, Ab, e, s);
+      } else {
+        EpiCholUpd<2, 4, 256, 256> e{Gw, ld, K0, st.info, sinv + K0, ld};
+        err = launch_gemm_big<4, 2, 2, 4, 32, 2, 2, 2, f16>(g, Ab, Ab, e, s);
+      }
       if (err != hipSuccess) return err;
     }
     // the 256 x 256 diagonal block

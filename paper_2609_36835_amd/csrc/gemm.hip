@@ -51,12 +51,36 @@ hipError_t launch_gram(int dtype, const void *X, float *G, float *Gc, int P, int
   EpiSym e{G, Gc, tp * tp, (int)tp};
   if (dtype == ARCKV_BF16) {
     BigShape g2{P, (int)tp, (int)tp, (int)np_, 2 * tp * np_, tp * np_, np_, 2 * tp * np_, tp * np_, np_, true, 4};
+    // few 256 x 256 tiles (small t, few pairs): 128 x 128 ones, two workgroups
+    // per CU (267 -> 140 us at 8 pairs, t = 819, n = 4096)
+    if ((int64_t)P * (tp / 256) * (tp / 256 + 1) / 2 < kFewTiles) {
+      EpiSymBig<2, 2> e3{G, Gc, tp * tp, (int)tp};
+      return launch_gemm_big<2, 2, 2, 2, 32, 2, 2, 2>(g2, (const bf16 *)X, (const bf16 *)X, e3, s);
+    }
     EpiSymBig<2, 4> e2{G, Gc, tp * tp, (int)tp};
     return launch_gemm_big<4, 2, 2, 4, 32, 2, 2, 2>(g2, (const bf16 *)X, (const bf16 *)X, e2, s);
   }
   g.a_pair = g.b_pair = tp * np_;
   g.a_plane = g.b_plane = 0;
   return launch_gemm<float, 1, 1>(g, (const float *)X, (const float *)X, e, s);
+}
+
+// out[r][c] = sum_k A[r][k] B[c][k] (minus lam X) for 128 columns c, split bf16
+// operands.  With fewer 256-row tiles than CUs, 64-row tiles and four stages:
+// a tile's 128 slabs of 32 are then bound by their loads, which three slabs in
+// flight cover (223 -> 89 us at 8 pairs, t =
+// 1638, n = 4096).
+static hipError_t gemm_cols128(const BigShape &g, const bf16 *A, const bf16 *B, float *out, const float *X,
+                               const float *lam, hipStream_t s) {
+  const int64_t pair = (int64_t)g.M * kHeadDim;
+  if ((int64_t)g.batch * g.M / 256 < 2 * kFewTiles) {
+    EpiStoreBig<1, 2> e{out, pair, kHeadDim, X, lam};
+    BigShape g1 = g;
+    g1.group_m = g.M / 64;
+    return launch_gemm_big<2, 2, 1, 2, 32, 2, 2, 4>(g1, A, B, e, s);
+  }
+  EpiStoreBig<2, 2> e{out, pair, kHeadDim, X, lam};
+  return launch_gemm_big<4, 2, 2, 2, 32, 2, 2, 2>(g, A, B, e, s);
 }
 
 // Right-hand side P^T Y: PT [P][planes][tp][np], YT [P][planes][128][np] -> Bm [P][tp][128].
@@ -74,8 +98,7 @@ hipError_t launch_rhs_gemm(int dtype, const void *PT, const void *YT, float *Bm,
   if (dtype == ARCKV_BF16) {
     BigShape g2{P, (int)tp, kHeadDim, (int)np_, 2 * tp * np_, tp * np_, np_, 2 * (int64_t)kHeadDim * np_,
                 (int64_t)kHeadDim * np_, np_, false, (int)(tp / 256)};
-    EpiStoreBig<2, 2> e2{Bm, tp * kHeadDim, kHeadDim, nullptr, nullptr};
-    return launch_gemm_big<4, 2, 2, 2, 32, 2, 2, 2>(g2, (const bf16 *)PT, (const bf16 *)YT, e2, s);
+    return gemm_cols128(g2, (const bf16 *)PT, (const bf16 *)YT, Bm, nullptr, nullptr, s);
   }
   g.a_pair = tp * np_;
   g.a_plane = 0;
@@ -110,8 +133,14 @@ hipError_t launch_value_residual(int dtype, const void *XT, const void *Pm, cons
   if (split) {
     BigShape gb{P, kHeadDim, (int)np_, (int)tp, pl * kHeadDim * tp, kHeadDim * tp, tp, pl * np_ * tp, np_ * tp, tp,
                 false, 1};
-    EpiValueResidBig<2, 2> ep{(bf16 *)UT, pl * kHeadDim * np_, kHeadDim * np_, (int)np_, n, Y};
-    e = launch_gemm_big<2, 4, 2, 2, 32, 2, 2, 2>(gb, (const bf16 *)XT, (const bf16 *)Pm, ep, s);
+    // fewer 256-query tiles than CUs: 64 queries per tile, two workgroups per CU
+    if ((int64_t)P * np_ / 256 < 2 * kFewTiles) {
+      EpiValueResidBig<2, 1> ep{(bf16 *)UT, pl * kHeadDim * np_, kHeadDim * np_, (int)np_, n, Y};
+      e = launch_gemm_big<2, 2, 2, 1, 32, 2, 2, 3>(gb, (const bf16 *)XT, (const bf16 *)Pm, ep, s);
+    } else {
+      EpiValueResidBig<2, 2> ep{(bf16 *)UT, pl * kHeadDim * np_, kHeadDim * np_, (int)np_, n, Y};
+      e = launch_gemm_big<2, 4, 2, 2, 32, 2, 2, 2>(gb, (const bf16 *)XT, (const bf16 *)Pm, ep, s);
+    }
   } else {
     EpiValueResid<false> ep{UT, kHeadDim * np_, 0, (int)np_, n, Y};
     e = launch_gemm<float, 1, 1>(g1, (const float *)XT, (const float *)Pm, ep, s);
@@ -134,8 +163,7 @@ hipError_t launch_value_residual(int dtype, const void *XT, const void *Pm, cons
   if (split) {
     BigShape gb{P, (int)tp, kHeadDim, (int)np_, pl * tp * np_, tp * np_, np_, pl * kHeadDim * np_, kHeadDim * np_, np_,
                 false, (int)(tp / 256)};
-    EpiStoreBig<2, 2> eb{R, tp * kHeadDim, kHeadDim, X, lam};
-    return launch_gemm_big<4, 2, 2, 2, 32, 2, 2, 2>(gb, (const bf16 *)PT, (const bf16 *)UT, eb, s);
+    return gemm_cols128(gb, (const bf16 *)PT, (const bf16 *)UT, R, X, lam, s);
   }
   return launch_gemm<float, 1, 1>(g2, (const float *)PT, (const float *)UT, e2, s);
 }

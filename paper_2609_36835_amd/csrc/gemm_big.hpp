@@ -430,6 +430,10 @@ struct EpiValueResidBig {
   }
 };
 
+// A contraction with fewer large tiles than this (half of the 256 CUs) takes
+// smaller ones where a small-tile form is instantiated.
+constexpr int kFewTiles = 128;
+
 template <int WM, int WN, int TM, int TN, int BK, int NA, int NB, int NS, typename E = bf16, class Epi>
 hipError_t launch_gemm_big(const BigShape &g, const bf16 *A, const bf16 *B, const Epi &epi, hipStream_t s) {
   using C = BigCfg<WM, WN, TM, TN, BK, NA, NB, NS>;
