@@ -147,6 +147,115 @@ __global__ void __launch_bounds__(256) k_rowstats(const T *__restrict__ K, const
   }
 }
 
+// fp32 inputs, few queries in all: a workgroup takes 16 queries and its eight
+// waves every eighth tile of 16 keys, each with its own running maximum, sum and
+// Y; the eight meet in LDS at the end.  Operands go straight from global memory
+// into 16 x 16 x 4 MFMA fragments: lane l = 16 g + r supplies row r, columns
+// 4 g .. 4 g + 3 of a 16 x 16 tile of both operands, and a product X Y^T formed
+// with the operands given as (Y, X) lands in that layout again, so the
+// probabilities feed the value product from their registers.  With 128 queries
+// per workgroup, 256 queries of one pair ran on two CUs: 190 -> 32 us at T = 1024.
+constexpr int kRsFewF32 = 64;   // workgroups of 128 queries, a quarter of the CUs
+
+__global__ void __launch_bounds__(512) k_rowstats_f32_few(const float *__restrict__ K, const float *__restrict__ V,
+                                                          const float *__restrict__ Q, float *__restrict__ z,
+                                                          float *__restrict__ m, float *__restrict__ Y, int Tn,
+                                                          int n, float scale) {
+  constexpr int NW = 8;
+  __shared__ float sO[NW][16 * kHeadDim], smx[NW][16], ssm[NW][16];
+  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 15, g = lane >> 4;
+  const int q0 = blockIdx.x * 16;
+  const float *Kb = K + (size_t)b * Tn * kHeadDim, *Vb = V + (size_t)b * Tn * kHeadDim;
+  f32x4 qf[8], o[8];
+#pragma unroll
+  for (int kk = 0; kk < 8; ++kk) {
+    qf[kk] = *reinterpret_cast<const f32x4 *>(Q + ((size_t)b * n + min(q0 + r, n - 1)) * kHeadDim + 16 * kk + 4 * g);
+    o[kk] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  const float c2 = scale * 1.4426950408889634f;   // exp(s x) = exp2(c2 x)
+  float run_max = -INFINITY, run_sum = 0.0f;
+  for (int k0 = 16 * wave; k0 < Tn; k0 += 16 * NW) {   // uniform over the wave
+    f32x4 kf[8], vf[8];
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk)
+      kf[kk] = *reinterpret_cast<const f32x4 *>(Kb + (size_t)min(k0 + r, Tn - 1) * kHeadDim + 16 * kk + 4 * g);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float *vr = Vb + (size_t)min(k0 + 4 * g + e, Tn - 1) * kHeadDim + r;
+#pragma unroll
+      for (int ct = 0; ct < 8; ++ct) vf[ct][e] = vr[16 * ct];
+    }
+    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+#pragma unroll
+    for (int kk = 0; kk < 8; kk += 2)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kk][e], qf[kk][e], s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kk + 1][e], qf[kk + 1][e], s1, 0, 0, 0);
+      }
+    // this lane: query r, keys k0 + 4 g .. + 3
+    f32x4 p;
+    float bmax = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      p[e] = k0 + 4 * g + e < Tn ? s0[e] + s1[e] : -INFINITY;
+      bmax = fmaxf(bmax, p[e]);
+    }
+    bmax = fmaxf(bmax, __shfl_xor(bmax, 16, 64));
+    bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
+    const float new_max = fmaxf(run_max, bmax);
+    const float alpha = exp2f((run_max - new_max) * c2);
+    run_max = new_max;
+    run_sum *= alpha;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      p[e] = exp2f((p[e] - new_max) * c2);
+      run_sum += p[e];
+    }
+#pragma unroll
+    for (int ct = 0; ct < 8; ++ct) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[ct][e] *= alpha;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[ct][e], p[e], o[ct], 0, 0, 0);
+    }
+  }
+  run_sum += __shfl_xor(run_sum, 16, 64);
+  run_sum += __shfl_xor(run_sum, 32, 64);
+#pragma unroll
+  for (int ct = 0; ct < 8; ++ct)
+    *reinterpret_cast<f32x4 *>(&sO[wave][r * kHeadDim + 16 * ct + 4 * g]) = o[ct];
+  if (g == 0) {
+    smx[wave][r] = run_max;   // -inf and 0 where the wave had no tile
+    ssm[wave][r] = run_sum;
+  }
+  __syncthreads();
+  // four consecutive columns of one query per thread
+  const int qr = tid >> 5, c = 4 * (tid & 31);
+  float M = smx[0][qr];   // wave 0 always has a tile
+#pragma unroll
+  for (int w = 1; w < NW; ++w) M = fmaxf(M, smx[w][qr]);
+  float sum = 0.0f;
+  f32x4 y = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    const float a = exp2f((smx[w][qr] - M) * c2);
+    const f32x4 v = *reinterpret_cast<const f32x4 *>(&sO[w][qr * kHeadDim + c]);
+    sum += a * ssm[w][qr];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) y[e] += a * v[e];
+  }
+  const int q = q0 + qr;
+  if (q >= n) return;
+  const float inv = 1.0f / sum;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) y[e] *= inv;
+  *reinterpret_cast<f32x4 *>(Y + ((size_t)b * n + q) * kHeadDim + c) = y;
+  if (c == 0) {
+    z[(size_t)b * n + q] = M * scale;
+    m[(size_t)b * n + q] = sum;
+  }
+}
 
 // ---------------------------------------------------------------- bf16 path
 // 256 queries per workgroup (8 waves x 32), 64-key tiles in two LDS stages.
@@ -160,22 +269,32 @@ __global__ void __launch_bounds__(256) k_rowstats(const T *__restrict__ K, const
 // those keys in the other half-wave, so four bf16 values are exchanged with a
 // cross-half shuffle per k-step.  Workgroups are remapped so the query tiles of
 // one pair share an XCD (and its L2 copy of that pair's keys and values).
+// KS = 2 splits the keys inside the workgroup: 128 queries, waves 0 .. 3 take
+// keys 0 .. 31 of each tile and waves 4 .. 7 keys 32 .. 63, and the two partial
+// (maximum, sum, Y) meet in LDS at the end.  It is for calls whose 256-query
+// tiles cover at most half of the CUs: twice the workgroups, each with half of
+// the products and exponentials per tile (240 -> 170 us at 8
+// pairs, T = 8192, n = 4096).
 constexpr int kRsQ = 256, kRsK = 64;
 constexpr int kRsKBytes = kRsK * kHeadDim * 2;            // 16 KB
 constexpr int kRsStage = 2 * kRsKBytes;                   // K tile + V^T tile
 
 typedef __attribute__((address_space(3))) void rs_lds_t;
 
+template <int KS>
 __global__ void __launch_bounds__(512, 1) k_rowstats_bf16(const bf16 *__restrict__ K, const bf16 *__restrict__ V,
                                                           const bf16 *__restrict__ Q, float *__restrict__ z,
                                                           float *__restrict__ m, float *__restrict__ Y, int Tn, int n,
                                                           float scale, int qtiles) {
+  constexpr int NSB = 2 / KS, QW = 8 / KS;   // 32-key blocks per wave and tile, query groups of 32
   __shared__ __attribute__((aligned(1024))) char sbuf[2 * kRsStage];
+  __shared__ float smx[KS > 1 ? 128 : 1], ssm[KS > 1 ? 128 : 1];
   const int64_t tile = xcd_remap(blockIdx.x, gridDim.x);
   const int b = (int)(tile / qtiles), qt = (int)(tile % qtiles);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int h = lane >> 5, col = lane & 31;
-  const int q = qt * kRsQ + wave * 32 + col;
+  const int grp = KS > 1 ? wave / QW : 0;   // key half of each tile
+  const int q = qt * (kRsQ / KS) + (wave % QW) * 32 + col;
   const bool qvalid = q < n;
   const bf16 *Kb = K + (size_t)b * Tn * kHeadDim;
   const bf16 *Vb = V + (size_t)b * Tn * kHeadDim;
@@ -234,13 +353,13 @@ __global__ void __launch_bounds__(512, 1) k_rowstats_bf16(const bf16 *__restrict
   for (int cs = 0; cs < 4; ++cs) accY[cs] = zero16();
 
   const int nt = (Tn + kRsK - 1) / kRsK;
-  // S = K Q^T for the 64 keys in the K part of LDS stage st
-  auto scores = [&](int st, f32x16 (&S)[2]) {
+  // S = K Q^T for this wave's keys in the K part of LDS stage st
+  auto scores = [&](int st, f32x16 (&S)[NSB]) {
     const char *sk = sbuf + st * kRsStage;
 #pragma unroll
-    for (int ms = 0; ms < 2; ++ms) {
+    for (int ms = 0; ms < NSB; ++ms) {
       S[ms] = zero16();
-      const int row = 32 * ms + col;
+      const int row = 32 * (ms + grp) + col;
 #pragma unroll
       for (int ks = 0; ks < kHeadDim / 16; ++ks) {
         const bf16x8 a = *reinterpret_cast<const bf16x8 *>(sk + row * 256 + 16 * ((2 * ks + h) ^ (row & 15)));
@@ -255,7 +374,7 @@ __global__ void __launch_bounds__(512, 1) k_rowstats_bf16(const bf16 *__restrict
   // stale stage and are discarded).  Keys therefore run one tile ahead of
   // values: on entry stage (i + 1) & 1 holds K tile i + 1 and stage i & 1
   // holds V^T tile i; V tile i + 1 is in registers.
-  auto body = [&](int i, f32x16 (&S)[2], f32x16 (&Sn)[2]) {
+  auto body = [&](int i, f32x16 (&S)[NSB], f32x16 (&Sn)[NSB]) {
     const int k0 = i * kRsK, st = i & 1;
     if (i + 1 < nt) store_vt(st ^ 1);
     if (i + 2 < nt) {   // stage st: its K tile was read in tile i - 1, before the last barrier
@@ -264,14 +383,14 @@ __global__ void __launch_bounds__(512, 1) k_rowstats_bf16(const bf16 *__restrict
     }
     if (k0 + kRsK > Tn) {   // last tile: keys past Tn get no weight
 #pragma unroll
-      for (int ms = 0; ms < 2; ++ms)
+      for (int ms = 0; ms < NSB; ++ms)
 #pragma unroll
         for (int v = 0; v < 16; ++v)
-          if (k0 + 32 * ms + acc_row(v, lane) >= Tn) S[ms][v] = -INFINITY;
+          if (k0 + 32 * (ms + grp) + acc_row(v, lane) >= Tn) S[ms][v] = -INFINITY;
     }
     float bmax = -INFINITY;
 #pragma unroll
-    for (int ms = 0; ms < 2; ++ms)
+    for (int ms = 0; ms < NSB; ++ms)
 #pragma unroll
       for (int v = 0; v < 16; ++v) bmax = fmaxf(bmax, S[ms][v]);
     bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
@@ -293,7 +412,7 @@ __global__ void __launch_bounds__(512, 1) k_rowstats_bf16(const bf16 *__restrict
     const float mc2 = new_max * c2;
     float psum = 0.0f;
 #pragma unroll
-    for (int ms = 0; ms < 2; ++ms)
+    for (int ms = 0; ms < NSB; ++ms)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const float p = __builtin_amdgcn_exp2f(fmaf(S[ms][v], c2, -mc2));
@@ -303,7 +422,7 @@ __global__ void __launch_bounds__(512, 1) k_rowstats_bf16(const bf16 *__restrict
     run_sum += psum;
     const char *svt = sbuf + st * kRsStage + kRsKBytes;
 #pragma unroll
-    for (int kk = 0; kk < kRsK / 16; ++kk) {
+    for (int kk = 0; kk < 2 * NSB; ++kk) {
       const int ms = kk >> 1, base = 8 * (kk & 1);
       uint32_t pk[4];
 #pragma unroll
@@ -327,7 +446,7 @@ __global__ void __launch_bounds__(512, 1) k_rowstats_bf16(const bf16 *__restrict
 #pragma unroll
       for (int cs = 0; cs < 4; ++cs) {
         const int c = 32 * cs + col;
-        const bf16x8 vf = *reinterpret_cast<const bf16x8 *>(svt + c * 128 + 16 * ((2 * kk + h) ^ ((c >> 1) & 7)));
+        const bf16x8 vf = *reinterpret_cast<const bf16x8 *>(svt + c * 128 + 16 * ((2 * (kk + 2 * grp) + h) ^ ((c >> 1) & 7)));
         accY[cs] = Mfma<bf16>::mma(vf, pf, accY[cs]);
       }
     }
@@ -343,7 +462,7 @@ __global__ void __launch_bounds__(512, 1) k_rowstats_bf16(const bf16 *__restrict
   if (nt > 1) load_v(kRsK);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  f32x16 Sa[2], Sb[2];
+  f32x16 Sa[NSB], Sb[NSB];
   scores(0, Sa);
   int i = 0;
   for (; i + 1 < nt; i += 2) {
@@ -352,6 +471,29 @@ __global__ void __launch_bounds__(512, 1) k_rowstats_bf16(const bf16 *__restrict
   }
   if (i < nt) body(i, Sa, Sb);
   run_sum += __shfl_xor(run_sum, 32, 64);
+  if constexpr (KS > 1) {   // the stages are free: every wave is past the last tile's barrier
+    float *sy = reinterpret_cast<float *>(sbuf) + (wave % QW) * 64 * 64 + lane;
+    if (grp == 1) {
+#pragma unroll
+      for (int cs = 0; cs < 4; ++cs)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) sy[(16 * cs + v) * 64] = accY[cs][v];
+      if (h == 0) {
+        smx[(wave % QW) * 32 + col] = run_max;
+        ssm[(wave % QW) * 32 + col] = run_sum;
+      }
+    }
+    __syncthreads();
+    if (grp == 1) return;
+    const float m1 = smx[wave * 32 + col], M = fmaxf(run_max, m1);
+    const float a0 = __builtin_amdgcn_exp2f((run_max - M) * c2), a1 = __builtin_amdgcn_exp2f((m1 - M) * c2);
+    run_max = M;
+    run_sum = run_sum * a0 + ssm[wave * 32 + col] * a1;
+#pragma unroll
+    for (int cs = 0; cs < 4; ++cs)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) accY[cs][v] = accY[cs][v] * a0 + sy[(16 * cs + v) * 64] * a1;
+  }
   if (!qvalid) return;
   const float inv = 1.0f / run_sum;
   float *yrow = Y + ((size_t)b * n + q) * kHeadDim;
@@ -373,11 +515,22 @@ hipError_t launch_rowstats(int dtype, const void *K, const void *V, const void *
                            int B, int T, int n, float scale, hipStream_t s) {
   if (dtype == ARCKV_BF16) {
     const int qtiles = (n + kRsQ - 1) / kRsQ;
-    hipLaunchKernelGGL(k_rowstats_bf16, dim3((unsigned)(qtiles * B)), dim3(512), 0, s, (const bf16 *)K,
-                       (const bf16 *)V, (const bf16 *)Q, z, m, Y, T, n, scale, qtiles);
+    if ((int64_t)qtiles * B <= 128 && T >= kRsK) {   // both key halves of the first tile hold a key
+      const int qt2 = (n + kRsQ / 2 - 1) / (kRsQ / 2);
+      hipLaunchKernelGGL(k_rowstats_bf16<2>, dim3((unsigned)(qt2 * B)), dim3(512), 0, s, (const bf16 *)K,
+                         (const bf16 *)V, (const bf16 *)Q, z, m, Y, T, n, scale, qt2);
+    } else {
+      hipLaunchKernelGGL(k_rowstats_bf16<1>, dim3((unsigned)(qtiles * B)), dim3(512), 0, s, (const bf16 *)K,
+                         (const bf16 *)V, (const bf16 *)Q, z, m, Y, T, n, scale, qtiles);
+    }
     return hipGetLastError();
   }
   dim3 grid((n + 127) / 128, B);
+  if ((int64_t)grid.x * B <= kRsFewF32) {
+    hipLaunchKernelGGL(k_rowstats_f32_few, dim3((n + 15) / 16, B), dim3(512), 0, s, (const float *)K,
+                       (const float *)V, (const float *)Q, z, m, Y, T, n, scale);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_rowstats<float>, grid, dim3(256), 0, s, (const float *)K, (const float *)V, (const float *)Q, z,
                      m, Y, T, n, scale);
   return hipGetLastError();
