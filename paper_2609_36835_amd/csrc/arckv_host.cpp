@@ -44,8 +44,8 @@ hipError_t launch_profiles(int dtype, const void *Q, const void *K, const float 
                            int t, void *Et, float *phi, int B, int T, int n, int64_t Tp, int64_t np_, float scale,
                            hipStream_t s);
 hipError_t launch_phic(int dtype, const void *Q, const void *Ckp, const float *z, void *PhiT, float *LT,
-                       const float *m, double *h, int B, int t, int n, int64_t tp, int64_t np_, float scale,
-                       hipStream_t s);
+                       const float *m, double *h, double *hpart, int B, int t, int n, int64_t tp, int64_t np_,
+                       float scale, hipStream_t s);
 hipError_t launch_zmax(const float *z, int B, int n, float *zmax, hipStream_t s);
 hipError_t launch_pair_norms(int dtype, const void *Q, const void *K, const int32_t *anchors, int P, int n, int T,
                              int t, void *pn, hipStream_t s);
@@ -316,7 +316,7 @@ static Plan make_plan(const Dims &d, int64_t P) {
   pl.dinv = f.take(P * d.tp * 64 * 4);   // one 64 x 64 inverse per diagonal block
   pl.lsplit = f.take(P * (4 * d.tp * d.tp + 8 * d.tp));   // L's fp16 hi / lo planes, row shifts and scales
   pl.h = f.take(P * d.tp * 8);
-  pl.w = f.take(P * d.tp * 8);
+  pl.w = f.take(P * d.tp * 8);   // w .. sw are contiguous (tp is a multiple of 256): launch_phic's hpart
   pl.y = f.take(P * d.tp * 8);
   pl.x = f.take(P * d.tp * 8);
   pl.res = f.take(P * d.tp * 8);
@@ -513,7 +513,8 @@ static arckv_status run_fit_bias_chunk(const Ctx &c, int b0, int P, const void *
       launch_nonfinite(Ck + (size_t)b0 * d.t * kHeadDimH, P, (int64_t)d.t * kHeadDimH, bad, stream) != hipSuccess)
     return ARCKV_ERR_HIP;
   // Phi_C^T (split planes), the logits L^T, and h = Phi_C^T m in one pass
-  STAGE(ST_PHIC, launch_phic(d.dtype, Qc, c.chunk<char>(c.pl.Ckp), zc, PhiT, LT, mc, h, P, d.t, d.n, d.tp, d.np_,
+  // (the solve's five vectors w, y, x, res and sw, not in use yet, hold its parts)
+  STAGE(ST_PHIC, launch_phic(d.dtype, Qc, c.chunk<char>(c.pl.Ckp), zc, PhiT, LT, mc, h, w, P, d.t, d.n, d.tp, d.np_,
                              c.scale, stream));
   STAGE(ST_GRAM_G, launch_gram(d.dtype, PhiT, Gw, Gc, P, d.tp, d.np_, stream));
   STAGE(ST_CHOL_G, launch_cholesky(Gw, Gc, P, d.t, d.tp, fp.delta_beta, fp.max_escalations, st, dinv,
@@ -831,7 +832,8 @@ arckv_status arckv_fit_values(const arckv_problem *prob, const void *K, const vo
     // logits of the compact keys (the exp-part is unused here; z only shifts it)
     const char *Qc = (const char *)Q_ref + (size_t)b0 * d.n * kHeadDimH * c.in_esz();
     STAGE(ST_PHIC, launch_phic(d.dtype, Qc, c.chunk<char>(c.pl.Ckp), nullptr, c.chunk<char>(c.pl.PhiT),
-                               c.chunk<float>(c.pl.LT), nullptr, nullptr, Pc, d.t, d.n, d.tp, d.np_, c.scale, stream));
+                               c.chunk<float>(c.pl.LT), nullptr, nullptr, nullptr, Pc, d.t, d.n, d.tp, d.np_, c.scale,
+                               stream));
     FitState st = fit_state(c, c.pl.st_a, c.pl.info_a, b0);
     CHECK(run_fit_values_chunk(c, b0, Pc, Y, C_k, beta, *p, C_v, st));
   }

@@ -25,6 +25,13 @@ typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 
 enum { MODE_PROFILE = 0, MODE_PHIC = 1 };
 
+// PHIC: where the query range blockIdx.z of pair b leaves its part of h_row:
+// range 0 in hout, range z > 0 in the z-th [pairs][tp] block of hpart.
+__device__ __forceinline__ double *h_slot(double *hout, double *hpart, int b, int64_t tp, int row) {
+  double *base = blockIdx.z == 0 ? hout : hpart + (size_t)(blockIdx.z - 1) * gridDim.y * tp;
+  return base + (size_t)b * tp + row;
+}
+
 template <typename T, int MODE>
 __global__ void __launch_bounds__(256) k_expgen(const T *__restrict__ Q, const void *__restrict__ Bsrc,
                                                 int64_t b_pair_stride, int64_t b_plane_stride, int b_rows,
@@ -33,7 +40,8 @@ __global__ void __launch_bounds__(256) k_expgen(const T *__restrict__ Q, const v
                                                 float *__restrict__ aux, int64_t aux_pair_stride, int n,
                                                 int n_pad, float scale, const int32_t *__restrict__ anchors, int t,
                                                 void *__restrict__ uout, float *__restrict__ ssq, int64_t tp,
-                                                const float *__restrict__ mvec, double *__restrict__ hout) {
+                                                const float *__restrict__ mvec, double *__restrict__ hout,
+                                                double *__restrict__ hpart, int tiles_per) {
   using M = Mfma<T>;
   constexpr int KPL = M::KPL, KSTEP = M::KSTEP, NKS = kHeadDim / KSTEP;
   constexpr bool SPLIT_B = (MODE == MODE_PHIC) && sizeof(T) == 2;   // compact keys kept as bf16 hi + lo
@@ -121,7 +129,8 @@ __global__ void __launch_bounds__(256) k_expgen(const T *__restrict__ Q, const v
   };
   const int row0 = blockIdx.x * 128 + wave * 32;          // first output row of this wave
 
-  for (int i0 = 0; i0 < n_pad; i0 += 64) {
+  const int i_lo = 64 * tiles_per * blockIdx.z, i_hi = min(n_pad, i_lo + 64 * tiles_per);
+  for (int i0 = i_lo; i0 < i_hi; i0 += 64) {
     for (int c = tid; c < 64 * (kHeadDim / EPC); c += 256) {
       int r = c / (kHeadDim / EPC), cc = (c % (kHeadDim / EPC)) * EPC;
       f32x4 v = {0.f, 0.f, 0.f, 0.f};
@@ -176,7 +185,7 @@ __global__ void __launch_bounds__(256) k_expgen(const T *__restrict__ Q, const v
   }
   if (MODE == MODE_PHIC && hout) {
     hsum += __shfl_xor(hsum, 32, 64);
-    if (h == 0) hout[(size_t)b * tp + row] = hsum;
+    if (h == 0) *h_slot(hout, hpart, b, tp, row) = hsum;
   }
 }
 
@@ -212,7 +221,8 @@ __global__ void __launch_bounds__(256, 2) k_expgen_bf16(const bf16 *__restrict__
                                                      int n_pad, float scale, const int32_t *__restrict__ anchors,
                                                      int t, bf16 *__restrict__ uout, float *__restrict__ ssq,
                                                      int64_t tp, const float *__restrict__ mvec,
-                                                     double *__restrict__ hout) {
+                                                     double *__restrict__ hout, double *__restrict__ hpart,
+                                                     int tiles_per) {
   constexpr int NB = MODE == MODE_PHIC ? 2 : 1;           // compact keys kept as bf16 hi + lo
   constexpr int NKS = kHeadDim / 16;
   constexpr int QB = 64 * kHeadDim * 2;                   // one Q stage (16 KB)
@@ -327,7 +337,7 @@ __global__ void __launch_bounds__(256, 2) k_expgen_bf16(const bf16 *__restrict__
     wave_fence();
   };
 
-  const int ntile = n_pad / 64;
+  const int it_lo = tiles_per * blockIdx.z, it_hi = min(n_pad / 64, it_lo + tiles_per);
   // without z (logits only) the shift is zero; the stages stay zero-filled
   if (MODE == MODE_PHIC && !shift && tid < 128) sZ[tid] = 0.0f;
   // profile: destination row of each of this lane's four store passes (row
@@ -339,12 +349,12 @@ __global__ void __launch_bounds__(256, 2) k_expgen_bf16(const bf16 *__restrict__
   }
   // wave-uniform: this wave's 32 rows are all real keys
   const bool rows_full = row0 + 32 <= b_rows;
-  issue_q(0, 0);
+  issue_q(64 * it_lo, it_lo & 1);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  for (int it = 0; it < ntile; ++it) {
+  for (int it = it_lo; it < it_hi; ++it) {
     const int i0 = it * 64, st = it & 1;
-    if (it + 1 < ntile) issue_q(i0 + 64, st ^ 1);
+    if (it + 1 < it_hi) issue_q(i0 + 64, st ^ 1);
     const char *sq = sQ + st * QB;
     if constexpr (MODE == MODE_PROFILE) {
       // E' = 2^(acc c2 - zs2) by the hardware exponential (results below
@@ -451,8 +461,18 @@ __global__ void __launch_bounds__(256, 2) k_expgen_bf16(const bf16 *__restrict__
   }
   if (MODE == MODE_PHIC && hout) {
     hsum += __shfl_xor(hsum, 32, 64);
-    if (h == 0) hout[(size_t)b * tp + row] = hsum;
+    if (h == 0) *h_slot(hout, hpart, b, tp, row) = hsum;
   }
+}
+
+// h += the parts of the query ranges 1 .. parts, in order.
+__global__ void __launch_bounds__(256) k_h_sum(double *__restrict__ h, const double *__restrict__ hpart, int64_t count,
+                                               int parts) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= count) return;
+  double v = h[i];
+  for (int p = 0; p < parts; ++p) v += hpart[(size_t)p * count + i];
+  h[i] = v;
 }
 
 template <int MODE>
@@ -473,32 +493,48 @@ hipError_t launch_profiles(int dtype, const void *Q, const void *K, const float 
     hipLaunchKernelGGL((k_expgen_bf16<MODE_PROFILE>), grid, dim3(256), eg_lds_bytes<MODE_PROFILE>(), s, (const bf16 *)Q, (const bf16 *)K,
                        (int64_t)T * kHeadDim, (int64_t)0, T, zmerge, (bf16 *)Et, Tp * np_, (int64_t)0, phi,
                        (int64_t)T, n, (int)np_, scale, anchors, t, (bf16 *)nullptr, (float *)nullptr, (int64_t)0,
-                       (const float *)nullptr, (double *)nullptr);
+                       (const float *)nullptr, (double *)nullptr, (double *)nullptr, (int)(np_ / 64));
   } else
     hipLaunchKernelGGL((k_expgen<float, MODE_PROFILE>), grid, dim3(256), 0, s, (const float *)Q, K,
                        (int64_t)T * kHeadDim, (int64_t)0, T, zmerge, Et, Tp * np_, (int64_t)0, phi, (int64_t)T,
                        n, (int)np_, scale, anchors, t, (void *)nullptr, (float *)nullptr, (int64_t)0,
-                       (const float *)nullptr, (double *)nullptr);
+                       (const float *)nullptr, (double *)nullptr, (double *)nullptr, (int)(np_ / 64));
   return hipGetLastError();
 }
 
 // Ckp: padded compact keys [B][planes][tp][128]; Phi^T [B][planes][tp][np]; L^T [B][tp][np].
-// With m and h given, also h_r = sum_i Phi[i][r] m_i (float64) [B][tp].
+// With m and h given, also h_r = sum_i Phi[i][r] m_i (float64) [B][tp]; hpart
+// holds kPhicRanges - 1 more [B][tp] blocks of scratch for it.
+// While the 128-row tiles fill less than half of the chip's 512 places (two
+// workgroups per CU), the query sweep of each is cut into up to kPhicRanges
+// ranges with a workgroup each: 230 -> 99 us at 8 pairs, t = 1638, n = 4096 and 234
+// -> 67 us at t = 819.
+constexpr int kPhicRanges = 6;
 hipError_t launch_phic(int dtype, const void *Q, const void *Ckp, const float *z, void *PhiT, float *LT,
-                       const float *m, double *h, int B, int t, int n, int64_t tp, int64_t np_, float scale,
-                       hipStream_t s) {
-  if (h && !m) return hipErrorInvalidValue;   // h = Phi_C^T m needs m
-  dim3 grid(tp / 128, B);
+                       const float *m, double *h, double *hpart, int B, int t, int n, int64_t tp, int64_t np_,
+                       float scale, hipStream_t s) {
+  if (h && (!m || !hpart)) return hipErrorInvalidValue;   // h = Phi_C^T m needs m and the scratch
+  const int64_t groups = tp / 128 * B, tiles = np_ / 64;
+  int64_t ranges = 512 / groups;
+  ranges = ranges < 1 ? 1 : ranges > kPhicRanges ? kPhicRanges : ranges;
+  if (ranges > tiles) ranges = tiles;
+  const int per = (int)((tiles + ranges - 1) / ranges);
+  ranges = (tiles + per - 1) / per;
+  dim3 grid((unsigned)(tp / 128), B, (unsigned)ranges);
   if (dtype == ARCKV_BF16) {
     hipError_t e = eg_set_lds<MODE_PHIC>();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_expgen_bf16<MODE_PHIC>), grid, dim3(256), eg_lds_bytes<MODE_PHIC>(), s, (const bf16 *)Q, (const bf16 *)Ckp,
                        2 * tp * kHeadDim, tp * kHeadDim, t, z, (bf16 *)PhiT, 2 * tp * np_, tp * np_, LT, tp * np_,
-                       n, (int)np_, scale, (const int32_t *)nullptr, 0, (bf16 *)nullptr, (float *)nullptr, tp, m, h);
+                       n, (int)np_, scale, (const int32_t *)nullptr, 0, (bf16 *)nullptr, (float *)nullptr, tp, m, h,
+                       hpart, per);
   } else
     hipLaunchKernelGGL((k_expgen<float, MODE_PHIC>), grid, dim3(256), 0, s, (const float *)Q, Ckp,
                        tp * kHeadDim, (int64_t)0, t, z, PhiT, tp * np_, (int64_t)0, LT, tp * np_, n, (int)np_,
-                       scale, (const int32_t *)nullptr, 0, (void *)nullptr, (float *)nullptr, tp, m, h);
+                       scale, (const int32_t *)nullptr, 0, (void *)nullptr, (float *)nullptr, tp, m, h, hpart, per);
+  if (h && ranges > 1)
+    hipLaunchKernelGGL(k_h_sum, dim3((unsigned)((B * tp + 255) / 256)), dim3(256), 0, s, h, hpart, B * tp,
+                       (int)ranges - 1);
   return hipGetLastError();
 }
 
