@@ -22,58 +22,84 @@ __global__ void __launch_bounds__(256) k_zmax(const float *__restrict__ z, int n
   if (tid == 0) zmax[b] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
 }
 
-// Groups whose cursors fit in LDS (64 KB) take the LDS variant.
-constexpr int kSortLdsGroups = 16384;
+// Stable counting sort of positions by group, one workgroup of 16 waves per
+// pair: offsets [t+1] and perm [T] (positions grouped by kappa, ascending
+// within each group).  The positions are cut into S contiguous segments of whole
+// 64-position chunks, each with its own row of counters: a wave counts its
+// segment, the counters become each segment's first slot in every group (the
+// segments before it included), and the wave places its chunks in order.  The
+// S t counters are in LDS (kLds, S = 16, 8, 4 or 2, at most kSortLdsCounters);
+// above 16,384 groups there is one segment with its cursors in cursor [B][t].
+// One wave placing every chunk of a pair took 213 us at T = 15,001 and
+// t = 1500; now 28 us.
+constexpr int kSortLdsCounters = 32768;   // 128 KB
 
-// One workgroup per pair.  Produces offsets [t+1] and perm [T] (positions
-// grouped by kappa, ascending position within each group).  The cursors live
-// in LDS (kLds, t <= kSortLdsGroups) or in cursor [B][t] (global scratch).
-// Four waves clear and count; wave 0 alone scans and places, one 64-position
-// chunk at a time in order, which keeps every group in ascending position.
 template <bool kLds>
-__global__ void __launch_bounds__(256) k_group_sort(const int32_t *__restrict__ kappa, int T, int t,
-                                                    int32_t *__restrict__ offsets, int32_t *__restrict__ cursor,
-                                                    int32_t *__restrict__ perm) {
-  __shared__ int32_t lcur[kLds ? kSortLdsGroups : 1];
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+__global__ void __launch_bounds__(1024) k_group_sort(const int32_t *__restrict__ kappa, int T, int t, int S,
+                                                     int32_t *__restrict__ offsets, int32_t *__restrict__ cursor,
+                                                     int32_t *__restrict__ perm) {
+  extern __shared__ int32_t sort_smem[];   // kLds: [S][t] counters
+  __shared__ int32_t wsum[16];
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int32_t *kp = kappa + (size_t)b * T;
   int32_t *off = offsets + (size_t)b * (t + 1);
-  int32_t *cur = kLds ? lcur : cursor + (size_t)b * t;
+  int32_t *cnt = kLds ? sort_smem : cursor + (size_t)b * t;
   int32_t *pm = perm + (size_t)b * T;
-  // every access to cur[] is an atomic, fenced between phases
-  for (int r = tid; r < t; r += 256) atomicExch(&cur[r], 0);
-  if (!kLds) __threadfence();
-  __syncthreads();
-  for (int j = tid; j < T; j += 256) atomicAdd(&cur[kp[j]], 1);
-  if (!kLds) __threadfence();
-  __syncthreads();
-  if (tid >= 64) return;
-  // exclusive scan of the counts
-  int32_t carry = 0;
-  for (int r0 = 0; r0 < t; r0 += 64) {
-    const int r = r0 + lane;
-    int32_t c = r < t ? atomicAdd(&cur[r], 0) : 0;
-    int32_t x = c;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      int32_t y = __shfl_up(x, d, 64);
-      if (lane >= d) x += y;
-    }
-    if (r < t) {
-      off[r] = carry + x - c;
-      atomicExch(&cur[r], carry + x - c);
-    }
-    carry += __shfl(x, 63, 64);
+  const int chunks = (T + 63) / 64, per = (chunks + S - 1) / S;
+  const int lo = min(wave * per, chunks) * 64, hi = min(min((wave + 1) * per, chunks) * 64, T);   // this wave's segment
+  // global counters: every access is an atomic, fenced between phases
+  for (int r = tid; r < S * t; r += 1024) {
+    if (kLds) cnt[r] = 0;
+    else atomicExch(&cnt[r], 0);
   }
-  if (lane == 0) off[t] = carry;
   if (!kLds) __threadfence();
+  __syncthreads();
+  if (kLds) {
+    if (wave < S)
+      for (int j = lo + lane; j < hi; j += 64) atomicAdd(&cnt[wave * t + kp[j]], 1);
+  } else {
+    for (int j = tid; j < T; j += 1024) atomicAdd(&cnt[kp[j]], 1);
+    __threadfence();
+  }
+  __syncthreads();
+  // exclusive scan over (group, segment), a contiguous range of groups per thread
+  const int gper = (t + 1023) / 1024, g0 = min(tid * gper, t), g1 = min(g0 + gper, t);
+  int32_t mine = 0;
+  for (int r = g0; r < g1; ++r)
+    for (int s = 0; s < S; ++s) mine += kLds ? cnt[s * t + r] : atomicAdd(&cnt[r], 0);
+  int32_t x = mine;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int32_t y = __shfl_up(x, d, 64);
+    if (lane >= d) x += y;
+  }
+  if (lane == 63) wsum[wave] = x;
+  __syncthreads();
+  int32_t base = x - mine;
+  for (int w = 0; w < wave; ++w) base += wsum[w];
+  for (int r = g0; r < g1; ++r) {
+    off[r] = base;
+    for (int s = 0; s < S; ++s) {
+      const int32_t c = kLds ? cnt[s * t + r] : atomicAdd(&cnt[r], 0);
+      if (kLds) cnt[s * t + r] = base;
+      else atomicExch(&cnt[r], base);
+      base += c;
+    }
+  }
+  if (tid == 1023) off[t] = base;   // the last thread's range ends at t
+  if (!kLds) __threadfence();
+  __syncthreads();
+  if (wave >= S) return;
+  int32_t *cur = cnt + (kLds ? wave * t : 0);
   int nbits = 1;
   while ((1 << nbits) < t) ++nbits;
   const uint64_t lanemask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  for (int j0 = 0; j0 < T; j0 += 64) {
+  int32_t next = lo + lane < hi ? kp[lo + lane] : 0;
+  for (int j0 = lo; j0 < hi; j0 += 64) {
     const int j = j0 + lane;
-    const bool in = j < T;
-    const int32_t r = in ? kp[j] : 0;
+    const bool in = j < hi;
+    const int32_t r = next;
+    next = j + 64 < hi ? kp[j + 64] : 0;
     uint64_t match = __ballot(in);
     for (int bit = 0; bit < nbits; ++bit) {
       uint64_t bal = __ballot(in && ((r >> bit) & 1));
@@ -81,10 +107,10 @@ __global__ void __launch_bounds__(256) k_group_sort(const int32_t *__restrict__ 
     }
     const int rank = __popcll(match & lanemask);
     const int leader = __ffsll((long long)match) - 1;
-    int32_t base = 0;
-    if (in && lane == leader) base = atomicAdd(&cur[r], __popcll(match));
-    base = __shfl(base, leader < 0 ? 0 : leader, 64);
-    if (in && base + rank < T) pm[base + rank] = j;
+    int32_t slot = 0;
+    if (in && lane == leader) slot = atomicAdd(&cur[r], __popcll(match));
+    slot = __shfl(slot, leader < 0 ? 0 : leader, 64);
+    if (in && slot + rank < T) pm[slot + rank] = j;
   }
 }
 
@@ -190,10 +216,18 @@ hipError_t launch_group_merge(int dtype, const void *K, const float *phi, const 
                               const int32_t *anchors, int B, int T, int t, int64_t tp, float lambda,
                               int32_t *offsets, int32_t *cursor, int32_t *perm, float *Ck, void *Ckp,
                               hipStream_t s) {
-  if (t <= kSortLdsGroups)
-    hipLaunchKernelGGL(k_group_sort<true>, dim3(B), dim3(256), 0, s, kappa, T, t, offsets, cursor, perm);
-  else
-    hipLaunchKernelGGL(k_group_sort<false>, dim3(B), dim3(256), 0, s, kappa, T, t, offsets, cursor, perm);
+  int S = 16;
+  while (S > 1 && (int64_t)S * t > kSortLdsCounters) S /= 2;
+  if (S > 1) {
+    const int lds = S * t * (int)sizeof(int32_t);
+    const hipError_t e =
+        hipFuncSetAttribute((const void *)k_group_sort<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            kSortLdsCounters * (int)sizeof(int32_t));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_group_sort<true>, dim3(B), dim3(1024), lds, s, kappa, T, t, S, offsets, cursor, perm);
+  } else {
+    hipLaunchKernelGGL(k_group_sort<false>, dim3(B), dim3(1024), 0, s, kappa, T, t, 1, offsets, cursor, perm);
+  }
   dim3 grid((unsigned)(tp / 4), B);
   if (dtype == ARCKV_BF16)
     hipLaunchKernelGGL(k_group_merge<bf16>, grid, dim3(256), 0, s, (const bf16 *)K, phi, offsets, perm, anchors, T,
