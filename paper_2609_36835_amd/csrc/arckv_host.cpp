@@ -48,10 +48,11 @@ hipError_t launch_phic(int dtype, const void *Q, const void *Ckp, const float *z
                        float scale, hipStream_t s);
 hipError_t launch_zmax(const float *z, int B, int n, float *zmax, hipStream_t s);
 hipError_t launch_pair_norms(int dtype, const void *Q, const void *K, const int32_t *anchors, int P, int n, int T,
-                             int t, void *pn, hipStream_t s);
+                             int t, void *pn, const AssignLists &L, hipStream_t s);
 hipError_t launch_anchor_profiles(int dtype, const void *Q, const void *K, const int32_t *anchors,
                                   const float *zmerge, int P, int n, int T, int t, int64_t tp, int64_t np_,
-                                  float scale, float *Ua, double *anorm, void *U, hipStream_t s);
+                                  float scale, float *Ua, double *anorm, double *npart, int64_t npart_blocks, void *U,
+                                  hipStream_t s);
 hipError_t launch_assign_finalize(int dtype, const void *K, const uint64_t *part1, const uint64_t *part2,
                                   const uint32_t *part3, int MT, int TR, int64_t Np, const int32_t *anchors,
                                   const float *phi, const float *zmerge, const void *pn, int P, int T, int t, int n,
@@ -458,9 +459,11 @@ static arckv_status run_merge_chunk(const Ctx &c, int b0, int P, const void *K, 
   const int mt_used = (int)(d.tp / TR);
   STAGE(ST_PROFILES, launch_profiles(d.dtype, Qc, Kc, zm, anc, d.t, Et, phi + (size_t)b0 * d.T, P, d.T, d.n, d.Tp,
                                      d.np_, c.scale, stream));
-  STAGE(ST_ANCHOR_PROF, launch_pair_norms(d.dtype, Qc, Kc, anc, P, d.n, d.T, d.t, pn, stream));
+  STAGE(ST_ANCHOR_PROF, launch_pair_norms(d.dtype, Qc, Kc, anc, P, d.n, d.T, d.t, pn, L, stream));
+  // part1, which the contraction fills later, holds the parts of the anchors' norms
   STAGE(ST_ANCHOR_PROF, launch_anchor_profiles(d.dtype, Qc, Kc, anc, zm, P, d.n, d.T, d.t, d.tp, d.np_, c.scale, Ua,
-                                               anorm, U, stream));
+                                               anorm, reinterpret_cast<double *>(part1), d.MT * d.Tp / d.tp, U,
+                                               stream));
   STAGE(ST_ASSIGN, launch_assign_gemm(d.dtype, U, Et, part1, part2, part3, P, d.t, d.tp, Tc, d.Tp, d.np_, stream));
   STAGE(ST_FINALIZE, launch_assign_finalize(d.dtype, Kc, part1, part2, part3, mt_used, TR, Tc, anc, phib, zm, pn, P,
                                             d.T, d.t, d.n, c.scale, kap, L, stream));

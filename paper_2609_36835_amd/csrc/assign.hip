@@ -55,52 +55,60 @@ __device__ inline void pair_block(int nx, int P, int &x, int &b) {
   x = (int)(tile % nx);
 }
 
-// ---------------------------------------------------------------- norms
+// ---------------------------------------------------------------- counters and norms
+// Clears the work-list counters, the statistics and pn of P pairs.
+__global__ void __launch_bounds__(256) k_assign_clear(AssignLists L, AssignPair *__restrict__ pn, int P) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < P * kAssignStats) L.stats[i] = 0;
+  if (i >= P) return;
+  L.fcnt[i] = L.dcnt[i] = L.pcnt[i] = 0;
+  pn[i] = {0.0, 0.0};
+}
+
+// Sum of squares of a 128-element row, in float64, loaded 16 bytes at a time.
+template <typename E>
+__device__ inline double row_sumsq(const E *x) {
+  typedef __attribute__((__vector_size__(16))) E EV;
+  constexpr int N = 16 / sizeof(E);
+  double ss = 0.0;
+#pragma unroll 4
+  for (int k = 0; k < kHeadDim; k += N) {
+    const EV w = *reinterpret_cast<const EV *>(x + k);
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const double v = (double)(float)w[u];
+      ss = fma(v, v, ss);
+    }
+  }
+  return ss;
+}
+
 // pn[b] = {max_i ||q_i||, max_r ||k_{s_r}||}, in float64, rounded up by one part
-// in 1e12 so that the bounds built on them stay upper bounds.
+// in 1e12 so that the bounds built on them stay upper bounds.  A row per
+// thread over the n queries and the t anchors; the workgroups' maxima meet in
+// an integer maximum of the (non-negative) doubles' bits.
 template <typename E>
 __global__ void __launch_bounds__(256) k_pair_norms(const E *__restrict__ Q, const E *__restrict__ K,
                                                     const int32_t *__restrict__ anchors, int n, int T, int t,
                                                     AssignPair *__restrict__ pn) {
-  __shared__ double red[2][4];
-  const int b = blockIdx.x, tid = threadIdx.x;
-  double mq = 0.0, ma = 0.0;
-  for (int i = tid; i < n; i += 256) {
-    const E *q = Q + ((size_t)b * n + i) * kHeadDim;
-    double ss = 0.0;
-    for (int k = 0; k < kHeadDim; ++k) {
-      const double v = (double)(float)q[k];
-      ss = fma(v, v, ss);
-    }
-    mq = fmax(mq, ss);
-  }
-  for (int r = tid; r < t; r += 256) {
-    const E *kr = K + ((size_t)b * T + anchors[(size_t)b * t + r]) * kHeadDim;
-    double ss = 0.0;
-    for (int k = 0; k < kHeadDim; ++k) {
-      const double v = (double)(float)kr[k];
-      ss = fma(v, v, ss);
-    }
-    ma = fmax(ma, ss);
-  }
+  const int b = blockIdx.y, i = blockIdx.x * 256 + threadIdx.x;
+  const bool isq = i < n;
+  double v = 0.0;
+  if (isq) v = row_sumsq(Q + ((size_t)b * n + i) * kHeadDim);
+  else if (i - n < t) v = row_sumsq(K + ((size_t)b * T + anchors[(size_t)b * t + i - n]) * kHeadDim);
+  double mq = isq ? v : 0.0, ma = isq ? 0.0 : v;
   for (int m = 32; m >= 1; m >>= 1) {
     mq = fmax(mq, __shfl_xor(mq, m, 64));
     ma = fmax(ma, __shfl_xor(ma, m, 64));
   }
-  if ((tid & 63) == 0) {
-    red[0][tid >> 6] = mq;
-    red[1][tid >> 6] = ma;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    double a = 0.0, c = 0.0;
-    for (int w = 0; w < 4; ++w) {
-      a = fmax(a, red[0][w]);
-      c = fmax(c, red[1][w]);
-    }
-    pn[b].qmax = sqrt(a) * (1.0 + 1e-12);
-    pn[b].amax = sqrt(c) * (1.0 + 1e-12);
-  }
+  if ((threadIdx.x & 63) != 0) return;
+  auto top = [](double *p, double ss) {
+    if (ss > 0.0)
+      atomicMax(reinterpret_cast<unsigned long long *>(p),
+                (unsigned long long)__double_as_longlong(sqrt(ss) * (1.0 + 1e-12)));
+  };
+  top(&pn[b].qmax, mq);
+  top(&pn[b].amax, ma);
 }
 
 // Logit of one (query, key) element from the eight 16-wide slices of the head
@@ -121,15 +129,15 @@ __device__ inline double exp32_err(double A, double Z) {
 // ---------------------------------------------------------------- anchor profiles
 // Precise anchor profiles e_ir = exp(s q_i.k_{s_r} - z_merge) for bf16 inputs:
 // logits from eight MFMA slices added in a fixed order (kSliceTerms), the
-// exponential in fp32 (exp32_err).  Ua [P][tp][np] float32 (zero for i >= n),
-// anorm [P][tp] = ||e_r||_2, accumulated in float64.  A workgroup
-// owns 128 anchors (32 per wave, kept as MFMA B fragments) and sweeps all
-// queries in tiles of 64.
+// exponential in fp32 (exp32_err).  Ua [P][tp][np] float32 (zero for i >= n);
+// npart [ranges][P][tp] the squared norms' parts, accumulated in float64.  A
+// workgroup owns 128 anchors (32 per wave, kept as MFMA B fragments) and one
+// range of the queries, swept in tiles of 64.
 __global__ void __launch_bounds__(256) k_prof_anchor_bf16(const bf16 *__restrict__ Q, const bf16 *__restrict__ K,
                                                           const int32_t *__restrict__ anchors,
                                                           const float *__restrict__ zmerge, int n, int T, int t,
-                                                          int64_t tp, int64_t np_, double scale,
-                                                          float *__restrict__ Ua, double *__restrict__ anorm) {
+                                                          int64_t tp, int64_t np_, int tiles_per, double scale,
+                                                          float *__restrict__ Ua, double *__restrict__ npart) {
   constexpr int SQ = kHeadDim + 8;
   __shared__ __attribute__((aligned(16))) bf16 sQ[64 * SQ];
   const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -155,15 +163,16 @@ __global__ void __launch_bounds__(256) k_prof_anchor_bf16(const bf16 *__restrict
                           : f32x4{0.f, 0.f, 0.f, 0.f};
     }
   };
-  fetch_q(0);
-  for (int i0 = 0; i0 < np_; i0 += 64) {
+  const int i_lo = 64 * tiles_per * blockIdx.z, i_hi = (int)min(np_, (int64_t)i_lo + 64 * tiles_per);
+  fetch_q(i_lo);
+  for (int i0 = i_lo; i0 < i_hi; i0 += 64) {
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int c = tid + 256 * u, rr = c / 16, cc = (c % 16) * 8;
       *reinterpret_cast<f32x4 *>(&sQ[rr * SQ + cc]) = qn[u];
     }
-    if (i0 + 64 < np_) fetch_q(i0 + 64);
+    if (i0 + 64 < i_hi) fetch_q(i0 + 64);
     __syncthreads();
 #pragma unroll
     for (int ms = 0; ms < 2; ++ms) {
@@ -192,7 +201,7 @@ __global__ void __launch_bounds__(256) k_prof_anchor_bf16(const bf16 *__restrict
     }
   }
   ss += __shfl_xor(ss, 32, 64);
-  if (rvalid && h == 0) anorm[(size_t)b * tp + r] = sqrt(ss);
+  if (rvalid && h == 0) npart[((size_t)blockIdx.z * gridDim.y + b) * tp + r] = ss;
 }
 
 // fp32 inputs: the same profiles with float64 logits and exponentials (one
@@ -201,7 +210,7 @@ __global__ void __launch_bounds__(256) k_prof_anchor_f32(const float *__restrict
                                                          const int32_t *__restrict__ anchors,
                                                          const float *__restrict__ zmerge, int n, int T, int t,
                                                          int64_t tp, int64_t np_, double scale,
-                                                         float *__restrict__ Ua, double *__restrict__ anorm) {
+                                                         float *__restrict__ Ua, double *__restrict__ npart) {
   __shared__ double kr[kHeadDim];
   __shared__ double red[4];
   const int b = blockIdx.y, r = blockIdx.x, tid = threadIdx.x;
@@ -224,24 +233,30 @@ __global__ void __launch_bounds__(256) k_prof_anchor_f32(const float *__restrict
   ss = wave_sum(ss);
   if ((tid & 63) == 0) red[tid >> 6] = ss;
   __syncthreads();
-  if (tid == 0) anorm[(size_t)b * tp + r] = sqrt(red[0] + red[1] + red[2] + red[3]);
+  if (tid == 0) npart[(size_t)b * tp + r] = red[0] + red[1] + red[2] + red[3];
 }
 
-// The contraction's anchor operand U [P][tp][np]: Ua / anorm, stored in fp16
+// anorm [P][tp] = ||e_r||_2 from the parts of its square, and the
+// contraction's anchor operand U [P][tp][np]: Ua / anorm, stored in fp16
 // scaled by 2^15 for bf16 inputs (one rounding of the fp32 product) or in
 // fp32; rows r >= t and columns i >= n are zero.  One wave per row, four
 // consecutive columns per lane (np_ is a multiple of 256).
 template <typename T>
-__global__ void __launch_bounds__(256) k_anchor_u(const float *__restrict__ Ua, const double *__restrict__ anorm,
-                                                  int n, int t, int64_t tp, int64_t np_, float uscale,
-                                                  T *__restrict__ U) {
+__global__ void __launch_bounds__(256) k_anchor_u(const float *__restrict__ Ua, const double *__restrict__ npart,
+                                                  int ranges, int n, int t, int64_t tp, int64_t np_, float uscale,
+                                                  double *__restrict__ anorm, T *__restrict__ U) {
   typedef __attribute__((__vector_size__(4 * sizeof(T)))) T T4;
   const int b = blockIdx.y, lane = threadIdx.x & 63;
   const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (r >= tp) return;
   T *urow = U + ((size_t)b * tp + r) * np_;
   const float *arow = Ua + ((size_t)b * tp + r) * np_;
-  const double nr = r < t ? anorm[(size_t)b * tp + r] : 0.0;
+  double nr = 0.0;
+  if (r < t) {
+    for (int z = 0; z < ranges; ++z) nr += npart[((size_t)z * gridDim.y + b) * tp + r];
+    nr = sqrt(nr);
+    if (lane == 0) anorm[(size_t)b * tp + r] = nr;
+  }
   const float inv = nr > 0.0 ? (float)((double)uscale / nr) : 0.0f;
   for (int64_t i = 4 * lane; i < np_; i += 256) {
     f32x4 a = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -310,12 +325,7 @@ __device__ inline float threshold_a(float s1, const BoundA &bd) {
 
 template <typename E>
 __device__ inline double row_norm(const E *x) {
-  double ss = 0.0;
-  for (int k = 0; k < kHeadDim; ++k) {
-    const double v = (double)(float)x[k];
-    ss = fma(v, v, ss);
-  }
-  return sqrt(ss) * (1.0 + 1e-12);
+  return sqrt(row_sumsq(x)) * (1.0 + 1e-12);
 }
 
 // Candidate anchors of one key after pass A.  For each anchor tile the best
@@ -1097,32 +1107,50 @@ __global__ void __launch_bounds__(256) k_assign_exact(const E *__restrict__ Q, c
 }
 
 // ---------------------------------------------------------------- launchers
+// Clears the work lists' counters and the statistics, then pn.
 hipError_t launch_pair_norms(int dtype, const void *Q, const void *K, const int32_t *anchors, int P, int n, int T,
-                             int t, void *pn, hipStream_t s) {
+                             int t, void *pn, const AssignLists &L, hipStream_t s) {
+  hipLaunchKernelGGL(k_assign_clear, dim3((unsigned)((P * kAssignStats + 255) / 256)), dim3(256), 0, s, L,
+                     (AssignPair *)pn, P);
+  const dim3 g((unsigned)(((int64_t)n + t + 255) / 256), P);
   if (dtype == ARCKV_BF16)
-    hipLaunchKernelGGL(k_pair_norms<bf16>, dim3(P), dim3(256), 0, s, (const bf16 *)Q, (const bf16 *)K, anchors, n,
-                       T, t, (AssignPair *)pn);
+    hipLaunchKernelGGL(k_pair_norms<bf16>, g, dim3(256), 0, s, (const bf16 *)Q, (const bf16 *)K, anchors, n, T, t,
+                       (AssignPair *)pn);
   else
-    hipLaunchKernelGGL(k_pair_norms<float>, dim3(P), dim3(256), 0, s, (const float *)Q, (const float *)K, anchors,
-                       n, T, t, (AssignPair *)pn);
+    hipLaunchKernelGGL(k_pair_norms<float>, g, dim3(256), 0, s, (const float *)Q, (const float *)K, anchors, n, T, t,
+                       (AssignPair *)pn);
   return hipGetLastError();
 }
 
+// npart: scratch for npart_blocks [P][tp] blocks of doubles (at least one).
+// While the 128-anchor groups are fewer than kAnchorGroups workgroups (four per
+// CU), each one's query sweep is cut into up to eight ranges: 8 pairs with
+// n = 4096, t = 819 took 155 us whole, 36 us in ranges; n = 3000, t = 1500: 130
+// and 44 us.
+constexpr int kAnchorGroups = 1024;
 hipError_t launch_anchor_profiles(int dtype, const void *Q, const void *K, const int32_t *anchors,
                                   const float *zmerge, int P, int n, int T, int t, int64_t tp, int64_t np_,
-                                  float scale, float *Ua, double *anorm, void *U, hipStream_t s) {
+                                  float scale, float *Ua, double *anorm, double *npart, int64_t npart_blocks, void *U,
+                                  hipStream_t s) {
   if (dtype == ARCKV_BF16) {
-    hipLaunchKernelGGL(k_prof_anchor_bf16, dim3((unsigned)((t + 127) / 128), P), dim3(256), 0, s, (const bf16 *)Q,
-                       (const bf16 *)K, anchors, zmerge, n, T, t, tp, np_, (double)scale, Ua, anorm);
+    const int64_t groups = (int64_t)((t + 127) / 128) * P, tiles = np_ / 64;
+    int64_t ranges = kAnchorGroups / groups;
+    for (int64_t lim : {(int64_t)8, npart_blocks, tiles}) ranges = ranges < lim ? ranges : lim;
+    if (ranges < 1) ranges = 1;
+    const int per = (int)((tiles + ranges - 1) / ranges);
+    ranges = (tiles + per - 1) / per;
+    hipLaunchKernelGGL(k_prof_anchor_bf16, dim3((unsigned)((t + 127) / 128), P, (unsigned)ranges), dim3(256), 0, s,
+                       (const bf16 *)Q, (const bf16 *)K, anchors, zmerge, n, T, t, tp, np_, per, (double)scale, Ua,
+                       npart);
     if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
     hipLaunchKernelGGL(k_anchor_u<f16>, dim3((unsigned)(tp / 4), P), dim3(256), 0, s, (const float *)Ua,
-                       (const double *)anorm, n, t, tp, np_, kProfScale, (f16 *)U);
+                       (const double *)npart, (int)ranges, n, t, tp, np_, kProfScale, anorm, (f16 *)U);
   } else {
     hipLaunchKernelGGL(k_prof_anchor_f32, dim3((unsigned)t, P), dim3(256), 0, s, (const float *)Q, (const float *)K,
-                       anchors, zmerge, n, T, t, tp, np_, (double)scale, Ua, anorm);
+                       anchors, zmerge, n, T, t, tp, np_, (double)scale, Ua, npart);
     if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
     hipLaunchKernelGGL(k_anchor_u<float>, dim3((unsigned)(tp / 4), P), dim3(256), 0, s, (const float *)Ua,
-                       (const double *)anorm, n, t, tp, np_, 1.0f, (float *)U);
+                       (const double *)npart, 1, n, t, tp, np_, 1.0f, anorm, (float *)U);
   }
   return hipGetLastError();
 }
@@ -1138,17 +1166,12 @@ hipError_t launch_fill_i32(int32_t *p, int64_t count, int32_t v, hipStream_t s) 
   return hipGetLastError();
 }
 
-// Pass A decision (clears the counters first).  MT anchor tiles of TR rows;
+// Pass A decision.  MT anchor tiles of TR rows;
 // Np = the partials' row stride (compacted key columns).
 hipError_t launch_assign_finalize(int dtype, const void *K, const uint64_t *part1, const uint64_t *part2,
                                   const uint32_t *part3, int MT, int TR, int64_t Np, const int32_t *anchors,
                                   const float *phi, const float *zmerge, const void *pn, int P, int T, int t, int n,
                                   float scale, int32_t *kappa, const AssignLists &L, hipStream_t s) {
-  hipError_t e = launch_fill_i32(L.fcnt, P, 0, s);
-  if (e == hipSuccess) e = launch_fill_i32(L.dcnt, P, 0, s);
-  if (e == hipSuccess) e = launch_fill_i32(L.pcnt, P, 0, s);
-  if (e == hipSuccess) e = launch_fill_i32(L.stats, (int64_t)P * kAssignStats, 0, s);
-  if (e != hipSuccess) return e;
   const dim3 gf((unsigned)((T + 255) / 256), P);
   if (dtype == ARCKV_BF16)
     hipLaunchKernelGGL(k_assign_finalize<bf16>, gf, dim3(256), 0, s, part1, part2, part3, MT, Np, anchors,
