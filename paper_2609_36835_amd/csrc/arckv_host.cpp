@@ -87,7 +87,7 @@ hipError_t launch_mass_solve(float *Gw, const float *Gc, float *dinv, void *lspl
 hipError_t launch_cholesky(float *Gw, const float *Gc, int B, int t, int64_t ld, float delta0, int max_esc,
                            FitState st, float *dinv, void *lsplit, const int32_t *bad, int32_t *cnt,
                            hipStream_t s);
-hipError_t launch_nonfinite(const float *a, int B, int64_t per, int32_t *bad, hipStream_t s);
+hipError_t launch_nonfinite(const FiniteCheck &f, int B, int32_t *bad, hipStream_t s);
 hipError_t launch_cholesky_factor(float *Gw, const float *Gc, int B, int t, int64_t ld, float delta0, int max_esc,
                                   FitState st, float *dinv, void *lsplit, hipStream_t s);
 hipError_t launch_nnls(const float *Gc, float *Gw, const double *h, const float *LT, const float *z, const float *m,
@@ -509,12 +509,9 @@ static arckv_status run_fit_bias_chunk(const Ctx &c, int b0, int P, const void *
   float *dinv = c.chunk<float>(c.pl.dinv);
   // pairs whose inputs (z, m, C_k, and Y when given) hold a non-finite value report info = -1
   int32_t *bad = c.pers<int32_t>(c.pl.bad) + b0;
-  if (launch_fill_i32(bad, P, 0, stream) != hipSuccess || launch_nonfinite(zc, P, d.n, bad, stream) != hipSuccess ||
-      (Y && launch_nonfinite(Y + (size_t)b0 * d.n * kHeadDimH, P, (int64_t)d.n * kHeadDimH, bad, stream) !=
-                hipSuccess) ||
-      launch_nonfinite(mc, P, d.n, bad, stream) != hipSuccess ||
-      launch_nonfinite(Ck + (size_t)b0 * d.t * kHeadDimH, P, (int64_t)d.t * kHeadDimH, bad, stream) != hipSuccess)
-    return ARCKV_ERR_HIP;
+  const FiniteCheck fc{{zc, mc, Ck + (size_t)b0 * d.t * kHeadDimH, Y ? Y + (size_t)b0 * d.n * kHeadDimH : nullptr},
+                       {d.n, d.n, (int64_t)d.t * kHeadDimH, (int64_t)d.n * kHeadDimH}};
+  if (launch_nonfinite(fc, P, bad, stream) != hipSuccess) return ARCKV_ERR_HIP;
   // Phi_C^T (split planes), the logits L^T, and h = Phi_C^T m in one pass
   // (the solve's five vectors w, y, x, res and sw, not in use yet, hold its parts)
   STAGE(ST_PHIC, launch_phic(d.dtype, Qc, c.chunk<char>(c.pl.Ckp), zc, PhiT, LT, mc, h, w, P, d.t, d.n, d.tp, d.np_,
@@ -567,11 +564,9 @@ static arckv_status run_fit_values_chunk(const Ctx &c, int b0, int P, const floa
   // pairs whose inputs (Y, C_k, beta) hold a non-finite value report info = -1
   // (a failed mass fit leaves beta NaN)
   int32_t *bad = c.pers<int32_t>(c.pl.bad) + b0;
-  if (launch_fill_i32(bad, P, 0, stream) != hipSuccess ||
-      launch_nonfinite(Yc, P, (int64_t)d.n * kHeadDimH, bad, stream) != hipSuccess ||
-      launch_nonfinite(Ck + (size_t)b0 * d.t * kHeadDimH, P, (int64_t)d.t * kHeadDimH, bad, stream) != hipSuccess ||
-      launch_nonfinite(beta + (size_t)b0 * d.t, P, d.t, bad, stream) != hipSuccess)
-    return ARCKV_ERR_HIP;
+  const FiniteCheck fc{{Yc, Ck + (size_t)b0 * d.t * kHeadDimH, beta + (size_t)b0 * d.t, nullptr},
+                       {(int64_t)d.n * kHeadDimH, (int64_t)d.t * kHeadDimH, d.t, 0}};
+  if (launch_nonfinite(fc, P, bad, stream) != hipSuccess) return ARCKV_ERR_HIP;
   // P^T for the Gram and right-hand side, and P (query-major) for the refinement residuals
   STAGE(ST_PHAT, launch_phat(d.dtype, LT, c.pers<float>(c.pl.beta_ws) + (size_t)b0 * d.tp, P, d.n, d.t, d.tp,
                              d.np_, PT, fp.value_refine_steps > 0 ? Pm : nullptr, stream));

@@ -14,6 +14,14 @@ struct FitState {
   int32_t *info;   // [P] status (0 ok, > 0 failed pivot + 1, < 0 see arckv.h and fit.hip)
 };
 
+// Arrays of one fit checked for non-finite values, per[q] floats per pair each
+// (a[q] null: none).
+struct FiniteCheck {
+  static constexpr int kMax = 4;
+  const float *a[kMax];
+  int64_t per[kMax];
+};
+
 // Work arrays of the exact non-negative fit ([P][tp] unless noted).
 struct NnlsWork {
   int32_t *F, *idx, *bidx, *pos;   // free flags, free and bound lists, slot of each key
