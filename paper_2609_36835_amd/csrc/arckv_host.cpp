@@ -204,9 +204,10 @@ static Dims make_dims(const arckv_problem *p, int t) {
 // Candidates per cached key, on average, that the assignment's pool can hold.
 // The pool and every list of the later passes live in E^T's place, which is
 // dead once the contraction has left its partials, so the pool is sized by
-// what E^T leaves free: per key 4 + 8 bytes for each candidate, and
-// kPassDEntryBytes for each entry of the float64 pass (one per key and one
-// per kPassDSplit candidates); 36 for the smallest E^T row (256 fp16 values).
+// what E^T leaves free: per key 4 bytes for each candidate and 16 for each query
+// range of its similarity, and kPassDEntryBytes for each entry of the float64
+// pass (one per key and one per kPassDSplit candidates); 11 to 19 for the smallest
+// E^T row (256 fp16 values), 117 for 4096 queries.
 // A key whose list does not fit is decided in float64 over all t anchors,
 // n t float64 exponentials where a pooled candidate costs n fp32 products: on
 // 32K-token caches a pair with 320K-750K candidates (10-23 per key; keys whose
@@ -214,12 +215,12 @@ static Dims make_dims(const arckv_problem *p, int t) {
 // anchor tiles) overflowed a pool of 8 per key, and the float64 pass took
 // 294-1107 ms of a 256-pair call instead of 7.
 constexpr int64_t kPoolPerKeyMax = 256;
-constexpr int64_t kPassDEntryBytes = 36;   // dkey, dn, doff, dgrp, dgn, dr, ditem (4 each), dsim (8)
+constexpr int64_t kPassDEntryBytes = 24;   // dkey, dn, doff, dgrp, dgn, ditem
 
 static int64_t pool_per_key(const Dims &d) {
   // 64 bytes per key are left for the entries' rounding and alignment
   const int64_t room = d.np_ * d.esz - kPassDEntryBytes - 64;
-  const int64_t k = room * kPassDSplit / (12 * kPassDSplit + kPassDEntryBytes);
+  const int64_t k = room * kPassDSplit / ((4 + 16 * query_ranges(d.n)) * kPassDSplit + kPassDEntryBytes);
   const int64_t cap = ((1ll << 30) / d.Tp) > 8 ? (1ll << 30) / d.Tp : 8;   // pool offsets are int32
   const int64_t m = k < kPoolPerKeyMax ? k : kPoolPerKeyMax;
   return m < cap ? m : cap;
@@ -242,7 +243,7 @@ struct Plan {
   // chunk region (offsets relative to chunk base)
   int64_t Ckp;
   int64_t Et, U, Ua, anorm, pn, part1, part2, part3, fcnt, fkey, foff, fn, pcnt, pool, psim, dcnt, dkey, dn,
-      doff, goff, dgrp, dgn, dsim, dr, ditem;   // merge phase
+      doff, goff, dgrp, dgn, ditem;   // merge phase
   int64_t offsets, cursor, perm;
   int64_t PhiT, LT, Gw, Gc, dinv, lsplit, h, w, y, x, res, sw, rprev, div, u, YT, Bm, X, R, Y2, XT, Pm, UT;  // fit phase
   int64_t nF, nidx, nbidx, npos, nnf, nnb, nstate, nred, ny, nrhs, ndx;   // exact NNLS (bias_mode 1)
@@ -280,15 +281,13 @@ static Plan make_plan(const Dims &d, int64_t P) {
     Bump l;
     l.off = pl.Et;
     const int64_t ppk = pool_per_key(d), dcap = pass_d_capacity(d.Tp, ppk);
-    pl.psim = l.take(P * ppk * d.Tp * 8);
-    pl.dsim = l.take(P * dcap * 8);
+    pl.psim = l.take(P * 2 * query_ranges(d.n) * ppk * d.Tp * 8);
     pl.pool = l.take(P * ppk * d.Tp * 4);
     pl.dkey = l.take(P * dcap * 4);
     pl.dn = l.take(P * dcap * 4);
     pl.doff = l.take(P * dcap * 4);
     pl.dgrp = l.take(P * dcap * 4);
     pl.dgn = l.take(P * dcap * 4);
-    pl.dr = l.take(P * dcap * 4);
     pl.ditem = l.take(P * (dcap + 2) * 4);
     if (l.off > m.off) m.off = l.off;   // never with the rule of pool_per_key; keeps the plan safe
   }
@@ -444,12 +443,11 @@ static arckv_status run_merge_chunk(const Ctx &c, int b0, int P, const void *K, 
   const int64_t ppk = pool_per_key(d);
   AssignLists L{c.chunk<int32_t>(c.pl.fcnt), c.chunk<int32_t>(c.pl.fkey),  c.chunk<int32_t>(c.pl.foff),
                 c.chunk<int32_t>(c.pl.fn),   c.chunk<int32_t>(c.pl.pcnt),  c.chunk<int32_t>(c.pl.pool),
-                c.chunk<double>(c.pl.psim),  ppk * d.Tp,                   c.chunk<int32_t>(c.pl.dcnt),
+                c.chunk<double>(c.pl.psim),  ppk * d.Tp, query_ranges(d.n), c.chunk<int32_t>(c.pl.dcnt),
                 c.chunk<int32_t>(c.pl.dkey), c.chunk<int32_t>(c.pl.dn),    c.chunk<int32_t>(c.pl.doff),
                 c.pers<int32_t>(c.pl.astats) + (size_t)b0 * kAssignStats, d.Tp,
                 c.chunk<int32_t>(c.pl.goff), d.Tp / 64 + 2,
-                c.chunk<int32_t>(c.pl.dgrp), c.chunk<int32_t>(c.pl.dgn), c.chunk<double>(c.pl.dsim),
-                c.chunk<int32_t>(c.pl.dr),   c.chunk<int32_t>(c.pl.ditem), pass_d_capacity(d.Tp, ppk)};
+                c.chunk<int32_t>(c.pl.dgrp), c.chunk<int32_t>(c.pl.dgn), c.chunk<int32_t>(c.pl.ditem), pass_d_capacity(d.Tp, ppk)};
   const float *zm = zmax + b0;
   int32_t *kap = kappa + (size_t)b0 * d.T;
   const float *phib = phi + (size_t)b0 * d.T;

@@ -483,12 +483,16 @@ __device__ __forceinline__ void lds_only_barrier() {
 //   rounding of the two profiles and of the partial products.
 // A key whose best similarity exceeds every other candidate's by more than the
 // bound on both is decided; the survivors of the others go to pass D.
-// Work distribution: k_refine_plan lays out each pair's items (goff); a fixed
-// grid of kRefineBlocks workgroups per pair takes items it = blockIdx.x,
-// blockIdx.x + kRefineBlocks, ..., so the chunks of one group with many
+// Work distribution: k_refine_plan lays out each pair's (group, chunk) pieces
+// (goff), and every piece is cut into nspl query ranges, each an item of its own
+// that leaves a part of the similarities (summed in order by k_assign_decide);
+// a fixed grid of kRefineBlocks workgroups per pair takes consecutive runs of
+// items, so few pieces still use many CUs, the chunks of one group with many
 // candidates (keys whose candidates include whole anchor tiles) spread over
-// workgroups instead of running in sequence on one.  The queries are swept in
-// tiles of 128.  Per tile the eight waves form the 64 keys' profiles (one
+// workgroups, and a workgroup with several ranges of one piece sets it up once.
+// One range: 154 us at 8 pairs, T = 8192 (n = 4096); in ranges 95 us (fp32, 2 pairs
+// of T = 1024, n = 256: 100 and 17 us).
+// The queries are swept in tiles of 128.  Per tile the eight waves form the 64 keys' profiles (one
 // 32 x 32 MFMA tile each: a key half by a quarter of the queries) into a
 // shared LDS tile; each wave takes 32 candidates, two per load instruction: a
 // half-wave covers one candidate's 128 queries, four per lane, so every load
@@ -507,7 +511,7 @@ __global__ void __launch_bounds__(512, 2) k_assign_refine(const E *__restrict__ 
   constexpr bool BF = sizeof(E) == 2;
   constexpr int NK = 64, NW = 8, CPW = kRefineCpw, CAP = NW * CPW, QT = 128, SE = QT + 4;
   constexpr int SKB = BF ? kHeadDim + 8 : kHeadDim + 4;   // key-row stride (elements)
-  __shared__ int32_t kpos[NK], koff[NK], kbase[NK + 1], khalf, item_g, item_c0;
+  __shared__ int32_t kpos[NK], koff[NK], kbase[NK + 1], khalf, item_g, item_c0, item_sp;
   __shared__ int32_t cr[CAP];
   __shared__ int32_t ck[CAP];
   __shared__ __attribute__((aligned(16))) E sK[NK * SKB];
@@ -523,26 +527,33 @@ __global__ void __launch_bounds__(512, 2) k_assign_refine(const E *__restrict__ 
   const E *Qb = Q + (size_t)b * n * kHeadDim;
   const float *Uab = Ua + (size_t)b * tp * np_;
   int32_t *pool = L.pool + (size_t)b * L.pcap;
-  double *psim = L.psim + (size_t)b * L.pcap;
+  const int nspl = L.nspl;
+  double *psim = L.psim + (size_t)b * 2 * nspl * L.pcap;
+  const int tiles_per = ((n + QT - 1) / QT + nspl - 1) / nspl;   // query tiles per range
   const int kt = wave >> 2, qsub = wave & 3;   // this wave's key half and query quarter in the profile phase
   const int G = (F + NK - 1) / NK;
   const int32_t *goff = L.goff + (size_t)b * L.gcap;
-  const int items = F > 0 ? goff[G] : 0;
-  int cur = -1;   // the group whose keys are in the shared arrays
-  for (int it = bx; it < items; it += kRefineBlocks) {   // uniform over the workgroup
+  const int items = F > 0 ? goff[G] * nspl : 0;
+  const int run = (items + kRefineBlocks - 1) / kRefineBlocks;
+  int cur = -1, cur_c0 = -1;   // the group and the chunk in the shared arrays
+  for (int it = bx * run; it < min(items, (bx + 1) * run); ++it) {   // uniform over the workgroup
     __syncthreads();   // the previous item is done with the shared arrays
-    if (tid == 0) {   // the group g with goff[g] <= it < goff[g + 1]
+    if (tid == 0) {   // the group g with goff[g] <= piece < goff[g + 1]
+      const int piece = it / nspl;
       int lo = 0, hi = G;
       while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
-        if (goff[mid] <= it) lo = mid;
+        if (goff[mid] <= piece) lo = mid;
         else hi = mid;
       }
       item_g = lo;
-      item_c0 = (it - goff[lo]) * CAP;
+      item_c0 = (piece - goff[lo]) * CAP;
+      item_sp = it - piece * nspl;
     }
     __syncthreads();
-    const int g = item_g, c0 = item_c0;
+    const int g = item_g, c0 = item_c0, sp = item_sp;
+    const bool same = g == cur && c0 == cur_c0;   // another range of the piece set up before
+    cur_c0 = c0;
     if (g != cur) {   // load the group's keys (uniform)
       cur = g;
       const int f0 = g * NK, nk = min(NK, F - f0);
@@ -556,13 +567,16 @@ __global__ void __launch_bounds__(512, 2) k_assign_refine(const E *__restrict__ 
         }
       }
       __syncthreads();
-      if (tid == 0) {
-        int acc = 0;
-        for (int k = 0; k < NK; ++k) {
-          kbase[k] = acc;
-          acc += k < nk ? L.fn[(size_t)b * L.cap + f0 + k] : 0;
+      if (wave == 0) {   // first candidate slot of each key: a prefix sum over the wave
+        const int m = lane < nk ? L.fn[(size_t)b * L.cap + f0 + lane] : 0;
+        int x = m;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+          const int y = __shfl_up(x, d, 64);
+          if (lane >= d) x += y;
         }
-        kbase[NK] = acc;
+        kbase[lane] = x - m;
+        if (lane == 63) kbase[NK] = x;
       }
       for (int x = tid; x < NK * kHeadDim; x += NW * 64) {   // the keys' rows (zero for empty slots)
         const int k = x / kHeadDim, c = x % kHeadDim;
@@ -573,6 +587,7 @@ __global__ void __launch_bounds__(512, 2) k_assign_refine(const E *__restrict__ 
     const int total = kbase[NK];
     {
       const int cn = min(CAP, total - c0);
+      if (!same) {
       __syncthreads();   // the previous chunk is done with cr / ck / khalf
       if (tid == 0) khalf = 0;
       __syncthreads();
@@ -594,13 +609,14 @@ __global__ void __launch_bounds__(512, 2) k_assign_refine(const E *__restrict__ 
         cr[c] = r;
       }
       __syncthreads();
+      }
       const int need = khalf;
+      const int i_lo = QT * tiles_per * sp, i_hi = min(n, i_lo + QT * tiles_per);   // this item's queries
       double acc[CPW / 2];
 #pragma unroll
       for (int u = 0; u < CPW / 2; ++u) acc[u] = 0.0;
       const int cw0 = wave * CPW;   // this wave's candidates cw0 + 2u + h
       const int qo = 4 * col;        // half-wave lane col covers queries i0 + 4 col .. + 3
-      const bool prof = (need >> kt) & 1;   // this wave forms profiles in this chunk
       // Loads are unconditional so that the compiler can count them exactly
       // across the tile loop (a load under a branch may not have been issued,
       // which forces a full drain at the next use): an empty candidate slot
@@ -632,63 +648,70 @@ __global__ void __launch_bounds__(512, 2) k_assign_refine(const E *__restrict__ 
       };
       f32x4 w[CPW / 2];
       if constexpr (BF) {
-        load_q(0);
+        load_q(min(i_lo, n - 1));
         // the same issue order as at the end of each tile (query fragments,
         // then anchor values), so that the counts agree at the loop head
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int u = 0; u < CPW / 2; ++u) w[u] = load_w(0, u);
+        for (int u = 0; u < CPW / 2; ++u) w[u] = load_w(i_lo < n ? i_lo : 0, u);
       }
-      for (int i0 = 0; i0 < n; i0 += QT) {
-        const int nxt = i0 + QT < n ? i0 + QT : i0;   // the last tile reloads itself
+      for (int i0 = i_lo; i0 < i_hi; i0 += QT) {   // none in a range past the last query
+        const int nxt = i0 + QT < i_hi ? i0 + QT : i0;   // the last tile reloads itself
         if constexpr (!BF) {
 #pragma unroll
           for (int u = 0; u < CPW / 2; ++u) w[u] = load_w(i0, u);
         }
         // ---- the 64 keys' profiles on queries [i0, i0 + 128) (bf16: always, so
         // that no load or MFMA of the tile loop sits under a branch)
-        if (BF || prof) {
-          double l[BF ? 1 : 16];
+        if constexpr (BF) {
           f32x16 lsum;
-          if constexpr (BF) {
-            const bf16 *krow = reinterpret_cast<const bf16 *>(sK) + (kt * 32 + col) * SKB + 8 * h;
+          const bf16 *krow = reinterpret_cast<const bf16 *>(sK) + (kt * 32 + col) * SKB + 8 * h;
 #pragma unroll
-            for (int ks = 0; ks < 8; ++ks) {
-              const bf16x8 bk = *reinterpret_cast<const bf16x8 *>(krow + ks * 16);
-              const f32x16 part = Mfma<bf16>::mma(qa[ks], bk, zero16());
-              if (ks == 0) lsum = part;
-              else {
+          for (int ks = 0; ks < 8; ++ks) {
+            const bf16x8 bk = *reinterpret_cast<const bf16x8 *>(krow + ks * 16);
+            const f32x16 part = Mfma<bf16>::mma(qa[ks], bk, zero16());
+            if (ks == 0) lsum = part;
+            else {
 #pragma unroll
-                for (int v = 0; v < 16; ++v) lsum[v] += part[v];
-              }
-            }
-          } else {
-#pragma unroll
-            for (int v = 0; v < 16; ++v) l[v] = 0.0;
-            const float *krow = reinterpret_cast<const float *>(sK) + (kt * 32 + col) * SKB;
-            for (int k = 0; k < kHeadDim; k += 4) {
-              const f32x4 kv = *reinterpret_cast<const f32x4 *>(krow + k);
-#pragma unroll
-              for (int v = 0; v < 16; ++v) {
-                const int qi = i0 + 32 * qsub + acc_row(v, lane);
-                if (qi < n) {
-                  const f32x4 qv = *reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(Qb) +
-                                                                   (size_t)qi * kHeadDim + k);
-#pragma unroll
-                  for (int e = 0; e < 4; ++e) l[v] = fma((double)qv[e], (double)kv[e], l[v]);
-                }
-              }
+              for (int v = 0; v < 16; ++v) lsum[v] += part[v];
             }
           }
 #pragma unroll
           for (int v = 0; v < 16; ++v) {
             const int qi = 32 * qsub + acc_row(v, lane);
-            float ev = 0.0f;
-            if (i0 + qi < n) {
-              if constexpr (BF) ev = __builtin_amdgcn_exp2f(fmaf(lsum[v], c2, -zs2));
-              else ev = (float)exp(s * l[v] - zm);
-            }
+            const float ev = i0 + qi < n ? __builtin_amdgcn_exp2f(fmaf(lsum[v], c2, -zs2)) : 0.0f;
             eS[(kt * 32 + col) * SE + qi] = ev;
+          }
+        } else {
+          // float64 logits on fp64 MFMA (16 x 16 x 4; fp32 values are exact in
+          // fp64): wave w forms queries 16 w .. + 15 of the tile against the four
+          // 16-key groups, each lane supplying k = 16 g + 4 lk + u to product u of
+          // group g
+          const int lr = lane & 15, lk = lane >> 4;
+          const float *qrow = reinterpret_cast<const float *>(Qb) + (size_t)min(i0 + 16 * wave + lr, n - 1) * kHeadDim + 4 * lk;
+          f32x4 bq[8];
+#pragma unroll
+          for (int gg = 0; gg < 8; ++gg) bq[gg] = *reinterpret_cast<const f32x4 *>(qrow + 16 * gg);
+          const int qi = 16 * wave + lr;
+#pragma unroll
+          for (int k4 = 0; k4 < 4; ++k4) {
+            if (!((need >> (k4 >> 1)) & 1)) continue;   // no candidate of this key half in the chunk
+            const float *krow = reinterpret_cast<const float *>(sK) + (16 * k4 + lr) * SKB + 4 * lk;
+            f64x4 l0 = {0.0, 0.0, 0.0, 0.0}, l1 = l0;
+#pragma unroll
+            for (int gg = 0; gg < 8; gg += 2) {
+              const f32x4 a0 = *reinterpret_cast<const f32x4 *>(krow + 16 * gg);
+              const f32x4 a1 = *reinterpret_cast<const f32x4 *>(krow + 16 * gg + 16);
+#pragma unroll
+              for (int u = 0; u < 4; ++u) {
+                l0 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a0[u], (double)bq[gg][u], l0, 0, 0, 0);
+                l1 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a1[u], (double)bq[gg + 1][u], l1, 0, 0, 0);
+              }
+            }
+            // lane holds keys 16 k4 + 4 r + lk for query 16 w + lr
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              eS[(16 * k4 + 4 * r + lk) * SE + qi] = i0 + qi < n ? (float)exp(s * (l0[r] + l1[r]) - zm) : 0.0f;
           }
         }
         if constexpr (BF) load_q(nxt);   // the MFMAs above have read qa
@@ -716,7 +739,7 @@ __global__ void __launch_bounds__(512, 2) k_assign_refine(const E *__restrict__ 
         const int c = cw0 + 2 * u + h;
         if (col == 0 && c < cn) {
           const int k = ck[c];
-          psim[koff[k] + c0 + c - kbase[k]] = d / anorm[(size_t)b * tp + cr[c]];
+          psim[(size_t)sp * L.pcap + koff[k] + c0 + c - kbase[k]] = d / anorm[(size_t)b * tp + cr[c]];
         }
       }
     }
@@ -778,7 +801,12 @@ __global__ void __launch_bounds__(256) k_assign_decide(const E *__restrict__ K, 
   const AssignPair pp = pn[b];
   const double zm = (double)zmerge[b];
   int32_t *pool = L.pool + (size_t)b * L.pcap;
-  const double *psim = L.psim + (size_t)b * L.pcap;
+  const double *psim = L.psim + (size_t)b * 2 * L.nspl * L.pcap;
+  auto sim = [&](int c) {   // the query ranges' parts, in order
+    double v = psim[c];
+    for (int sp = 1; sp < L.nspl; ++sp) v += psim[(size_t)sp * L.pcap + c];
+    return v;
+  };
   for (int f = blockIdx.x * 4 + wave; f < F; f += gridDim.x * 4) {   // uniform over the wave
     const size_t q = (size_t)b * L.cap + f;
     const int j = L.fkey[q], o = L.foff[q], m = L.fn[q];
@@ -786,7 +814,7 @@ __global__ void __launch_bounds__(256) k_assign_decide(const E *__restrict__ K, 
     double bs = -INFINITY;
     int br = 0x7FFFFFFF;
     for (int c = lane; c < m; c += 64) {
-      const double v = psim[o + c];
+      const double v = sim(o + c);
       const int r = pool[o + c];
       if (v > bs || (v == bs && r < br)) {
         bs = v;
@@ -825,7 +853,7 @@ __global__ void __launch_bounds__(256) k_assign_decide(const E *__restrict__ K, 
     int ns = 0;
     for (int c0 = 0; c0 < m; c0 += 64) {
       const int c = c0 + lane;
-      const bool keep = c < m && psim[o + c] >= thc;
+      const bool keep = c < m && sim(o + c) >= thc;
       const int r = keep ? pool[o + c] : 0;
       const uint64_t mask = __ballot(keep);
       if (keep) pool[o + ns + __popcll(mask & ((1ull << lane) - 1ull))] = r;
@@ -845,8 +873,13 @@ __global__ void __launch_bounds__(256) k_assign_decide(const E *__restrict__ K, 
 // it = blockIdx.x, blockIdx.x + kExactBlocks, ...  An item's keys and
 // candidate anchors share one sweep over the queries in tiles of 64, and an
 // entry with more candidates than fit (all t anchors) continues in the next
-// sweep.  An entry of a split key leaves its best (similarity, anchor) for
-// k_exact_merge instead of deciding the key.
+// sweep.
+// The queries of an item are cut into nspl ranges, each a work item of its own;
+// a candidate's parts of the dot product and of the squared norm take the place
+// of its refined similarities, which are read by then, and k_exact_merge adds
+// them in order and decides.  An entry over all t anchors runs over all queries
+// and decides by itself.  Whole sweeps took 288 us at 8 pairs of T = 8192,
+// n = 4096, with some ten items per pair; in ranges 75 us.
 constexpr int kExactBlocks = 128;
 
 // Pass D work items: greedy packing of consecutive entries into items of at
@@ -858,13 +891,14 @@ __global__ void __launch_bounds__(256) k_exact_plan(AssignLists L) {
   __shared__ int32_t sdn[W];
   const int b = blockIdx.x, tid = threadIdx.x;
   const int D = L.dcnt[b];
-  const int32_t *dn = L.dn + (size_t)b * L.dcap;
+  const int32_t *dn = L.dn + (size_t)b * L.dcap, *doff = L.doff + (size_t)b * L.dcap;
   int32_t *items = L.ditem + (size_t)b * (L.dcap + 2);
   int nit = 0, nv = 0;   // thread 0 only
   for (int w0 = 0; w0 < D; w0 += W) {   // uniform over the workgroup
     const int nw = min(W, D - w0);
     __syncthreads();   // thread 0 is done with the previous window
-    for (int x = tid; x < nw; x += 256) sdn[x] = dn[w0 + x];
+    // an entry over all t anchors has an item of its own however few they are
+    for (int x = tid; x < nw; x += 256) sdn[x] = doff[w0 + x] < 0 ? 32 : dn[w0 + x];
     __syncthreads();
     if (tid == 0) {
       for (int x = 0; x < nw; ++x) {
@@ -883,27 +917,36 @@ __global__ void __launch_bounds__(256) k_exact_plan(AssignLists L) {
   }
 }
 
-// A split key's decision from its entries' bests: the largest similarity,
-// equal ones to the lower r (the same order as within an entry).  One thread
-// per first entry of a split key.
+// Decisions, one thread per entry: the largest similarity of its candidates
+// and, for the first entry of a split key, of all the key's entries (which are
+// consecutive, as are their candidates), equal ones to the lower r.
 __global__ void __launch_bounds__(256) k_exact_merge(int T, int32_t *__restrict__ kappa, AssignLists L) {
   const int b = blockIdx.y;
   const int D = L.dcnt[b];
+  const double *part = L.psim + (size_t)b * 2 * L.nspl * L.pcap;
+  const int32_t *pool = L.pool + (size_t)b * L.pcap;
   for (int di = blockIdx.x * 256 + threadIdx.x; di < D; di += gridDim.x * 256) {
     const size_t q = (size_t)b * L.dcap + di;
-    if (L.dgrp[q] != di) continue;
-    const int ne = L.dgn[q];
-    double bs = L.dsim[q];
-    int br = L.dr[q];
-    for (int e = 1; e < ne; ++e) {
-      const double sim = L.dsim[q + e];
-      const int r = L.dr[q + e];
+    const int o = L.doff[q], grp = L.dgrp[q];
+    if (o < 0 || (grp >= 0 && grp != di)) continue;   // decided in its item, or with the key's first entry
+    int m = L.dn[q];
+    for (int e = 1; grp >= 0 && e < L.dgn[q]; ++e) m += L.dn[q + e];
+    double bs = -1.0;
+    int br = 0x7FFFFFFF;
+    for (int c = 0; c < m; ++c) {
+      double dot = 0.0, nn = 0.0;
+      for (int sp = 0; sp < L.nspl; ++sp) {
+        dot += part[(size_t)(2 * sp) * L.pcap + o + c];
+        nn += part[(size_t)(2 * sp + 1) * L.pcap + o + c];
+      }
+      const double sim = nn > 0.0 ? dot / sqrt(nn) : 0.0;
+      const int r = pool[o + c];
       if (sim > bs || (sim == bs && r < br)) {
         bs = sim;
         br = r;
       }
     }
-    kappa[(size_t)b * T + L.dkey[q]] = br;
+    if (br != 0x7FFFFFFF) kappa[(size_t)b * T + L.dkey[q]] = br;
   }
 }
 
@@ -916,10 +959,10 @@ __global__ void __launch_bounds__(256) k_assign_exact(const E *__restrict__ Q, c
   __shared__ __attribute__((aligned(16))) float sK[NV * SK];
   __shared__ __attribute__((aligned(16))) float sQ[NQ * SK];
   __shared__ double sE[NV * (NQ + 1)];
-  __shared__ int32_t vpos[NV], vown[NV], vr[NV];
+  __shared__ int32_t vpos[NV], vown[NV], vr[NV], vpool[NV];
   __shared__ double vdot[NV], vnn[NV];
   // batch segments: first and one-past-last vector, continues, final
-  __shared__ int32_t sg_v0[NV], sg_v1[NV], sg_cont[NV], sg_final[NV], sg_di[NV];
+  __shared__ int32_t sg_v0[NV], sg_v1[NV], sg_cont[NV], sg_final[NV];
   __shared__ int32_t nv_s, nseg_s, di_s, ci_s, done_s;
   __shared__ double run_sim;
   __shared__ int32_t run_r;
@@ -930,13 +973,6 @@ __global__ void __launch_bounds__(256) k_assign_exact(const E *__restrict__ Q, c
   const int32_t *S = anchors + (size_t)b * t;
   const double zm = (double)zmerge[b];
   const E *Qb = Q + (size_t)b * n * kHeadDim;
-  auto n_cand = [&](int di) { return L.dn[(size_t)b * L.dcap + di]; };
-  auto cand_at = [&](int di, int ci) {   // doff < 0: every anchor is a candidate
-    const int off = L.doff[(size_t)b * L.dcap + di];
-    return off < 0 ? ci : L.pool[(size_t)b * L.pcap + off + ci];
-  };
-  // register tile of the logit pass: vectors tv, tv + 16 and queries tq + 16 m, m = 0..3
-  const int tv = tid >> 4, tq = tid & 15;
   // rows of 128 elements of E as 4 floats per thread-step (bf16: 4 values = 8 bytes)
   auto load4 = [](const E *p) -> f32x4 {
     if constexpr (sizeof(E) == 2) {
@@ -947,9 +983,16 @@ __global__ void __launch_bounds__(256) k_assign_exact(const E *__restrict__ Q, c
     }
   };
   const int32_t *items = L.ditem + (size_t)b * (L.dcap + 2);
-  const int nitems = D > 0 ? items[0] : 0;
-  for (int it = bx; it < nitems; it += kExactBlocks) {   // uniform over the workgroup
-    const int g0 = items[1 + it], g1 = items[2 + it];
+  const int nspl = L.nspl, nitems = D > 0 ? items[0] * nspl : 0;
+  const int run = (nitems + kExactBlocks - 1) / kExactBlocks;
+  const int tiles_per = ((n + NQ - 1) / NQ + nspl - 1) / nspl;
+  double *part = L.psim + (size_t)b * 2 * nspl * L.pcap;
+  for (int it = bx * run; it < min(nitems, (bx + 1) * run); ++it) {   // uniform over the workgroup
+    const int item = it / nspl, sp = it - item * nspl;
+    const int g0 = items[1 + item], g1 = items[2 + item];
+    const bool direct = L.doff[(size_t)b * L.dcap + g0] < 0;   // all t anchors: all queries, decided here
+    if (direct && sp != 0) continue;
+    const int i_lo = direct ? 0 : NQ * tiles_per * sp, i_hi = direct ? n : min(n, i_lo + NQ * tiles_per);
     __syncthreads();   // every thread has left the previous item's loop
     if (tid == 0) {
       di_s = g0;
@@ -958,36 +1001,61 @@ __global__ void __launch_bounds__(256) k_assign_exact(const E *__restrict__ Q, c
     }
     __syncthreads();
     while (!done_s) {
-      if (tid == 0) {   // build the next batch from keys di_s .. g1 - 1
-        int nv = 0, ns = 0, di = di_s, ci = ci_s;
-        while (di < g1 && nv + 2 <= NV) {
-          const int nck = n_cand(di);
-          sg_cont[ns] = ci > 0;
-          sg_di[ns] = di;
-          sg_v0[ns] = nv;
-          vpos[nv] = L.dkey[(size_t)b * L.dcap + di];
-          vown[nv] = -1;
-          vr[nv] = -1;
-          const int kv = nv++;
-          while (nv < NV && ci < nck) {
-            const int r = cand_at(di, ci++);
-            vpos[nv] = S[r];
-            vown[nv] = kv;
-            vr[nv] = r;
-            ++nv;
-          }
-          sg_v1[ns] = nv;
-          sg_final[ns] = ci >= nck;
-          ++ns;
-          if (ci >= nck) {
-            ++di;
-            ci = 0;
+      // the next batch, built by the first wave: lane e holds entry di_s + e (an
+      // item has at most 16 that fit a batch), a prefix sum gives its first vector,
+      // and lane v then looks up vector v
+      if (tid < 64) {
+        const int di0 = di_s, ci0 = ci_s, e = tid;
+        const size_t q = (size_t)b * L.dcap + di0 + e;
+        const bool have = e < 16 && di0 + e < g1;
+        const int left = have ? L.dn[q] - (e == 0 ? ci0 : 0) : 0;   // candidates of the entry not yet taken
+        const int key = have ? L.dkey[q] : 0, off = have ? L.doff[q] : 0;
+        int x = have ? 1 + left : 0;
+        const int need = x;
+#pragma unroll
+        for (int d = 1; d < 16; d <<= 1) {
+          const int y = __shfl_up(x, d, 64);
+          if (tid >= d) x += y;
+        }
+        const int v0 = x - need;
+        // an entry takes part if its key and one candidate fit; the last one may be cut off
+        const bool in = have && v0 + 2 <= NV;
+        const int v1 = min(v0 + need, NV);
+        const uint64_t im = __ballot(in);
+        const int ns = __popcll(im);   // entries 0 .. ns - 1
+        if (in) {
+          sg_cont[e] = e == 0 && ci0 > 0;
+          sg_v0[e] = v0;
+          sg_v1[e] = v1;
+          sg_final[e] = v1 == v0 + need;
+        }
+        const int nv = __shfl(v1, ns - 1, 64);
+        int en = 0;   // this lane's vector: its entry is the last with v0 <= tid
+        for (int k = 1; k < ns; ++k) en += __shfl(v0, k, 64) <= tid;
+        const int ev0 = __shfl(v0, en, 64), ekey = __shfl(key, en, 64), eoff = __shfl(off, en, 64);
+        if (tid < nv) {
+          const int ci = tid - ev0 - 1 + (en == 0 ? ci0 : 0);
+          if (tid == ev0) {
+            vpos[tid] = ekey;
+            vown[tid] = -1;
+            vr[tid] = -1;
+            vpool[tid] = -1;
+          } else {
+            const int r = eoff < 0 ? ci : L.pool[(size_t)b * L.pcap + eoff + ci];   // every anchor is a candidate
+            vpos[tid] = S[r];
+            vown[tid] = ev0;
+            vr[tid] = r;
+            vpool[tid] = eoff + ci;
           }
         }
-        nv_s = nv;
-        nseg_s = ns;
-        di_s = di;
-        ci_s = ci;
+        const int lv0 = __shfl(v0, ns - 1, 64), lneed = __shfl(need, ns - 1, 64);
+        if (tid == 0) {
+          const bool cut = nv < lv0 + lneed;   // the last entry goes on in the next batch
+          nv_s = nv;
+          nseg_s = ns;
+          di_s = di0 + ns - (cut ? 1 : 0);
+          ci_s = cut ? (ns == 1 ? ci0 : 0) + nv - lv0 - 1 : 0;
+        }
       }
       __syncthreads();
       const int nv = nv_s;
@@ -1014,8 +1082,8 @@ __global__ void __launch_bounds__(256) k_assign_exact(const E *__restrict__ Q, c
           qn[c] = j0 + q < n ? *reinterpret_cast<const Raw *>(Qb + (size_t)(j0 + q) * kHeadDim + k) : Raw{};
         }
       };
-      fetch_q(0);
-      for (int i0 = 0; i0 < n; i0 += NQ) {
+      fetch_q(i_lo);
+      for (int i0 = i_lo; i0 < i_hi; i0 += NQ) {   // none in a range past the last query
         __syncthreads();   // every wave is done with the previous tile
 #pragma unroll
         for (int c = 0; c < QCH; ++c) {
@@ -1025,7 +1093,7 @@ __global__ void __launch_bounds__(256) k_assign_exact(const E *__restrict__ Q, c
           for (int u = 0; u < 4; ++u) w[u] = (float)qn[c][u];
           *reinterpret_cast<f32x4 *>(&sQ[q * SK + k]) = w;
         }
-        if (i0 + NQ < n) fetch_q(i0 + NQ);
+        if (i0 + NQ < i_hi) fetch_q(i0 + NQ);
         __syncthreads();
         // logits on fp64 MFMA (16 x 16 x 4): wave w owns queries 16 w .. 16 w + 15
         // of the tile and both 16-vector halves; each lane supplies k = 16 g + 4 lk + u
@@ -1071,12 +1139,17 @@ __global__ void __launch_bounds__(256) k_assign_exact(const E *__restrict__ Q, c
         acc_n += nn;
       }
       if (rq == 0) {
-        vdot[rv] = acc_d;
-        vnn[rv] = acc_n;
+        if (direct) {
+          vdot[rv] = acc_d;
+          vnn[rv] = acc_n;
+        } else if (vo >= 0) {
+          part[(size_t)(2 * sp) * L.pcap + vpool[rv]] = acc_d;
+          part[(size_t)(2 * sp + 1) * L.pcap + vpool[rv]] = acc_n;
+        }
       }
       __syncthreads();
       if (tid == 0) {
-        for (int g = 0; g < nseg_s; ++g) {
+        for (int g = 0; direct && g < nseg_s; ++g) {
           double bs = sg_cont[g] ? run_sim : -1.0;
           int br = sg_cont[g] ? run_r : 0x7FFFFFFF;
           for (int v = sg_v0[g] + 1; v < sg_v1[g]; ++v) {
@@ -1087,13 +1160,7 @@ __global__ void __launch_bounds__(256) k_assign_exact(const E *__restrict__ Q, c
             }
           }
           if (sg_final[g]) {
-            const size_t q = (size_t)b * L.dcap + sg_di[g];
-            if (L.dgrp[q] >= 0) {   // part of a split key: k_exact_merge decides
-              L.dsim[q] = bs;
-              L.dr[q] = br;
-            } else if (br != 0x7FFFFFFF) {
-              kappa[(size_t)b * T + vpos[sg_v0[g]]] = br;
-            }
+            if (br != 0x7FFFFFFF) kappa[(size_t)b * T + vpos[sg_v0[g]]] = br;
           } else {
             run_sim = bs;
             run_r = br;
@@ -1215,7 +1282,7 @@ hipError_t launch_assign_exact(int dtype, const void *Q, const void *K, const in
   else
     hipLaunchKernelGGL(k_assign_exact<float>, dim3(kExactBlocks, P), dim3(256), 0, s, (const float *)Q,
                        (const float *)K, anchors, zmerge, T, t, n, (double)scale, kappa, L);
-  hipLaunchKernelGGL(k_exact_merge, dim3(8, P), dim3(256), 0, s, T, kappa, L);
+  hipLaunchKernelGGL(k_exact_merge, dim3(32, P), dim3(256), 0, s, T, kappa, L);
   return hipGetLastError();
 }
 

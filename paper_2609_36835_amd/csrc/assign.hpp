@@ -20,6 +20,16 @@ inline int64_t pass_d_capacity(int64_t Tp, int64_t pool_per_key) {
   return Tp + (pool_per_key * Tp + kPassDSplit - 1) / kPassDSplit + 1;
 }
 
+// Query ranges into which a work item of the refine and of the float64 pass is
+// cut, by the number n of queries alone, so that decisions do not depend on how
+// many pairs run together: a call over few pairs has a few dozen items, each a
+// serial sweep over its queries, on 256 CUs.  More than four cost more in setting
+// the items up than they gain.
+inline int query_ranges(int64_t n) {
+  const int64_t tiles = (n + 127) / 128;
+  return tiles >= 16 ? 4 : tiles >= 2 ? 2 : 1;
+}
+
 struct AssignLists {
   int32_t *fcnt;    // [P] keys queued for the refine pass
   int32_t *fkey;    // [P][cap]
@@ -27,8 +37,11 @@ struct AssignLists {
   int32_t *fn;      // [P][cap] its number of candidates
   int32_t *pcnt;    // [P] candidates in the pool
   int32_t *pool;    // [P][pcap] candidate anchors, contiguous per queued key
-  double *psim;     // [P][pcap] their refined similarities
+  double *psim;     // [P][2 nspl][pcap]: the first nspl arrays the parts of their refined similarities, then
+                    // (float64 pass) array 2 i the part i of a candidate's dot product, 2 i + 1 of its
+                    // squared norm
   int64_t pcap;     // pool capacity per pair
+  int32_t nspl;     // query ranges (query_ranges)
   int32_t *dcnt;    // [P] entries queued for the float64 pass (a key with many pool survivors is split
                     // into several entries of consecutive survivors)
   int32_t *dkey;    // [P][dcap] the entry's key
@@ -45,8 +58,6 @@ struct AssignLists {
   int64_t gcap;     // >= cap / 64 + 1
   int32_t *dgrp;    // [P][dcap] first entry of the entry's key when the key is split, else -1
   int32_t *dgn;     // [P][dcap] entries of the entry's key
-  double *dsim;     // [P][dcap] best similarity of a split entry's candidates
-  int32_t *dr;      // [P][dcap] its anchor
   int32_t *ditem;   // [P][dcap + 2] pass D work items: count, first entry of each item, then dcnt
   int64_t dcap;     // entry capacity per pair
 };

@@ -383,12 +383,12 @@ def test_merge_many_groups(t):
 @pytest.mark.parametrize("n,pooled", [(256, False), (1024, True)])
 def test_every_anchor_a_candidate(n, pooled):
     """One key 30 logits above the rest leaves every other profile below fp16's
-    range, so each key lists all t anchors: 100 candidates per key fit the pool
-    that E^T's rows of 1024 values leave room for (149 per key), and overflow
-    the one of 256-value rows (31), whose last keys go to the float64 pass with
-    all anchors.  Either way kappa is the float64 argmax."""
+    range, so each of the 640 keys lists all 60 anchors.  The pool that E^T's
+    rows of 1024 values leave room for (52 candidates per cached key) holds
+    them; that of 256-value rows (11) overflows, and its last keys go to the
+    float64 pass with all anchors.  Either way kappa is the float64 argmax."""
     rng = np.random.default_rng(n)
-    T, t = 700, 100
+    T, t = 700, 60
     s = 1.0 / math.sqrt(128)
     K = rng.standard_normal((T, 128)).astype(np.float32)
     V = rng.standard_normal((T, 128)).astype(np.float32)
