@@ -986,14 +986,17 @@ struct DsaPlan {
 static DsaPlan dsa_plan(int64_t P, int64_t T, int64_t n, int64_t n_pos) {
   DsaPlan d;
   Bump b;
+  // kbar takes the place of the value head's projected keys and values, which
+  // are dead by then (whole tiles of 32 rows)
+  d.kbar = b.off;
   d.ka = b.take(P * T * 128 * 2);
   d.va = b.take(P * T * 128 * 2);
+  b.off = d.kbar + rup(P * rup(T, 32) * 1024 * 2, 256);
   d.qa = b.take(P * n * 128 * 2);
   d.c = b.take(P * n * 128 * 4);
   d.za = b.take(P * n * 4);
   d.ma = b.take(P * n * 4);
   d.qbar = b.take(P * n * 1024 * 2);
-  d.kbar = b.take(P * T * 1024 * 2);
   d.w = b.take(P * n_pos * 8 * 4);
   d.z = b.take(P * n * 4);
   d.m = b.take(P * n * 4);

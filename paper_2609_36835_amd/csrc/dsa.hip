@@ -50,55 +50,97 @@ __device__ inline bf16x8 load_frag(const float *p) {
 }
 }  // namespace
 
-// out[p][row][a 128 + c] for rows < nrows; grid (ceil(nrows / 128), n_blocks, B).
-// X1 [B][nrows][128] bf16; X2 (nullable) [B][nrows][128] of X2T; W1, W2
-// [B][n_blocks 128][128] bf16.
-template <typename X2T, bool NORM>
+// Element (row, head a, c) of kbar: the fragments k_dsa_index reads, so that a
+// wave's load of one (32-row tile, head, k-step) is one 1 KB run: [tile][a][k-step
+// c / 16][c / 8 % 2][row % 32][c % 8].  Row-major rows of 2 KB gave each of its
+// loads 32 bytes from 32 rows, and the passes took 975 and 987
+// us for 8 pairs of T = 8192 where they now take 632 and 677.
+__host__ __device__ inline int64_t dsa_tiles(int64_t T) { return (T + 31) / 32; }
+__device__ inline size_t dsa_kbar_at(int64_t row, int a, int c) {
+  return (size_t)((row >> 5) * kDsaH + a) * (32 * kDsaW) + (c >> 4) * 512 + ((c >> 3) & 1) * 256 + (row & 31) * 8 +
+         (c & 7);
+}
+
+// out[p][row][a 128 + c] for rows < nrows (TILED: dsa_kbar_at); grid
+// (ceil(nrows / 128), B).  X1 [B][nrows][128] bf16; X2 (nullable) [B][nrows][128]
+// of X2T; W1, W2 [B][n_blocks 128][128] bf16.  A wave keeps its 32 rows'
+// fragments in registers over all blocks; a block's W1 and W2 go through LDS
+// (rows of 256 bytes, 16-byte chunks XOR-swizzled by the row), shared by the four
+// waves.  Reading W's fragments from global memory by every wave, and X again for
+// every block, took 179 us for 8 pairs of 8192 keys; now 57 us (the queries: 109 and 58 us).
+template <typename X2T, bool NORM, bool TILED>
 __global__ void __launch_bounds__(256) k_dsa_proj(const bf16 *__restrict__ X1, const X2T *__restrict__ X2,
                                                   const bf16 *__restrict__ W1, const bf16 *__restrict__ W2,
                                                   int nrows, int n_blocks, bf16 *__restrict__ out) {
-  const int p = blockIdx.z, a = blockIdx.y;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  extern __shared__ __attribute__((aligned(16))) char proj_smem[];   // [1 or 2][128][256 B]
+  const int p = blockIdx.y, tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
   const int h = lane >> 5, col = lane & 31;
   const int row = blockIdx.x * 128 + wave * 32 + col;
   const bool valid = row < nrows;
   const size_t xoff = ((size_t)p * nrows + (valid ? row : 0)) * kDsaW + 8 * h;
-  const size_t woff = ((size_t)p * n_blocks * kDsaW + (size_t)a * kDsaW) * kDsaW + 8 * h;
-  f32x16 acc[4];
+  bf16x8 x1[8], x2[8];
 #pragma unroll
-  for (int mt = 0; mt < 4; ++mt) acc[mt] = zero16();
-  for (int src = 0; src < (X2 ? 2 : 1); ++src) {
-    const bf16 *W = src == 0 ? W1 : W2;
+  for (int ks = 0; ks < 8; ++ks) x1[ks] = load_frag(X1 + xoff + 16 * ks);
+  if (X2) {
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      const bf16x8 xb = src == 0 ? load_frag(X1 + xoff + 16 * ks) : load_frag(X2 + xoff + 16 * ks);
+    for (int ks = 0; ks < 8; ++ks) x2[ks] = load_frag(X2 + xoff + 16 * ks);
+  }
+  for (int a = 0; a < n_blocks; ++a) {
+    const size_t woff = ((size_t)p * n_blocks + a) * kDsaW * kDsaW;
+    __syncthreads();   // the previous block's fragments have been read
+    for (int src = 0; src < (X2 ? 2 : 1); ++src) {
+      const bf16 *W = (src == 0 ? W1 : W2) + woff;
+      f32x4 w[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) w[u] = *reinterpret_cast<const f32x4 *>(W + 8 * (tid + 256 * u));
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int e = tid + 256 * u, r = e >> 4, c = e & 15;
+        *reinterpret_cast<f32x4 *>(proj_smem + src * 32768 + r * 256 + 16 * (c ^ (r & 15))) = w[u];
+      }
+    }
+    __syncthreads();
+    f32x16 acc[4];
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) acc[mt] = zero16();
+    auto products = [&](const bf16x8 (&x)[8], const char *sw) {
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks)
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) {
+          const int r = 32 * mt + col;
+          const bf16x8 wf = *reinterpret_cast<const bf16x8 *>(sw + r * 256 + 16 * ((2 * ks + h) ^ (r & 15)));
+          acc[mt] = Mfma<bf16>::mma(wf, x[ks], acc[mt]);
+        }
+    };
+    products(x1, proj_smem);
+    if (X2) products(x2, proj_smem + 32768);
+    // lane (h, col): input row `row`, output columns 32 mt + 8 g + 4 h + e
+    float sc = 1.0f;
+    if (NORM) {
+      float ss = 0.0f;
 #pragma unroll
       for (int mt = 0; mt < 4; ++mt)
-        acc[mt] = Mfma<bf16>::mma(load_frag(W + woff + (size_t)(32 * mt + col) * kDsaW + 16 * ks), xb, acc[mt]);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) ss = fmaf(acc[mt][v], acc[mt][v], ss);
+      ss += __shfl_xor(ss, 32, 64);
+      sc = 1.0f / sqrtf(ss / (float)kDsaW + kRmsEps);
     }
-  }
-  // lane (h, col): input row `row`, output columns 32 mt + 8 g + 4 h + e
-  float sc = 1.0f;
-  if (NORM) {
-    float ss = 0.0f;
+    if (!valid) continue;   // no barrier until every lane is back at the loop head
+    bf16 *o = TILED ? out + (size_t)p * dsa_tiles(nrows) * 32 * kDsaH * kDsaW
+                    : out + ((size_t)p * nrows + row) * ((size_t)n_blocks * kDsaW) + (size_t)a * kDsaW + 4 * h;
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) ss = fmaf(acc[mt][v], acc[mt][v], ss);
-    ss += __shfl_xor(ss, 32, 64);
-    sc = 1.0f / sqrtf(ss / (float)kDsaW + kRmsEps);
+      for (int g = 0; g < 4; ++g) {
+        bf16x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = (bf16)(acc[mt][4 * g + e] * sc);
+        *reinterpret_cast<bf16x4 *>(TILED ? o + dsa_kbar_at(row, a, 32 * mt + 8 * g + 4 * h) : o + 32 * mt + 8 * g) =
+            v;
+      }
   }
-  if (!valid) return;
-  bf16 *o = out + ((size_t)p * nrows + row) * ((size_t)n_blocks * kDsaW) + (size_t)a * kDsaW + 4 * h;
-#pragma unroll
-  for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      bf16x4 v;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = (bf16)(acc[mt][4 * g + e] * sc);
-      *reinterpret_cast<bf16x4 *>(o + 32 * mt + 8 * g) = v;
-    }
 }
 
 // w[p][r][a] = L_x[p][a] . x_{(p_off + p) / x_group, r} + b_x[p][a]; grid (n_pos, B), one wave.
@@ -136,7 +178,9 @@ __global__ void __launch_bounds__(64 * kDsaWaves) __attribute__((amdgpu_waves_pe
   char *sq = dsa_smem;                                                  // 64 x 2048 B
   float *sw = reinterpret_cast<float *>(dsa_smem + kDsaQB * 2048);     // [64][8]
   float *sred = sw + kDsaQB * kDsaH;                                    // [waves][64][2]
-  const int p = blockIdx.y, q0 = blockIdx.x * kDsaQB;
+  // the query blocks of a pair share an XCD and its L2 copy of the pair's keys
+  const int64_t blk = xcd_remap((int64_t)blockIdx.y * gridDim.x + blockIdx.x, (int64_t)gridDim.x * gridDim.y);
+  const int p = (int)(blk / gridDim.x), qb = (int)(blk % gridDim.x), q0 = qb * kDsaQB;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int h = lane >> 5, col = lane & 31;
   const float inv_sqrt = 1.0f / sqrtf((float)kDsaW);
@@ -164,7 +208,7 @@ __global__ void __launch_bounds__(64 * kDsaWaves) __attribute__((amdgpu_waves_pe
     }
   }
   float run_m[2] = {-INFINITY, -INFINITY}, run_s[2] = {0.0f, 0.0f};   // PASS 1
-  const bf16 *kb = kbar + (size_t)p * T * (kDsaH * kDsaW) + 8 * h;
+  const bf16 *kb = kbar + (size_t)p * dsa_tiles(T) * 32 * kDsaH * kDsaW + 8 * lane;
   const int nkb = (T + kDsaKB - 1) / kDsaKB;
   // a ring of two heads' key fragments for the wave's key tiles (128 VGPRs):
   // head a's slot is refilled with head a + 2 (or, for the last two heads, the
@@ -175,10 +219,11 @@ __global__ void __launch_bounds__(64 * kDsaWaves) __attribute__((amdgpu_waves_pe
   auto fetch = [&](int kbk_, int a, bf16x8 (&f)[kDsaKT][8]) {
 #pragma unroll
     for (int kt = 0; kt < kDsaKT; ++kt) {
-      const int key = kbk_ * kDsaKB + wave * (32 * kDsaKT) + 32 * kt + col;
-      const bf16 *krow = kb + (size_t)(key < T ? key : 0) * (kDsaH * kDsaW) + a * kDsaW;
+      // a tile past the last key reads the last one; its results are not used
+      const int64_t tile = min((int64_t)(kbk_ * kDsaWaves + wave) * kDsaKT + kt, dsa_tiles(T) - 1);
+      const bf16 *kf = kb + (tile * kDsaH + a) * (32 * kDsaW);
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) f[kt][ks] = key < T ? load_frag(krow + 16 * ks) : Mfma<bf16>::zero();
+      for (int ks = 0; ks < 8; ++ks) f[kt][ks] = load_frag(kf + 512 * ks);
     }
   };
 #pragma unroll
@@ -253,7 +298,7 @@ __global__ void __launch_bounds__(64 * kDsaWaves) __attribute__((amdgpu_waves_pe
       }
     } else {
       // pi^2 summed over this workgroup's 64 queries, per key
-      float *pp = part + ((size_t)p * gridDim.x + blockIdx.x) * T;
+      float *pp = part + ((size_t)p * gridDim.x + qb) * T;
 #pragma unroll
       for (int kt = 0; kt < kDsaKT; ++kt) {
         float cs[16];
@@ -321,23 +366,27 @@ __global__ void __launch_bounds__(256) k_dsa_pool(const float *__restrict__ part
   s[(size_t)p * T + j] = sqrtf(acc / (float)n);
 }
 
+template <typename X2T, bool NORM, bool TILED>
+static hipError_t dsa_proj(const void *X1, const void *X2, const void *W1, const void *W2, int B, int nrows,
+                           int n_blocks, void *out, hipStream_t s) {
+  const int lds = X2 ? 65536 : 32768;
+  const hipError_t e = hipFuncSetAttribute((const void *)k_dsa_proj<X2T, NORM, TILED>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_dsa_proj<X2T, NORM, TILED>), dim3((unsigned)((nrows + 127) / 128), (unsigned)B), dim3(256), lds,
+                     s, (const bf16 *)X1, (const X2T *)X2, (const bf16 *)W1, (const bf16 *)W2, nrows, n_blocks,
+                     (bf16 *)out);
+  return hipGetLastError();
+}
+
+// The value head's projections (one block, row-major), qbar (x2_f32, eight
+// blocks, row-major, normalised) and kbar (eight blocks, tiled, normalised).
 hipError_t launch_dsa_proj(const void *X1, const void *X2, bool x2_f32, const void *W1, const void *W2, int B,
                            int nrows, int n_blocks, bool norm, void *out, hipStream_t s) {
-  dim3 grid((unsigned)((nrows + 127) / 128), (unsigned)n_blocks, (unsigned)B);
-  auto o = (bf16 *)out;
-  if (!X2) {
-    if (norm) hipLaunchKernelGGL((k_dsa_proj<bf16, true>), grid, dim3(256), 0, s, (const bf16 *)X1,
-                                 (const bf16 *)nullptr, (const bf16 *)W1, (const bf16 *)nullptr, nrows, n_blocks, o);
-    else hipLaunchKernelGGL((k_dsa_proj<bf16, false>), grid, dim3(256), 0, s, (const bf16 *)X1,
-                            (const bf16 *)nullptr, (const bf16 *)W1, (const bf16 *)nullptr, nrows, n_blocks, o);
-  } else if (x2_f32) {
-    hipLaunchKernelGGL((k_dsa_proj<float, true>), grid, dim3(256), 0, s, (const bf16 *)X1, (const float *)X2,
-                       (const bf16 *)W1, (const bf16 *)W2, nrows, n_blocks, o);
-  } else {
-    hipLaunchKernelGGL((k_dsa_proj<bf16, true>), grid, dim3(256), 0, s, (const bf16 *)X1, (const bf16 *)X2,
-                       (const bf16 *)W1, (const bf16 *)W2, nrows, n_blocks, o);
-  }
-  return hipGetLastError();
+  if (!X2 && !norm) return dsa_proj<bf16, false, false>(X1, nullptr, W1, nullptr, B, nrows, n_blocks, out, s);
+  if (!X2 || !norm) return hipErrorInvalidValue;
+  if (x2_f32) return dsa_proj<float, true, false>(X1, X2, W1, W2, B, nrows, n_blocks, out, s);
+  return dsa_proj<bf16, true, true>(X1, X2, W1, W2, B, nrows, n_blocks, out, s);
 }
 
 hipError_t launch_dsa_w(const void *X, const void *Lx, const float *bx, int B, int n_pos, int dx, int x_group,
