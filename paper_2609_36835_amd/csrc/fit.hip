@@ -255,14 +255,15 @@ __device__ __forceinline__ void factor16_update(float (&a)[16], float nl, std::i
 // work); y holds columns 4 g .. 4 g + 3 of row r of the identity and becomes
 // row r of L^-1 before its scaling by 1 / L_rr.  a[c] becomes L_rc for r > c;
 // entries above the diagonal are never read by another lane.  piv and inv
-// collect row r's pivot and 1 / L_rr.
-template <int C>
+// collect row r's pivot and 1 / L_rr.  1 / sqrt(pivot) is the hardware estimate
+// and one Newton step (about one unit in the last place); TINY scales pivots near
+// its underflow by 2^64 first.
+constexpr float kTinyPivot = 0x1p-96f;
+template <int C, bool TINY>
 __device__ __forceinline__ void factor16(float (&a)[16], f32x4 &y, float &piv, float &inv, int r) {
   if constexpr (C < 16) {
     const float p = row_bcast<C>(a[C]);
-    // 1 / sqrt(p): the hardware estimate and one Newton step (about one unit
-    // in the last place); pivots near its underflow are scaled by 2^64 first
-    const bool small = p < 0x1p-96f;
+    const bool small = TINY && p < kTinyPivot;
     const float q = small ? p * 0x1p64f : p;
     const float r0 = __builtin_amdgcn_rsqf(q);
     const float r1 = fmaf(0.5f * r0, fmaf(-(q * r0), r0, 1.0f), r0);
@@ -275,7 +276,7 @@ __device__ __forceinline__ void factor16(float (&a)[16], f32x4 &y, float &piv, f
     const float nx = nl * rs;
 #pragma unroll
     for (int v = 0; v < 4; ++v) y[v] = fmaf(row_bcast<C>(y[v]), nx, y[v]);
-    factor16<C + 1>(a, y, piv, inv, r);
+    factor16<C + 1, TINY>(a, y, piv, inv, r);
   }
 }
 
@@ -328,18 +329,26 @@ __global__ void __launch_bounds__(1024) k_chol_diag256(float *__restrict__ Gw, i
     if (wave == k) {
       put(k, k, cc);
       float a[16];
-      __builtin_amdgcn_wave_barrier();
+      auto row = [&]() {   // row r of the tile
+        __builtin_amdgcn_wave_barrier();
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const f32x4 v = *reinterpret_cast<const f32x4 *>(tile(k, k) + 64 * q + 4 * r);
+        for (int q = 0; q < 4; ++q) {
+          const f32x4 v = *reinterpret_cast<const f32x4 *>(tile(k, k) + 64 * q + 4 * r);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) a[4 * q + e] = v[e];
-      }
-      __builtin_amdgcn_wave_barrier();
+          for (int e = 0; e < 4; ++e) a[4 * q + e] = v[e];
+        }
+        __builtin_amdgcn_wave_barrier();
+      };
       f32x4 y = eye;
       float piv = 0.0f, inv = 0.0f;
       __builtin_amdgcn_s_setprio(3);   // the step's critical chain
-      factor16<0>(a, y, piv, inv, r);
+      row();
+      factor16<0, false>(a, y, piv, inv, r);
+      if (__ballot(!(piv >= kTinyPivot))) {   // a failed or a tiny pivot: again, with the scaling
+        row();
+        y = eye;
+        factor16<0, true>(a, y, piv, inv, r);
+      }
       __builtin_amdgcn_s_setprio(0);
       const uint64_t bad = __ballot(!(piv > 0.0f) || !isfinite(piv)) & 0xffffull;
       if (bad != 0 && lane == 0) *fail = K0 + 16 * k + __ffsll((unsigned long long)bad);
@@ -700,34 +709,39 @@ __device__ inline DiagInv diag_inv(const void *lsplit, int64_t ld, int b, int64_
   return {reinterpret_cast<const float *>(p), reinterpret_cast<const float *>(p + (size_t)ld * ld), ld / 2};
 }
 
-// One workgroup per (block, pair), after the factorisation: the lower 16 x 16
-// tiles of L and the inverses of its diagonal tiles (from dinv) in LDS; wave j
-// solves tile column j of X = L^-1 by substitution, X_ij = -X_ii sum_m L_im
-// X_mj, its tiles transposed in registers.  Columns are independent, so no
-// barrier; column 0's 135 tile products on fp32 MFMA bound it.
+// After the factorisation, the lower 16 x 16 tiles of L and the inverses of its
+// diagonal tiles (from dinv) in LDS; a wave solves one tile column j of X = L^-1
+// by substitution, X_ij = -X_ii sum_m L_im X_mj, its tiles transposed in registers.
+// Columns are independent, so no barrier.  One workgroup of 16 waves per (block,
+// pair) is bound by the CU's fp32 MFMA rate; while there are few of them, four
+// workgroups of four waves and four columns each (z, 7 - z, 8 + z, 15 - z) share
+// a block: 26 -> 23 us at 8 pairs of ld = 1024, 28 -> 23 us
+// at ld = 1792.
 __global__ void __launch_bounds__(1024) k_chol_inv256(const float *__restrict__ Gw, int64_t ld,
                                                       const float *__restrict__ dinv, void *__restrict__ lsplit,
                                                       const int32_t *__restrict__ info) {
   extern __shared__ __attribute__((aligned(16))) float diag_smem[];
   const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 15, g = lane >> 4;
   if (info[b] != 0) return;   // uniform over the workgroup
+  const int nw = blockDim.x >> 6;   // 16 or 4
   const int64_t K0 = (int64_t)blockIdx.x * 256;
   auto tile = [&](int i, int m) { return diag_smem + (i * (i + 1) / 2 + m) * 256; };
   auto get = [&](int i, int m) { return *reinterpret_cast<const f32x4 *>(tile(i, m) + 4 * lane); };
-  const float *grow = Gw + (size_t)b * ld * ld + (size_t)(K0 + 16 * wave + r) * ld + K0 + 4 * g;
-  const float *drow = dinv + ((size_t)b * (ld / kNB) + K0 / kNB + (wave >> 2)) * kNB * kNB +
-                      (16 * (wave & 3) + r) * kNB + 16 * (wave & 3) + 4 * g;
-  {
+  for (int i = wave; i < 16; i += nw) {   // tile row i
+    const float *grow = Gw + (size_t)b * ld * ld + (size_t)(K0 + 16 * i + r) * ld + K0 + 4 * g;
+    const float *drow = dinv + ((size_t)b * (ld / kNB) + K0 / kNB + (i >> 2)) * kNB * kNB +
+                        (16 * (i & 3) + r) * kNB + 16 * (i & 3) + 4 * g;
     f32x4 v[16];
 #pragma unroll
     for (int m = 0; m < 16; ++m)
-      if (m <= wave) v[m] = *reinterpret_cast<const f32x4 *>(m < wave ? grow + 16 * m : drow);
+      if (m <= i) v[m] = *reinterpret_cast<const f32x4 *>(m < i ? grow + 16 * m : drow);
 #pragma unroll
     for (int m = 0; m < 16; ++m)
-      if (m <= wave) *reinterpret_cast<f32x4 *>(tile(wave, m) + 4 * lane) = v[m];
+      if (m <= i) *reinterpret_cast<f32x4 *>(tile(i, m) + 4 * lane) = v[m];
   }
   __syncthreads();
-  const int j = wave;
+  const int z = blockIdx.z;
+  const int j = nw == 16 ? wave : wave == 0 ? z : wave == 1 ? 7 - z : wave == 2 ? 8 + z : 15 - z;
   float *out = const_cast<float *>(diag_inv(lsplit, ld, b, K0).at(0, j < 8 ? 0 : 128)) + 16 * (j & 7) + r;
   const int64_t ldf = ld / 2;
   f32x4 xt[16];
@@ -1679,7 +1693,8 @@ hipError_t launch_cholesky_factor(float *Gw, const float *Gc, int B, int t, int6
   const hipError_t ei = hipFuncSetAttribute((const void *)k_chol_inv256, hipFuncAttributeMaxDynamicSharedMemorySize,
                                             (int)kDiag256Lds);
   if (ei != hipSuccess) return ei;
-  hipLaunchKernelGGL(k_chol_inv256, dim3((unsigned)(ld / kOuter), B), dim3(1024), kDiag256Lds, s, Gw, ld, dinv,
+  const int nblk = (int)(ld / kOuter), split = (int64_t)nblk * B <= 64 ? 4 : 1;   // as long as a CU per workgroup is left
+  hipLaunchKernelGGL(k_chol_inv256, dim3((unsigned)nblk, B, split), dim3(1024 / split), kDiag256Lds, s, Gw, ld, dinv,
                      lsplit, st.info);
   (void)Gc;
   (void)delta0;
