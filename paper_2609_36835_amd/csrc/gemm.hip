@@ -62,7 +62,7 @@ hipError_t launch_gram(int dtype, const void *X, float *G, float *Gc, int P, int
   }
   g.a_pair = g.b_pair = tp * np_;
   g.a_plane = g.b_plane = 0;
-  return launch_gemm<float, 1, 1>(g, (const float *)X, (const float *)X, e, s);
+  return launch_gemm<float, 1, 1, true>(g, (const float *)X, (const float *)X, e, s);
 }
 
 // out[r][c] = sum_k A[r][k] B[c][k] (minus lam X) for 128 columns c, split bf16
@@ -104,7 +104,7 @@ hipError_t launch_rhs_gemm(int dtype, const void *PT, const void *YT, float *Bm,
   g.a_plane = 0;
   g.b_pair = (int64_t)kHeadDim * np_;
   g.b_plane = 0;
-  return launch_gemm<float, 1, 1>(g, (const float *)PT, (const float *)YT, e, s);
+  return launch_gemm<float, 1, 1, true>(g, (const float *)PT, (const float *)YT, e, s);
 }
 
 // Value-fit refinement residual from the data, in two contractions over the
@@ -143,7 +143,7 @@ hipError_t launch_value_residual(int dtype, const void *XT, const void *Pm, cons
     }
   } else {
     EpiValueResid<false> ep{UT, kHeadDim * np_, 0, (int)np_, n, Y};
-    e = launch_gemm<float, 1, 1>(g1, (const float *)XT, (const float *)Pm, ep, s);
+    e = launch_gemm<float, 1, 1, true>(g1, (const float *)XT, (const float *)Pm, ep, s);
   }
   if (e != hipSuccess) return e;
   GemmShape g2;
@@ -165,7 +165,7 @@ hipError_t launch_value_residual(int dtype, const void *XT, const void *Pm, cons
                 false, (int)(tp / 256)};
     return gemm_cols128(gb, (const bf16 *)PT, (const bf16 *)UT, R, X, lam, s);
   }
-  return launch_gemm<float, 1, 1>(g2, (const float *)PT, (const float *)UT, e2, s);
+  return launch_gemm<float, 1, 1, true>(g2, (const float *)PT, (const float *)UT, e2, s);
 }
 
 }  // namespace arckv

@@ -8,8 +8,9 @@
 // Operands may carry two bf16 planes (hi, lo); the product then adds the
 // three leading terms, giving ~16 significant bits per operand.
 //
-// Tiles: 128 x 128 per workgroup, 4 waves of 64 x 64 (2 x 2 MFMA 32x32 tiles),
-// K staged through LDS in slabs of 32 with register prefetch of the next slab.
+// Tiles: 128 x 128 per workgroup, 4 waves of 64 x 64 (TS = 2: 2 x 2 MFMA 32x32
+// tiles), K staged through LDS in slabs of 32 with register prefetch of the next
+// slab; 64 x 64 per workgroup (TS = 1) for contractions of few tiles.
 // Dimensions M, N, K must be multiples of the tile (callers pad workspace).
 // Workgroups are remapped so each XCD receives a contiguous, M-grouped range
 // of tiles (operand reuse in that XCD's L2).
@@ -28,9 +29,9 @@ struct GemmShape {
 
 constexpr int kGBM = 128, kGBN = 128, kGBK = 32;
 
-// Decode a logical tile id into (batch, mt, nt).
-__device__ inline void gemm_tile(const GemmShape &g, int64_t tile, int &p, int &mt, int &nt) {
-  const int MT = g.M / kGBM, NT = g.N / kGBN;
+// Decode a logical tile id (tiles of bt x bt) into (batch, mt, nt).
+__device__ inline void gemm_tile(const GemmShape &g, int bt, int64_t tile, int &p, int &mt, int &nt) {
+  const int MT = g.M / bt, NT = g.N / bt;
   if (g.syrk) {
     const int64_t per = (int64_t)MT * (MT + 1) / 2;
     p = (int)(tile / per);
@@ -56,32 +57,32 @@ __device__ inline void gemm_tile(const GemmShape &g, int64_t tile, int &p, int &
   nt = (int)(rr / gsize);
 }
 
-__host__ inline int64_t gemm_tiles(const GemmShape &g) {
-  const int64_t MT = g.M / kGBM, NT = g.N / kGBN;
+__host__ inline int64_t gemm_tiles(const GemmShape &g, int bt) {
+  const int64_t MT = g.M / bt, NT = g.N / bt;
   return (int64_t)g.batch * (g.syrk ? MT * (MT + 1) / 2 : MT * NT);
 }
 
-template <typename T, int NA, int NB, class Epi>
+template <typename T, int NA, int NB, int TS, class Epi>
 __global__ void __launch_bounds__(256) k_gemm_tn(GemmShape g, const T *__restrict__ A, const T *__restrict__ B,
                                                  Epi epi) {
   using Mf = Mfma<T>;
-  constexpr int KPL = Mf::KPL, KSTEP = Mf::KSTEP;
+  constexpr int KPL = Mf::KPL, KSTEP = Mf::KSTEP, BT = 64 * TS;
   constexpr int EPC = 16 / sizeof(T);             // elements per 16-byte chunk
   constexpr int SL = kGBK + EPC;                  // padded LDS row stride (elements)
   constexpr int CPR = kGBK / EPC;                 // chunks per row
-  constexpr int CH = kGBM * CPR / 256;            // chunks per thread per plane
-  __shared__ __attribute__((aligned(16))) T sA[NA][kGBM * SL];
-  __shared__ __attribute__((aligned(16))) T sB[NB][kGBN * SL];
+  constexpr int CH = BT * CPR / 256;            // chunks per thread per plane
+  __shared__ __attribute__((aligned(16))) T sA[NA][BT * SL];
+  __shared__ __attribute__((aligned(16))) T sB[NB][BT * SL];
 
   const int64_t nblocks = gridDim.x;
   const int64_t tile = xcd_remap(blockIdx.x, nblocks);
   int p, mt, nt;
-  gemm_tile(g, tile, p, mt, nt);
+  gemm_tile(g, BT, tile, p, mt, nt);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   const int h = lane >> 5, col = lane & 31;
-  const T *Ab = A + (size_t)p * g.a_pair + (size_t)mt * kGBM * g.lda;
-  const T *Bb = B + (size_t)p * g.b_pair + (size_t)nt * kGBN * g.ldb;
+  const T *Ab = A + (size_t)p * g.a_pair + (size_t)mt * BT * g.lda;
+  const T *Bb = B + (size_t)p * g.b_pair + (size_t)nt * BT * g.ldb;
 
   f32x4 ra[NA][CH], rb[NB][CH];
   auto prefetch = [&](int k0) {
@@ -96,11 +97,11 @@ __global__ void __launch_bounds__(256) k_gemm_tn(GemmShape g, const T *__restric
         rb[q][c] = *reinterpret_cast<const f32x4 *>(Bb + q * g.b_plane + (size_t)r * g.ldb + k0 + cc);
     }
   };
-  f32x16 acc[2][2];
+  f32x16 acc[TS][TS];
   #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < TS; ++i)
     #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = zero16();
+    for (int j = 0; j < TS; ++j) acc[i][j] = zero16();
 
   prefetch(0);
   for (int k0 = 0; k0 < g.K; k0 += kGBK) {
@@ -117,25 +118,25 @@ __global__ void __launch_bounds__(256) k_gemm_tn(GemmShape g, const T *__restric
     if (k0 + kGBK < g.K) prefetch(k0 + kGBK);
     #pragma unroll
     for (int ks = 0; ks < kGBK / KSTEP; ++ks) {
-      typename Mf::frag fa[NA][2], fb[NB][2];
+      typename Mf::frag fa[NA][TS], fb[NB][TS];
       #pragma unroll
-      for (int i = 0; i < 2; ++i) {
+      for (int i = 0; i < TS; ++i) {
         #pragma unroll
-        for (int q = 0; q < NA; ++q) fa[q][i] = Mf::load(&sA[q][(wm * 64 + 32 * i + col) * SL + ks * KSTEP + KPL * h]);
+        for (int q = 0; q < NA; ++q) fa[q][i] = Mf::load(&sA[q][(wm * 32 * TS + 32 * i + col) * SL + ks * KSTEP + KPL * h]);
         #pragma unroll
-        for (int q = 0; q < NB; ++q) fb[q][i] = Mf::load(&sB[q][(wn * 64 + 32 * i + col) * SL + ks * KSTEP + KPL * h]);
+        for (int q = 0; q < NB; ++q) fb[q][i] = Mf::load(&sB[q][(wn * 32 * TS + 32 * i + col) * SL + ks * KSTEP + KPL * h]);
       }
       #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < TS; ++i)
         #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < TS; ++j) {
           acc[i][j] = Mf::mma(fa[0][i], fb[0][j], acc[i][j]);
           if constexpr (NB > 1) acc[i][j] = Mf::mma(fa[0][i], fb[1][j], acc[i][j]);
           if constexpr (NA > 1) acc[i][j] = Mf::mma(fa[1][i], fb[0][j], acc[i][j]);
         }
     }
   }
-  epi(acc, p, mt * kGBM + wm * 64, nt * kGBN + wn * 64, mt, nt, lane, wm);
+  epi(acc, p, mt * BT + wm * 32 * TS, nt * BT + wn * 32 * TS, mt, nt, lane, wm);
 }
 
 // ------------------------------------------------------------------ epilogues
@@ -200,14 +201,15 @@ struct EpiSym {
   float *G, *Gc;
   int64_t pair_stride;  // ld * ld
   int ld;
-  __device__ __forceinline__ void operator()(f32x16 (&acc)[2][2], int p, int row0, int col0, int mt, int nt, int lane,
+  template <int TS>
+  __device__ __forceinline__ void operator()(f32x16 (&acc)[TS][TS], int p, int row0, int col0, int mt, int nt, int lane,
                              int) const {
     const int h = lane >> 5, col = lane & 31;
     float *Gp = G + (size_t)p * pair_stride, *Gcp = Gc + (size_t)p * pair_stride;
     #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < TS; ++i)
       #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+      for (int j = 0; j < TS; ++j) {
         const int c = col0 + 32 * j + col;
         #pragma unroll
         for (int g = 0; g < 4; ++g) {
@@ -235,13 +237,14 @@ struct EpiStore {
   int ld;
   const float *X;        // nullptr: plain store
   const float *lam;      // [P]
-  __device__ __forceinline__ void operator()(f32x16 (&acc)[2][2], int p, int row0, int col0, int, int, int lane, int) const {
+  template <int TS>
+  __device__ __forceinline__ void operator()(f32x16 (&acc)[TS][TS], int p, int row0, int col0, int, int, int lane, int) const {
     const size_t base = (size_t)p * pair_stride;
     const int col = lane & 31;
     #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < TS; ++i)
       #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+      for (int j = 0; j < TS; ++j) {
         const int c = col0 + 32 * j + col;
         #pragma unroll
         for (int v = 0; v < 16; ++v) {
@@ -263,12 +266,13 @@ struct EpiValueResid {
   int64_t pair_stride, plane_stride;   // elements
   int ld, n;
   const float *Y;                      // [P][n][128]
-  __device__ __forceinline__ void operator()(f32x16 (&acc)[2][2], int p, int row0, int col0, int, int, int lane, int) const {
+  template <int TS>
+  __device__ __forceinline__ void operator()(f32x16 (&acc)[TS][TS], int p, int row0, int col0, int, int, int lane, int) const {
     const int h = lane >> 5, col = lane & 31;
     #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < TS; ++i)
       #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+      for (int j = 0; j < TS; ++j) {
         const int q = col0 + 32 * j + col;   // query index
         #pragma unroll
         for (int g = 0; g < 4; ++g) {
@@ -293,11 +297,24 @@ struct EpiValueResid {
   }
 };
 
-template <typename T, int NA, int NB, class Epi>
+// SMALL: 64 x 64 tiles where 128 x 128 ones are fewer than a quarter of the CUs
+// (fp32 at t = 102, n = 256: Phi_C, Gram and residual
+// products 29.4, 24.6 and 24.0 us with 128 x 128 tiles, 11.3, 9.6 and 10.1 us so); not for EpiArgmax, whose partials are
+// per 128 rows.
+template <typename T, int NA, int NB, bool SMALL = false, class Epi>
 hipError_t launch_gemm(const GemmShape &g, const T *A, const T *B, const Epi &epi, hipStream_t s) {
-  const int64_t tiles = gemm_tiles(g);
+  const int64_t tiles = gemm_tiles(g, kGBM);
   if (tiles == 0) return hipSuccess;
-  hipLaunchKernelGGL((k_gemm_tn<T, NA, NB, Epi>), dim3((unsigned)tiles), dim3(256), 0, s, g, A, B, epi);
+  if constexpr (SMALL) {
+    if (tiles < 64) {
+      GemmShape g1 = g;
+      g1.group_m = 2 * g.group_m;
+      hipLaunchKernelGGL((k_gemm_tn<T, NA, NB, 1, Epi>), dim3((unsigned)gemm_tiles(g, kGBM / 2)), dim3(256), 0, s, g1, A,
+                         B, epi);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((k_gemm_tn<T, NA, NB, 2, Epi>), dim3((unsigned)tiles), dim3(256), 0, s, g, A, B, epi);
   return hipGetLastError();
 }
 
