@@ -12,12 +12,16 @@
 //   k_attend_partial  a workgroup of 8 waves takes 256 consecutive keys of
 //                     the concatenated block; each wave scores its 32 keys
 //                     against the G queries on MFMA 16x16x32 (keys as rows,
-//                     queries as zero-padded columns), takes the softmax of
-//                     its chunk, and accumulates P V on the VALU (each lane
-//                     owns 8 dims of 4 interleaved keys, probabilities
-//                     broadcast from LDS).  The eight waves' (max, sum, o) are
+//                     queries as columns), takes the softmax of its chunk, and
+//                     forms P V on MFMA too: the lane that holds a query's
+//                     probabilities is the one that feeds them, so they pass
+//                     through no LDS.  The eight waves' (max, sum, o) are
 //                     merged in LDS into one partial per workgroup.  All of
-//                     the chunk's K and V loads are issued up front.
+//                     the chunk's K and V loads are issued up front, without
+//                     branches.  Small calls are bound by the launches and one
+//                     round trip to memory: 8 pairs of 856 keys take 9.1 us
+//                     (11.1 us with P V on the VALU and loads under branches);
+//                     512 pairs of 3533 keys, 169 us (184), 5.5 TB/s.
 //   k_attend_combine  merges the partials of a pair with the usual
 //                     max-rescaling and writes o.
 #include <mutex>
@@ -37,12 +41,21 @@ __device__ inline f32x4_t mfma16(bf16x8 a, bf16x8 b, f32x4_t c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// Row `key` of the concatenated block [compact (t rows); fixed (F rows)], or
-// nullptr past the end.
+// The upper halves of two 32-bit words, one after the other.
+__device__ inline uint32_t upper_halves(uint32_t first, uint32_t second) {
+  return __builtin_amdgcn_perm(second, first, 0x07060302u);
+}
+__device__ inline uint32_t lower_halves(uint32_t first, uint32_t second) {
+  return __builtin_amdgcn_perm(second, first, 0x05040100u);
+}
+
+// Row `key` of the concatenated block [compact (t rows); fixed (F rows)], the last
+// row past the end.  By selection only: with branches the compiler waits for some
+// loads inside them, a memory round trip each.
 __device__ inline const bf16 *att_row(const bf16 *C, const bf16 *Fx, int p, int t, int F, int key) {
-  if (key < t) return C + ((size_t)p * t + key) * kHeadDim;
-  if (key < t + F) return Fx + ((size_t)p * F + (key - t)) * kHeadDim;
-  return nullptr;
+  key = min(key, t + F - 1);
+  const bool c = key < t;
+  return (c ? C : Fx) + ((int64_t)p * (c ? t : F) + (c ? key : key - t)) * kHeadDim;
 }
 }  // namespace
 
@@ -53,8 +66,7 @@ __global__ void __launch_bounds__(64 * kAttW) k_attend_partial(int t, int F, flo
                                                          const bf16 *__restrict__ Vf, float *__restrict__ part_o,
                                                          float *__restrict__ part_ml, int nch) {
   static_assert(G >= 1 && G <= 8, "query rows per pair");
-  __shared__ float sP[kAttW][kAttKPW][G];       // probabilities of each wave's keys
-  __shared__ float sO[kAttW][G][kHeadDim];      // per-wave partial outputs
+  __shared__ __align__(16) float sO[kAttW][G][kHeadDim];   // per-wave partial outputs
   __shared__ float sM[kAttW][G], sL[kAttW][G];
   const int p = blockIdx.y, ch = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -63,28 +75,38 @@ __global__ void __launch_bounds__(64 * kAttW) k_attend_partial(int t, int F, flo
   const int g = lane >> 4, r = lane & 15;        // MFMA lane coordinates
 
   // ---- issue every load of the chunk: K as MFMA A fragments (key rows), V rows
-  // for the PV pass (lane = key group g (keys key0 + 4 i + g) x dims 8 r .. 8 r + 7)
-  const bf16x8 zero8 = Mfma<bf16>::zero();
+  // for the PV pass (lane = the keys of its logits below x dims 8 r .. 8 r + 7)
   constexpr int KT = kAttKPW / 16, VI = kAttKPW / 4;
   bf16x8 kf[KT][4];
 #pragma unroll
   for (int kt = 0; kt < KT; ++kt) {
     const bf16 *row = att_row(Ck, Kf, p, t, F, key0 + 16 * kt + r);
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-      kf[kt][ks] = row ? *reinterpret_cast<const bf16x8 *>(row + 32 * ks + 8 * g) : zero8;
+    for (int ks = 0; ks < 4; ++ks) kf[kt][ks] = *reinterpret_cast<const bf16x8 *>(row + 32 * ks + 8 * g);
   }
-  bf16x8 vf[VI];
-#pragma unroll
-  for (int i = 0; i < VI; ++i) {
-    const bf16 *row = att_row(Cv, Vf, p, t, F, key0 + 4 * i + g);
-    vf[i] = row ? *reinterpret_cast<const bf16x8 *>(row + 8 * r) : zero8;
-  }
-  // queries as the B operand: column r = query row r (zero for r >= G)
+  // queries as the B operand: column r = query row r (the last one again for r >= G)
   bf16x8 qf[4];
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks)
-    qf[ks] = r < G ? *reinterpret_cast<const bf16x8 *>(Q + ((size_t)p * G + r) * kHeadDim + 32 * ks + 8 * g) : zero8;
+    qf[ks] = *reinterpret_cast<const bf16x8 *>(Q + ((size_t)p * G + min(r, G - 1)) * kHeadDim + 32 * ks + 8 * g);
+  // the biases of this lane's keys, with the other loads: after the products
+  // they would cost a memory round trip of their own
+  float bv[VI];
+#pragma unroll
+  for (int i = 0; i < VI; ++i) bv[i] = 0.0f;
+  if (beta && key0 < t) {
+#pragma unroll
+    for (int i = 0; i < VI; ++i) bv[i] = beta[(size_t)p * t + min(key0 + 16 * (i / 4) + 4 * g + i % 4, t - 1)];
+  }
+  union Frag {
+    uint32_t w[4];
+    bf16x8 v;
+  };
+  Frag vf[VI];
+#pragma unroll
+  for (int i = 0; i < VI; ++i)
+    vf[i].v = *reinterpret_cast<const bf16x8 *>(att_row(Cv, Vf, p, t, F, key0 + 16 * (i / 4) + 4 * g + i % 4) + 8 * r);
+  __builtin_amdgcn_sched_barrier(0);   // the loads stay above the products
 
   // ---- logits: lane (g, r) holds keys key0 + 16 kt + 4 g + j (j < 4) for query r
   float sv[VI];
@@ -96,9 +118,7 @@ __global__ void __launch_bounds__(64 * kAttW) k_attend_partial(int t, int F, flo
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int key = key0 + 16 * kt + 4 * g + j;
-      float b = 0.0f;
-      if (beta && key < t) b = beta[(size_t)p * t + key];
-      sv[4 * kt + j] = key < L ? fmaf(scale, acc[j], b) : -INFINITY;
+      sv[4 * kt + j] = key < L ? fmaf(scale, acc[j], key < t ? bv[4 * kt + j] : 0.0f) : -INFINITY;
     }
   }
   // ---- softmax of the wave's keys per query (reduce the lane's VI, then over g)
@@ -116,50 +136,58 @@ __global__ void __launch_bounds__(64 * kAttW) k_attend_partial(int t, int F, flo
   }
   l += __shfl_xor(l, 16, 64);
   l += __shfl_xor(l, 32, 64);
-  if (r < G) {
-#pragma unroll
-    for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) sP[wave][16 * kt + 4 * g + j][r] = sv[4 * kt + j];
-    if (g == 0) {
-      sM[wave][r] = m;
-      sL[wave][r] = l;
-    }
+  if (g == 0 && r < G) {
+    sM[wave][r] = m;
+    sL[wave][r] = l;
   }
-  __syncthreads();
-  // ---- P V: lane (g, r) accumulates keys 4 i + g, dims 8 r .. 8 r + 7
-  float o[G][8];
+  // ---- P V on MFMA over the wave's 32 keys: lane (g, r) holds query r's
+  // probabilities of keys 16 (i / 4) + 4 g + i % 4, which is an A operand's row r
+  // with those keys as its contraction slots 8 g + i, and V's same keys at dims
+  // 8 r + e, which is column r of eight B operands, one per e.  Each probability
+  // goes in as three bf16 terms (truncated, so all of one sign) that sum to it
+  // exactly; the first has products of its own, which alone carry an infinite value
+  // (0 times it in the other terms would be NaN).
+  Frag ph, pm, pl;
 #pragma unroll
-  for (int q = 0; q < G; ++q)
+  for (int k = 0; k < 4; ++k) {
+    uint32_t h[2], mi[2], lo[2];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) o[q][e] = 0.0f;
-#pragma unroll
-  for (int i = 0; i < VI; ++i) {
-    float pq[G];
-#pragma unroll
-    for (int q = 0; q < G; ++q) pq[q] = sP[wave][4 * i + g][q];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float v = (float)vf[i][e];
-#pragma unroll
-      for (int q = 0; q < G; ++q) o[q][e] = fmaf(pq[q], v, o[q][e]);
+    for (int c = 0; c < 2; ++c) {
+      const float x = sv[2 * k + c];
+      h[c] = __float_as_uint(x) & 0xffff0000u;
+      const float x1 = x - __uint_as_float(h[c]);
+      mi[c] = __float_as_uint(x1) & 0xffff0000u;
+      lo[c] = __float_as_uint(x1 - __uint_as_float(mi[c]));
     }
+    ph.w[k] = upper_halves(h[0], h[1]);
+    pm.w[k] = upper_halves(mi[0], mi[1]);
+    pl.w[k] = upper_halves(lo[0], lo[1]);
+  }
+  // a row past the end stands for zeros (its probability is zero, but zero times
+  // an infinite value is not)
+#pragma unroll
+  for (int i = 0; i < VI; ++i)
+    if (key0 + 16 * (i / 4) + 4 * g + i % 4 >= L) vf[i] = Frag{};
+  float o[4][8];   // row 4 g + j = query, column 8 r + e
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    Frag b;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      b.w[k] = e & 1 ? upper_halves(vf[2 * k].w[e / 2], vf[2 * k + 1].w[e / 2])
+                     : lower_halves(vf[2 * k].w[e / 2], vf[2 * k + 1].w[e / 2]);
+    const f32x4_t first = mfma16(ph.v, b.v, f32x4_t{0.0f, 0.0f, 0.0f, 0.0f});
+    const f32x4_t rest = mfma16(pm.v, b.v, mfma16(pl.v, b.v, f32x4_t{0.0f, 0.0f, 0.0f, 0.0f}));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) o[j][e] = fabsf(first[j]) < INFINITY ? first[j] + rest[j] : first[j];
   }
 #pragma unroll
-  for (int q = 0; q < G; ++q)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      float x = o[q][e];
-      x += __shfl_xor(x, 16, 64);
-      x += __shfl_xor(x, 32, 64);
-      o[q][e] = x;
+  for (int j = 0; j < 4; ++j)
+    if (4 * g + j < G) {
+      float *to = &sO[wave][4 * g + j][8 * r];
+      *reinterpret_cast<float4 *>(to) = make_float4(o[j][0], o[j][1], o[j][2], o[j][3]);
+      *reinterpret_cast<float4 *>(to + 4) = make_float4(o[j][4], o[j][5], o[j][6], o[j][7]);
     }
-  if (g == 0) {
-#pragma unroll
-    for (int q = 0; q < G; ++q)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) sO[wave][q][8 * r + e] = o[q][e];
-  }
   __syncthreads();
   // ---- merge the waves: one partial (max, sum, o) per query for the chunk
   float *po = part_o + (((size_t)p * nch + ch) * G) * kHeadDim;
