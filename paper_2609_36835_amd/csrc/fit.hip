@@ -226,91 +226,164 @@ __global__ void __launch_bounds__(256) k_nonfinite(FiniteCheck f, int32_t *__res
 }
 
 // ------------------------------------------------- the panel's diagonal block
-// 16 x 16 fp32 tiles in LDS and in registers share one layout: element (r, c)
-// at float 64 (c / 4) + 4 r + c % 4, so lane l = 16 g + r holds columns
-// 4 g .. 4 g + 3 of row r as four consecutive floats (one conflict-free 16-byte
-// access per lane).  tile_mac(acc, X, Y) adds X Y^T: with the MFMA's operands
-// given as (Y, X) its output lands in this layout again, so a result feeds the
-// next product without leaving the registers.
-__device__ inline f32x4 tile_mac(f32x4 acc, f32x4 x, f32x4 y) {
+// 16 x 16 fp32 tiles in LDS: element (r, c) at float 64 (c % 4) + 4 r + c / 4, so
+// lane 16 g + r reads columns g, 4 + g, 8 + g, 12 + g of row r with one
+// conflict-free 16-byte access.  fp32 MFMA adds its products one by one, each with
+// one rounding, so the four instructions of diag_mac(acc, X, Y) add X Y^T in
+// column order, exactly as fused multiply-adds would.  With Y read by
+// diag_get_perm (row 4 (r % 4) + r / 4) the result is in the same layout; with Y
+// read by diag_get lane 16 g + r gets columns 4 g .. 4 g + 3 of row r.
+__device__ __forceinline__ f32x4 diag_get(const float *tile, int lane) {
+  return *reinterpret_cast<const f32x4 *>(tile + 4 * lane);
+}
+__device__ __forceinline__ f32x4 diag_get_perm(const float *tile, int lane) {
+  return *reinterpret_cast<const f32x4 *>(tile + 4 * ((lane & 0x30) + 4 * (lane & 3) + ((lane >> 2) & 3)));
+}
+__device__ __forceinline__ f32x4 diag_mac(f32x4 acc, f32x4 x, f32x4 y) {
 #pragma unroll
   for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(y[s], x[s], acc, 0, 0, 0);
   return acc;
 }
-
-// Lane N of each row of 16 lanes, broadcast over that row.
+// The same for N accumulators with one Y, side by side: a product that waits for the
+// one before it takes longer than its issue.
 template <int N>
-__device__ __forceinline__ float row_bcast(float v) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x150 + N, 0xf, 0xf, true));
-}
-
-// a[C + 1 ..] += nl L_qC for the columns q = C + 1 .. 15 (lane q's a[C] is L_qC).
-template <int C, int... Q>
-__device__ __forceinline__ void factor16_update(float (&a)[16], float nl, std::integer_sequence<int, Q...>) {
-  ((a[C + 1 + Q] = fmaf(row_bcast<C + 1 + Q>(a[C]), nl, a[C + 1 + Q])), ...);
-}
-
-// Columns C .. 15 of a 16 x 16 factorisation in one wave: lane r of every row
-// of 16 lanes holds row r of A in a[] (the four rows of lanes repeat the
-// work); y holds columns 4 g .. 4 g + 3 of row r of the identity and becomes
-// row r of L^-1 before its scaling by 1 / L_rr.  a[c] becomes L_rc for r > c;
-// entries above the diagonal are never read by another lane.  piv and inv
-// collect row r's pivot and 1 / L_rr.  1 / sqrt(pivot) is the hardware estimate
-// and one Newton step (about one unit in the last place); TINY scales pivots near
-// its underflow by 2^64 first.
-constexpr float kTinyPivot = 0x1p-96f;
-template <int C, bool TINY>
-__device__ __forceinline__ void factor16(float (&a)[16], f32x4 &y, float &piv, float &inv, int r) {
-  if constexpr (C < 16) {
-    const float p = row_bcast<C>(a[C]);
-    const bool small = TINY && p < kTinyPivot;
-    const float q = small ? p * 0x1p64f : p;
-    const float r0 = __builtin_amdgcn_rsqf(q);
-    const float r1 = fmaf(0.5f * r0, fmaf(-(q * r0), r0, 1.0f), r0);
-    const float rs = small ? r1 * 0x1p32f : r1;
-    piv = r == C ? p : piv;
-    inv = r == C ? rs : inv;
-    a[C] *= rs;
-    const float nl = r > C ? -a[C] : 0.0f;
-    factor16_update<C>(a, nl, std::make_integer_sequence<int, 15 - C>{});
-    const float nx = nl * rs;
+__device__ __forceinline__ void diag_mac_n(f32x4 *acc, const f32x4 *x, f32x4 y) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) y[v] = fmaf(row_bcast<C>(y[v]), nx, y[v]);
-    factor16<C + 1, TINY>(a, y, piv, inv, r);
+  for (int s = 0; s < 4; ++s)
+#pragma unroll
+    for (int u = 0; u < N; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(y[s], x[u][s], acc[u], 0, 0, 0);
+}
+// Row r of a tile into (or from) one lane's 16 registers.
+__device__ __forceinline__ void diag_row(const float *tile, int r, float (&a)[16]) {
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const f32x4 v = *reinterpret_cast<const f32x4 *>(tile + 64 * g + 4 * r);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) a[4 * s + g] = v[s];
+  }
+}
+__device__ __forceinline__ void diag_put_row(float *tile, int r, const float (&a)[16]) {
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+    *reinterpret_cast<f32x4 *>(tile + 64 * g + 4 * r) = f32x4{a[g], a[4 + g], a[8 + g], a[12 + g]};
+}
+
+// Workgroup barrier for LDS alone: the stores to global memory, which the kernel
+// does not read back, stay in flight.
+__device__ __forceinline__ void diag_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+__device__ __forceinline__ float lane_value(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+
+// v with lane LANE replaced by the wave-uniform x.
+template <int LANE>
+__device__ __forceinline__ float lane_put(float v, float x) {
+  asm("s_nop 1\n\tv_writelane_b32 %0, %1, %2" : "+v"(v) : "s"(x), "n"(LANE));
+  return v;
+}
+
+// a[q] -= l col_q for q = C + 1 .. 15, col_q lane q's col.  The lanes are read
+// first: a vector instruction has to wait two cycles for a scalar just read.
+template <int C>
+__device__ __forceinline__ void sub_column(float (&a)[16], float col, float l) {
+  float v[16];
+#pragma unroll
+  for (int q = C + 1; q < 16; ++q) v[q] = lane_value(col, q);
+#pragma unroll
+  for (int q = C + 1; q < 16; ++q) a[q] = fmaf(-v[q], l, a[q]);
+}
+
+// sqrt(p) and its reciprocal from the hardware's estimate r0 of 1 / sqrt(p) with one
+// residual each: the root correctly rounded, the reciprocal too but for a root
+// whose significand is all ones.  TINY scales p below 2^-96 by 2^64 first, whose
+// residuals would underflow.
+constexpr float kTinyPivot = 0x1p-96f;
+template <bool TINY>
+__device__ __forceinline__ void pivot_root(float p, float &root, float &inv) {
+  const bool small = TINY && p < kTinyPivot;
+  const float q = small ? p * 0x1p64f : p;
+  const float r0 = __builtin_amdgcn_rsqf(q);
+  const float d0 = q * r0;
+  const float d = fmaf(fmaf(-d0, d0, q), 0.5f * r0, d0);
+  const float i = fmaf(fmaf(-d, r0, 1.0f), r0, r0);
+  root = small ? d * 0x1p-32f : d;
+  inv = small ? i * 0x1p32f : i;
+}
+
+// Columns C .. 15 of the factorisation of up to 64 rows in one wave, one row per
+// lane, lanes 0 .. 15 the diagonal tile's.  a[c] becomes L_rc (of the diagonal
+// tile for r > c only; entries above are never read by another lane); lane C
+// of the first 16 keeps column C's pivot in piv.
+template <int C, bool TINY>
+__device__ __forceinline__ void factor_columns(float (&a)[16], float &piv) {
+  if constexpr (C < 16) {
+    float root, inv;
+    const float p = lane_value(a[C], C);
+    pivot_root<TINY>(p, root, inv);
+    piv = lane_put<C>(piv, p);
+    a[C] *= inv;
+    sub_column<C>(a, a[C], a[C]);
+    factor_columns<C + 1, TINY>(a, piv);
+  }
+}
+
+// Rows C .. 15 of the substitution L X = Y, one column per lane: y[c] becomes
+// X_c = Y_c inv_c, L and inv as factor_columns leaves them.
+template <int C>
+__device__ __forceinline__ void substitute_rows(float (&y)[16], const float (&a)[16], float inv) {
+  if constexpr (C < 16) {
+    y[C] *= lane_value(inv, C);
+    sub_column<C>(y, a[C], y[C]);
+    substitute_rows<C + 1>(y, a, inv);
   }
 }
 
 // The 256 x 256 diagonal block at K0 in one workgroup per pair: L in place and
-// the inverses of its four 64 x 64 diagonal blocks to dinv.  The block is held
-// in LDS as its 136 lower 16 x 16 tiles; wave i owns tile row i.  Step k
-// (16 columns): wave k factors tile (k, k) and inverts it, while the waves
-// below form what columns 0 .. k - 1 subtract from column k + 1
-// (left-looking); then L_ik = A_ik L_kk^-T from registers, and the last
-// product of column k + 1, L_ik L_k+1,k^T, from the rows just written.  Two
-// barriers per step.  nk = ceil((t - K0) / 16) steps, at most 16: the padding
-// is an identity already.  A failed pivot records info = column + 1.
+// the inverses X of its four 64 x 64 diagonal blocks to dinv.  The block is held
+// in LDS as its 136 lower 16 x 16 tiles.  For each 64-wide step K (tile columns
+// 4 K .. 4 K + 3), with wave 4 K + s the owner of tile column 4 K + s inside the
+// diagonal block and wave i that of tile row i below it:
+//   phase p = 0 .. 3: wave p of the block factors tile column p (its rows down to
+//     the block's end, one per lane), after the product of column p - 1 that just
+//     became visible; wave p - 1 meanwhile forms X's tile row p - 1 by
+//     substitution, one column per lane; phase 4: X's last tile row.  The waves of
+//     the blocks below spend the phases on step K - 1's update of their tiles,
+//     A -= L L^T over its 64 columns.
+//   panel: the rows below, L_i = A_i X^T.
+// Every entry sees the operations, in the order, of a column-by-column
+// factorisation of each 64 x 64 block, a row-by-row substitution for its inverse
+// and 64-wide products for the rest.  nb = ceil((t - K0) / 64) steps, at most 4:
+// the padding is an identity already.  A failed pivot records info = column + 1.
 //
-// Bound by the chain of its 256 pivots (16 factorisations of one wave, about
-// 0.9 us each) with the fp32 MFMA products of the trailing tiles under it.
-// One launch in place of ten (four 64-column factorisations of 35 us, whose
-// 1024 threads each took every column's square root and division, and three
-// panel and three update launches on single blocks): 197 -> 45 us
-// per block at 8 pairs.
-constexpr size_t kDiag256Lds = (size_t)136 * 256 * sizeof(float) + 16;
+// Bound by the chain of its 256 pivots (16 tile columns of about 1.6 us, 0.7 us of
+// them the pivots).  One launch in place of ten (64-column factorisations of 35 us
+// and three panel and three update launches on single blocks): 197 -> 48 us per
+// block at 8 pairs.  Keeping the operations' order costs 4 us against a form with
+// explicit 16 x 16 inverses, whose roundings, of the same size, moved the fitted
+// biases of nearly square systems (t = 3277, n = 4096) by up to 0.56 of their scale.
+constexpr int kDiagXn = 260;   // floats of a tile of X: its column-wise stores hit 16 banks
+constexpr size_t kDiag256Lds = (size_t)(136 * 256 + 6 * 256 + 10 * kDiagXn + 16) * sizeof(float);
 
-__global__ void __launch_bounds__(1024) k_chol_diag256(float *__restrict__ Gw, int64_t ld, int K0, int nk,
+__global__ void __launch_bounds__(1024) k_chol_diag256(float *__restrict__ Gw, int64_t ld, int K0, int nb,
                                                        int32_t *__restrict__ info, float *__restrict__ dinv) {
   extern __shared__ __attribute__((aligned(16))) float diag_smem[];
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 15, g = lane >> 4;
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (info[b] != 0) return;   // uniform over the workgroup
-  int32_t *fail = reinterpret_cast<int32_t *>(diag_smem + 136 * 256);
+  float *const sXt = diag_smem + 136 * 256, *const sXn = sXt + 6 * 256;
+  int32_t *fail = reinterpret_cast<int32_t *>(sXn + 10 * kDiagXn);   // of every tile column: a slot is written in one phase only
   auto tile = [&](int i, int m) { return diag_smem + (i * (i + 1) / 2 + m) * 256; };
-  auto get = [&](int i, int m) { return *reinterpret_cast<const f32x4 *>(tile(i, m) + 4 * lane); };
-  auto put = [&](int i, int m, f32x4 v) { *reinterpret_cast<f32x4 *>(tile(i, m) + 4 * lane) = v; };
+  auto xt = [&](int i, int m) { return sXt + (i * (i + 1) / 2 + m) * 256; };        // X_im^T, i <= 2
+  auto xn = [&](int i, int m) { return sXn + (i * (i + 1) / 2 + m) * kDiagXn; };   // X_im
   float *D = Gw + (size_t)b * ld * ld + (size_t)K0 * ld + K0;
   float *grow = D + (size_t)(16 * wave + r) * ld + 4 * g;   // this lane's part of tile row `wave`
-  const f32x4 eye = {4 * g == r ? 1.0f : 0.0f, 4 * g + 1 == r ? 1.0f : 0.0f, 4 * g + 2 == r ? 1.0f : 0.0f,
-                     4 * g + 3 == r ? 1.0f : 0.0f};
+  float *Xb = dinv + ((size_t)b * (ld / kNB) + K0 / kNB) * kNB * kNB;
+  // columns 4 g .. 4 g + 3 of row r into a tile
+  auto put_quad = [&](float *to, f32x4 v) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) to[64 * e + 4 * r + g] = v[e];
+  };
   {
     f32x4 v[16];
 #pragma unroll
@@ -318,108 +391,153 @@ __global__ void __launch_bounds__(1024) k_chol_diag256(float *__restrict__ Gw, i
       if (m <= wave) v[m] = *reinterpret_cast<const f32x4 *>(grow + 16 * m);
 #pragma unroll
     for (int m = 0; m < 16; ++m)
-      if (m <= wave) put(wave, m, v[m]);
+      if (m <= wave) put_quad(tile(wave, m), v[m]);
   }
-  if (wave >= nk) put(wave, wave, eye);
-  if (tid == 0) *fail = 0;
+  if (tid < 16) fail[tid] = 0;
+  const int blk = wave >> 2, s = wave & 3;
+  if (blk >= nb) {   // a block of padding: identity
+#pragma unroll
+    for (int c = 0; c < 16; ++c) Xb[(size_t)blk * kNB * kNB + (16 * s + c) * kNB + lane] = 16 * s + c == lane ? 1.0f : 0.0f;
+  }
   __syncthreads();
-  const bool live = wave < nk;
-  f32x4 cc = get(wave, 0), cn = cc;   // this row's tile of column k, and of column k + 1 without L_ik's product
-  for (int k = 0; k < nk; ++k) {   // uniform over the workgroup
-    if (wave == k) {
-      put(k, k, cc);
-      float a[16];
-      auto row = [&]() {   // row r of the tile
-        __builtin_amdgcn_wave_barrier();
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  int32_t failed = 0;
+  for (int K = 0; K < nb; ++K) {   // uniform over the workgroup, as the phases
+    const int k0 = 4 * K, j = k0 + s;
+    f32x4 cc[4], yt[3];   // the column's tiles; X's tile row s (transposed) before its substitution
+    float a[16], inv;
+    const bool mine = blk == K, below = blk > K && blk < nb;
+    const int todo = below && K > 0 ? wave - k0 + 1 : 0;   // tiles of this row that step K - 1 updates
+    if (mine) {
+      // step K - 1's product (a wave with fewer tiles repeats its last one: the four
+      // chains then run side by side without branches)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f32x4 v = *reinterpret_cast<const f32x4 *>(tile(k, k) + 64 * q + 4 * r);
+      for (int u = 0; u < 4; ++u) cc[u] = zero;
+      if (K > 0) {
+#pragma unroll 1
+        for (int m = k0 - 4; m < k0; ++m) {
+          const f32x4 y = diag_get_perm(tile(j, m), lane);
+          f32x4 x[4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) a[4 * q + e] = v[e];
+          for (int u = 0; u < 4; ++u) x[u] = diag_get(tile(min(j + u, k0 + 3), m), lane);
+          __builtin_amdgcn_sched_barrier(0);
+          diag_mac_n<4>(cc, x, y);
         }
-        __builtin_amdgcn_wave_barrier();
-      };
-      f32x4 y = eye;
-      float piv = 0.0f, inv = 0.0f;
-      __builtin_amdgcn_s_setprio(3);   // the step's critical chain
-      row();
-      factor16<0, false>(a, y, piv, inv, r);
-      if (__ballot(!(piv >= kTinyPivot))) {   // a failed or a tiny pivot: again, with the scaling
-        row();
-        y = eye;
-        factor16<0, true>(a, y, piv, inv, r);
       }
-      __builtin_amdgcn_s_setprio(0);
-      const uint64_t bad = __ballot(!(piv > 0.0f) || !isfinite(piv)) & 0xffffull;
-      if (bad != 0 && lane == 0) *fail = K0 + 16 * k + __ffsll((unsigned long long)bad);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) y[v] *= inv;
-      put(k, k, y);   // the tile's inverse, which the panel and the block inverses read
-      // this lane's columns of L (bit masks: a select over the array elements
-      // would index the array in scratch memory)
+      for (int u = 0; u < 4; ++u) cc[u] = diag_get(tile(min(j + u, k0 + 3), j), lane) - cc[u];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        int l = 0;
+      for (int u = 0; u < 3; ++u) yt[u] = zero;
+    }
+#pragma unroll 1
+    for (int p = 0; p < 5; ++p) {
+      if (mine) {
+        if (p > 0 && p < 4 && s >= p) {   // column p - 1's product, just visible
+          const f32x4 y = diag_get_perm(tile(j, k0 + p - 1), lane);
+          f32x4 x[3];   // (a wave with fewer tiles repeats its last one)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) l |= __float_as_int(a[4 * q + v]) & (g == q ? -1 : 0);
-        const int c = 4 * g + v;
-        if (c <= r) grow[16 * k + v] = c == r ? piv * inv : __int_as_float(l);
+          for (int u = 0; u < 3; ++u) x[u] = -diag_get(tile(min(j + u, k0 + 3), k0 + p - 1), lane);
+          __builtin_amdgcn_sched_barrier(0);
+          diag_mac_n<3>(cc, x, y);
+        }
+        if (s == p) {
+          __builtin_amdgcn_s_setprio(3);   // the critical chain
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (s + u < 4) *reinterpret_cast<f32x4 *>(tile(j + u, j) + 4 * lane) = cc[u];
+          __builtin_amdgcn_wave_barrier();
+          float *own = tile(j + (s + g < 4 ? g : 0), j);   // lanes past the block's end repeat the diagonal tile
+          float piv = 0.0f, root;
+          diag_row(own, r, a);
+          factor_columns<0, false>(a, piv);
+          pivot_root<false>(piv, root, inv);
+          if (__ballot(g == 0 && !(piv >= kTinyPivot && piv < INFINITY))) {   // a failed or tiny pivot: again, scaled
+            diag_row(own, r, a);
+            factor_columns<0, true>(a, piv);
+            pivot_root<true>(piv, root, inv);
+            const uint64_t bad = __ballot(g == 0 && !(piv > 0.0f && piv < INFINITY));
+            if (bad != 0 && lane == 0) fail[j] = K0 + 16 * j + __ffsll((unsigned long long)bad);
+          }
+          __builtin_amdgcn_wave_barrier();
+          if (s + g < 4) diag_put_row(own, r, a);
+          if (g == 0) own[64 * (r & 3) + 4 * r + (r >> 2)] = root;
+          __builtin_amdgcn_s_setprio(0);
+        }
+        if (p > 1 && s >= p - 1) {   // X's tile row p - 2 is visible
+#pragma unroll
+          for (int u = 0; u < 3; ++u)
+            if (u <= p - 2)
+              yt[u] = diag_mac(yt[u], -diag_get(xt(p - 2, u), lane), diag_get_perm(tile(j, k0 + p - 2), lane));
+        }
+        if (s == p - 1) {   // X's tile row s
+#pragma unroll
+          for (int u = 0; u < 3; ++u)
+            if (u < s) *reinterpret_cast<f32x4 *>(xn(s, u) + 4 * lane) = yt[u];
+          __builtin_amdgcn_wave_barrier();
+          float y[16];
+          diag_row(xn(s, min(g, s)), r, y);
+#pragma unroll
+          for (int c = 0; c < 16; ++c) y[c] = g < s ? y[c] : g == s && c == r ? 1.0f : 0.0f;
+          __builtin_amdgcn_wave_barrier();
+          substitute_rows<0>(y, a, inv);
+          if (g <= s) {
+            if (s < 3) diag_put_row(xt(s, g), r, y);
+            float *to = xn(s, g) + 64 * (r & 3) + (r >> 2);
+#pragma unroll
+            for (int c = 0; c < 16; ++c) to[4 * c] = y[c];
+          }
+          float *to = Xb + (size_t)K * kNB * kNB + 16 * s * kNB + lane;
+#pragma unroll
+          for (int c = 0; c < 16; ++c) to[c * kNB] = y[c];
+        }
+      } else if (todo > 0) {
+        for (int m = k0 + p * todo / 5; m < k0 + (p + 1) * todo / 5; ++m) {
+          f32x4 acc = zero;
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            acc = diag_mac(acc, diag_get(tile(wave, k0 - 4 + q), lane), diag_get_perm(tile(m, k0 - 4 + q), lane));
+          float *t = tile(wave, m) + 4 * lane;
+          *reinterpret_cast<f32x4 *>(t) = *reinterpret_cast<const f32x4 *>(t) - acc;
+        }
       }
-    } else if (wave > k && live && k + 1 < nk) {
-      f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
-      int m = 0;
-      for (; m + 1 < k; m += 2) {
-        s0 = tile_mac(s0, get(wave, m), get(k + 1, m));
-        s1 = tile_mac(s1, get(wave, m + 1), get(k + 1, m + 1));
+      diag_barrier();
+    }
+#pragma unroll
+    for (int p = 3; p >= 0; --p) failed = fail[k0 + p] ? fail[k0 + p] : failed;
+    if (failed) break;   // uniform
+    if (mine) {   // tile row j of the block's L
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+        if (m <= s) {
+          const float *t = tile(j, k0 + m) + 4 * r + g;
+          const f32x4 v = {t[0], t[64], t[128], t[192]};
+          if (m < s) {
+            *reinterpret_cast<f32x4 *>(grow + 16 * (k0 + m)) = v;
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (4 * g + e <= r) grow[16 * (k0 + m) + e] = v[e];
+          }
+        }
+    } else if (below) {
+      f32x4 x[4], l[4];
+#pragma unroll
+      for (int m = 0; m < 4; ++m) x[m] = diag_get(tile(wave, k0 + m), lane);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        l[u] = zero;
+#pragma unroll
+        for (int m = 0; m <= u; ++m) l[u] = diag_mac(l[u], x[m], diag_get(xn(u, m), lane));
       }
-      if (m < k) s0 = tile_mac(s0, get(wave, m), get(k + 1, m));
-      cn = get(wave, k + 1);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) cn[v] -= s0[v] + s1[v];
+      for (int u = 0; u < 4; ++u) {
+        put_quad(tile(wave, k0 + u), l[u]);
+        *reinterpret_cast<f32x4 *>(grow + 16 * (k0 + u)) = l[u];
+      }
     }
-    __syncthreads();
-    if (*fail) break;   // uniform: every thread reads it between two barriers
-    f32x4 lik = {0.f, 0.f, 0.f, 0.f};
-    if (wave > k && live) {
-      lik = tile_mac(lik, cc, get(k, k));
-      put(wave, k, lik);
-      *reinterpret_cast<f32x4 *>(grow + 16 * k) = lik;
-    }
-    __syncthreads();
-    if (wave > k && live && k + 1 < nk) {
-      const f32x4 u = tile_mac(f32x4{0.f, 0.f, 0.f, 0.f}, lik, get(k + 1, k));
-#pragma unroll
-      for (int v = 0; v < 4; ++v) cc[v] = cn[v] - u[v];
-    }
+    diag_barrier();
   }
-  if (*fail) {
-    if (tid == 0) info[b] = *fail;
-    return;
-  }
-  // inverse of the 64 x 64 diagonal block q, tile column j per wave: with
-  // X = L^-1, X_ij = -X_ii sum_m L_im X_mj, kept transposed (xt = X_mj^T)
-  const int q = wave >> 2, j = wave & 3, q4 = 4 * q;
-  float *Xi = dinv + ((size_t)b * (ld / kNB) + K0 / kNB + q) * kNB * kNB;
-  f32x4 xt[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    f32x4 x = {0.f, 0.f, 0.f, 0.f};
-    if (i == j) {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) x[v] = tile(q4 + j, q4 + j)[64 * (r >> 2) + 4 * (4 * g + v) + (r & 3)];
-    } else if (i > j) {
-      f32x4 st = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int m = 0; m < i; ++m)
-        if (m >= j) st = tile_mac(st, xt[m], get(q4 + i, q4 + m));
-      x = tile_mac(x, st, get(q4 + i, q4 + i));
-#pragma unroll
-      for (int v = 0; v < 4; ++v) x[v] = -x[v];
-    }
-    xt[i] = x;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) Xi[(16 * i + 4 * g + v) * kNB + 16 * j + r] = x[v];
-  }
+  if (failed && tid == 0) info[b] = failed;
 }
 
 // Left-looking update of the column panel K0 .. K0 + 255:
@@ -709,6 +827,18 @@ __device__ inline DiagInv diag_inv(const void *lsplit, int64_t ld, int b, int64_
   return {reinterpret_cast<const float *>(p), reinterpret_cast<const float *>(p + (size_t)ld * ld), ld / 2};
 }
 
+// 16 x 16 fp32 tiles in LDS and in registers share one layout: element (r, c)
+// at float 64 (c / 4) + 4 r + c % 4, so lane l = 16 g + r holds columns
+// 4 g .. 4 g + 3 of row r as four consecutive floats (one conflict-free 16-byte
+// access per lane).  tile_mac(acc, X, Y) adds X Y^T: with the MFMA's operands
+// given as (Y, X) its output lands in this layout again, so a result feeds the
+// next product without leaving the registers.
+__device__ inline f32x4 tile_mac(f32x4 acc, f32x4 x, f32x4 y) {
+#pragma unroll
+  for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(y[s], x[s], acc, 0, 0, 0);
+  return acc;
+}
+
 // After the factorisation, the lower 16 x 16 tiles of L and the inverses of its
 // diagonal tiles (from dinv) in LDS; a wave solves one tile column j of X = L^-1
 // by substitution, X_ij = -X_ii sum_m L_im X_mj, its tiles transposed in registers.
@@ -717,6 +847,8 @@ __device__ inline DiagInv diag_inv(const void *lsplit, int64_t ld, int b, int64_
 // workgroups of four waves and four columns each (z, 7 - z, 8 + z, 15 - z) share
 // a block: 26 -> 23 us at 8 pairs of ld = 1024, 28 -> 23 us
 // at ld = 1792.
+constexpr size_t kInv256Lds = (size_t)136 * 256 * sizeof(float);
+
 __global__ void __launch_bounds__(1024) k_chol_inv256(const float *__restrict__ Gw, int64_t ld,
                                                       const float *__restrict__ dinv, void *__restrict__ lsplit,
                                                       const int32_t *__restrict__ info) {
@@ -1683,18 +1815,18 @@ hipError_t launch_cholesky_factor(float *Gw, const float *Gc, int B, int t, int6
       if (err != hipSuccess) return err;
     }
     // the 256 x 256 diagonal block
-    const int nk = t - K0 < kOuter ? (t - K0 + 15) / 16 : 16;
-    hipLaunchKernelGGL(k_chol_diag256, dim3(B), dim3(1024), kDiag256Lds, s, Gw, ld, K0, nk > 0 ? nk : 0, st.info, dinv);
+    const int nb = t - K0 < kOuter ? (t - K0 + kNB - 1) / kNB : kOuter / kNB;
+    hipLaunchKernelGGL(k_chol_diag256, dim3(B), dim3(1024), kDiag256Lds, s, Gw, ld, K0, nb > 0 ? nb : 0, st.info, dinv);
     // the rows below: all four steps, written back once, with their planes
     if (K1 < ld)
       hipLaunchKernelGGL(k_chol_strip16, dim3((unsigned)((ld - K1) / kStripRows), B), dim3(512), kStrip16Lds, s, Gw,
                          ld, K0, dinv, Lp, shift, st.info);
   }
   const hipError_t ei = hipFuncSetAttribute((const void *)k_chol_inv256, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                            (int)kDiag256Lds);
+                                            (int)kInv256Lds);
   if (ei != hipSuccess) return ei;
   const int nblk = (int)(ld / kOuter), split = (int64_t)nblk * B <= 64 ? 4 : 1;   // as long as a CU per workgroup is left
-  hipLaunchKernelGGL(k_chol_inv256, dim3((unsigned)nblk, B, split), dim3(1024 / split), kDiag256Lds, s, Gw, ld, dinv,
+  hipLaunchKernelGGL(k_chol_inv256, dim3((unsigned)nblk, B, split), dim3(1024 / split), kInv256Lds, s, Gw, ld, dinv,
                      lsplit, st.info);
   (void)Gc;
   (void)delta0;
