@@ -595,11 +595,15 @@ struct EpiCholUpd {
 // the panel step L_rk = A_rk L_kk^-T (with the stored inverse), then the
 // update of the panel's later blocks j, A_rj -= L_rk L_jk^T; then the rows' L
 // is written back with the fp16 hi / lo planes of the left-looking updates'
-// operand.  A workgroup of 8 waves keeps 128 rows x 256 columns in LDS, so
-// the strip is read and written once instead of once per step; each
-// 128 x 64 product is 4 x 2 waves of 32 x 32.
-constexpr int kStripRows = 128;
-
+// operand.  A workgroup keeps ROWS rows x 256 columns in LDS, so the strip is
+// read and written once instead of once per step; each ROWS x 64 product is
+// ROWS / 32 x 2 waves of 32 x 32.
+// Bound by each wave's chain of ten steps.  At 8 pairs of ld = 1792: 29.1 us with
+// the products' elements going to LDS one at a time (64 operations per wave and
+// update) and B split between the barriers; 25.0 us with four at a time and the
+// next B split under the products; 22.3 us with strips of 64 rows, one wave per
+// SIMD, which is taken while every such strip has a CU of its own (kStripFew).
+//
 // k_chol_strip16: the strip on fp16 MFMA (32x32x16), every product as hi.hi + hi.lo +
 // lo.hi of fp16 planes (about 2^-22 relative, as in the trailing
 // contraction).  With s_x = 2^shift[x] (sqrt(A_xx) s_x in [2^13, 2^14)):
@@ -613,26 +617,36 @@ constexpr int kStripRows = 128;
 // The planes left in LDS are the split the left-looking contractions read,
 // and G gets (hi + lo) / s_r.  LDS rows are unpadded with their 16-byte chunks XOR-swizzled by
 // row, so each quarter-wave's fragment reads touch 16 distinct bank groups.
-constexpr size_t kStrip16Lds = ((size_t)2 * kStripRows * 256 + (size_t)2 * kNB * kNB) * sizeof(f16) +
-                               (size_t)(kNB + kStripRows + 256) * sizeof(int32_t);
+constexpr int kStripFew = 256;   // strips of 64 rows that still have a CU each
+constexpr size_t strip16_lds(int rows) {
+  return ((size_t)2 * rows * 256 + (size_t)2 * kNB * kNB) * sizeof(f16) + (size_t)(kNB + rows + 256) * sizeof(int32_t);
+}
 
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+// max(v, the lane that the DPP control CTRL names).
+template <int CTRL>
+__device__ __forceinline__ float row_max(float v) {
+  return fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true)));
+}
+
+template <int ROWS>
+__global__ void __launch_bounds__(4 * ROWS) __attribute__((amdgpu_waves_per_eu(1, 2)))
 k_chol_strip16(float *__restrict__ Gw, int64_t ld, int K0, const float *__restrict__ dinv, f16 *__restrict__ Lp,
                const int32_t *__restrict__ shift, const int32_t *__restrict__ info) {
   extern __shared__ __attribute__((aligned(16))) char strip16_smem[];
   f16 *sTh = reinterpret_cast<f16 *>(strip16_smem);        // [128][256] hi
-  f16 *sTl = sTh + kStripRows * 256;                         // [128][256] lo
-  f16 *sBh = sTl + kStripRows * 256;                         // [64][64] hi
+  f16 *sTl = sTh + ROWS * 256;                         // [128][256] lo
+  f16 *sBh = sTl + ROWS * 256;                         // [64][64] hi
   f16 *sBl = sBh + kNB * kNB;                                // [64][64] lo
-  int32_t *sBe = reinterpret_cast<int32_t *>(sBl + kNB * kNB);   // [64] row exponents of B
-  int32_t *sSh = sBe + kNB;                                  // [128] row shifts of the strip
-  int32_t *sShC = sSh + kStripRows;                          // [256] shifts of the panel's columns
+  float *sBs = reinterpret_cast<float *>(sBl + kNB * kNB);   // [64] scales that take a product with B's rows to its units
+  int32_t *sSh = reinterpret_cast<int32_t *>(sBs + kNB);     // [128] row shifts of the strip
+  int32_t *sShC = sSh + ROWS;                          // [256] shifts of the panel's columns
+  constexpr int kThreads = 4 * ROWS, kB = kNB * kNB / 4 / kThreads;   // quads of B per thread
   const int b = blockIdx.y;
   if (info[b] != 0) return;   // uniform over the workgroup
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1, h = lane >> 5, col = lane & 31;
   const int K1 = K0 + 256;
-  const int64_t R = K1 + (int64_t)blockIdx.x * kStripRows;
+  const int64_t R = K1 + (int64_t)blockIdx.x * ROWS;
   float *G = Gw + (size_t)b * ld * ld;
   const int nb = (int)(ld / kNB);
   // element (r, c) of a plane: T rows of 32 chunks, B rows of 8 chunks
@@ -645,50 +659,64 @@ k_chol_strip16(float *__restrict__ Gw, int64_t ld, int K0, const float *__restri
       lo[q] = (f16)(x[q] - (float)hi[q]);
     }
   };
-  if (tid < kStripRows) sSh[tid] = shift[(size_t)b * ld + R + tid];
+  if (tid < ROWS) sSh[tid] = shift[(size_t)b * ld + R + tid];
   if (tid < 256) sShC[tid] = shift[(size_t)b * ld + K0 + tid];
   constexpr int kSteps = 10;
   constexpr int8_t step_k[kSteps] = {0, 0, 0, 0, 1, 1, 1, 2, 2, 3};
   constexpr int8_t step_j[kSteps] = {0, 1, 2, 3, 1, 2, 3, 2, 3, 3};
-  f32x4 pre[2];
+  f32x4 pre[2][kB];   // of steps st + 1 and st + 2
   auto load_b = [&](int st) {
     const int k = step_k[st], j = step_j[st];
     const float *src = j == k ? dinv + ((size_t)b * nb + K0 / kNB + k) * kNB * kNB
                               : G + (size_t)(K0 + kNB * j) * ld + K0 + kNB * k;
     const int64_t lds = j == k ? kNB : ld;
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const int e = tid + 512 * c, i = e >> 4, c4 = (e & 15) * 4;
-      pre[c] = *reinterpret_cast<const f32x4 *>(src + (size_t)i * lds + c4);
+    for (int c = 0; c < kB; ++c) {
+      const int e = tid + kThreads * c, i = e >> 4, c4 = (e & 15) * 4;
+      pre[st & 1][c] = *reinterpret_cast<const f32x4 *>(src + (size_t)i * lds + c4);
     }
   };
   // B rows scaled by their own power of two (16 consecutive lanes hold a row);
   // for D_k its columns first take 2^14 / s_m
-  auto stash_b = [&](int k, bool panel) {
+  f16x4 bhi[kB], blo[kB];
+  float bsc[kB];
+  auto split_b = [&](int st) {
+    const int k = step_k[st], j = step_j[st];
+    const bool panel = j == k;
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const int e = tid + 512 * c, i = e >> 4, c4 = (e & 15) * 4;
+    for (int c = 0; c < kB; ++c) {
+      const int e = tid + kThreads * c, i = e >> 4, c4 = (e & 15) * 4;
+      f32x4 x = pre[st & 1][c];
       if (panel) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) pre[c][q] = ldexpf(pre[c][q], 14 - sShC[64 * k + c4 + q]);
+        for (int q = 0; q < 4; ++q) x[q] = ldexpf(x[q], 14 - sShC[64 * k + c4 + q]);
       }
-      float m = fmaxf(fmaxf(fabsf(pre[c][0]), fabsf(pre[c][1])), fmaxf(fabsf(pre[c][2]), fabsf(pre[c][3])));
-#pragma unroll
-      for (int o = 1; o < 16; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+      float m = fmaxf(fmaxf(fabsf(x[0]), fabsf(x[1])), fmaxf(fabsf(x[2]), fabsf(x[3])));
+      m = row_max<0xB1>(m);    // lanes 1 apart, 2 apart,
+      m = row_max<0x4E>(m);
+      m = row_max<0x141>(m);   // the other half of 8, the other half of 16
+      m = row_max<0x140>(m);
       int ex = 0;
       if (m > 0.0f) frexpf(m, &ex);
       const int sc = max(min(14 - ex, 126), -126);
-      f32x4 x;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) x[q] = ldexpf(pre[c][q], sc);
-      f16x4 hi, lo;
-      split4(x, hi, lo);
-      *reinterpret_cast<f16x4 *>(&sBh[bix(i, c4)]) = hi;
-      *reinterpret_cast<f16x4 *>(&sBl[bix(i, c4)]) = lo;
-      if ((e & 15) == 0) sBe[i] = sc;
+      for (int q = 0; q < 4; ++q) x[q] = ldexpf(x[q], sc);
+      split4(x, bhi[c], blo[c]);
+      bsc[c] = ldexpf(1.0f, panel ? -sc : sShC[64 * j + i] - 14 - sc);
     }
   };
-  // this wave's 32 x 32 block of T[:, 64 ka ..] x B^T, in the scaled units
+  auto stash_b = [&]() {
+#pragma unroll
+    for (int c = 0; c < kB; ++c) {
+      const int e = tid + kThreads * c, i = e >> 4, c4 = (e & 15) * 4;
+      *reinterpret_cast<f16x4 *>(&sBh[bix(i, c4)]) = bhi[c];
+      *reinterpret_cast<f16x4 *>(&sBl[bix(i, c4)]) = blo[c];
+      if ((e & 15) == 0) sBs[i] = bsc[c];
+    }
+  };
+  // this wave's 32 x 32 block of T[:, 64 ka ..] x B^T, in the scaled units: with B as
+  // the first operand a lane holds row arow, its columns 32 wn + 8 q + 4 h .. + 3 in
+  // accumulators 4 q .. 4 q + 3, which go to LDS four at a time
   const int arow = 32 * wm + col, brow = 32 * wn + col;
   auto product = [&](int ka) {
     f32x16 acc = zero16();
@@ -699,24 +727,25 @@ k_chol_strip16(float *__restrict__ Gw, int64_t ld, int K0, const float *__restri
       const bf16x8 al = *reinterpret_cast<const bf16x8 *>(&sTl[tix(arow, ca)]);
       const bf16x8 bh = *reinterpret_cast<const bf16x8 *>(&sBh[bix(brow, cb)]);
       const bf16x8 bl = *reinterpret_cast<const bf16x8 *>(&sBl[bix(brow, cb)]);
-      acc = mma16<f16>(ah, bh, acc);
-      acc = mma16<f16>(ah, bl, acc);
-      acc = mma16<f16>(al, bh, acc);
+      acc = mma16<f16>(bh, ah, acc);
+      acc = mma16<f16>(bl, ah, acc);
+      acc = mma16<f16>(bh, al, acc);
     }
     return acc;
   };
   {  // the strip, 128 rows x 64 groups of 4, scaled by s_r s_c 2^-14 and split
-    f32x4 v[kStripRows * 64 / 512];
+    f32x4 v[ROWS * 64 / kThreads];
 #pragma unroll
-    for (int i = 0; i < kStripRows * 64 / 512; ++i) {
-      const int e = tid + 512 * i, r = e >> 6, c4 = (e & 63) * 4;
+    for (int i = 0; i < ROWS * 64 / kThreads; ++i) {
+      const int e = tid + kThreads * i, r = e >> 6, c4 = (e & 63) * 4;
       v[i] = *reinterpret_cast<const f32x4 *>(G + (size_t)(R + r) * ld + K0 + c4);
     }
     load_b(0);
+    load_b(1);
     __syncthreads();   // sSh, sShC
 #pragma unroll
-    for (int i = 0; i < kStripRows * 64 / 512; ++i) {
-      const int e = tid + 512 * i, r = e >> 6, c4 = (e & 63) * 4;
+    for (int i = 0; i < ROWS * 64 / kThreads; ++i) {
+      const int e = tid + kThreads * i, r = e >> 6, c4 = (e & 63) * 4;
       const int sh = sSh[r] - 14;
       f32x4 x;
 #pragma unroll
@@ -727,13 +756,14 @@ k_chol_strip16(float *__restrict__ Gw, int64_t ld, int K0, const float *__restri
       *reinterpret_cast<f16x4 *>(&sTl[tix(r, c4)]) = lo;
     }
   }
+  split_b(0);
   // block kb (final after its panel step): planes and L = (hi + lo) / s_r of
   // all 128 rows, four columns per thread-group, issued while later steps run
   f16 *hib = Lp + (size_t)b * 2 * ld * ld, *lob = hib + (size_t)ld * ld;
   auto write_block = [&](int kb) {
 #pragma unroll
-    for (int q = 0; q < kStripRows * 16 / 512; ++q) {
-      const int g = tid + 512 * q, rr = g >> 4, c = 64 * kb + (g & 15) * 4;
+    for (int q = 0; q < ROWS * 16 / kThreads; ++q) {
+      const int g = tid + kThreads * q, rr = g >> 4, c = 64 * kb + (g & 15) * 4;
       const int64_t r = R + rr;
       const f16x4 hi = *reinterpret_cast<const f16x4 *>(&sTh[tix(rr, c)]);
       const f16x4 lo = *reinterpret_cast<const f16x4 *>(&sTl[tix(rr, c)]);
@@ -751,31 +781,33 @@ k_chol_strip16(float *__restrict__ Gw, int64_t ld, int K0, const float *__restri
     const int k = step_k[st], j = step_j[st];
     __syncthreads();   // the strip is up to date and every wave is done with sB
     if (st > 0 && step_j[st - 1] == step_k[st - 1]) write_block(step_k[st - 1]);
-    stash_b(k, j == k);
-    if (st + 1 < kSteps) load_b(st + 1);
+    stash_b();
+    if (st + 2 < kSteps) load_b(st + 2);
     __syncthreads();
     const f32x16 acc = product(k);
-    if (j == k) {      // panel step: L_k s_r replaces block k
-      const float inv_b = ldexpf(1.0f, -sBe[brow]);
-      __syncthreads();
+    if (st + 1 < kSteps) split_b(st + 1);   // under the products
+    // panel step: L_k s_r replaces block k, once every wave has read it; update of
+    // block j (this wave's own entries), in its units s_r s_c 2^-14
+    if (j == k) __syncthreads();
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int r = 32 * wm + acc_row(v, lane), c = 64 * k + 32 * wn + col;
-        const float x = acc[v] * inv_b;
-        const f16 hi = (f16)x;
-        sTh[tix(r, c)] = hi;
-        sTl[tix(r, c)] = (f16)(x - (float)hi);
-      }
-    } else {           // update of block j (this wave's own entries), in its units s_r s_c 2^-14
-      const float inv_b = ldexpf(1.0f, sShC[64 * j + brow] - 14 - sBe[brow]);
+    for (int q = 0; q < 4; ++q) {
+      const int cl = 32 * wn + 8 * q + 4 * h;
+      const f32x4 sc = *reinterpret_cast<const f32x4 *>(&sBs[cl]);
+      f16x4 &th = *reinterpret_cast<f16x4 *>(&sTh[tix(arow, 64 * j + cl)]);
+      f16x4 &tl = *reinterpret_cast<f16x4 *>(&sTl[tix(arow, 64 * j + cl)]);
+      f32x4 x;
+      if (j == k) {
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int r = 32 * wm + acc_row(v, lane), c = 64 * j + 32 * wn + col;
-        const float x = ((float)sTh[tix(r, c)] + (float)sTl[tix(r, c)]) - acc[v] * inv_b;
-        const f16 hi = (f16)x;
-        sTh[tix(r, c)] = hi;
-        sTl[tix(r, c)] = (f16)(x - (float)hi);
+        for (int e = 0; e < 4; ++e) x[e] = acc[4 * q + e] * sc[e];
+      } else {
+        const f16x4 hi = th, lo = tl;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = ((float)hi[e] + (float)lo[e]) - acc[4 * q + e] * sc[e];
       }
+      f16x4 hi, lo;
+      split4(x, hi, lo);
+      th = hi;
+      tl = lo;
     }
   }
   __syncthreads();
@@ -1785,9 +1817,14 @@ hipError_t launch_cholesky_factor(float *Gw, const float *Gc, int B, int t, int6
   float *sinv = reinterpret_cast<float *>(shift + (size_t)B * ld);
   hipLaunchKernelGGL(k_chol_scales, dim3((unsigned)((ld + 255) / 256), B), dim3(256), 0, s, Gw, ld, shift, sinv,
                      st.info);
-  const hipError_t ea = hipFuncSetAttribute((const void *)k_chol_strip16, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                            (int)kStrip16Lds);
-  if (ea != hipSuccess) return ea;
+  auto strip = [&](auto kern, int rows, int K0) {
+    const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             (int)strip16_lds(rows));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((ld - K0 - kOuter) / rows), B), dim3(4 * rows), strip16_lds(rows), s, Gw,
+                       ld, K0, dinv, Lp, shift, st.info);
+    return hipGetLastError();
+  };
   const hipError_t ed = hipFuncSetAttribute((const void *)k_chol_diag256, hipFuncAttributeMaxDynamicSharedMemorySize,
                                             (int)kDiag256Lds);
   if (ed != hipSuccess) return ed;
@@ -1818,9 +1855,11 @@ hipError_t launch_cholesky_factor(float *Gw, const float *Gc, int B, int t, int6
     const int nb = t - K0 < kOuter ? (t - K0 + kNB - 1) / kNB : kOuter / kNB;
     hipLaunchKernelGGL(k_chol_diag256, dim3(B), dim3(1024), kDiag256Lds, s, Gw, ld, K0, nb > 0 ? nb : 0, st.info, dinv);
     // the rows below: all four steps, written back once, with their planes
-    if (K1 < ld)
-      hipLaunchKernelGGL(k_chol_strip16, dim3((unsigned)((ld - K1) / kStripRows), B), dim3(512), kStrip16Lds, s, Gw,
-                         ld, K0, dinv, Lp, shift, st.info);
+    if (K1 < ld) {
+      const bool few = (ld - K1) / 64 * B <= kStripFew;
+      const hipError_t e = few ? strip(k_chol_strip16<64>, 64, K0) : strip(k_chol_strip16<128>, 128, K0);
+      if (e != hipSuccess) return e;
+    }
   }
   const hipError_t ei = hipFuncSetAttribute((const void *)k_chol_inv256, hipFuncAttributeMaxDynamicSharedMemorySize,
                                             (int)kInv256Lds);
