@@ -881,17 +881,18 @@ __device__ inline f32x4 tile_mac(f32x4 acc, f32x4 x, f32x4 y) {
 // at ld = 1792.
 constexpr size_t kInv256Lds = (size_t)136 * 256 * sizeof(float);
 
-__global__ void __launch_bounds__(1024) k_chol_inv256(const float *__restrict__ Gw, int64_t ld,
-                                                      const float *__restrict__ dinv, void *__restrict__ lsplit,
-                                                      const int32_t *__restrict__ info) {
+template <int NW>
+__global__ void __launch_bounds__(64 * NW) k_chol_inv256(const float *__restrict__ Gw, int64_t ld, int t,
+                                                         const float *__restrict__ dinv, void *__restrict__ lsplit,
+                                                         const int32_t *__restrict__ info) {
   extern __shared__ __attribute__((aligned(16))) float diag_smem[];
   const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 15, g = lane >> 4;
   if (info[b] != 0) return;   // uniform over the workgroup
-  const int nw = blockDim.x >> 6;   // 16 or 4
   const int64_t K0 = (int64_t)blockIdx.x * 256;
+  const int nk = (int)((t - K0 + 15) / 16);   // tile rows that are not padding
   auto tile = [&](int i, int m) { return diag_smem + (i * (i + 1) / 2 + m) * 256; };
   auto get = [&](int i, int m) { return *reinterpret_cast<const f32x4 *>(tile(i, m) + 4 * lane); };
-  for (int i = wave; i < 16; i += nw) {   // tile row i
+  for (int i = wave; i < 16; i += NW) {   // tile row i
     const float *grow = Gw + (size_t)b * ld * ld + (size_t)(K0 + 16 * i + r) * ld + K0 + 4 * g;
     const float *drow = dinv + ((size_t)b * (ld / kNB) + K0 / kNB + (i >> 2)) * kNB * kNB +
                         (16 * (i & 3) + r) * kNB + 16 * (i & 3) + 4 * g;
@@ -905,7 +906,7 @@ __global__ void __launch_bounds__(1024) k_chol_inv256(const float *__restrict__ 
   }
   __syncthreads();
   const int z = blockIdx.z;
-  const int j = nw == 16 ? wave : wave == 0 ? z : wave == 1 ? 7 - z : wave == 2 ? 8 + z : 15 - z;
+  const int j = NW == 16 ? wave : wave == 0 ? z : wave == 1 ? 7 - z : wave == 2 ? 8 + z : 15 - z;
   float *out = const_cast<float *>(diag_inv(lsplit, ld, b, K0).at(0, j < 8 ? 0 : 128)) + 16 * (j & 7) + r;
   const int64_t ldf = ld / 2;
   f32x4 xt[16];
@@ -915,17 +916,32 @@ __global__ void __launch_bounds__(1024) k_chol_inv256(const float *__restrict__ 
     if (i == j) {
 #pragma unroll
       for (int v = 0; v < 4; ++v) x[v] = tile(j, j)[64 * (r >> 2) + 4 * (4 * g + v) + (r & 3)];
-    } else if (i > j) {
+    } else if (i > j && i < nk) {
       f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+      if constexpr (NW == 4) {   // the row's tiles of L first, and no branches between the products
+        f32x4 l[16];
 #pragma unroll
-      for (int m = 0; m < i; ++m)
-        if (m >= j) {
-          if (m & 1) s1 = tile_mac(s1, xt[m], get(i, m));
-          else s0 = tile_mac(s0, xt[m], get(i, m));
+        for (int m = 0; m <= i; ++m) l[m] = get(i, m);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int m = 0; m < i; ++m) {   // (xt[m] is zero for m < j)
+          if (m & 1) s1 = tile_mac(s1, xt[m], l[m]);
+          else s0 = tile_mac(s0, xt[m], l[m]);
         }
 #pragma unroll
-      for (int v = 0; v < 4; ++v) s0[v] = -(s0[v] + s1[v]);
-      x = tile_mac(x, s0, get(i, i));
+        for (int v = 0; v < 4; ++v) s0[v] = -(s0[v] + s1[v]);
+        x = tile_mac(x, s0, l[i]);
+      } else {
+#pragma unroll
+        for (int m = 0; m < i; ++m)
+          if (m >= j) {
+            if (m & 1) s1 = tile_mac(s1, xt[m], get(i, m));
+            else s0 = tile_mac(s0, xt[m], get(i, m));
+          }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) s0[v] = -(s0[v] + s1[v]);
+        x = tile_mac(x, s0, get(i, i));
+      }
     }
     xt[i] = x;
     if (i >= (j & ~3)) {   // with the zero tiles above the diagonal inside the 64 x 64 block
@@ -1861,12 +1877,17 @@ hipError_t launch_cholesky_factor(float *Gw, const float *Gc, int B, int t, int6
       if (e != hipSuccess) return e;
     }
   }
-  const hipError_t ei = hipFuncSetAttribute((const void *)k_chol_inv256, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                            (int)kInv256Lds);
+  const int nblk = (int)(ld / kOuter);
+  auto inv = [&](auto kern, int nw) {
+    const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kInv256Lds);
+    if (e == hipSuccess)
+      hipLaunchKernelGGL(kern, dim3((unsigned)nblk, B, 16 / nw), dim3(64 * nw), kInv256Lds, s, Gw, ld, t, dinv, lsplit,
+                         st.info);
+    return e;
+  };
+  // four workgroups per block as long as each has a CU
+  const hipError_t ei = (int64_t)nblk * B <= 64 ? inv(k_chol_inv256<4>, 4) : inv(k_chol_inv256<16>, 16);
   if (ei != hipSuccess) return ei;
-  const int nblk = (int)(ld / kOuter), split = (int64_t)nblk * B <= 64 ? 4 : 1;   // as long as a CU per workgroup is left
-  hipLaunchKernelGGL(k_chol_inv256, dim3((unsigned)nblk, B, split), dim3(1024 / split), kInv256Lds, s, Gw, ld, dinv,
-                     lsplit, st.info);
   (void)Gc;
   (void)delta0;
   (void)max_esc;
