@@ -877,8 +877,8 @@ __device__ inline f32x4 tile_mac(f32x4 acc, f32x4 x, f32x4 y) {
 // Columns are independent, so no barrier.  One workgroup of 16 waves per (block,
 // pair) is bound by the CU's fp32 MFMA rate; while there are few of them, four
 // workgroups of four waves and four columns each (z, 7 - z, 8 + z, 15 - z) share
-// a block: 26 -> 23 us at 8 pairs of ld = 1024, 28 -> 23 us
-// at ld = 1792.
+// a block, with the registers to read a whole tile row of L ahead of its products:
+// 26 -> 18 us at 8 pairs of ld = 1024, 28 -> 19 us at ld = 1792.
 constexpr size_t kInv256Lds = (size_t)136 * 256 * sizeof(float);
 
 template <int NW>
@@ -1157,11 +1157,15 @@ __global__ void __launch_bounds__(512) k_mass_resid_rows(const float *__restrict
   }
 }
 
-// Stage 2: res_r = sum_i Phi[i][r] u_i - lam w_r.  Each wave takes four
-// compact keys (16 per workgroup) so that the z and u loads are shared by
-// them; four queries per lane per step (16-byte loads of the L^T rows and of
-// u).  With a list, slot k handles key list[k] (k < count) and writes only there.
-constexpr int kResKeys = 4;   // compact keys per wave
+// Stage 2: res_r = sum_i Phi[i][r] u_i - lam w_r.  A workgroup takes four
+// compact keys, so that the z and u loads are shared by them, and each of its four
+// waves every fourth run of 256 queries, four per lane (16-byte loads of the L^T
+// rows and of u); the waves' sums meet in LDS.  Bound by the reads of L^T; a wave
+// that swept all queries of its keys alone was bound by their latency: 36 -> 21 us
+// at 8 pairs of n = 4096, t = 819, 56 -> 41 us at t = 1638; 64 pairs at t = 3277,
+// 615 -> 598 us.
+// With a list, slot k handles key list[k] (k < count) and writes only there.
+constexpr int kResKeys = 4;   // compact keys per workgroup
 __global__ void __launch_bounds__(256) k_mass_resid_cols(const float *__restrict__ LT, const float *__restrict__ z,
                                                          const double *__restrict__ u, const double *__restrict__ w,
                                                          const float *__restrict__ lam, int n, int t, int64_t tp,
@@ -1170,12 +1174,13 @@ __global__ void __launch_bounds__(256) k_mass_resid_cols(const float *__restrict
                                                          const int32_t *__restrict__ list,
                                                          const int32_t *__restrict__ count) {
   typedef __attribute__((__vector_size__(2 * sizeof(double)))) double f64x2;
-  const int b = blockIdx.y, lane = threadIdx.x & 63;
-  const int k0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * kResKeys;   // first slot of this wave
-  if (k0 >= tp || info[b] != 0) return;
+  __shared__ double red[4][kResKeys];
+  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int k0 = blockIdx.x * kResKeys;   // first slot of this workgroup
+  if (info[b] != 0) return;
   const int lim = list ? count[b] : t;   // slots k < lim are live keys
-  if (k0 >= lim) {
-    if (!list && lane < kResKeys) res[(size_t)b * tp + k0 + lane] = 0.0;   // padding keys r >= t
+  if (k0 >= lim) {   // uniform over the workgroup
+    if (!list && tid < kResKeys) res[(size_t)b * tp + k0 + tid] = 0.0;   // padding keys r >= t
     return;
   }
   int r[kResKeys];
@@ -1189,7 +1194,8 @@ __global__ void __launch_bounds__(256) k_mass_resid_cols(const float *__restrict
   const float *zb = z + (size_t)b * n;
   const double *ub = u + (size_t)b * np_;   // zero beyond n
   double acc[kResKeys] = {0.0, 0.0, 0.0, 0.0};
-  for (int i0 = 4 * lane; i0 < n; i0 += 256) {
+#pragma unroll 2
+  for (int i0 = 256 * wave + 4 * lane; i0 < n; i0 += 1024) {
     const f64x2 u01 = *reinterpret_cast<const f64x2 *>(ub + i0);
     const f64x2 u23 = *reinterpret_cast<const f64x2 *>(ub + i0 + 2);
     const double uu[4] = {u01[0], u01[1], u23[0], u23[1]};
@@ -1209,12 +1215,18 @@ __global__ void __launch_bounds__(256) k_mass_resid_cols(const float *__restrict
 #pragma unroll
   for (int q = 0; q < kResKeys; ++q) {
     const double sum = wave_sum(acc[q]);
-    if (lane == 0 && k0 + q < lim)
-      res[(size_t)b * tp + r[q]] = sum - (double)lam[b] * w[(size_t)b * tp + r[q]];
+    if (lane == 0) red[wave][q] = sum;
   }
-  if (!list && lane >= kResKeys && lane < 2 * kResKeys) {   // padding keys r >= t within this wave's slots
-    const int k = k0 + lane - kResKeys;
-    if (k >= lim && k < tp) res[(size_t)b * tp + k] = 0.0;
+  __syncthreads();
+  if (tid < kResKeys) {
+    const int k = k0 + tid;
+    if (k < lim) {
+      const int rk = list ? list[(size_t)b * tp + k] : k;
+      const double sum = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
+      res[(size_t)b * tp + rk] = sum - (double)lam[b] * w[(size_t)b * tp + rk];
+    } else if (!list) {
+      res[(size_t)b * tp + k] = 0.0;   // padding keys r >= t
+    }
   }
 }
 
@@ -1928,7 +1940,7 @@ hipError_t launch_mass_residual(const float *LT, const float *z, const float *m,
                                 const int32_t *row_count, const int32_t *col_list, const int32_t *col_count) {
   hipLaunchKernelGGL(k_mass_resid_rows, dim3((unsigned)(np_ / 64), B), dim3(512), 0, s, LT, z, m, w, n, t, tp, np_,
                      u, info, row_list, row_count);
-  hipLaunchKernelGGL(k_mass_resid_cols, dim3((unsigned)(tp / (4 * kResKeys)), B), dim3(256), 0, s, LT, z, u, w, lam,
+  hipLaunchKernelGGL(k_mass_resid_cols, dim3((unsigned)(tp / kResKeys), B), dim3(256), 0, s, LT, z, u, w, lam,
                      n, t, tp, np_, res, info, col_list, col_count);
   return hipGetLastError();
 }
