@@ -961,47 +961,56 @@ __global__ void __launch_bounds__(64 * NW) k_chol_inv256(const float *__restrict
 // (and adds it to `acc` on the backward pass when given).  Forward step 0
 // reads the rhs, later steps the work vector s; the backward pass updates y in
 // place.  Bound by the launches and the two dependent reads of one: 64-row
-// blocks took four times the launches at 4.3 us each, these 7.9 us: 725 -> 332 us for
-// the six passes of 8 pairs at t = 1638; 64 pairs at t = 3277: 22.2 -> 20.5 ms
-// per 256 pairs for the mass fit's solve stage with its residuals.
+// blocks took four times the launches at 4.3 us each, these 7.5 us (7.9 with the
+// vector's read and the pair's state waited for before the other reads): 725 -> 315
+// us for the six passes of 8 pairs at t = 1638; 64 pairs at t = 3277: 22.2 -> 20.5
+// ms per 256 pairs for the mass fit's solve stage with its residuals.
 template <bool FWD>
 __global__ void __launch_bounds__(1024) k_trsv256(const float *__restrict__ Gw, const void *__restrict__ lsplit,
                                                   int64_t ld, int K, int per, const double *__restrict__ rhs,
                                                   double *__restrict__ work, double *__restrict__ out,
                                                   double *__restrict__ acc, const int32_t *__restrict__ info) {
   __shared__ double sv[256], sol[256], red[16][256];
-  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (info[b] != 0) return;
+  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int32_t skip = info[b];   // looked at after the loads: they need not wait for it
   const int64_t K0 = (int64_t)K * 256;
   const int nch = (int)(FWD ? (ld - K0 - 256) / 64 : K0 / 64);   // chunks of 64 targets
   const int ch0 = blockIdx.x * per, ch1 = min(ch0 + per, nch);
   const float *L = Gw + (size_t)b * ld * ld;
   const DiagInv D = diag_inv(lsplit, ld, b, K0);
   const double *src = (FWD && K == 0 ? rhs : work) + (size_t)b * ld;
-  if (tid < 256) sv[tid] = src[K0 + tid];
+  const double own = src[K0 + (tid & 255)];
   // the chunk's part of L, loaded ahead of its use: forward 16 lanes per
   // target row, backward 16 lanes per row of the block
   const int q = tid & 15, rg = tid >> 4;
   f32x4 lv[4];
+  double old = 0.0;   // the target's value before the update
+  const double *prev = (FWD && K == 0 ? rhs : work) + (size_t)b * ld;
   auto load_l = [&](int ch) {
+    old = prev[FWD ? K0 + 256 + 64 * ch + rg : (int64_t)64 * ch + lane];
 #pragma unroll
     for (int u = 0; u < 4; ++u)
       lv[u] = *reinterpret_cast<const f32x4 *>(FWD ? L + (size_t)(K0 + 256 + 64 * ch + rg) * ld + K0 + 4 * (q + 16 * u)
                                                    : L + (size_t)(K0 + rg + 64 * u) * ld + 64 * ch + 4 * q);
   };
   if constexpr (FWD) {
-    // y_K: four lanes per row, interleaved over its 16-byte groups up to the diagonal
+    // y_K: four lanes per row, interleaved over its 16-byte groups up to the end of
+    // the diagonal's 16 x 16 tile, whose upper entries are stored zeros; a wave has
+    // 16 rows, so its loads stand under no lane mask
     const int r = tid >> 2, p = tid & 3;
     f32x4 d[16];
 #pragma unroll
     for (int u = 0; u < 16; ++u)
-      if (4 * (p + 4 * u) <= r) d[u] = *reinterpret_cast<const f32x4 *>(D.at(r, 4 * (p + 4 * u)));
+      if (u <= wave) d[u] = *reinterpret_cast<const f32x4 *>(D.at(r, 4 * (p + 4 * u)));
     if (ch0 < ch1) load_l(ch0);
+    if (tid < 256) sv[tid] = own;
     __syncthreads();
+    if (skip != 0) return;   // uniform over the workgroup
     double s0 = 0.0, s1 = 0.0;
 #pragma unroll
     for (int u = 0; u < 16; ++u)
-      if (4 * (p + 4 * u) <= r) {
+      if (u <= wave) {
         const double *v = sv + 4 * (p + 4 * u);
         s0 = fma((double)d[u][0], v[0], s0);
         s1 = fma((double)d[u][1], v[1], s1);
@@ -1019,7 +1028,9 @@ __global__ void __launch_bounds__(1024) k_trsv256(const float *__restrict__ Gw, 
     for (int u = 0; u < 16; ++u)
       if (16 * u + wave >= 4 * lane) d[u] = *reinterpret_cast<const f32x4 *>(D.at(16 * u + wave, 4 * lane));
     if (ch0 < ch1) load_l(ch0);
+    if (tid < 256) sv[tid] = own;
     __syncthreads();
+    if (skip != 0) return;   // uniform over the workgroup
     double s[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int u = 0; u < 16; ++u)
@@ -1050,13 +1061,11 @@ __global__ void __launch_bounds__(1024) k_trsv256(const float *__restrict__ Gw, 
       for (int u = 0; u < 4; ++u)
 #pragma unroll
         for (int e = 0; e < 4; ++e) s = fma((double)lv[u][e], sol[4 * (q + 16 * u) + e], s);
+      const double base = old;
       if (ch + 1 < ch1) load_l(ch + 1);
 #pragma unroll
       for (int m = 8; m >= 1; m >>= 1) s += __shfl_xor(s, m, 64);
-      if (q == 0) {
-        const size_t e = (size_t)b * ld + K0 + 256 + 64 * ch + rg;
-        work[e] = (K == 0 ? rhs[e] : work[e]) - s;
-      }
+      if (q == 0) work[(size_t)b * ld + K0 + 256 + 64 * ch + rg] = base - s;
     } else {
       double s[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -1065,6 +1074,7 @@ __global__ void __launch_bounds__(1024) k_trsv256(const float *__restrict__ Gw, 
 #pragma unroll
         for (int e = 0; e < 4; ++e) s[e] = fma((double)lv[u][e], v, s[e]);
       }
+      const double base = old;
       if (ch + 1 < ch1) load_l(ch + 1);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -1081,7 +1091,7 @@ __global__ void __launch_bounds__(1024) k_trsv256(const float *__restrict__ Gw, 
         double x = 0.0;
 #pragma unroll
         for (int w = 0; w < 16; ++w) x += red[w][tid];
-        work[(size_t)b * ld + 64 * ch + tid] -= x;
+        work[(size_t)b * ld + 64 * ch + tid] = base - x;
       }
     }
   }
