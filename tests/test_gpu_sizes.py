@@ -1,0 +1,164 @@
+"""Sizes at the borders of the kernels' splits: tile edges, remainders, and both
+sides of every rule that picks a variant by size, against float64."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from tests import test_gpu_edges as edges
+from tests.gpu_common import certify_flips, gpu_assignment, np64
+
+pytestmark = pytest.mark.gpu
+
+S128 = 1.0 / math.sqrt(128)
+DT = {"f32": torch.float32, "bf16": torch.bfloat16}
+
+
+def A():
+    from paper_2609_36835_amd import arckv
+    return arckv
+
+
+def randn(seed, *shape, dtype=torch.float32):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    return torch.randn(*shape, generator=g, device="cuda").to(dtype)
+
+
+# (pairs, queries, compact keys, shift of z).  256-wide Cholesky panels with 64-wide
+# blocks and 16-wide tile columns; 48 pairs of t = 1024 are past the rules for few
+# strips (256 of 64 rows), few block inverses (64), and few rows of the
+# 128-column solves (512 chunks).  A shift of 40 puts every pivot below 2^-96.
+FITS = [(1, 16, 1, 0), (2, 63, 15, 0), (2, 200, 64, 0), (2, 300, 65, 0), (1, 600, 255, 0), (1, 600, 256, 0),
+        (2, 700, 257, 0), (1, 1100, 513, 0), (1, 300, 100, 40), (48, 1300, 1024, 0)]
+
+
+@pytest.mark.parametrize("B,n,t,shift", FITS)
+def test_mass_fit_sizes(B, n, t, shift):
+    """The masses are those of known weights.  The fp32 evaluation of Phi_C (logits up to
+    about 5 in size, one exponential) is off by at most 3e-6 relative, which moves a
+    least-squares solution by at most twice cond(Phi_C) times that; the ridge is in the
+    reference."""
+    P = min(B, 2)
+    print(f"mass fit B={B} n={n} t={t} shift={shift}", flush=True)
+    Q, Ck = randn(1, P, n, 128), randn(2, P, t, 128)
+    w = 0.5 + 1.5 * torch.rand(P, t, device="cuda", dtype=torch.float64)
+    Phi = [torch.exp(q.double() @ c.double().T * S128 - shift) for q, c in zip(Q, Ck)]
+    m = torch.stack([p @ x for p, x in zip(Phi, w)]).float()
+    z = torch.full((P, n), float(shift), device="cuda")
+    rep = lambda x: x.repeat(B // P, *[1] * (x.dim() - 1)).contiguous()
+    beta, info, dused = A().fit_bias(rep(Q), rep(Ck), rep(z), rep(m), A().default_params(b_min=-30.0), scale=S128, T=4 * t)
+    assert torch.all(info == 0) and torch.all(torch.isfinite(beta))
+    sv = [torch.linalg.svdvals(p) for p in Phi]
+    for b in range(B):
+        p = Phi[b % P]
+        G = p.T @ p
+        G.diagonal().add_(float(dused[b]) * float(G.diagonal().mean()))
+        ref = torch.linalg.solve(G, p.T @ m[b % P].double())
+        tol = 6e-6 * float(sv[b % P][0] / sv[b % P][-1])
+        err = float((torch.exp(beta[b].double()) - ref).norm() / ref.norm())
+        assert err <= tol, (b, err, tol)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,n,t", [f[:3] for f in FITS if f[3] == 0])
+def test_value_fit_sizes(B, n, t, dtype):
+    """The fitted block's outputs on the queries against the float64 fit at the same ridge, at
+    the fp32 bar of the parity tests (compact keys and operands enter as split planes)."""
+    P = min(B, 2)
+    print(f"value fit {dtype} B={B} n={n} t={t}", flush=True)
+    Q, Ck, Y = randn(3, P, n, 128, dtype=DT[dtype]), randn(4, P, t, 128), randn(5, P, n, 128)
+    beta = 0.5 * randn(6, P, t)
+    rep = lambda x: x.repeat(B // P, 1, 1).contiguous() if x.dim() == 3 else x.repeat(B // P, 1).contiguous()
+    Cv, info, dused = A().fit_values(rep(Q), rep(Ck), rep(beta), rep(Y), scale=S128, T=4 * t)
+    assert torch.all(info == 0)
+    for b in range(B):
+        p = torch.softmax(Q[b % P].double() @ Ck[b % P].double().T * S128 + beta[b % P].double(), dim=1)
+        M = p.T @ p
+        M.diagonal().add_(float(dused[b]) * float(M.diagonal().mean()))
+        ref = p @ torch.linalg.solve(M, p.T @ Y[b % P].double())
+        err = float(((p @ Cv[b].double() - ref).norm(dim=1) / ref.norm(dim=1)).max())
+        assert err <= 1e-4, (b, err)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("T", [1, 63, 64, 65, 129, 1000])
+def test_rowstats_sizes(T, dtype):
+    """Few query tiles: key halves inside a workgroup, for fp32 a wave per key range.  z and m to
+    fp32 sums; bf16 inputs round the probabilities of Y's product to 2^-8."""
+    print(f"rowstats {dtype} T={T}", flush=True)
+    K, V, Q = (randn(i, 2, k, 128, dtype=DT[dtype]) for i, k in ((7, T), (8, T), (9, 130)))
+    z, m, Y = A().rowstats(K, V, Q, scale=S128)
+    for b in range(2):
+        L = Q[b].double() @ K[b].double().T * S128
+        zr = L.amax(dim=1)
+        E = torch.exp(L - zr[:, None])
+        Yr = (E @ V[b].double()) / E.sum(dim=1, keepdim=True)
+        assert float((z[b] - zr).abs().max()) <= 1e-5
+        assert float((m[b] / E.sum(dim=1) - 1).abs().max()) <= 2e-5
+        assert float((Y[b] - Yr).abs().max()) <= (2e-5 if dtype == "f32" else 2.0 ** -8) * float(V[b].float().abs().max())
+
+
+@pytest.mark.parametrize("B,T", [(1, 1), (1, 15), (2, 17), (3, 1000), (9, 4099)])
+def test_score_f32_sizes(B, T):
+    """16 or 64 tokens per step.  The bound is that of sums of 256 and 64 fp32 terms in any order."""
+    print(f"score f32 B={B} T={T}", flush=True)
+    K, V = randn(10, B, T, 128), randn(11, B, T, 128)
+    W1, b1, w2, b2 = randn(12, B, 64, 256) / 16, randn(13, B, 64), randn(14, B, 64) / 8, randn(15, B)
+    out = A().score(K, V, W1, b1, w2, b2)
+    for b in range(B):
+        X = torch.cat([K[b], V[b]], dim=1).double()
+        x = X @ W1[b].double().T + b1[b].double()
+        h = 0.5 * x * (1.0 + torch.erf(x / math.sqrt(2.0)))
+        ref = h @ w2[b].double() + b2[b].double()
+        e = 2.0 ** -24
+        eh = 260 * e * (X.abs() @ W1[b].double().abs().T + b1[b].double().abs()) * 1.13 + 8 * e * h.abs() + 1e-7
+        bound = (eh + 66 * e * h.abs()) @ w2[b].double().abs() + 66 * e * b2[b].double().abs()
+        assert torch.all((out[b].double() - ref).abs() <= bound)
+
+
+@pytest.mark.parametrize("t", [1, 2048, 2049, 4097, 8193])
+def test_group_sort_segments(t):
+    """16, 8, 4 and 2 segments of the positions (their counters fill 32,768 words of LDS)."""
+    print(f"merge t={t}", flush=True)
+    edges.test_merge_many_groups(t)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n", [1, 127, 128, 129, 257, 520])
+def test_assignment_query_ranges(n, dtype):
+    """Anchors in close pairs, so that keys are refined and decided in float64, over query
+    counts on both sides of the ranges' tiles; kappa is the float64 argmax."""
+    print(f"assignment {dtype} n={n}", flush=True)
+    rng = np.random.default_rng(n)
+    T, t = 600, 40
+    K = rng.standard_normal((T, 128)).astype(np.float32)
+    S = np.sort(rng.choice(T, t, replace=False))
+    K[S[1::2]] = K[S[::2]] * (1.0 + 2.0 ** -6)
+    Kd, Qd = (torch.from_numpy(x).to(DT[dtype]) for x in (K, rng.standard_normal((n, 128)).astype(np.float32)))
+    kap, st = gpu_assignment(Kd[None].cuda(), Kd[None].cuda(), Qd[None].cuda(), torch.from_numpy(S.astype(np.int32))[None].cuda(),
+                             S128)
+    K64, Q64 = np64(Kd), np64(Qd)
+    ref, _, _ = oracle.profiles_assign_phi(Q64, K64, S, S128)
+    certify_flips(kap, ref, Q64, K64, S, S128)
+
+
+@pytest.mark.parametrize("G,t,F", [(1, 1, 0), (2, 31, 0), (4, 33, 37), (8, 256, 1), (4, 0, 70)])
+def test_attend_infinite_values(G, t, F):
+    """An infinite value stays in its dimension, also in the last row, whose repeats stand in for
+    the rows past the end."""
+    print(f"attend G={G} t={t} F={F}", flush=True)
+    Q, C, X = randn(16, 2, G, 128, dtype=torch.bfloat16), randn(17, 2, t, 128, dtype=torch.bfloat16), \
+        randn(18, 2, F, 128, dtype=torch.bfloat16)
+    Cv, Xv = randn(19, 2, t, 128, dtype=torch.bfloat16), randn(20, 2, F, 128, dtype=torch.bfloat16)
+    beta = randn(21, 2, t)
+    none = lambda x: x if x.shape[1] else None
+    call = lambda: A().attend(Q, none(C), beta if t else None, none(Cv), none(X), none(Xv), scale=S128)
+    plain = call()
+    (Xv if F else Cv)[:, -1, 5] = math.inf
+    (Cv if t else Xv)[:, 0, 77] = -math.inf
+    out = call()
+    assert torch.all(out[:, :, 5] == math.inf) and torch.all(out[:, :, 77] == -math.inf)
+    keep = [i for i in range(128) if i not in (5, 77)]
+    assert torch.equal(out[:, :, keep], plain[:, :, keep])
