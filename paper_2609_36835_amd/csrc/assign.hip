@@ -333,26 +333,29 @@ __device__ inline double row_norm(const E *x) {
 // threshold may hold more, and contributes all its anchors ("overflow").
 struct CandA {
   int singles, overflow;
+  int count;   // the candidates, with every anchor of an overflowing tile
   float th;
   uint64_t g1;
 };
 
 __device__ inline CandA cand_a(const uint64_t *p1, const uint64_t *p2, const uint32_t *p3, int64_t stride, int MT,
-                               int t, float th_or_nan, uint64_t g1) {
+                               int t, int TR, float th_or_nan, uint64_t g1) {
   CandA c;
   c.g1 = g1;
   c.th = th_or_nan;
   c.singles = 0;
   c.overflow = 0;
+  c.count = 0;
+#pragma unroll 4
   for (int mt = 0; mt < MT; ++mt) {
     const uint64_t a = p1[(size_t)mt * stride], b2 = p2[(size_t)mt * stride];
     const float v3 = __uint_as_float(p3[(size_t)mt * stride]);
-    if (v3 >= c.th) {
-      ++c.overflow;
-      continue;
-    }
-    if (a != 0ull && packed_r(a) < (uint32_t)t && packed_sim(a) >= c.th) ++c.singles;
-    if (b2 != 0ull && packed_r(b2) < (uint32_t)t && packed_sim(b2) >= c.th) ++c.singles;
+    const bool over = v3 >= c.th;
+    const int one = (int)(a != 0ull && packed_r(a) < (uint32_t)t && packed_sim(a) >= c.th) +
+                    (int)(b2 != 0ull && packed_r(b2) < (uint32_t)t && packed_sim(b2) >= c.th);
+    c.overflow += over;
+    c.singles += over ? 0 : one;
+    c.count += over ? min(t, (mt + 1) * TR) - mt * TR : one;
   }
   return c;
 }
@@ -406,29 +409,24 @@ __global__ void __launch_bounds__(256) k_assign_finalize(
   const uint64_t *p1 = part1 + c, *p2 = part2 + c;
   const uint32_t *p3 = part3 + c;
   uint64_t g1 = 0;
+#pragma unroll 4
   for (int mt = 0; mt < MT; ++mt) g1 = max(g1, p1[(size_t)mt * Np]);
   const uint32_t r1 = packed_r(g1);
   const double kn = row_norm(K + ((size_t)b * T + j) * kHeadDim);
   const BoundA bd = bound_a(sizeof(E) == 2, n, s, (double)zmerge[b], pn[b], kn, (double)phi[(size_t)b * T + j]);
   const float th = threshold_a(packed_sim(g1), bd);
-  const CandA ca = cand_a(p1, p2, p3, Np, MT, t, th, g1);
+  const CandA ca = cand_a(p1, p2, p3, Np, MT, t, TR, th, g1);
   kappa[(size_t)b * T + j] = (int32_t)(r1 < (uint32_t)t ? r1 : 0u);
   if (ca.overflow == 0 && ca.singles == 1) return;
   int32_t *st = L.stats + (size_t)b * kAssignStats;
   atomicAdd(&st[0], 1);
   if (ca.overflow) atomicAdd(&st[7], 1);
   // the key's candidates: the best two above the threshold of each tile, or
-  // every anchor of a tile whose third value reaches it
-  int nc = 0;
-  for (int mt = 0; mt < MT; ++mt) {
-    if (__uint_as_float(p3[(size_t)mt * Np]) >= th) {
-      nc += min(t, (mt + 1) * TR) - mt * TR;
-      continue;
-    }
-    const uint64_t a = p1[(size_t)mt * Np], a2 = p2[(size_t)mt * Np];
-    nc += (a != 0ull && packed_r(a) < (uint32_t)t && packed_sim(a) >= th);
-    nc += (a2 != 0ull && packed_r(a2) < (uint32_t)t && packed_sim(a2) >= th);
-  }
+  // every anchor of a tile whose third value reaches it (four tiles' partials at a
+  // time, as above: one after the other, each of three walks took a round trip per
+  // tile; 692 -> 573 us at 64 pairs of T = 32768, t = 3277)
+  auto listed = [&](uint64_t a) { return a != 0ull && packed_r(a) < (uint32_t)t && packed_sim(a) >= th; };
+  const int nc = ca.count;
   atomicAdd(&st[2], nc);
   if (nc == 0) {   // no finite similarity reaches the threshold (non-finite input): the pass-A best stands
     atomicAdd(&st[3], 1);
@@ -442,14 +440,27 @@ __global__ void __launch_bounds__(256) k_assign_finalize(
   }
   int32_t *pl = L.pool + (size_t)b * L.pcap + off;
   int k = 0;
-  for (int mt = 0; mt < MT; ++mt) {
-    if (__uint_as_float(p3[(size_t)mt * Np]) >= th) {
-      for (int r = mt * TR; r < min(t, (mt + 1) * TR); ++r) pl[k++] = r;
-      continue;
+  for (int m0 = 0; m0 < MT; m0 += 4) {
+    float v3[4];
+    uint64_t a[4], a2[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const size_t at = (size_t)min(m0 + u, MT - 1) * Np;
+      v3[u] = __uint_as_float(p3[at]);
+      a[u] = p1[at];
+      a2[u] = p2[at];
     }
-    const uint64_t a = p1[(size_t)mt * Np], a2 = p2[(size_t)mt * Np];
-    if (a != 0ull && packed_r(a) < (uint32_t)t && packed_sim(a) >= th) pl[k++] = (int32_t)packed_r(a);
-    if (a2 != 0ull && packed_r(a2) < (uint32_t)t && packed_sim(a2) >= th) pl[k++] = (int32_t)packed_r(a2);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int mt = m0 + u;
+      if (mt >= MT) break;
+      if (v3[u] >= th) {
+        for (int r = mt * TR; r < min(t, (mt + 1) * TR); ++r) pl[k++] = r;
+        continue;
+      }
+      if (listed(a[u])) pl[k++] = (int32_t)packed_r(a[u]);
+      if (listed(a2[u])) pl[k++] = (int32_t)packed_r(a2[u]);
+    }
   }
   const int slot = atomicAdd(&L.fcnt[b], 1);
   L.fkey[(size_t)b * L.cap + slot] = j;
