@@ -1424,7 +1424,8 @@ __global__ void __launch_bounds__(256) k_transpose128(const float *__restrict__ 
 // The remaining rows are updated by their own workgroups, so a call over few
 // pairs fills the chip where one workgroup per pair (a left-looking solve)
 // ran on as many CUs as there are pairs; at many pairs it is bound by the
-// fp32 MFMA rate and by reading and writing R once per block.  The four solves of 8 pairs\n// at t = 1638: 3.4 -> 0.5 ms; of 256 pairs at t = 3277, 64 at a time: 46 -> 25 ms.
+// fp32 MFMA rate and by reading and writing R once per block.  The four solves of 8 pairs
+// at t = 1638: 3.4 -> 0.5 ms; of 256 pairs at t = 3277, 64 at a time: 46 -> 25 ms.
 // R is overwritten; X must not alias it.
 template <bool FWD>
 __global__ void __launch_bounds__(256) k_trsm_diag(const void *__restrict__ lsplit, int64_t ld, int K,
@@ -1564,6 +1565,121 @@ __global__ void __launch_bounds__(256) k_values_out(const float *__restrict__ Xp
   const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (e >= (int64_t)t * kHeadDim) return;
   Cv[(size_t)b * t * kHeadDim + e] = info[b] != 0 ? NAN : Xp[(size_t)b * tp * kHeadDim + e];
+}
+
+// The same solves left-looking, one workgroup per pair (8 waves = 2 row tiles x 4
+// column tiles of 32), 64-row blocks.  For block kb the update  acc = sum_p L_kb,p X_p
+// (forward) or  sum_p L_p,kb^T X_p  (backward) is an MFMA product with the L tile and
+// the X tile staged in LDS; then X_kb = D (R_kb - acc) with D = L_kb,kb^-1 or its
+// transpose.  L is read once and R and X once each, where the right-looking form
+// rewrites R for every block; but its time is that of one pair on one CU.
+constexpr int kTrsmRB = 64, kTrsmSLD = kTrsmRB + 1, kTrsmSXD = kHeadDim + 1;
+constexpr size_t kTrsmLds = (size_t)2 * (kTrsmRB * kTrsmSLD + kTrsmRB * kTrsmSXD) * sizeof(float);
+
+template <bool FWD>
+__global__ void __launch_bounds__(512) k_trsm_mfma(const float *__restrict__ Gw, int64_t ld,
+                                                   const float *__restrict__ dinv, int t,
+                                                   const float *__restrict__ R, float *__restrict__ X,
+                                                   const int32_t *__restrict__ info) {
+  constexpr int RB = kTrsmRB, SLD = kTrsmSLD, SXD = kTrsmSXD;
+  extern __shared__ float trsm_smem[];
+  auto sL = [&](int bf) { return trsm_smem + bf * RB * SLD; };
+  auto sX = [&](int bf) { return trsm_smem + 2 * RB * SLD + bf * RB * SXD; };
+  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (info[b] != 0) return;
+  const int wr = wave >> 2, wc = wave & 3, h = lane >> 5, col = lane & 31;
+  const float *L = Gw + (size_t)b * ld * ld;
+  const float *Rb = R + (size_t)b * ld * kHeadDim;
+  float *Xb = X + (size_t)b * ld * kHeadDim;
+  const int nb = (t + RB - 1) / RB;   // the blocks past t are padding: X is zero there
+  const float *Db = dinv + (size_t)b * (ld / RB) * RB * RB;
+  for (int64_t e = (int64_t)nb * RB * kHeadDim + 4 * tid; e < ld * kHeadDim; e += 4 * 512)
+    *reinterpret_cast<f32x4 *>(Xb + e) = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 rl[2], rx[4];
+  // tile (i, k) of the operand: forward L[r0+i][p0+k], backward L[p0+k][r0+i]
+  auto fetch = [&](int r0, int p0) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const int e = tid + 512 * c, i = e / 16, k4 = (e % 16) * 4;
+      rl[c] = FWD ? *reinterpret_cast<const f32x4 *>(L + (size_t)(r0 + i) * ld + p0 + k4)
+                  : *reinterpret_cast<const f32x4 *>(L + (size_t)(p0 + i) * ld + r0 + k4);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int e = tid + 512 * c, i = e / 32, k4 = (e % 32) * 4;
+      rx[c] = *reinterpret_cast<const f32x4 *>(Xb + (size_t)(p0 + i) * kHeadDim + k4);
+    }
+  };
+  auto stash = [&](int bf) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const int e = tid + 512 * c, i = e / 16, k4 = (e % 16) * 4;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (FWD) sL(bf)[i * SLD + k4 + q] = rl[c][q];
+        else sL(bf)[(k4 + q) * SLD + i] = rl[c][q];
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int e = tid + 512 * c, i = e / 32, k4 = (e % 32) * 4;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) sX(bf)[i * SXD + k4 + q] = rx[c][q];
+    }
+  };
+  for (int step = 0; step < nb; ++step) {
+    const int kb = FWD ? step : nb - 1 - step;
+    const int r0 = kb * RB;
+    f32x16 acc = zero16();
+    const int pb0 = FWD ? 0 : kb + 1, pb1 = FWD ? kb : nb;
+    int bf = 0;
+    if (pb0 < pb1) {
+      __syncthreads();
+      fetch(r0, pb0 * RB);
+      stash(0);
+      __syncthreads();
+    }
+    for (int pb = pb0; pb < pb1; ++pb) {
+      const bool more = pb + 1 < pb1;
+      if (more) fetch(r0, (pb + 1) * RB);
+#pragma unroll 8
+      for (int ks = 0; ks < RB / 2; ++ks)
+        acc = Mfma<float>::mma(sL(bf)[(32 * wr + col) * SLD + 2 * ks + h],
+                               sX(bf)[(2 * ks + h) * SXD + 32 * wc + col], acc);
+      if (more) stash(bf ^ 1);
+      __syncthreads();
+      bf ^= 1;
+    }
+    __syncthreads();
+    // right-hand side minus update into sX(0); D into sL(0) (row r = output row)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int r = 32 * wr + acc_row(v, lane), c = 32 * wc + col;
+      sX(0)[r * SXD + c] = Rb[(size_t)(r0 + r) * kHeadDim + c] - acc[v];
+    }
+    const float *Dk = Db + (size_t)kb * RB * RB;
+    for (int e = tid; e < RB * RB / 4; e += 512) {
+      const int i = e / 16, k4 = (e % 16) * 4;
+      const f32x4 v = *reinterpret_cast<const f32x4 *>(Dk + i * RB + k4);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (FWD) sL(0)[i * SLD + k4 + q] = v[q];
+        else sL(0)[(k4 + q) * SLD + i] = v[q];
+      }
+    }
+    __syncthreads();
+    f32x16 out = zero16();
+#pragma unroll 8
+    for (int ks = 0; ks < RB / 2; ++ks)
+      out = Mfma<float>::mma(sL(0)[(32 * wr + col) * SLD + 2 * ks + h], sX(0)[(2 * ks + h) * SXD + 32 * wc + col],
+                             out);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int r = 32 * wr + acc_row(v, lane), c = 32 * wc + col;
+      Xb[(size_t)(r0 + r) * kHeadDim + c] = out[v];
+    }
+    __threadfence_block();
+  }
 }
 
 // --------------------------------------------------------------- exact NNLS (bias_mode 1)
@@ -2084,8 +2200,27 @@ static hipError_t trsm(const float *Gw, const void *lsplit, int B, int64_t ld, f
   return hipGetLastError();
 }
 
-hipError_t launch_trsm(bool fwd, const float *Gw, const void *lsplit, int B, int64_t ld, float *R, float *X, float *xt,
-                       const int32_t *info, hipStream_t s) {
+// Pairs of a call above which its solves take a workgroup per pair, for each 256 pairs
+// that share the CUs: its time is that of one pair and rises slowly with the pairs, the
+// right-looking form's is in proportion to them.  Four solves and the refinement's
+// products, right-looking and left-looking: t = 819, 128 pairs 2.1 and 1.6 ms; t = 1638,
+// 96 pairs 4.1 and 4.9, 128: 5.4 and 5.3, 256: 10.2 and 6.9, 288: 11.5 and 11.3, 384:
+// 15.2 and 12.3; t = 3277, 128 pairs 16.2 and 19.2, 160: 20.1 and 20.6, 192: 23.9 and
+// 22.1, 256: 31.7 and 25.3 ms.
+static bool trsm_per_pair(int B, int t) { return B > (t <= 2048 ? 120 : 160) * ((B + 255) / 256); }
+
+hipError_t launch_trsm(bool fwd, const float *Gw, const float *dinv, const void *lsplit, int B, int t, int64_t ld,
+                       float *R, float *X, float *xt, const int32_t *info, hipStream_t s) {
+  if (trsm_per_pair(B, t)) {
+    const void *kern = fwd ? (const void *)k_trsm_mfma<true> : (const void *)k_trsm_mfma<false>;
+    const hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTrsmLds);
+    if (e != hipSuccess) return e;
+    if (fwd)
+      hipLaunchKernelGGL(k_trsm_mfma<true>, dim3(1, B), dim3(512), kTrsmLds, s, Gw, ld, dinv, t, R, X, info);
+    else
+      hipLaunchKernelGGL(k_trsm_mfma<false>, dim3(1, B), dim3(512), kTrsmLds, s, Gw, ld, dinv, t, R, X, info);
+    return hipGetLastError();
+  }
   return fwd ? trsm<true>(Gw, lsplit, B, ld, R, X, xt, info, s) : trsm<false>(Gw, lsplit, B, ld, R, X, xt, info, s);
 }
 

@@ -32,6 +32,8 @@ def randn(seed, *shape, dtype=torch.float32):
 # 128-column solves (512 chunks).  A shift of 40 puts every pivot below 2^-96.
 FITS = [(1, 16, 1, 0), (2, 63, 15, 0), (2, 200, 64, 0), (2, 300, 65, 0), (1, 600, 255, 0), (1, 600, 256, 0),
         (2, 700, 257, 0), (1, 1100, 513, 0), (1, 300, 100, 40), (48, 1300, 1024, 0)]
+# pairs for most of the CUs, whose 128-column solves take a workgroup per pair
+MANY_PAIRS = [(256, 40, 1), (122, 300, 65), (254, 700, 257), (162, 2200, 2049)]
 
 
 @pytest.mark.parametrize("B,n,t,shift", FITS)
@@ -62,7 +64,7 @@ def test_mass_fit_sizes(B, n, t, shift):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("B,n,t", [f[:3] for f in FITS if f[3] == 0])
+@pytest.mark.parametrize("B,n,t", [f[:3] for f in FITS if f[3] == 0] + MANY_PAIRS)
 def test_value_fit_sizes(B, n, t, dtype):
     """The fitted block's outputs on the queries against the float64 fit at the same ridge, at
     the fp32 bar of the parity tests (compact keys and operands enter as split planes)."""
