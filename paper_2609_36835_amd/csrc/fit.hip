@@ -1396,11 +1396,22 @@ __global__ void __launch_bounds__(256) k_transpose128(const float *__restrict__ 
   __shared__ float s[64][kHeadDim + 1];
   const int b = blockIdx.y, tid = threadIdx.x;
   const int i0 = blockIdx.x * 64;
-  for (int e = tid; e < 64 * kHeadDim; e += 256) {
-    const int r = e / kHeadDim, c = e % kHeadDim;
-    s[r][c] = (i0 + r < rows) ? in[(size_t)b * in_pair + (size_t)(i0 + r) * kHeadDim + c] : 0.0f;
+  // every row's read is issued before the first is used: under the row test a workgroup
+  // waited for them in turn, 11.6 us a call at 1 pair of 256 rows (value fit of 8 pairs,
+  // t = 1638, with its two calls 2056 -> 2042 us)
+  float x[64 * kHeadDim / 256];
+#pragma unroll
+  for (int k = 0; k < 64 * kHeadDim / 256; ++k) {
+    const int e = tid + 256 * k, r = e / kHeadDim, c = e % kHeadDim;
+    x[k] = in[(size_t)b * in_pair + (size_t)min(i0 + r, rows - 1) * kHeadDim + c];
+  }
+#pragma unroll
+  for (int k = 0; k < 64 * kHeadDim / 256; ++k) {
+    const int e = tid + 256 * k, r = e / kHeadDim, c = e % kHeadDim;
+    s[r][c] = i0 + r < rows ? x[k] : 0.0f;
   }
   __syncthreads();
+#pragma unroll 8
   for (int e = tid; e < 64 * kHeadDim; e += 256) {
     const int c = e / 64, r = e % 64;
     const float v = s[r][c];
