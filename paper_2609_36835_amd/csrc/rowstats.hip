@@ -270,11 +270,14 @@ __global__ void __launch_bounds__(512) k_rowstats_f32_few(const float *__restric
 // cross-half shuffle per k-step.  Workgroups are remapped so the query tiles of
 // one pair share an XCD (and its L2 copy of that pair's keys and values).
 // KS = 2 splits the keys inside the workgroup: 128 queries, waves 0 .. 3 take
-// keys 0 .. 31 of each tile and waves 4 .. 7 keys 32 .. 63, and the two partial
-// (maximum, sum, Y) meet in LDS at the end.  It is for calls whose 256-query
-// tiles cover at most half of the CUs: twice the workgroups, each with half of
-// the products and exponentials per tile (240 -> 170 us at 8
-// pairs, T = 8192, n = 4096).
+// keys 0 .. 31 of each tile and waves 4 .. 7 keys 32 .. 63.  Both halves run under
+// the maximum of the whole tile, which they exchange in LDS one tile ahead: the
+// probabilities are rounded to bf16 relative to that maximum, so with a maximum
+// of its own each half would round others than KS = 1 does, and a pair's Y
+// would differ by 9e-4 between a small and a large call.  The two partial (sum,
+// Y) meet in LDS at the end.  KS = 2 is for calls whose 256-query tiles cover at
+// most half of the CUs: twice the workgroups, each with half of the products and
+// exponentials per tile (240 -> 173 us at 8 pairs, T = 8192, n = 4096).
 constexpr int kRsQ = 256, kRsK = 64;
 constexpr int kRsKBytes = kRsK * kHeadDim * 2;            // 16 KB
 constexpr int kRsStage = 2 * kRsKBytes;                   // K tile + V^T tile
@@ -288,7 +291,7 @@ __global__ void __launch_bounds__(512, 1) k_rowstats_bf16(const bf16 *__restrict
                                                           float scale, int qtiles) {
   constexpr int NSB = 2 / KS, QW = 8 / KS;   // 32-key blocks per wave and tile, query groups of 32
   __shared__ __attribute__((aligned(1024))) char sbuf[2 * kRsStage];
-  __shared__ float smx[KS > 1 ? 128 : 1], ssm[KS > 1 ? 128 : 1];
+  __shared__ float smx[2][KS > 1 ? 256 : 1], ssm[KS > 1 ? 128 : 1];   // smx[tile & 1][key half][query]
   const int64_t tile = xcd_remap(blockIdx.x, gridDim.x);
   const int b = (int)(tile / qtiles), qt = (int)(tile % qtiles);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -367,6 +370,31 @@ __global__ void __launch_bounds__(512, 1) k_rowstats_bf16(const bf16 *__restrict
       }
     }
   };
+  // largest score of tile i over this wave's keys, per query; keys past Tn get no weight
+  auto tile_max = [&](int i, f32x16 (&S)[NSB]) {
+    if (i * kRsK + kRsK > Tn) {   // last tile
+#pragma unroll
+      for (int ms = 0; ms < NSB; ++ms)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          if (i * kRsK + 32 * (ms + grp) + acc_row(v, lane) >= Tn) S[ms][v] = -INFINITY;
+    }
+    float bmax = -INFINITY;
+#pragma unroll
+    for (int ms = 0; ms < NSB; ++ms)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) bmax = fmaxf(bmax, S[ms][v]);
+    const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(bmax), __float_as_uint(bmax), false, false);
+    return fmaxf(__uint_as_float(x[0]), __uint_as_float(x[1]));   // the half-waves' maxima
+  };
+  // KS = 2: tile i's maximum over this wave's keys, for the other half to read
+  // after the barrier that ends tile i - 1
+  const int qs = (wave % QW) * 32 + col;
+  float own_max = -INFINITY;
+  auto share_max = [&](int i, f32x16 (&S)[NSB]) {
+    own_max = tile_max(i, S);
+    if (h == 0) smx[i & 1][128 * grp + qs] = own_max;
+  };
   // Tile i: the online softmax of its scores S and Y^T += V^T P^T from the V
   // part of stage i & 1.  The scores of tile i + 1 (K part of stage (i + 1) & 1)
   // go to Sn in the same basic block as the exponentials, so the matrix cores
@@ -376,24 +404,15 @@ __global__ void __launch_bounds__(512, 1) k_rowstats_bf16(const bf16 *__restrict
   // holds V^T tile i; V tile i + 1 is in registers.
   auto body = [&](int i, f32x16 (&S)[NSB], f32x16 (&Sn)[NSB]) {
     const int k0 = i * kRsK, st = i & 1;
+    const float other_max = KS > 1 ? smx[i & 1][128 * (1 - grp) + qs] : 0.0f;
     if (i + 1 < nt) store_vt(st ^ 1);
     if (i + 2 < nt) {   // stage st: its K tile was read in tile i - 1, before the last barrier
       issue_k(k0 + 2 * kRsK, st);
       load_v(k0 + 2 * kRsK);
     }
-    if (k0 + kRsK > Tn) {   // last tile: keys past Tn get no weight
-#pragma unroll
-      for (int ms = 0; ms < NSB; ++ms)
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-          if (k0 + 32 * (ms + grp) + acc_row(v, lane) >= Tn) S[ms][v] = -INFINITY;
-    }
-    float bmax = -INFINITY;
-#pragma unroll
-    for (int ms = 0; ms < NSB; ++ms)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) bmax = fmaxf(bmax, S[ms][v]);
-    bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
+    float bmax;
+    if constexpr (KS > 1) bmax = fmaxf(own_max, other_max);
+    else bmax = tile_max(i, S);
     const float new_max = fmaxf(run_max, bmax);
     // The accumulators are rescaled only when some row's maximum grew (rare
     // after the first tiles); unchanged rows take alpha = 1.  The exponentials
@@ -420,6 +439,7 @@ __global__ void __launch_bounds__(512, 1) k_rowstats_bf16(const bf16 *__restrict
         psum += p;
       }
     run_sum += psum;
+    if constexpr (KS > 1) share_max(i + 1, Sn);   // under the products; past the last tile not read
     const char *svt = sbuf + st * kRsStage + kRsKBytes;
 #pragma unroll
     for (int kk = 0; kk < 2 * NSB; ++kk) {
@@ -464,6 +484,10 @@ __global__ void __launch_bounds__(512, 1) k_rowstats_bf16(const bf16 *__restrict
   __syncthreads();
   f32x16 Sa[NSB], Sb[NSB];
   scores(0, Sa);
+  if constexpr (KS > 1) {
+    share_max(0, Sa);
+    __syncthreads();
+  }
   int i = 0;
   for (; i + 1 < nt; i += 2) {
     body(i, Sa, Sb);
@@ -478,21 +502,15 @@ __global__ void __launch_bounds__(512, 1) k_rowstats_bf16(const bf16 *__restrict
       for (int cs = 0; cs < 4; ++cs)
 #pragma unroll
         for (int v = 0; v < 16; ++v) sy[(16 * cs + v) * 64] = accY[cs][v];
-      if (h == 0) {
-        smx[(wave % QW) * 32 + col] = run_max;
-        ssm[(wave % QW) * 32 + col] = run_sum;
-      }
+      if (h == 0) ssm[qs] = run_sum;
     }
     __syncthreads();
     if (grp == 1) return;
-    const float m1 = smx[wave * 32 + col], M = fmaxf(run_max, m1);
-    const float a0 = __builtin_amdgcn_exp2f((run_max - M) * c2), a1 = __builtin_amdgcn_exp2f((m1 - M) * c2);
-    run_max = M;
-    run_sum = run_sum * a0 + ssm[wave * 32 + col] * a1;
+    run_sum += ssm[qs];   // both halves ran under the same maxima
 #pragma unroll
     for (int cs = 0; cs < 4; ++cs)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) accY[cs][v] = accY[cs][v] * a0 + sy[(16 * cs + v) * 64] * a1;
+      for (int v = 0; v < 16; ++v) accY[cs][v] += sy[(16 * cs + v) * 64];
   }
   if (!qvalid) return;
   const float inv = 1.0f / run_sum;
@@ -515,7 +533,7 @@ hipError_t launch_rowstats(int dtype, const void *K, const void *V, const void *
                            int B, int T, int n, float scale, hipStream_t s) {
   if (dtype == ARCKV_BF16) {
     const int qtiles = (n + kRsQ - 1) / kRsQ;
-    if ((int64_t)qtiles * B <= 128 && T >= kRsK) {   // both key halves of the first tile hold a key
+    if ((int64_t)qtiles * B <= 128) {
       const int qt2 = (n + kRsQ / 2 - 1) / (kRsQ / 2);
       hipLaunchKernelGGL(k_rowstats_bf16<2>, dim3((unsigned)(qt2 * B)), dim3(512), 0, s, (const bf16 *)K,
                          (const bf16 *)V, (const bf16 *)Q, z, m, Y, T, n, scale, qt2);

@@ -102,6 +102,20 @@ def test_rowstats_sizes(T, dtype):
         assert float((Y[b] - Yr).abs().max()) <= (2e-5 if dtype == "f32" else 2.0 ** -8) * float(V[b].float().abs().max())
 
 
+@pytest.mark.parametrize("T", [40, 64, 130, 200])
+def test_rowstats_alone_and_in_a_batch(T):
+    """A pair alone takes the form that splits the keys, in a batch of 65 the other; both round the
+    same probabilities to bf16, so they differ by the order of fp32 sums of T terms."""
+    print(f"rowstats alone and in a batch T={T}", flush=True)
+    K, V, Q = (randn(i, 65, k, 128, dtype=torch.bfloat16) for i, k in ((22, T), (23, T), (24, 300)))
+    z, m, Y = A().rowstats(K, V, Q, scale=S128)
+    for b in (0, 64):
+        z1, m1, Y1 = A().rowstats(*(x[b:b + 1].contiguous() for x in (K, V, Q)), scale=S128)
+        assert torch.equal(z1[0], z[b])
+        assert float((m1[0] / m[b] - 1).abs().max()) <= 2 * T * 2.0 ** -24
+        assert float((Y1[0] - Y[b]).abs().max()) <= 2 * T * 2.0 ** -24 * float(V[b].float().abs().max())
+
+
 @pytest.mark.parametrize("B,T", [(1, 1), (1, 15), (2, 17), (3, 1000), (9, 4099)])
 def test_score_f32_sizes(B, T):
     """16 or 64 tokens per step.  The bound is that of sums of 256 and 64 fp32 terms in any order."""
