@@ -21,7 +21,7 @@
 //                     branches.  Small calls are bound by the launches and one
 //                     round trip to memory: 8 pairs of 856 keys take 9.1 us
 //                     (11.1 us with P V on the VALU and loads under branches);
-//                     512 pairs of 3533 keys, 169 us (184), 5.5 TB/s.
+//                     512 pairs of 3533 keys, 160 us (197), 5.8 TB/s.
 //   k_attend_combine  merges the partials of a pair with the usual
 //                     max-rescaling and writes o.
 #include <mutex>
@@ -59,7 +59,7 @@ __device__ inline const bf16 *att_row(const bf16 *C, const bf16 *Fx, int p, int 
 }
 }  // namespace
 
-template <int G>
+template <int G, bool STREAM>
 __global__ void __launch_bounds__(64 * kAttW) k_attend_partial(int t, int F, float scale, const bf16 *__restrict__ Q,
                                                          const bf16 *__restrict__ Ck, const float *__restrict__ beta,
                                                          const bf16 *__restrict__ Cv, const bf16 *__restrict__ Kf,
@@ -104,8 +104,10 @@ __global__ void __launch_bounds__(64 * kAttW) k_attend_partial(int t, int F, flo
   };
   Frag vf[VI];
 #pragma unroll
-  for (int i = 0; i < VI; ++i)
-    vf[i].v = *reinterpret_cast<const bf16x8 *>(att_row(Cv, Vf, p, t, F, key0 + 16 * (i / 4) + 4 * g + i % 4) + 8 * r);
+  for (int i = 0; i < VI; ++i) {
+    const bf16x8 *v = reinterpret_cast<const bf16x8 *>(att_row(Cv, Vf, p, t, F, key0 + 16 * (i / 4) + 4 * g + i % 4) + 8 * r);
+    vf[i].v = STREAM ? __builtin_nontemporal_load(v) : *v;
+  }
   __builtin_amdgcn_sched_barrier(0);   // the loads stay above the products
 
   // ---- logits: lane (g, r) holds keys key0 + 16 kt + 4 g + j (j < 4) for query r
@@ -275,20 +277,31 @@ hipError_t attend_scratch(void **ptr) {
   return hipSuccess;
 }
 
+// Keys and values of a call, in bytes, above which the values are read as a
+// stream that the caches do not keep: what the 256 MB last-level cache holds.  Two
+// streams that both pass through it slow each other down: 512 pairs of 32768, 16384,
+// 8192 and 3533 keys take 1581, 756, 414 and 173 us with both kept (VALU products with
+// loads under branches: 1557, 754, 403 and 197), 1451, 704, 371 and 160 us so; with
+// both streamed 1601, 786, 390 and 178, with the keys alone 1556, 758, 385 and 182.  A
+// call that fits may find its values there again: 8 pairs of 8192 keys 11.9 us kept, 12.5
+// streamed.
+constexpr int64_t kAttendKept = (int64_t)256 << 20;
+
 hipError_t launch_attend(int P, int G, int t, int F, float scale, const void *Q, const void *Ck, const float *beta,
                          const void *Cv, const void *Kf, const void *Vf, float *part_o, float *part_ml, float *out,
                          hipStream_t s) {
   const int nch = attend_chunks(t, F);
   dim3 grid((unsigned)nch, (unsigned)P);
+  const bool stream_v = (int64_t)P * (t + F) * 4 * kHeadDim > kAttendKept;
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, grid, dim3(64 * kAttW), 0, s, t, F, scale, (const bf16 *)Q, (const bf16 *)Ck, beta,
                        (const bf16 *)Cv, (const bf16 *)Kf, (const bf16 *)Vf, part_o, part_ml, nch);
   };
   switch (G) {
-    case 1: go(k_attend_partial<1>); break;
-    case 2: go(k_attend_partial<2>); break;
-    case 4: go(k_attend_partial<4>); break;
-    case 8: go(k_attend_partial<8>); break;
+    case 1: stream_v ? go(k_attend_partial<1, true>) : go(k_attend_partial<1, false>); break;
+    case 2: stream_v ? go(k_attend_partial<2, true>) : go(k_attend_partial<2, false>); break;
+    case 4: stream_v ? go(k_attend_partial<4, true>) : go(k_attend_partial<4, false>); break;
+    case 8: stream_v ? go(k_attend_partial<8, true>) : go(k_attend_partial<8, false>); break;
     default: return hipErrorInvalidValue;
   }
   hipError_t e = hipGetLastError();

@@ -178,3 +178,17 @@ def test_attend_infinite_values(G, t, F):
     assert torch.all(out[:, :, 5] == math.inf) and torch.all(out[:, :, 77] == -math.inf)
     keep = [i for i in range(128) if i not in (5, 77)]
     assert torch.equal(out[:, :, keep], plain[:, :, keep])
+
+
+def test_attend_streamed_values():
+    """A call whose keys and values exceed the last-level cache reads the values as a stream; each
+    pair's output is that of the pair alone."""
+    print("attend streamed", flush=True)
+    P, t, F = 130, 4000, 99
+    Q, C, Cv = randn(25, P, 4, 128, dtype=torch.bfloat16), randn(26, P, t, 128, dtype=torch.bfloat16), \
+        randn(27, P, t, 128, dtype=torch.bfloat16)
+    X, Xv, beta = randn(28, P, F, 128, dtype=torch.bfloat16), randn(29, P, F, 128, dtype=torch.bfloat16), randn(30, P, t)
+    out = A().attend(Q, C, beta, Cv, X, Xv, scale=S128)
+    for b in (0, 77, P - 1):
+        one = A().attend(*(x[b:b + 1].contiguous() for x in (Q, C, beta, Cv, X, Xv)), scale=S128)
+        assert torch.equal(one[0], out[b])
