@@ -90,6 +90,8 @@ hipError_t launch_cholesky(float *Gw, const float *Gc, int B, int t, int64_t ld,
 hipError_t launch_nonfinite(const FiniteCheck &f, int B, int32_t *bad, hipStream_t s);
 hipError_t launch_cholesky_factor(float *Gw, const float *Gc, int B, int t, int64_t ld, float delta0, int max_esc,
                                   FitState st, float *dinv, void *lsplit, hipStream_t s);
+hipError_t launch_inv256(const float *Gw, int B, int t, int64_t ld, const float *dinv, void *lsplit,
+                         const int32_t *info, hipStream_t s);
 hipError_t launch_nnls(const float *Gc, float *Gw, const double *h, const float *LT, const float *z, const float *m,
                        int B, int n, int t, int64_t tp, int64_t np_, int max_iter, int refine_steps, FitState st,
                        float *dinv, void *lsplit, NnlsWork nw, double *x, double *sw, double *yw, double *u,
@@ -578,6 +580,7 @@ static arckv_status run_fit_values_chunk(const Ctx &c, int b0, int P, const floa
   }
   STAGE(ST_CHOL_A, launch_cholesky(Gw, Gc, P, d.t, d.tp, fp.delta_v, fp.max_escalations, st, dinv,
                                    c.chunk<char>(c.pl.lsplit), bad, c.pers<int32_t>(c.pl.cnt), stream));
+  STAGE(ST_CHOL_A, launch_inv256(Gw, P, d.t, d.tp, dinv, c.chunk<char>(c.pl.lsplit), st.info, stream));
   {
     StageScope _sc(ST_SOLVE_V, stream);
     const void *lsp = c.chunk<char>(c.pl.lsplit);

@@ -20,14 +20,14 @@
 //                                     and updates on a 128 x 256 strip held in
 //                                     LDS as hi / lo planes (fp16 MFMA), then
 //                                     L and its planes written back
-//                      k_chol_inv256  the inverses of the 256 x 256 diagonal
-//                                     blocks, for the solves
 //                    a failed pivot records info = column + 1 for that pair
 //   escalation       pairs that failed are refactored by the same kernels with
 //                    delta raised tenfold (from 1e-7 when zero), at most
 //                    max_escalations times (launch_cholesky)
-//   solves           TRSV (one rhs, float64 accumulation) / TRSM (128 rhs, fp32
-//                    MFMA), both right-looking in 256-row blocks
+//   solves           TRSV (one rhs, float64 accumulation, by the 64 x 64 diagonal
+//                    inverses) / TRSM (128 rhs, fp32 MFMA, by the inverses of the
+//                    256 x 256 diagonal blocks, k_chol_inv256), both right-looking
+//                    in 256-row blocks
 //   residuals        rhs - (M + lam I) x, float64 (mass fit) or float32 MFMA
 //                    (value fit), for iterative refinement
 #include "common.hpp"
@@ -840,7 +840,7 @@ __global__ void __launch_bounds__(256) k_chol_scales(const float *__restrict__ G
 }
 
 // ------------------------------------------------- inverses of the 256-wide diagonal blocks
-// D_K = L_KK^-1, 256 x 256 lower triangular in fp32, for the triangular solves,
+// D_K = L_KK^-1, 256 x 256 lower triangular in fp32, for the value fit's solves,
 // which then take ld / 256 steps.  It is kept in the unused diagonal block of
 // the planes of L (the contractions read rows below a panel only): of row r,
 // columns 0 .. 127 in the hi plane's 512 bytes at (K0 + r, K0) and columns
@@ -952,25 +952,42 @@ __global__ void __launch_bounds__(64 * NW) k_chol_inv256(const float *__restrict
 }
 
 // --------------------------------------------------------------- one right-hand side
+// The sum over each 16 consecutive lanes, in every one of them.
+template <int CTRL>
+__device__ __forceinline__ double row16_add(double v) {
+  const uint64_t u = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+  return v + __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+__device__ __forceinline__ double row16_sum(double v) {   // rotations by 8, 4, 2 and 1 lanes
+  return row16_add<0x121>(row16_add<0x122>(row16_add<0x124>(row16_add<0x128>(v))));
+}
+
 // One-rhs triangular solves, float64 vectors, right-looking over 256-row
 // blocks K with one launch per block:
-//   forward  L y = rhs:   y_K = D_K s_K,     s_i -= L_iK y_K      (rows i below)
-//   backward L^T x = y:   x_K = D_K^T y_K,   y_i -= L_Ki^T x_K    (columns i before)
-// Every workgroup forms the block solution (a 256 x 256 triangular product)
-// and updates `per` chunks of 64 targets; workgroup 0 also writes the solution
-// (and adds it to `acc` on the backward pass when given).  Forward step 0
-// reads the rhs, later steps the work vector s; the backward pass updates y in
-// place.  Bound by the launches and the two dependent reads of one: 64-row
-// blocks took four times the launches at 4.3 us each, these 7.5 us (7.9 with the
-// vector's read and the pair's state waited for before the other reads): 725 -> 315
-// us for the six passes of 8 pairs at t = 1638; 64 pairs at t = 3277: 22.2 -> 20.5
-// ms per 256 pairs for the mass fit's solve stage with its residuals.
+//   forward  L y = rhs:   L_KK y_K = s_K,     s_i -= L_iK y_K      (rows i below)
+//   backward L^T x = y:   L_KK^T x_K = y_K,   y_i -= L_Ki^T x_K    (columns i before)
+// Every workgroup forms the block solution in four steps of 64 rows with the
+// inverses D_k of the 64 x 64 diagonal blocks (dinv), and updates `per` chunks
+// of 64 targets; workgroup 0 also writes the solution (and adds it to `acc` on
+// the backward pass when given).  Forward step 0 reads the rhs, later steps the
+// work vector s; the backward pass updates y in place.  The steps of 64 are part of
+// the result: with fp32 inverses of whole 256 x 256 blocks the refinement of
+// nearly square systems ends elsewhere (t = 3277, n = 4096: biases 1.7e-4 apart in
+// norm).  Bound by the launches, the two dependent reads and the four steps of
+// one: 8 pairs at t = 1638, 8.0 and 8.4 us forward and backward (7.4 and 7.5 with the
+// inverse of the whole block, which takes 19 us per factorisation to form; 64-row
+// blocks with a launch each, four launches of 4.3 us); 256 pairs at t = 3277: 18.5 -> 18.0
+// ms for the mass fit's solve stage with its residuals.
 template <bool FWD>
-__global__ void __launch_bounds__(1024) k_trsv256(const float *__restrict__ Gw, const void *__restrict__ lsplit,
+__global__ void __launch_bounds__(1024) k_trsv256(const float *__restrict__ Gw, const float *__restrict__ dinv,
                                                   int64_t ld, int K, int per, const double *__restrict__ rhs,
                                                   double *__restrict__ work, double *__restrict__ out,
                                                   double *__restrict__ acc, const int32_t *__restrict__ info) {
-  __shared__ double sv[256], sol[256], red[16][256];
+  constexpr int SR = 68;   // stride of red: 16 rows of one column in different banks
+  __shared__ __attribute__((aligned(16))) double sv[256], sol[256];
+  __shared__ double red[FWD ? 1 : 3 * 16 * SR];
   const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int32_t skip = info[b];   // looked at after the loads: they need not wait for it
@@ -978,7 +995,8 @@ __global__ void __launch_bounds__(1024) k_trsv256(const float *__restrict__ Gw, 
   const int nch = (int)(FWD ? (ld - K0 - 256) / 64 : K0 / 64);   // chunks of 64 targets
   const int ch0 = blockIdx.x * per, ch1 = min(ch0 + per, nch);
   const float *L = Gw + (size_t)b * ld * ld;
-  const DiagInv D = diag_inv(lsplit, ld, b, K0);
+  const float *LK = L + (size_t)K0 * ld + K0;                          // the diagonal block
+  const float *D = dinv + ((size_t)b * (ld / kNB) + K0 / kNB) * kNB * kNB;   // its four inverses
   const double *src = (FWD && K == 0 ? rhs : work) + (size_t)b * ld;
   const double own = src[K0 + (tid & 255)];
   // the chunk's part of L, loaded ahead of its use: forward 16 lanes per
@@ -994,62 +1012,75 @@ __global__ void __launch_bounds__(1024) k_trsv256(const float *__restrict__ Gw, 
       lv[u] = *reinterpret_cast<const f32x4 *>(FWD ? L + (size_t)(K0 + 256 + 64 * ch + rg) * ld + K0 + 4 * (q + 16 * u)
                                                    : L + (size_t)(K0 + rg + 64 * u) * ld + 64 * ch + 4 * q);
   };
-  if constexpr (FWD) {
-    // y_K: four lanes per row, interleaved over its 16-byte groups up to the end of
-    // the diagonal's 16 x 16 tile, whose upper entries are stored zeros; a wave has
-    // 16 rows, so its loads stand under no lane mask
-    const int r = tid >> 2, p = tid & 3;
-    f32x4 d[16];
+  // d[k]: the thread's part of D_k; l[j (j - 1) / 2 + k]: of block (j, k) of L, j > k.
+  // Forward: row rg, columns 4 q .. + 3; backward: rows 4 wave .. + 3, column lane.
+  f32x4 d[4], l[6];
 #pragma unroll
-    for (int u = 0; u < 16; ++u)
-      if (u <= wave) d[u] = *reinterpret_cast<const f32x4 *>(D.at(r, 4 * (p + 4 * u)));
-    if (ch0 < ch1) load_l(ch0);
-    if (tid < 256) sv[tid] = own;
-    __syncthreads();
-    if (skip != 0) return;   // uniform over the workgroup
-    double s0 = 0.0, s1 = 0.0;
+  for (int k = 0; k < 4; ++k) {
+    if constexpr (FWD) {
+      d[k] = *reinterpret_cast<const f32x4 *>(D + (kNB * k + rg) * kNB + 4 * q);
+    } else {
 #pragma unroll
-    for (int u = 0; u < 16; ++u)
-      if (u <= wave) {
-        const double *v = sv + 4 * (p + 4 * u);
-        s0 = fma((double)d[u][0], v[0], s0);
-        s1 = fma((double)d[u][1], v[1], s1);
-        s0 = fma((double)d[u][2], v[2], s0);
-        s1 = fma((double)d[u][3], v[3], s1);
-      }
-    double s = s0 + s1;
-    s += __shfl_xor(s, 1, 64);
-    s += __shfl_xor(s, 2, 64);
-    if (p == 0) sol[r] = s;
-  } else {
-    // x_K: a lane per four columns, a wave per 16 rows r = wave (mod 16)
-    f32x4 d[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u)
-      if (16 * u + wave >= 4 * lane) d[u] = *reinterpret_cast<const f32x4 *>(D.at(16 * u + wave, 4 * lane));
-    if (ch0 < ch1) load_l(ch0);
-    if (tid < 256) sv[tid] = own;
-    __syncthreads();
-    if (skip != 0) return;   // uniform over the workgroup
-    double s[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int u = 0; u < 16; ++u)
-      if (16 * u + wave >= 4 * lane) {
-        const double v = sv[16 * u + wave];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s[e] = fma((double)d[u][e], v, s[e]);
-      }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) red[wave][4 * lane + e] = s[e];
-    __syncthreads();
-    if (tid < 256) {
-      double x = 0.0;
-#pragma unroll
-      for (int w = 0; w < 16; ++w) x += red[w][tid];
-      sol[tid] = x;
+      for (int e = 0; e < 4; ++e) d[k][e] = D[(kNB * k + 4 * wave + e) * kNB + lane];
     }
   }
+#pragma unroll
+  for (int j = 1; j < 4; ++j)
+#pragma unroll
+    for (int k = 0; k < j; ++k) {
+      f32x4 &v = l[j * (j - 1) / 2 + k];
+      if constexpr (FWD) {
+        v = *reinterpret_cast<const f32x4 *>(LK + (size_t)(kNB * j + rg) * ld + kNB * k + 4 * q);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = LK[(size_t)(kNB * j + 4 * wave + e) * ld + kNB * k + lane];
+      }
+    }
+  if (ch0 < ch1) load_l(ch0);
+  if (tid < 256) sv[tid] = own;
   __syncthreads();
+  if (skip != 0) return;   // uniform over the workgroup
+  auto dot4 = [](f32x4 x, const double *v) {
+    double s = 0.0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s = fma((double)x[e], v[e], s);
+    return s;
+  };
+  if constexpr (FWD) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const double s = row16_sum(dot4(d[k], sv + kNB * k + 4 * q));
+      if (q == 0) sol[kNB * k + rg] = s;
+      __syncthreads();
+      if (k == 3) break;
+#pragma unroll
+      for (int j = k + 1; j < 4; ++j) {
+        const double u = row16_sum(dot4(l[j * (j - 1) / 2 + k], sol + kNB * k + 4 * q));
+        if (q == 0) sv[kNB * j + rg] -= u;
+      }
+      __syncthreads();
+    }
+  } else {
+#pragma unroll
+    for (int k = 3; k >= 0; --k) {
+      red[wave * SR + lane] = dot4(d[k], sv + kNB * k + 4 * wave);
+      __syncthreads();
+      const double s = row16_sum(red[q * SR + rg]);
+      if (q == 0) sol[kNB * k + rg] = s;
+      __syncthreads();
+      if (k == 0) break;
+#pragma unroll
+      for (int j = 0; j < k; ++j)
+        red[(16 * j + wave) * SR + lane] = dot4(l[k * (k - 1) / 2 + j], sol + kNB * k + 4 * wave);
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < k; ++j) {
+        const double u = row16_sum(red[(16 * j + q) * SR + rg]);
+        if (q == 0) sv[kNB * j + rg] -= u;
+      }
+      __syncthreads();
+    }
+  }
   if (blockIdx.x == 0 && tid < 256) {
     out[(size_t)b * ld + K0 + tid] = sol[tid];
     if (!FWD && acc) acc[(size_t)b * ld + K0 + tid] += sol[tid];
@@ -1084,13 +1115,13 @@ __global__ void __launch_bounds__(1024) k_trsv256(const float *__restrict__ Gw, 
       __syncthreads();   // the previous use of red is over
       if (lane < 16) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) red[wave][4 * lane + e] = s[e];
+        for (int e = 0; e < 4; ++e) red[wave * SR + 4 * lane + e] = s[e];
       }
       __syncthreads();
       if (tid < 64) {
         double x = 0.0;
 #pragma unroll
-        for (int w = 0; w < 16; ++w) x += red[w][tid];
+        for (int w = 0; w < 16; ++w) x += red[w * SR + tid];
         work[(size_t)b * ld + 64 * ch + tid] = base - x;
       }
     }
@@ -1914,7 +1945,7 @@ __global__ void k_nnls_finish(const int32_t *__restrict__ state, int B, int32_t 
 
 // ------------------------------------------------------------------ launchers
 hipError_t launch_fill_i32(int32_t *p, int64_t count, int32_t v, hipStream_t s);
-hipError_t launch_trsv(const float *Gw, const void *lsplit, int B, int64_t ld, const double *rhs, double *sw,
+hipError_t launch_trsv(const float *Gw, const float *dinv, int B, int64_t ld, const double *rhs, double *sw,
                        double *y, double *x, double *acc, const int32_t *info, hipStream_t s);
 hipError_t launch_cholesky_factor(float *Gw, const float *Gc, int B, int t, int64_t ld, float delta0, int max_esc,
                                   FitState st, float *dinv, void *lsplit, hipStream_t s);
@@ -2026,21 +2057,25 @@ hipError_t launch_cholesky_factor(float *Gw, const float *Gc, int B, int t, int6
       if (e != hipSuccess) return e;
     }
   }
-  const int nblk = (int)(ld / kOuter);
-  auto inv = [&](auto kern, int nw) {
-    const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kInv256Lds);
-    if (e == hipSuccess)
-      hipLaunchKernelGGL(kern, dim3((unsigned)nblk, B, 16 / nw), dim3(64 * nw), kInv256Lds, s, Gw, ld, t, dinv, lsplit,
-                         st.info);
-    return e;
-  };
-  // four workgroups per block as long as each has a CU
-  const hipError_t ei = (int64_t)nblk * B <= 64 ? inv(k_chol_inv256<4>, 4) : inv(k_chol_inv256<16>, 16);
-  if (ei != hipSuccess) return ei;
   (void)Gc;
   (void)delta0;
   (void)max_esc;
   return hipGetLastError();
+}
+
+// The inverses of the factored pairs' 256 x 256 diagonal blocks, for launch_trsm.
+hipError_t launch_inv256(const float *Gw, int B, int t, int64_t ld, const float *dinv, void *lsplit,
+                         const int32_t *info, hipStream_t s) {
+  const int nblk = (int)(ld / 256);
+  auto inv = [&](auto kern, int nw) {
+    const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kInv256Lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)nblk, B, 16 / nw), dim3(64 * nw), kInv256Lds, s, Gw, ld, t, dinv, lsplit,
+                       info);
+    return hipGetLastError();
+  };
+  // four workgroups per block as long as each has a CU
+  return (int64_t)nblk * B <= 64 ? inv(k_chol_inv256<4>, 4) : inv(k_chol_inv256<16>, 16);
 }
 
 // Forward L y = rhs then backward L^T x = y; sw and y are work vectors
@@ -2049,7 +2084,7 @@ hipError_t launch_cholesky_factor(float *Gw, const float *Gc, int B, int t, int6
 // up to four (256 rows, as much of L as of D_K) once the launch holds more
 // than kTrsvGroups of them, so that D_K is not re-read for every 64 rows.
 constexpr int kTrsvGroups = 512;
-hipError_t launch_trsv(const float *Gw, const void *lsplit, int B, int64_t ld, const double *rhs, double *sw,
+hipError_t launch_trsv(const float *Gw, const float *dinv, int B, int64_t ld, const double *rhs, double *sw,
                        double *y, double *x, double *acc, const int32_t *info, hipStream_t s) {
   const int nblk = (int)(ld / 256);
   auto groups = [&](int nch, int &per) {
@@ -2060,12 +2095,12 @@ hipError_t launch_trsv(const float *Gw, const void *lsplit, int B, int64_t ld, c
   int per = 1;
   for (int K = 0; K < nblk; ++K) {
     const int ng = groups(4 * (nblk - 1 - K), per);
-    hipLaunchKernelGGL(k_trsv256<true>, dim3(ng, B), dim3(1024), 0, s, Gw, lsplit, ld, K, per, rhs, sw, y,
+    hipLaunchKernelGGL(k_trsv256<true>, dim3(ng, B), dim3(1024), 0, s, Gw, dinv, ld, K, per, rhs, sw, y,
                        (double *)nullptr, info);
   }
   for (int K = nblk - 1; K >= 0; --K) {
     const int ng = groups(4 * K, per);
-    hipLaunchKernelGGL(k_trsv256<false>, dim3(ng, B), dim3(1024), 0, s, Gw, lsplit, ld, K, per,
+    hipLaunchKernelGGL(k_trsv256<false>, dim3(ng, B), dim3(1024), 0, s, Gw, dinv, ld, K, per,
                        (const double *)nullptr, y, x, acc, info);
   }
   return hipGetLastError();
@@ -2094,12 +2129,12 @@ hipError_t launch_mass_solve(float *Gw, const float *Gc, float *dinv, void *lspl
   const dim3 gb((B + 255) / 256);
   if ((e = launch_fill_i32(ms.div, B, 0, s)) != hipSuccess) return e;
   for (int round = 0;; ++round) {
-    if ((e = launch_trsv(Gw, lsplit, B, tp, ms.h, ms.sw, ms.y, ms.w, nullptr, st.info, s)) != hipSuccess) return e;
+    if ((e = launch_trsv(Gw, dinv, B, tp, ms.h, ms.sw, ms.y, ms.w, nullptr, st.info, s)) != hipSuccess) return e;
     for (int it = 0; it < refine_steps; ++it) {
       if ((e = launch_mass_residual(ms.LT, ms.z, ms.m, ms.w, st.lam, B, n, t, tp, np_, ms.u, ms.res, st.info, s,
                                       nullptr, nullptr, nullptr, nullptr)) != hipSuccess)
         return e;
-      if ((e = launch_trsv(Gw, lsplit, B, tp, ms.res, ms.sw, ms.y, ms.x, ms.w, st.info, s)) != hipSuccess) return e;
+      if ((e = launch_trsv(Gw, dinv, B, tp, ms.res, ms.sw, ms.y, ms.x, ms.w, st.info, s)) != hipSuccess) return e;
       hipLaunchKernelGGL(k_refine_watch, dim3(B), dim3(256), 0, s, ms.w, ms.x, tp, it, ms.rprev, ms.div, st,
                          max_esc);
     }
@@ -2148,7 +2183,7 @@ hipError_t launch_nnls(const float *Gc, float *Gw, const double *h, const float 
       // residual of the full ridged system against the data, h - (G + lam I) x
       hipLaunchKernelGGL(k_nnls_gather_vec, gf, dim3(256), 0, s, rs == 0 ? h : res, tp, nw.idx, nw.nf, st.info, ldf,
                          nw.rf);
-      if ((e = launch_trsv(Gw, lsplit, B, ldf, nw.rf, sw, yw, nw.xf, nullptr, st.info, s)) != hipSuccess) return e;
+      if ((e = launch_trsv(Gw, dinv, B, ldf, nw.rf, sw, yw, nw.xf, nullptr, st.info, s)) != hipSuccess) return e;
       hipLaunchKernelGGL(k_nnls_scatter, gv, dim3(256), 0, s, nw.xf, ldf, nw.pos, tp, st.info, rs > 0 ? 1 : 0, x);
       // x vanishes off F, so Phi_C x sums over the free keys; the residual is
       // needed on the free keys for a correction, on the bound keys (the dual)

@@ -1,6 +1,7 @@
 """Sizes at the borders of the kernels' splits: tile edges, remainders, and both
 sides of every rule that picks a variant by size, against float64."""
 import math
+import os
 
 import numpy as np
 import pytest
@@ -61,6 +62,22 @@ def test_mass_fit_sizes(B, n, t, shift):
         tol = 6e-6 * float(sv[b % P][0] / sv[b % P][-1])
         err = float((torch.exp(beta[b].double()) - ref).norm() / ref.norm())
         assert err <= tol, (b, err, tol)
+
+
+def test_mass_fit_nearly_square():
+    """The biases of a nearly square system depend on the form of the solves beneath the
+    refinement; these are those of solves by 64 x 64 diagonal inverses, to two units in the last
+    place of the largest (256 x 256 inverses: five)."""
+    print("mass fit nearly square", flush=True)
+    n, t = 520, 500
+    rng = np.random.default_rng(n * 1000 + t)
+    f = lambda x: torch.from_numpy(x.astype(np.float32)).cuda()
+    Q, C = f(rng.standard_normal((1, n, 128))), f(rng.standard_normal((1, t, 128)))
+    m, z = f(rng.random((1, n)) * t), f(rng.random((1, n)))
+    beta, info, _ = A().fit_bias(Q, C, 2.0 * z, m, A().default_params(b_min=-6.0), T=4 * t)
+    ref = np.loadtxt(os.path.join(os.path.dirname(__file__), "golden", "mass_fit_520_500.txt"))
+    assert int(info[0]) == 0
+    assert np.abs(np64(beta)[0] - ref).max() <= 2.0 ** -20
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
