@@ -102,8 +102,8 @@ hipError_t launch_phat(int dtype, const float *LT, const float *beta_ws, int B, 
                        int64_t np_, void *out, void *outm, hipStream_t s);
 hipError_t launch_transpose128(int dtype, const float *in, int B, int rows, int64_t in_pair, int64_t rows_pad,
                                void *out, int64_t out_pair, hipStream_t s);
-hipError_t launch_trsm(bool fwd, const float *Gw, const float *dinv, const void *lsplit, int B, int t, int64_t ld,
-                       float *R, float *X, float *xt, const int32_t *info, hipStream_t s);
+hipError_t launch_trsm(bool fwd, const float *Gw, const void *lsplit, int B, int64_t ld, float *R, float *X, float *xt,
+                       const int32_t *info, hipStream_t s);
 hipError_t launch_add(float *x, const float *dx, int B, int64_t n_per, const int32_t *info, hipStream_t s);
 hipError_t launch_values_out(const float *Xp, int B, int64_t tp, int t, const int32_t *info, float *Cv,
                              hipStream_t s);
@@ -585,8 +585,8 @@ static arckv_status run_fit_values_chunk(const Ctx &c, int b0, int P, const floa
     StageScope _sc(ST_SOLVE_V, stream);
     const void *lsp = c.chunk<char>(c.pl.lsplit);
     float *xt = c.chunk<float>(c.pl.XT);   // scratch of the solves; the residual's X^T is formed and read between them
-    if (launch_trsm(true, Gw, dinv, lsp, P, d.t, d.tp, Bm, Y2, xt, st.info, stream) != hipSuccess) return ARCKV_ERR_HIP;
-    if (launch_trsm(false, Gw, dinv, lsp, P, d.t, d.tp, Y2, X, xt, st.info, stream) != hipSuccess) return ARCKV_ERR_HIP;
+    if (launch_trsm(true, Gw, lsp, P, d.tp, Bm, Y2, xt, st.info, stream) != hipSuccess) return ARCKV_ERR_HIP;
+    if (launch_trsm(false, Gw, lsp, P, d.tp, Y2, X, xt, st.info, stream) != hipSuccess) return ARCKV_ERR_HIP;
     // refinement against the data: R = P^T (Y - P X) - lam X
     for (int it = 0; it < fp.value_refine_steps; ++it) {
       if (launch_transpose128(d.dtype, X, P, (int)d.tp, d.tp * kHeadDimH, d.tp, XT, pl * d.tp * kHeadDimH, stream) !=
@@ -594,8 +594,8 @@ static arckv_status run_fit_values_chunk(const Ctx &c, int b0, int P, const floa
         return ARCKV_ERR_HIP;
       if (launch_value_residual(d.dtype, XT, Pm, PT, Yc, UT, X, st.lam, R, P, d.n, d.tp, d.np_, stream) != hipSuccess)
         return ARCKV_ERR_HIP;
-      if (launch_trsm(true, Gw, dinv, lsp, P, d.t, d.tp, R, Y2, xt, st.info, stream) != hipSuccess) return ARCKV_ERR_HIP;
-      if (launch_trsm(false, Gw, dinv, lsp, P, d.t, d.tp, Y2, R, xt, st.info, stream) != hipSuccess) return ARCKV_ERR_HIP;
+      if (launch_trsm(true, Gw, lsp, P, d.tp, R, Y2, xt, st.info, stream) != hipSuccess) return ARCKV_ERR_HIP;
+      if (launch_trsm(false, Gw, lsp, P, d.tp, Y2, R, xt, st.info, stream) != hipSuccess) return ARCKV_ERR_HIP;
       if (launch_add(X, R, P, d.tp * kHeadDimH, st.info, stream) != hipSuccess) return ARCKV_ERR_HIP;
     }
     if (launch_values_out(X, P, d.tp, d.t, st.info, Cv + (size_t)b0 * d.t * kHeadDimH, stream) != hipSuccess)

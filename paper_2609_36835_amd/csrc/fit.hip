@@ -25,8 +25,9 @@
 //                    delta raised tenfold (from 1e-7 when zero), at most
 //                    max_escalations times (launch_cholesky)
 //   solves           TRSV (one rhs, float64 accumulation, by the 64 x 64 diagonal
-//                    inverses) / TRSM (128 rhs, fp32 MFMA, by the inverses of the
-//                    256 x 256 diagonal blocks, k_chol_inv256), both right-looking
+//                    inverses, right-looking) / TRSM (128 rhs, fp32 MFMA, by the
+//                    inverses of the 256 x 256 diagonal blocks, k_chol_inv256,
+//                    right-looking for few pairs and left-looking for many), both
 //                    in 256-row blocks
 //   residuals        rhs - (M + lam I) x, float64 (mass fit) or float32 MFMA
 //                    (value fit), for iterative refinement
@@ -1458,17 +1459,87 @@ __global__ void __launch_bounds__(256) k_transpose128(const float *__restrict__ 
 
 // --------------------------------------------------------------- 128 right-hand sides
 // L Y = R (forward) and L^T X = Y (backward) for 128 right-hand sides, fp32
-// MFMA throughout, right-looking over 256-row blocks K:
-//   k_trsm_diag  X_K = D_K R_K (or D_K^T R_K), one 16 x 16 tile per wave, written
-//                to X and, as 16 x 16 tiles of X_K^T in the fragments' layout, to
-//                xt [B][16 k tiles][8 column tiles][256]
-//   k_trsm_upd   R_i -= L_iK X_K (or L_Ki^T X_K) on the remaining rows
-// The remaining rows are updated by their own workgroups, so a call over few
-// pairs fills the chip where one workgroup per pair (a left-looking solve)
-// ran on as many CUs as there are pairs; at many pairs it is bound by the
-// fp32 MFMA rate and by reading and writing R once per block.  The four solves of 8 pairs
-// at t = 1638: 3.4 -> 0.5 ms; of 256 pairs at t = 3277, 64 at a time: 46 -> 25 ms.
+// MFMA throughout, in 256-row blocks K:
+//   k_trsm_diag       X_K = D_K R_K (or D_K^T R_K), written to X and, as 16 x 16 tiles
+//   k_trsm_diag_left  of X^T in the fragments' layout, to xt [B][ld / 16][8][256]
+//   k_trsm_upd        R_i -= L_iK X_K (or L_Ki^T X_K) on the remaining rows
+//   k_trsm_left       R_K -= L_Ki X_i (or L_iK^T X_i) for the solved blocks i in order
+// Few pairs are right-looking (diag, upd): the remaining rows are updated by
+// their own workgroups, so a call fills the chip.  Many are left-looking (left,
+// diag_left): a block's rows stay in registers while every solved block is applied,
+// so R is read and written once and not once per block, and the operands are staged
+// in LDS, whose tiles several waves read.  Both forms apply the blocks in the same
+// order with the same sums, so a pair's solution is the same bits however many are
+// solved together.
+// Four solves and the refinement's products, right- and left-looking, in ms: t = 3277,
+// 64 pairs 8.5 and 9.0, 96: 12.3 and 10.5, 128: 16.2 and 11.9, 256: 31.3 and 22.9; t =
+// 1638, 64 pairs 3.39 and 3.42, 128: 6.5 and 5.0, 256: 12.3 and 9.4; t = 819, 64 pairs
+// 1.26 and 1.19, 256: 5.7 and 4.5.  (One workgroup per pair for the whole solve: 24.8,
+// 9.0 and 3.9 at 256 pairs with 64-wide inverses, other sums; 24.9, 9.8 and 4.6 with these.)
+// k_trsm_left takes 36 us per applied block of 256 pairs, 0.76 of the fp32 MFMA rate,
+// and k_trsm_diag_left 44 us, most of it the reads and writes of R, X and xt.
 // R is overwritten; X must not alias it.
+
+// acc[i][j] += the product of 16 columns of L's row tiles i and 16 rows of X's column
+// tiles j: fragments l and x.
+template <int RT, int CT>
+__device__ __forceinline__ void trsm_mac(f32x4 (&acc)[RT][CT], const f32x4 (&l)[RT], const f32x4 (&x)[CT]) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int j = 0; j < CT; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[j][e], l[i][e], acc[i][j], 0, 0, 0);
+}
+
+// Tile (rt, ct) of X_K: the sum of its even and odd k tiles' products, column r and
+// rows 4 g .. 4 g + 3 in lane 16 g + r.
+__device__ __forceinline__ void trsm_put(float *X, float *xt, int64_t ld, int b, int K, int rt, int ct, int lane,
+                                         f32x4 even, f32x4 odd) {
+  const int r = lane & 15, g = lane >> 4;
+  f32x4 o;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) o[e] = even[e] + odd[e];
+  *reinterpret_cast<f32x4 *>(xt + (((size_t)b * (ld / 16) + 16 * K + rt) * 8 + ct) * 256 + 4 * lane) = o;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) X[((size_t)b * ld + 256 * (int64_t)K + 16 * rt + 4 * g + e) * kHeadDim + 16 * ct + r] = o[e];
+}
+
+// The parts of L_iK (forward; of L_Ki^T) and of X_K^T that one wave's products over
+// rows row0 .. + 31 and column tiles ct0 .. + CT - 1 read: a 16-byte load per lane
+// and tile (the backward rows of L: four 4-byte loads).
+template <bool FWD, int CT>
+struct TrsmOperands {
+  const float *L, *x;
+  int64_t ld;
+  __device__ __forceinline__ TrsmOperands(const float *Gw, const float *xt, int64_t ld, int b, int K, int64_t row0,
+                                          int ct0, int lane)
+      : ld(ld) {
+    const int r = lane & 15, g = lane >> 4;
+    const int64_t K0 = (int64_t)K * 256;
+    L = Gw + (size_t)b * ld * ld + (FWD ? (size_t)(row0 + r) * ld + K0 + 4 * g : (size_t)(K0 + 4 * g) * ld + row0 + r);
+    x = xt + (((size_t)b * (ld / 16) + 16 * K) * 8 + ct0) * 256 + 4 * lane;
+  }
+  __device__ __forceinline__ void load(int kt, f32x4 (&l)[2], f32x4 (&xv)[CT]) const {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      if constexpr (FWD) {
+        l[i] = *reinterpret_cast<const f32x4 *>(L + (size_t)(16 * i) * ld + 16 * kt);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) l[i][e] = L[(size_t)(16 * kt + e) * ld + 16 * i];
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < CT; ++j) xv[j] = *reinterpret_cast<const f32x4 *>(x + (size_t)(8 * kt + j) * 256);
+  }
+};
+
+// One 16 x 16 tile per wave, 16 rows x 64 columns per workgroup.  A tile is the sum
+// of its even and of its odd k tiles, over the k tiles where D has entries (or
+// stored zeros): up to the diagonal tile, or from it.  Every tile is loaded, so that
+// all loads are in flight at once; the others' values are replaced by zeros.
 template <bool FWD>
 __global__ void __launch_bounds__(256) k_trsm_diag(const void *__restrict__ lsplit, int64_t ld, int K,
                                                    const float *__restrict__ R, float *__restrict__ X,
@@ -1478,12 +1549,8 @@ __global__ void __launch_bounds__(256) k_trsm_diag(const void *__restrict__ lspl
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, g = lane >> 4;
   const int64_t K0 = (int64_t)K * 256;
   const DiagInv D = diag_inv(lsplit, ld, b, K0);
-  // workgroup: 16 rows x 64 columns; tile (rt, ct) per wave
   const int rt = blockIdx.x >> 1, ct = 4 * (blockIdx.x & 1) + wave;
   const float *Rb = R + ((size_t)b * ld + K0) * kHeadDim + 16 * ct + r;
-  // k tiles where D has entries (or stored zeros): up to the diagonal tile, or
-  // from it.  Every tile is loaded, so that all loads are in flight at once;
-  // the others' values are replaced by zeros.
   const int k0 = FWD ? 0 : rt, k1 = FWD ? rt + 1 : 16;
   f32x4 d[16], v[16];
 #pragma unroll
@@ -1511,17 +1578,11 @@ __global__ void __launch_bounds__(256) k_trsm_diag(const void *__restrict__ lspl
     if (kt & 1) s1 = tile_mac(s1, v[kt], d[kt]);
     else s0 = tile_mac(s0, v[kt], d[kt]);
   }
-  f32x4 o;   // column r of the tile, rows 4 g .. 4 g + 3
-#pragma unroll
-  for (int e = 0; e < 4; ++e) o[e] = s0[e] + s1[e];
-  *reinterpret_cast<f32x4 *>(xt + (((size_t)b * 16 + rt) * 8 + ct) * 256 + 4 * lane) = o;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) X[((size_t)b * ld + K0 + 16 * rt + 4 * g + e) * kHeadDim + 16 * ct + r] = o[e];
+  trsm_put(X, xt, ld, b, K, rt, ct, lane, s0, s1);
 }
 
 // 64 rows x 32 TN columns per workgroup, 32 x 16 TN per wave (2 x 2 waves);
-// fragments straight from global memory, a 16-byte load per lane and tile (the
-// backward rows of L: four 4-byte loads).
+// fragments straight from global memory.
 template <bool FWD, int TN>
 __global__ void __launch_bounds__(256) k_trsm_upd(const float *__restrict__ Gw, int64_t ld, int K,
                                                   float *__restrict__ R, const float *__restrict__ xt,
@@ -1530,53 +1591,28 @@ __global__ void __launch_bounds__(256) k_trsm_upd(const float *__restrict__ Gw, 
   const int b = blockIdx.y;
   if (info[b] != 0) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, g = lane >> 4;
-  const int64_t K0 = (int64_t)K * 256;
   const int cg = blockIdx.x % NCG, rc = blockIdx.x / NCG;
-  const int64_t row0 = (FWD ? K0 + 256 : 0) + 64 * (int64_t)rc + 32 * (wave & 1);
+  const int64_t row0 = (FWD ? (int64_t)K * 256 + 256 : 0) + 64 * (int64_t)rc + 32 * (wave & 1);
   const int ct0 = 2 * TN * cg + TN * (wave >> 1);
-  const float *Lb = Gw + (size_t)b * ld * ld + (FWD ? (size_t)(row0 + r) * ld + K0 + 4 * g
-                                                    : (size_t)(K0 + 4 * g) * ld + row0 + r);
-  const float *xb = xt + ((size_t)b * 16 * 8 + ct0) * 256 + 4 * lane;
+  const TrsmOperands<FWD, TN> op(Gw, xt, ld, b, K, row0, ct0, lane);
   f32x4 acc[2][TN];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto load = [&](int kt, f32x4 (&l)[2], f32x4 (&x)[TN]) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      if constexpr (FWD) {
-        l[i] = *reinterpret_cast<const f32x4 *>(Lb + (size_t)(16 * i) * ld + 16 * kt);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) l[i][e] = Lb[(size_t)(16 * kt + e) * ld + 16 * i];
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < TN; ++j) x[j] = *reinterpret_cast<const f32x4 *>(xb + (size_t)(8 * kt + j) * 256);
-  };
-  auto mac = [&](const f32x4 (&l)[2], const f32x4 (&x)[TN]) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[j][e], l[i][e], acc[i][j], 0, 0, 0);
-  };
   if constexpr (TN == 2) {   // few workgroups: a wave's whole operands in flight at once
     f32x4 l[16][2], x[16][TN];
 #pragma unroll
-    for (int kt = 0; kt < 16; ++kt) load(kt, l[kt], x[kt]);
+    for (int kt = 0; kt < 16; ++kt) op.load(kt, l[kt], x[kt]);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int kt = 0; kt < 16; ++kt) mac(l[kt], x[kt]);
+    for (int kt = 0; kt < 16; ++kt) trsm_mac(acc, l[kt], x[kt]);
   } else {
 #pragma unroll 4
     for (int kt = 0; kt < 16; ++kt) {
       f32x4 l[2], x[TN];
-      load(kt, l, x);
-      mac(l, x);
+      op.load(kt, l, x);
+      trsm_mac(acc, l, x);
     }
   }
 #pragma unroll
@@ -1589,6 +1625,187 @@ __global__ void __launch_bounds__(256) k_trsm_upd(const float *__restrict__ Gw, 
       for (int e = 0; e < 4; ++e) o[e] -= acc[i][j][e];
       *p = o;
     }
+}
+
+// The left-looking kernels stage their operands in LDS as 16 x 16 tiles, each by one
+// 16-byte direct-to-LDS load per lane (lane l fills floats 4 l .. 4 l + 3), in the order
+// that a wave's fragments are read without bank conflicts:
+//   rows   lane 16 g + r's fragment is row r, columns 4 g .. 4 g + 3, one 16-byte read
+//   cols   it is column r, rows 4 g .. 4 g + 3: row 4 g + e lies at float 16 (4 e + g)
+typedef __attribute__((address_space(3))) void trsm_lds_t;
+
+__device__ __forceinline__ int64_t stage_rows(int lane, int64_t ld) { return (lane & 15) * ld + 4 * (lane >> 4); }
+__device__ __forceinline__ int64_t stage_cols(int lane, int64_t ld) {
+  return (4 * ((lane >> 2) & 3) + (lane >> 4)) * ld + 4 * (lane & 3);
+}
+__device__ __forceinline__ void stage_tile(const float *src, float *tile) {
+  __builtin_amdgcn_global_load_lds((const void *)src, (trsm_lds_t *)tile, 16, 0, 0);
+}
+__device__ __forceinline__ f32x4 tile_rows(const float *tile, int lane) {
+  return *reinterpret_cast<const f32x4 *>(tile + 4 * lane);
+}
+__device__ __forceinline__ f32x4 tile_cols(const float *tile, int lane) {
+  const float *p = tile + 16 * (lane >> 4) + (lane & 15);
+  return f32x4{p[0], p[64], p[128], p[192]};
+}
+
+// Block K's rows, 128 per workgroup over all 128 columns, 32 x 64 per wave: every
+// solved block's product with its own sum, subtracted in the solve's order, as
+// k_trsm_upd subtracts them one launch at a time.  Two k tiles per stage, two stages.
+// A pair's two workgroups share an XCD, whose L2 they read the solution from.
+constexpr int kTrsmLeftRows = 128;
+template <bool FWD>
+__global__ void __launch_bounds__(512, 4) k_trsm_left(const float *__restrict__ Gw, int64_t ld, int K,
+                                                      float *__restrict__ R, const float *__restrict__ xt,
+                                                      const int32_t *__restrict__ info) {
+  constexpr int NS = 4;
+  __shared__ __attribute__((aligned(1024))) float stage[NS][16][256];   // 8 row tiles, 8 column tiles of a k tile
+  const int64_t tile = xcd_remap(blockIdx.x, gridDim.x);
+  const int b = (int)(tile >> 1), rc = (int)(tile & 1);
+  if (info[b] != 0) return;   // uniform over the workgroup
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wr = wave & 3, wc = wave >> 2;
+  const int64_t row0 = (int64_t)K * 256 + kTrsmLeftRows * rc;
+  const int nblk = (int)(ld / 256), stages = 16 * (FWD ? K : nblk - 1 - K);
+  const float *Lb = Gw + (size_t)b * ld * ld + (FWD ? row0 * ld + stage_rows(lane, ld) : row0 + stage_cols(lane, ld));
+  const float *xb = xt + (size_t)b * ld * kHeadDim + 4 * lane;
+  auto issue = [&](int q) {   // wave w loads tiles 2 w and 2 w + 1
+    const int64_t kt = 16 * (int64_t)(FWD ? q >> 4 : nblk - 1 - (q >> 4)) + (q & 15);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int m = 2 * wave + u;
+      const float *src = m < 8 ? Lb + (FWD ? 16 * m * ld + 16 * kt : 16 * kt * ld + 16 * m) : xb + (8 * kt + m - 8) * 256;
+      stage_tile(src, stage[q % NS][m]);
+    }
+  };
+  float *Rw = R + ((size_t)b * ld + row0 + 32 * wr + r) * kHeadDim + 64 * wc + 4 * g;
+  f32x4 o[2][4], acc[2][4];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      o[i][j] = *reinterpret_cast<const f32x4 *>(Rw + (size_t)(16 * i) * kHeadDim + 16 * j);
+      acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+  for (int q = 0; q < NS - 1; ++q) issue(q);
+  for (int q = 0; q < stages; ++q) {   // uniform over the launch
+    // stage q has landed, the younger ones may be in flight; after the barrier every
+    // wave's has, and stage q - 1, which is refilled next, has been read
+    if (q + NS - 2 < stages) wait_vmcnt<2 * (NS - 2)>();
+    else wait_vmcnt<0>();
+    wait_lgkmcnt0();
+    lds_barrier();
+    if (q + NS - 1 < stages) issue(q + NS - 1);
+    f32x4 l[2], x[4];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const float *t = stage[q % NS][2 * wr + i];
+      l[i] = FWD ? tile_rows(t, lane) : tile_cols(t, lane);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) x[j] = tile_rows(stage[q % NS][8 + 4 * wc + j], lane);
+    trsm_mac(acc, l, x);
+    asm volatile("" ::: "memory");   // the reads stay above the next wait
+    if ((q & 15) == 15) {   // a block is complete
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[i][j][e] -= acc[i][j][e];
+          acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) *reinterpret_cast<f32x4 *>(Rw + (size_t)(16 * i) * kHeadDim + 16 * j) = o[i][j];
+}
+
+// k_trsm_diag's sums, 32 columns per workgroup and four workgroups per pair: R_K's
+// columns are staged in LDS at once, and wave w streams the tiles of D of row tiles
+// w, 7 - w, 8 + w and 15 - w, 18 pairs of k tiles in all for every wave, straight
+// into its fragments, three pairs ahead.  No barrier but the one after R.
+template <bool FWD>
+__global__ void __launch_bounds__(256, 4) k_trsm_diag_left(const void *__restrict__ lsplit, int64_t ld, int K,
+                                                           const float *__restrict__ R, float *__restrict__ X,
+                                                           float *__restrict__ xt, const int32_t *__restrict__ info) {
+  __shared__ __attribute__((aligned(1024))) float sR[16][2][256];   // [k tile][column tile], cols order
+  const int64_t tile = xcd_remap(blockIdx.x, gridDim.x);
+  const int b = (int)(tile >> 2), cg = (int)(tile & 3);
+  if (info[b] != 0) return;   // uniform over the workgroup
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t K0 = (int64_t)K * 256;
+  const DiagInv D = diag_inv(lsplit, ld, b, K0);
+  const float *Rb = R + ((size_t)b * ld + K0) * kHeadDim + 32 * cg + stage_cols(lane, kHeadDim);
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    const int kt = 4 * wave + (u >> 1), j = u & 1;
+    stage_tile(Rb + (size_t)(16 * kt) * kHeadDim + 16 * j, sR[kt][j]);
+  }
+  // the wave's row tile i and its pairs of k tiles: up to the diagonal tile, or from it
+  auto row_tile = [&](int i) { return (i & 1 ? 8 * (i >> 1) + 7 - wave : 8 * (i >> 1) + wave); };
+  auto first_pair = [&](int i) { return FWD ? 0 : row_tile(i) >> 1; };
+  auto last_pair = [&](int i) { return FWD ? row_tile(i) >> 1 : 7; };
+  auto load_d = [&](int rt, int kt) {   // a tile past the range reads the diagonal one
+    const int k = FWD ? min(kt, rt) : max(kt, rt);
+    f32x4 d;
+    if constexpr (FWD) {
+      d = *reinterpret_cast<const f32x4 *>(D.at(16 * rt + r, 16 * k + 4 * g));
+    } else {
+      const float *dp = D.at(16 * k + 4 * g, 16 * rt) + r;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) d[e] = dp[(size_t)e * D.ldf];
+    }
+    return d;
+  };
+  f32x4 d[3][2];
+  int li = 0, lp = first_pair(0);   // the next pair to load
+  auto load_next = [&](f32x4 (&to)[2]) {
+    const int rt = row_tile(li);
+    to[0] = load_d(rt, 2 * lp);
+    to[1] = load_d(rt, 2 * lp + 1);
+    if (lp < last_pair(li)) ++lp;
+    else if (li < 3) lp = first_pair(++li);   // past the last pair: that one again
+  };
+#pragma unroll
+  for (int u = 0; u < 3; ++u) load_next(d[u]);
+  wait_vmcnt<0>();
+  __syncthreads();
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  f32x4 s[2][2] = {{zero, zero}, {zero, zero}};   // [kt & 1][column tile]
+  int i = 0, kp = first_pair(0);
+  for (int f = 0; f < 18; f += 3) {
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {
+      const int rt = row_tile(i);
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const int kt = 2 * kp + p;
+        if (FWD ? kt > rt : kt < rt) continue;   // uniform over the wave
+        const f32x4 v0 = tile_cols(sR[kt][0], lane), v1 = tile_cols(sR[kt][1], lane);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          s[p][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(d[u][p][e], v0[e], s[p][0], 0, 0, 0);
+          s[p][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(d[u][p][e], v1[e], s[p][1], 0, 0, 0);
+        }
+      }
+      load_next(d[u]);
+      if (kp < last_pair(i)) {
+        ++kp;
+      } else {   // the row tile is complete
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          trsm_put(X, xt, ld, b, K, rt, 2 * cg + j, lane, s[0][j], s[1][j]);
+          s[0][j] = s[1][j] = zero;
+        }
+        if (i < 3) kp = first_pair(++i);
+      }
+    }
+  }
 }
 
 __global__ void __launch_bounds__(256) k_add_copy(float *__restrict__ x, const float *__restrict__ dx, int64_t n_per,
@@ -1607,121 +1824,6 @@ __global__ void __launch_bounds__(256) k_values_out(const float *__restrict__ Xp
   const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (e >= (int64_t)t * kHeadDim) return;
   Cv[(size_t)b * t * kHeadDim + e] = info[b] != 0 ? NAN : Xp[(size_t)b * tp * kHeadDim + e];
-}
-
-// The same solves left-looking, one workgroup per pair (8 waves = 2 row tiles x 4
-// column tiles of 32), 64-row blocks.  For block kb the update  acc = sum_p L_kb,p X_p
-// (forward) or  sum_p L_p,kb^T X_p  (backward) is an MFMA product with the L tile and
-// the X tile staged in LDS; then X_kb = D (R_kb - acc) with D = L_kb,kb^-1 or its
-// transpose.  L is read once and R and X once each, where the right-looking form
-// rewrites R for every block; but its time is that of one pair on one CU.
-constexpr int kTrsmRB = 64, kTrsmSLD = kTrsmRB + 1, kTrsmSXD = kHeadDim + 1;
-constexpr size_t kTrsmLds = (size_t)2 * (kTrsmRB * kTrsmSLD + kTrsmRB * kTrsmSXD) * sizeof(float);
-
-template <bool FWD>
-__global__ void __launch_bounds__(512) k_trsm_mfma(const float *__restrict__ Gw, int64_t ld,
-                                                   const float *__restrict__ dinv, int t,
-                                                   const float *__restrict__ R, float *__restrict__ X,
-                                                   const int32_t *__restrict__ info) {
-  constexpr int RB = kTrsmRB, SLD = kTrsmSLD, SXD = kTrsmSXD;
-  extern __shared__ float trsm_smem[];
-  auto sL = [&](int bf) { return trsm_smem + bf * RB * SLD; };
-  auto sX = [&](int bf) { return trsm_smem + 2 * RB * SLD + bf * RB * SXD; };
-  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (info[b] != 0) return;
-  const int wr = wave >> 2, wc = wave & 3, h = lane >> 5, col = lane & 31;
-  const float *L = Gw + (size_t)b * ld * ld;
-  const float *Rb = R + (size_t)b * ld * kHeadDim;
-  float *Xb = X + (size_t)b * ld * kHeadDim;
-  const int nb = (t + RB - 1) / RB;   // the blocks past t are padding: X is zero there
-  const float *Db = dinv + (size_t)b * (ld / RB) * RB * RB;
-  for (int64_t e = (int64_t)nb * RB * kHeadDim + 4 * tid; e < ld * kHeadDim; e += 4 * 512)
-    *reinterpret_cast<f32x4 *>(Xb + e) = f32x4{0.f, 0.f, 0.f, 0.f};
-  f32x4 rl[2], rx[4];
-  // tile (i, k) of the operand: forward L[r0+i][p0+k], backward L[p0+k][r0+i]
-  auto fetch = [&](int r0, int p0) {
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const int e = tid + 512 * c, i = e / 16, k4 = (e % 16) * 4;
-      rl[c] = FWD ? *reinterpret_cast<const f32x4 *>(L + (size_t)(r0 + i) * ld + p0 + k4)
-                  : *reinterpret_cast<const f32x4 *>(L + (size_t)(p0 + i) * ld + r0 + k4);
-    }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int e = tid + 512 * c, i = e / 32, k4 = (e % 32) * 4;
-      rx[c] = *reinterpret_cast<const f32x4 *>(Xb + (size_t)(p0 + i) * kHeadDim + k4);
-    }
-  };
-  auto stash = [&](int bf) {
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const int e = tid + 512 * c, i = e / 16, k4 = (e % 16) * 4;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (FWD) sL(bf)[i * SLD + k4 + q] = rl[c][q];
-        else sL(bf)[(k4 + q) * SLD + i] = rl[c][q];
-      }
-    }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int e = tid + 512 * c, i = e / 32, k4 = (e % 32) * 4;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) sX(bf)[i * SXD + k4 + q] = rx[c][q];
-    }
-  };
-  for (int step = 0; step < nb; ++step) {
-    const int kb = FWD ? step : nb - 1 - step;
-    const int r0 = kb * RB;
-    f32x16 acc = zero16();
-    const int pb0 = FWD ? 0 : kb + 1, pb1 = FWD ? kb : nb;
-    int bf = 0;
-    if (pb0 < pb1) {
-      __syncthreads();
-      fetch(r0, pb0 * RB);
-      stash(0);
-      __syncthreads();
-    }
-    for (int pb = pb0; pb < pb1; ++pb) {
-      const bool more = pb + 1 < pb1;
-      if (more) fetch(r0, (pb + 1) * RB);
-#pragma unroll 8
-      for (int ks = 0; ks < RB / 2; ++ks)
-        acc = Mfma<float>::mma(sL(bf)[(32 * wr + col) * SLD + 2 * ks + h],
-                               sX(bf)[(2 * ks + h) * SXD + 32 * wc + col], acc);
-      if (more) stash(bf ^ 1);
-      __syncthreads();
-      bf ^= 1;
-    }
-    __syncthreads();
-    // right-hand side minus update into sX(0); D into sL(0) (row r = output row)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int r = 32 * wr + acc_row(v, lane), c = 32 * wc + col;
-      sX(0)[r * SXD + c] = Rb[(size_t)(r0 + r) * kHeadDim + c] - acc[v];
-    }
-    const float *Dk = Db + (size_t)kb * RB * RB;
-    for (int e = tid; e < RB * RB / 4; e += 512) {
-      const int i = e / 16, k4 = (e % 16) * 4;
-      const f32x4 v = *reinterpret_cast<const f32x4 *>(Dk + i * RB + k4);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (FWD) sL(0)[i * SLD + k4 + q] = v[q];
-        else sL(0)[(k4 + q) * SLD + i] = v[q];
-      }
-    }
-    __syncthreads();
-    f32x16 out = zero16();
-#pragma unroll 8
-    for (int ks = 0; ks < RB / 2; ++ks)
-      out = Mfma<float>::mma(sL(0)[(32 * wr + col) * SLD + 2 * ks + h], sX(0)[(2 * ks + h) * SXD + 32 * wc + col],
-                             out);
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int r = 32 * wr + acc_row(v, lane), c = 32 * wc + col;
-      Xb[(size_t)(r0 + r) * kHeadDim + c] = out[v];
-    }
-    __threadfence_block();
-  }
 }
 
 // --------------------------------------------------------------- exact NNLS (bias_mode 1)
@@ -2227,14 +2329,24 @@ hipError_t launch_transpose128(int dtype, const float *in, int B, int rows, int6
 }
 
 // L X = R (fwd) or L^T X = R for 128 right-hand sides; R is overwritten, xt is
-// scratch [B][256][128].  The update takes 64 columns per workgroup while that
-// leaves CUs idle, else all 128, which reads L once instead of twice.
+// scratch [B][ld][128].  From kTrsmLeftPairs pairs on left-looking (the figures above).
+// Right-looking updates take 64 columns per workgroup while that leaves CUs idle, else
+// all 128, which reads L once instead of twice.
+constexpr int kTrsmLeftPairs = 65;
 template <bool FWD>
 static hipError_t trsm(const float *Gw, const void *lsplit, int B, int64_t ld, float *R, float *X, float *xt,
                        const int32_t *info, hipStream_t s) {
   const int nblk = (int)(ld / 256);
+  const bool many = B >= kTrsmLeftPairs;
   for (int st = 0; st < nblk; ++st) {
     const int K = FWD ? st : nblk - 1 - st;
+    if (many) {
+      if (st > 0)
+        hipLaunchKernelGGL(k_trsm_left<FWD>, dim3(256 / kTrsmLeftRows * (unsigned)B), dim3(512), 0, s, Gw, ld, K, R,
+                           xt, info);
+      hipLaunchKernelGGL(k_trsm_diag_left<FWD>, dim3(4 * (unsigned)B), dim3(256), 0, s, lsplit, ld, K, R, X, xt, info);
+      continue;
+    }
     hipLaunchKernelGGL(k_trsm_diag<FWD>, dim3(32, B), dim3(256), 0, s, lsplit, ld, K, R, X, xt, info);
     const int chunks = 4 * (nblk - 1 - st);
     if (chunks == 0) break;
@@ -2246,27 +2358,8 @@ static hipError_t trsm(const float *Gw, const void *lsplit, int B, int64_t ld, f
   return hipGetLastError();
 }
 
-// Pairs of a call above which its solves take a workgroup per pair, for each 256 pairs
-// that share the CUs: its time is that of one pair and rises slowly with the pairs, the
-// right-looking form's is in proportion to them.  Four solves and the refinement's
-// products, right-looking and left-looking: t = 819, 128 pairs 2.1 and 1.6 ms; t = 1638,
-// 96 pairs 4.1 and 4.9, 128: 5.4 and 5.3, 256: 10.2 and 6.9, 288: 11.5 and 11.3, 384:
-// 15.2 and 12.3; t = 3277, 128 pairs 16.2 and 19.2, 160: 20.1 and 20.6, 192: 23.9 and
-// 22.1, 256: 31.7 and 25.3 ms.
-static bool trsm_per_pair(int B, int t) { return B > (t <= 2048 ? 120 : 160) * ((B + 255) / 256); }
-
-hipError_t launch_trsm(bool fwd, const float *Gw, const float *dinv, const void *lsplit, int B, int t, int64_t ld,
-                       float *R, float *X, float *xt, const int32_t *info, hipStream_t s) {
-  if (trsm_per_pair(B, t)) {
-    const void *kern = fwd ? (const void *)k_trsm_mfma<true> : (const void *)k_trsm_mfma<false>;
-    const hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTrsmLds);
-    if (e != hipSuccess) return e;
-    if (fwd)
-      hipLaunchKernelGGL(k_trsm_mfma<true>, dim3(1, B), dim3(512), kTrsmLds, s, Gw, ld, dinv, t, R, X, info);
-    else
-      hipLaunchKernelGGL(k_trsm_mfma<false>, dim3(1, B), dim3(512), kTrsmLds, s, Gw, ld, dinv, t, R, X, info);
-    return hipGetLastError();
-  }
+hipError_t launch_trsm(bool fwd, const float *Gw, const void *lsplit, int B, int64_t ld, float *R, float *X, float *xt,
+                       const int32_t *info, hipStream_t s) {
   return fwd ? trsm<true>(Gw, lsplit, B, ld, R, X, xt, info, s) : trsm<false>(Gw, lsplit, B, ld, R, X, xt, info, s);
 }
 

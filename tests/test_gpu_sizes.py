@@ -101,6 +101,26 @@ def test_value_fit_sizes(B, n, t, dtype):
         assert err <= 1e-4, (b, err)
 
 
+def chunked(call, B, chunks):
+    """call(params) once whole and in chunks of pairs: the same bits."""
+    whole = [x.clone() for x in call(pair_chunk=0)]
+    for c in chunks:
+        assert c < B
+        for x, y in zip(whole, call(pair_chunk=c)):
+            assert torch.equal(x, y), c
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,n,t", [(130, 200, 65), (70, 900, 600), (66, 1100, 1025)])
+def test_value_fit_chunks(B, n, t, dtype):
+    """Chunks on both sides of the rules for many pairs: the 128-column solves, the small
+    tiles of the contractions and of the factorisation."""
+    print(f"value fit chunks {dtype} B={B} n={n} t={t}", flush=True)
+    Q, Ck, Y = randn(31, B, n, 128, dtype=DT[dtype]), randn(32, B, t, 128), randn(33, B, n, 128)
+    beta = 0.5 * randn(34, B, t)
+    chunked(lambda **kw: A().fit_values(Q, Ck, beta, Y, A().default_params(**kw), scale=S128, T=4 * t), B, (1, 33, 65))
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("T", [1, 63, 64, 65, 129, 1000])
 def test_rowstats_sizes(T, dtype):
