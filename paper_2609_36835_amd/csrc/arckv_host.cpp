@@ -44,13 +44,13 @@ hipError_t launch_profiles(int dtype, const void *Q, const void *K, const float 
                            int t, void *Et, float *phi, int B, int T, int n, int64_t Tp, int64_t np_, float scale,
                            hipStream_t s);
 hipError_t launch_phic(int dtype, const void *Q, const void *Ckp, const float *z, void *PhiT, float *LT,
-                       const float *m, double *h, double *hpart, int B, int t, int n, int64_t tp, int64_t np_,
+                       const float *m, double *h, double *hpart, int B, int all, int t, int n, int64_t tp, int64_t np_,
                        float scale, hipStream_t s);
 hipError_t launch_zmax(const float *z, int B, int n, float *zmax, hipStream_t s);
 hipError_t launch_pair_norms(int dtype, const void *Q, const void *K, const int32_t *anchors, int P, int n, int T,
                              int t, void *pn, const AssignLists &L, hipStream_t s);
 hipError_t launch_anchor_profiles(int dtype, const void *Q, const void *K, const int32_t *anchors,
-                                  const float *zmerge, int P, int n, int T, int t, int64_t tp, int64_t np_,
+                                  const float *zmerge, int P, int all, int n, int T, int t, int64_t tp, int64_t np_,
                                   float scale, float *Ua, double *anorm, double *npart, int64_t npart_blocks, void *U,
                                   hipStream_t s);
 hipError_t launch_assign_finalize(int dtype, const void *K, const uint64_t *part1, const uint64_t *part2,
@@ -461,7 +461,7 @@ static arckv_status run_merge_chunk(const Ctx &c, int b0, int P, const void *K, 
                                      d.np_, c.scale, stream));
   STAGE(ST_ANCHOR_PROF, launch_pair_norms(d.dtype, Qc, Kc, anc, P, d.n, d.T, d.t, pn, L, stream));
   // part1, which the contraction fills later, holds the parts of the anchors' norms
-  STAGE(ST_ANCHOR_PROF, launch_anchor_profiles(d.dtype, Qc, Kc, anc, zm, P, d.n, d.T, d.t, d.tp, d.np_, c.scale, Ua,
+  STAGE(ST_ANCHOR_PROF, launch_anchor_profiles(d.dtype, Qc, Kc, anc, zm, P, d.B, d.n, d.T, d.t, d.tp, d.np_, c.scale, Ua,
                                                anorm, reinterpret_cast<double *>(part1), d.MT * d.Tp / d.tp, U,
                                                stream));
   STAGE(ST_ASSIGN, launch_assign_gemm(d.dtype, U, Et, part1, part2, part3, P, d.t, d.tp, Tc, d.Tp, d.np_, stream));
@@ -514,7 +514,7 @@ static arckv_status run_fit_bias_chunk(const Ctx &c, int b0, int P, const void *
   if (launch_nonfinite(fc, P, bad, stream) != hipSuccess) return ARCKV_ERR_HIP;
   // Phi_C^T (split planes), the logits L^T, and h = Phi_C^T m in one pass
   // (the solve's five vectors w, y, x, res and sw, not in use yet, hold its parts)
-  STAGE(ST_PHIC, launch_phic(d.dtype, Qc, c.chunk<char>(c.pl.Ckp), zc, PhiT, LT, mc, h, w, P, d.t, d.n, d.tp, d.np_,
+  STAGE(ST_PHIC, launch_phic(d.dtype, Qc, c.chunk<char>(c.pl.Ckp), zc, PhiT, LT, mc, h, w, P, d.B, d.t, d.n, d.tp, d.np_,
                              c.scale, stream));
   STAGE(ST_GRAM_G, launch_gram(d.dtype, PhiT, Gw, Gc, P, d.tp, d.np_, stream));
   STAGE(ST_CHOL_G, launch_cholesky(Gw, Gc, P, d.t, d.tp, fp.delta_beta, fp.max_escalations, st, dinv,
@@ -831,7 +831,7 @@ arckv_status arckv_fit_values(const arckv_problem *prob, const void *K, const vo
     // logits of the compact keys (the exp-part is unused here; z only shifts it)
     const char *Qc = (const char *)Q_ref + (size_t)b0 * d.n * kHeadDimH * c.in_esz();
     STAGE(ST_PHIC, launch_phic(d.dtype, Qc, c.chunk<char>(c.pl.Ckp), nullptr, c.chunk<char>(c.pl.PhiT),
-                               c.chunk<float>(c.pl.LT), nullptr, nullptr, nullptr, Pc, d.t, d.n, d.tp, d.np_, c.scale,
+                               c.chunk<float>(c.pl.LT), nullptr, nullptr, nullptr, Pc, d.B, d.t, d.n, d.tp, d.np_, c.scale,
                                stream));
     FitState st = fit_state(c, c.pl.st_a, c.pl.info_a, b0);
     CHECK(run_fit_values_chunk(c, b0, Pc, Y, C_k, beta, *p, C_v, st));

@@ -1201,17 +1201,18 @@ hipError_t launch_pair_norms(int dtype, const void *Q, const void *K, const int3
 }
 
 // npart: scratch for npart_blocks [P][tp] blocks of doubles (at least one).
-// While the 128-anchor groups are fewer than kAnchorGroups workgroups (four per
-// CU), each one's query sweep is cut into up to eight ranges: 8 pairs with
-// n = 4096, t = 819 took 155 us whole, 36 us in ranges; n = 3000, t = 1500: 130
-// and 44 us.
+// While the 128-anchor groups of the call's `all` pairs are fewer than kAnchorGroups
+// workgroups (four per CU), each one's query sweep is cut into up to eight ranges:
+// 8 pairs with n = 4096, t = 819 took 155 us whole, 36 us in ranges; n = 3000, t =
+// 1500: 130 and 44 us.  The pairs of the call, not the P of this chunk: the ranges
+// group the norms' sums, and a pair's result must not depend on its chunk.
 constexpr int kAnchorGroups = 1024;
 hipError_t launch_anchor_profiles(int dtype, const void *Q, const void *K, const int32_t *anchors,
-                                  const float *zmerge, int P, int n, int T, int t, int64_t tp, int64_t np_,
+                                  const float *zmerge, int P, int all, int n, int T, int t, int64_t tp, int64_t np_,
                                   float scale, float *Ua, double *anorm, double *npart, int64_t npart_blocks, void *U,
                                   hipStream_t s) {
   if (dtype == ARCKV_BF16) {
-    const int64_t groups = (int64_t)((t + 127) / 128) * P, tiles = np_ / 64;
+    const int64_t groups = (int64_t)((t + 127) / 128) * all, tiles = np_ / 64;
     int64_t ranges = kAnchorGroups / groups;
     for (int64_t lim : {(int64_t)8, npart_blocks, tiles}) ranges = ranges < lim ? ranges : lim;
     if (ranges < 1) ranges = 1;

@@ -505,16 +505,17 @@ hipError_t launch_profiles(int dtype, const void *Q, const void *K, const float 
 // Ckp: padded compact keys [B][planes][tp][128]; Phi^T [B][planes][tp][np]; L^T [B][tp][np].
 // With m and h given, also h_r = sum_i Phi[i][r] m_i (float64) [B][tp]; hpart
 // holds kPhicRanges - 1 more [B][tp] blocks of scratch for it.
-// While the 128-row tiles fill less than half of the chip's 512 places (two
-// workgroups per CU), the query sweep of each is cut into up to kPhicRanges
-// ranges with a workgroup each: 230 -> 99 us at 8 pairs, t = 1638, n = 4096 and 234
-// -> 67 us at t = 819.
+// While the 128-row tiles of the call's `all` pairs fill less than half of the chip's
+// 512 places (two workgroups per CU), the query sweep of each is cut into up to
+// kPhicRanges ranges with a workgroup each: 230 -> 99 us at 8 pairs, t = 1638, n = 4096
+// and 234 -> 67 us at t = 819.  The pairs of the call, not the B of this chunk: the
+// ranges group h's sum, and a pair's result must not depend on its chunk.
 constexpr int kPhicRanges = 6;
 hipError_t launch_phic(int dtype, const void *Q, const void *Ckp, const float *z, void *PhiT, float *LT,
-                       const float *m, double *h, double *hpart, int B, int t, int n, int64_t tp, int64_t np_,
+                       const float *m, double *h, double *hpart, int B, int all, int t, int n, int64_t tp, int64_t np_,
                        float scale, hipStream_t s) {
   if (h && (!m || !hpart)) return hipErrorInvalidValue;   // h = Phi_C^T m needs m and the scratch
-  const int64_t groups = tp / 128 * B, tiles = np_ / 64;
+  const int64_t groups = tp / 128 * all, tiles = np_ / 64;
   int64_t ranges = 512 / groups;
   ranges = ranges < 1 ? 1 : ranges > kPhicRanges ? kPhicRanges : ranges;
   if (ranges > tiles) ranges = tiles;

@@ -121,6 +121,29 @@ def test_value_fit_chunks(B, n, t, dtype):
     chunked(lambda **kw: A().fit_values(Q, Ck, beta, Y, A().default_params(**kw), scale=S128, T=4 * t), B, (1, 33, 65))
 
 
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("B,n,t", [(130, 520, 500), (66, 300, 250)])
+def test_mass_fit_chunks(B, n, t, mode):
+    """Unrefined weights of nearly square systems show a rounding of h = Phi_C^T m, whose
+    sum over the queries is cut into ranges."""
+    print(f"mass fit chunks B={B} n={n} t={t} mode={mode}", flush=True)
+    Q, Ck = randn(35, B, n, 128), randn(36, B, t, 128)
+    z, m = torch.full((B, n), 2.0, device="cuda"), t * torch.rand(B, n, device="cuda")
+    chunked(lambda **kw: A().fit_bias(Q, Ck, z, m, A().default_params(refine_steps=0, bias_mode=mode, **kw), scale=S128,
+                                      T=4 * t), B, (1, 10, 60))
+
+
+def test_merge_chunks():
+    """The anchors' norms are cut into query ranges by the pairs of the call, not of the chunk."""
+    print("merge chunks", flush=True)
+    B, T, n, t = 70, 1500, 700, 200
+    K, V, Q = randn(37, B, T, 128, dtype=torch.bfloat16), randn(38, B, T, 128, dtype=torch.bfloat16), \
+        randn(39, B, n, 128, dtype=torch.bfloat16)
+    W1, b1, w2, b2 = randn(40, B, 64, 256, dtype=torch.bfloat16) / 16, randn(41, B, 64), randn(42, B, 64) / 8, randn(43, B)
+    chunked(lambda **kw: A().compact(K, V, Q, W1, b1, w2, b2, t / T, scale=S128, params=A().default_params(**kw)), B,
+            (1, 12, 64))
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("T", [1, 63, 64, 65, 129, 1000])
 def test_rowstats_sizes(T, dtype):
