@@ -794,6 +794,20 @@ __global__ void __launch_bounds__(256) k_refine_plan(AssignLists L, int cap_c) {
   if (tid == 0) goff[G] = carry;
 }
 
+// The largest similarity of N consecutive lanes and its anchor, equal ones to the lower r.
+template <int N>
+__device__ __forceinline__ void best_of(double &sim, int &r) {
+#pragma unroll
+  for (int w = N / 2; w >= 1; w >>= 1) {
+    const double os = __shfl_xor(sim, w, 64);
+    const int orr = __shfl_xor(r, w, 64);
+    if (os > sim || (os == sim && orr < r)) {
+      sim = os;
+      r = orr;
+    }
+  }
+}
+
 // Pass C decision, one wave per queued key, once every chunk of its
 // candidates has its similarity: the best one (equal ones to the lower r)
 // becomes the key's anchor for now, the candidates within the bound of it
@@ -832,15 +846,7 @@ __global__ void __launch_bounds__(256) k_assign_decide(const E *__restrict__ K, 
         br = r;
       }
     }
-#pragma unroll
-    for (int w = 32; w >= 1; w >>= 1) {
-      const double ov = __shfl_xor(bs, w, 64);
-      const int orr = __shfl_xor(br, w, 64);
-      if (ov > bs || (ov == bs && orr < br)) {
-        bs = ov;
-        br = orr;
-      }
-    }
+    best_of<64>(bs, br);
     if (br == 0x7FFFFFFF) {   // no comparable similarity (non-finite input): the first candidate stands
       if (lane == 0) kappa[(size_t)b * T + j] = pool[o];
       continue;
@@ -928,23 +934,31 @@ __global__ void __launch_bounds__(256) k_exact_plan(AssignLists L) {
   }
 }
 
-// Decisions, one thread per entry: the largest similarity of its candidates
-// and, for the first entry of a split key, of all the key's entries (which are
-// consecutive, as are their candidates), equal ones to the lower r.
+// Decisions, 16 lanes per entry: the largest similarity of its candidates and, for
+// the first entry of a split key, of all the key's entries (which are consecutive, as
+// are their candidates), equal ones to the lower r.  One thread per entry read up to
+// t candidates of a tied key in turn, each 2 nspl float64 values: 50 us at 64 pairs of
+// T = 32768 (a wave per entry 21, 16 lanes 8).
 __global__ void __launch_bounds__(256) k_exact_merge(int T, int32_t *__restrict__ kappa, AssignLists L) {
-  const int b = blockIdx.y;
+  const int b = blockIdx.y, lane = threadIdx.x & 15;
   const int D = L.dcnt[b];
   const double *part = L.psim + (size_t)b * 2 * L.nspl * L.pcap;
   const int32_t *pool = L.pool + (size_t)b * L.pcap;
-  for (int di = blockIdx.x * 256 + threadIdx.x; di < D; di += gridDim.x * 256) {
+  for (int di = blockIdx.x * 16 + (threadIdx.x >> 4); di < D; di += gridDim.x * 16) {   // uniform over the 16 lanes
     const size_t q = (size_t)b * L.dcap + di;
     const int o = L.doff[q], grp = L.dgrp[q];
     if (o < 0 || (grp >= 0 && grp != di)) continue;   // decided in its item, or with the key's first entry
     int m = L.dn[q];
-    for (int e = 1; grp >= 0 && e < L.dgn[q]; ++e) m += L.dn[q + e];
+    if (grp >= 0) {
+      int more = 0;
+      for (int e = 1 + lane; e < L.dgn[q]; e += 16) more += L.dn[q + e];
+#pragma unroll
+      for (int w = 8; w >= 1; w >>= 1) more += __shfl_xor(more, w, 64);
+      m += more;
+    }
     double bs = -1.0;
     int br = 0x7FFFFFFF;
-    for (int c = 0; c < m; ++c) {
+    for (int c = lane; c < m; c += 16) {
       double dot = 0.0, nn = 0.0;
       for (int sp = 0; sp < L.nspl; ++sp) {
         dot += part[(size_t)(2 * sp) * L.pcap + o + c];
@@ -957,7 +971,8 @@ __global__ void __launch_bounds__(256) k_exact_merge(int T, int32_t *__restrict_
         br = r;
       }
     }
-    if (br != 0x7FFFFFFF) kappa[(size_t)b * T + L.dkey[q]] = br;
+    best_of<16>(bs, br);
+    if (lane == 0 && br != 0x7FFFFFFF) kappa[(size_t)b * T + L.dkey[q]] = br;
   }
 }
 
