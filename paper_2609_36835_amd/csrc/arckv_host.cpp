@@ -222,7 +222,7 @@ constexpr int64_t kPassDEntryBytes = 24;   // dkey, dn, doff, dgrp, dgn, ditem
 static int64_t pool_per_key(const Dims &d) {
   // 64 bytes per key are left for the entries' rounding and alignment
   const int64_t room = d.np_ * d.esz - kPassDEntryBytes - 64;
-  const int64_t k = room * kPassDSplit / ((4 + 16 * query_ranges(d.n)) * kPassDSplit + kPassDEntryBytes);
+  const int64_t k = room * kPassDSplit / ((4 + 16 * query_ranges(d.n, d.T)) * kPassDSplit + kPassDEntryBytes);
   const int64_t cap = ((1ll << 30) / d.Tp) > 8 ? (1ll << 30) / d.Tp : 8;   // pool offsets are int32
   const int64_t m = k < kPoolPerKeyMax ? k : kPoolPerKeyMax;
   return m < cap ? m : cap;
@@ -283,7 +283,7 @@ static Plan make_plan(const Dims &d, int64_t P) {
     Bump l;
     l.off = pl.Et;
     const int64_t ppk = pool_per_key(d), dcap = pass_d_capacity(d.Tp, ppk);
-    pl.psim = l.take(P * 2 * query_ranges(d.n) * ppk * d.Tp * 8);
+    pl.psim = l.take(P * 2 * query_ranges(d.n, d.T) * ppk * d.Tp * 8);
     pl.pool = l.take(P * ppk * d.Tp * 4);
     pl.dkey = l.take(P * dcap * 4);
     pl.dn = l.take(P * dcap * 4);
@@ -445,7 +445,7 @@ static arckv_status run_merge_chunk(const Ctx &c, int b0, int P, const void *K, 
   const int64_t ppk = pool_per_key(d);
   AssignLists L{c.chunk<int32_t>(c.pl.fcnt), c.chunk<int32_t>(c.pl.fkey),  c.chunk<int32_t>(c.pl.foff),
                 c.chunk<int32_t>(c.pl.fn),   c.chunk<int32_t>(c.pl.pcnt),  c.chunk<int32_t>(c.pl.pool),
-                c.chunk<double>(c.pl.psim),  ppk * d.Tp, query_ranges(d.n), c.chunk<int32_t>(c.pl.dcnt),
+                c.chunk<double>(c.pl.psim),  ppk * d.Tp, query_ranges(d.n, d.T), c.chunk<int32_t>(c.pl.dcnt),
                 c.chunk<int32_t>(c.pl.dkey), c.chunk<int32_t>(c.pl.dn),    c.chunk<int32_t>(c.pl.doff),
                 c.pers<int32_t>(c.pl.astats) + (size_t)b0 * kAssignStats, d.Tp,
                 c.chunk<int32_t>(c.pl.goff), d.Tp / 64 + 2,

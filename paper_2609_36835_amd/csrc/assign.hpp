@@ -21,13 +21,16 @@ inline int64_t pass_d_capacity(int64_t Tp, int64_t pool_per_key) {
 }
 
 // Query ranges into which a work item of the refine and of the float64 pass is
-// cut, by the number n of queries alone, so that decisions do not depend on how
-// many pairs run together: a call over few pairs has a few dozen items, each a
-// serial sweep over its queries, on 256 CUs.  More than four cost more in setting
-// the items up than they gain.
-inline int query_ranges(int64_t n) {
+// cut, by the numbers of queries and keys, so that decisions do not depend on how
+// many pairs run together: a pair of few keys has a few dozen items, each a serial
+// sweep over its queries, on 256 CUs.  More than four cost more in setting the items
+// up than they gain, and a pair of many keys has items enough for two: both passes with
+// 1, 2 and 4 ranges, in us: T = 8192, n = 4096, 8 pairs 455, 264, 177, 128 pairs 3349, 2182,
+// 1732; T = 15001, n = 3000, 8 pairs 379, 236, 239; T = 16384, n = 2100, 32 pairs 732, 676,
+// 762; T = 32768, n = 4096, 16 pairs 1016, 1034, 1104, 64 pairs 3723, 3660, 3922.
+inline int query_ranges(int64_t n, int64_t T) {
   const int64_t tiles = (n + 127) / 128;
-  return tiles >= 16 ? 4 : tiles >= 2 ? 2 : 1;
+  return tiles >= 16 && T < 16384 ? 4 : tiles >= 2 ? 2 : 1;
 }
 
 struct AssignLists {
