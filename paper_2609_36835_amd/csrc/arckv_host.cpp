@@ -247,7 +247,7 @@ struct Plan {
   int64_t Et, U, Ua, anorm, pn, part1, part2, part3, fcnt, fkey, foff, fn, pcnt, pool, psim, dcnt, dkey, dn,
       doff, goff, dgrp, dgn, ditem;   // merge phase
   int64_t offsets, cursor, perm;
-  int64_t PhiT, LT, Gw, Gc, dinv, lsplit, h, w, y, x, res, sw, rprev, div, u, YT, Bm, X, R, Y2, XT, Pm, UT;  // fit phase
+  int64_t PhiT, LT, Gw, Gc, dinv, lsplit, h, hpart, w, y, x, res, sw, rprev, div, u, YT, Bm, X, R, Y2, XT, Pm, UT;  // fit phase
   int64_t nF, nidx, nbidx, npos, nnf, nnb, nstate, nred, ny, nrhs, ndx;   // exact NNLS (bias_mode 1)
   int64_t chunk_bytes;
 };
@@ -318,11 +318,17 @@ static Plan make_plan(const Dims &d, int64_t P) {
   pl.dinv = f.take(P * d.tp * 64 * 4);   // one 64 x 64 inverse per diagonal block
   pl.lsplit = f.take(P * (4 * d.tp * d.tp + 8 * d.tp));   // L's fp16 hi / lo planes, row shifts and scales
   pl.h = f.take(P * d.tp * 8);
-  pl.w = f.take(P * d.tp * 8);   // w .. sw are contiguous (tp is a multiple of 256): launch_phic's hpart
-  pl.y = f.take(P * d.tp * 8);
-  pl.x = f.take(P * d.tp * 8);
-  pl.res = f.take(P * d.tp * 8);
-  pl.sw = f.take(P * d.tp * 8);
+  {
+    // the parts of h, in the place of the solve's vectors, which are formed after it
+    Bump v = f;
+    pl.hpart = v.take(P * (kPhicRanges - 1) * d.tp * 8);
+    pl.w = f.take(P * d.tp * 8);
+    pl.y = f.take(P * d.tp * 8);
+    pl.x = f.take(P * d.tp * 8);
+    pl.res = f.take(P * d.tp * 8);
+    pl.sw = f.take(P * d.tp * 8);
+    if (v.off > f.off) f.off = v.off;
+  }
   pl.rprev = f.take(P * 8);
   pl.div = f.take(P * 4);
   pl.u = f.take(P * d.np_ * 8);
@@ -513,9 +519,8 @@ static arckv_status run_fit_bias_chunk(const Ctx &c, int b0, int P, const void *
                        {d.n, d.n, (int64_t)d.t * kHeadDimH, (int64_t)d.n * kHeadDimH}};
   if (launch_nonfinite(fc, P, bad, stream) != hipSuccess) return ARCKV_ERR_HIP;
   // Phi_C^T (split planes), the logits L^T, and h = Phi_C^T m in one pass
-  // (the solve's five vectors w, y, x, res and sw, not in use yet, hold its parts)
-  STAGE(ST_PHIC, launch_phic(d.dtype, Qc, c.chunk<char>(c.pl.Ckp), zc, PhiT, LT, mc, h, w, P, d.B, d.t, d.n, d.tp, d.np_,
-                             c.scale, stream));
+  STAGE(ST_PHIC, launch_phic(d.dtype, Qc, c.chunk<char>(c.pl.Ckp), zc, PhiT, LT, mc, h,
+                             c.chunk<double>(c.pl.hpart), P, d.B, d.t, d.n, d.tp, d.np_, c.scale, stream));
   STAGE(ST_GRAM_G, launch_gram(d.dtype, PhiT, Gw, Gc, P, d.tp, d.np_, stream));
   STAGE(ST_CHOL_G, launch_cholesky(Gw, Gc, P, d.t, d.tp, fp.delta_beta, fp.max_escalations, st, dinv,
                                    c.chunk<char>(c.pl.lsplit), bad, c.pers<int32_t>(c.pl.cnt), stream));

@@ -19,6 +19,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "fit.hpp"
 
 namespace arckv {
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
@@ -510,7 +511,6 @@ hipError_t launch_profiles(int dtype, const void *Q, const void *K, const float 
 // kPhicRanges ranges with a workgroup each: 230 -> 99 us at 8 pairs, t = 1638, n = 4096
 // and 234 -> 67 us at t = 819.  The pairs of the call, not the B of this chunk: the
 // ranges group h's sum, and a pair's result must not depend on its chunk.
-constexpr int kPhicRanges = 6;
 hipError_t launch_phic(int dtype, const void *Q, const void *Ckp, const float *z, void *PhiT, float *LT,
                        const float *m, double *h, double *hpart, int B, int all, int t, int n, int64_t tp, int64_t np_,
                        float scale, hipStream_t s) {

@@ -6,6 +6,10 @@
 
 namespace arckv {
 
+// Most query ranges of one Phi_C sweep (launch_phic); range z > 0 leaves its part
+// of h in block z - 1 of kPhicRanges - 1 [P][tp] blocks of doubles.
+constexpr int kPhicRanges = 6;
+
 struct FitState {
   double *trace;   // [P] tr(M) of the unregularised Gram
   float *lam;      // [P] ridge lam = delta tr(M) / t
