@@ -208,8 +208,8 @@ static Dims make_dims(const arckv_problem *p, int t) {
 // dead once the contraction has left its partials, so the pool is sized by
 // what E^T leaves free: per key 4 bytes for each candidate and 16 for each query
 // range of its similarity, and kPassDEntryBytes for each entry of the float64
-// pass (one per key and one per kPassDSplit candidates); 11 to 19 for the smallest
-// E^T row (256 fp16 values), 117 for 4096 queries.
+// pass (one per key and one per kPassDSplit candidates); 20 for up to 128 queries and 11
+// for up to 256 (an E^T row of 256 fp16 values), 117 for 4096 (220 from 16,384 keys on).
 // A key whose list does not fit is decided in float64 over all t anchors,
 // n t float64 exponentials where a pooled candidate costs n fp32 products: on
 // 32K-token caches a pair with 320K-750K candidates (10-23 per key; keys whose
@@ -304,7 +304,7 @@ static Plan make_plan(const Dims &d, int64_t P) {
   pl.fkey = m.take(P * d.Tp * 4);
   pl.foff = m.take(P * d.Tp * 4);
   pl.fn = m.take(P * d.Tp * 4);
-  pl.pcnt = m.take(P * 4);
+  pl.pcnt = m.take(P * 8);
   pl.dcnt = m.take(P * 4);
   pl.goff = m.take(P * (d.Tp / 64 + 2) * 4);   // pass C work items per group of 64 queued keys
   pl.offsets = m.take(P * (int64_t)(d.t + 1) * 4);
@@ -450,7 +450,7 @@ static arckv_status run_merge_chunk(const Ctx &c, int b0, int P, const void *K, 
   uint32_t *part3 = c.chunk<uint32_t>(c.pl.part3);
   const int64_t ppk = pool_per_key(d);
   AssignLists L{c.chunk<int32_t>(c.pl.fcnt), c.chunk<int32_t>(c.pl.fkey),  c.chunk<int32_t>(c.pl.foff),
-                c.chunk<int32_t>(c.pl.fn),   c.chunk<int32_t>(c.pl.pcnt),  c.chunk<int32_t>(c.pl.pool),
+                c.chunk<int32_t>(c.pl.fn),   c.chunk<unsigned long long>(c.pl.pcnt),  c.chunk<int32_t>(c.pl.pool),
                 c.chunk<double>(c.pl.psim),  ppk * d.Tp, query_ranges(d.n, d.T), c.chunk<int32_t>(c.pl.dcnt),
                 c.chunk<int32_t>(c.pl.dkey), c.chunk<int32_t>(c.pl.dn),    c.chunk<int32_t>(c.pl.doff),
                 c.pers<int32_t>(c.pl.astats) + (size_t)b0 * kAssignStats, d.Tp,

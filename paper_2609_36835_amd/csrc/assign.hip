@@ -61,7 +61,8 @@ __global__ void __launch_bounds__(256) k_assign_clear(AssignLists L, AssignPair 
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i < P * kAssignStats) L.stats[i] = 0;
   if (i >= P) return;
-  L.fcnt[i] = L.dcnt[i] = L.pcnt[i] = 0;
+  L.fcnt[i] = L.dcnt[i] = 0;
+  L.pcnt[i] = 0;
   pn[i] = {0.0, 0.0};
 }
 
@@ -433,8 +434,8 @@ __global__ void __launch_bounds__(256) k_assign_finalize(
     atomicAdd(&st[4], 1);
     return;
   }
-  const int off = atomicAdd(&L.pcnt[b], nc);
-  if (off < 0 || (int64_t)off + nc > L.pcap) {   // pool full (near-equal profiles): decided in float64 over all t anchors
+  const int64_t off = (int64_t)atomicAdd(&L.pcnt[b], (unsigned long long)nc);
+  if (off + nc > L.pcap) {   // pool full (near-equal profiles): decided in float64 over all t anchors
     push_d(L, b, j, -1, t);
     return;
   }
@@ -464,7 +465,7 @@ __global__ void __launch_bounds__(256) k_assign_finalize(
   }
   const int slot = atomicAdd(&L.fcnt[b], 1);
   L.fkey[(size_t)b * L.cap + slot] = j;
-  L.foff[(size_t)b * L.cap + slot] = off;
+  L.foff[(size_t)b * L.cap + slot] = (int32_t)off;
   L.fn[(size_t)b * L.cap + slot] = nc;
   atomicAdd(&st[6], 1);
 }

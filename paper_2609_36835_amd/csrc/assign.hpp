@@ -38,7 +38,9 @@ struct AssignLists {
   int32_t *fkey;    // [P][cap]
   int32_t *foff;    // [P][cap] first candidate of the queued key in the pool
   int32_t *fn;      // [P][cap] its number of candidates
-  int32_t *pcnt;    // [P] candidates in the pool
+  // [P] candidates of all queued keys, in the pool or not: up to T t, which 32 bits do not hold (a count
+  // that wraps gives out places in the pool twice)
+  unsigned long long *pcnt;
   int32_t *pool;    // [P][pcap] candidate anchors, contiguous per queued key
   double *psim;     // [P][2 nspl][pcap]: the first nspl arrays the parts of their refined similarities, then
                     // (float64 pass) array 2 i the part i of a candidate's dot product, 2 i + 1 of its

@@ -39,6 +39,8 @@ static void check(int B, int T, int n, int t, int dtype, int64_t P) {
 }
 
 int main() {
+  // the pool's counter adds up to T t candidates
+  static_assert(sizeof(*AssignLists{}.pcnt) == 8, "a pool counter of 64 bits");
   for (int dtype : {ARCKV_F32, ARCKV_BF16})
     for (int B : {1, 3, 256})
       for (int T : {1, 255, 256, 257, 15001, 16383, 16384, 131072})

@@ -384,7 +384,7 @@ def test_merge_many_groups(t):
 def test_every_anchor_a_candidate(n, pooled):
     """One key 30 logits above the rest leaves every other profile below fp16's
     range, so each of the 640 keys lists all 60 anchors.  The pool that E^T's
-    rows of 1024 values leave room for (52 candidates per cached key) holds
+    rows of 1024 values leave room for (53 candidates per cached key) holds
     them; that of 256-value rows (11) overflows, and its last keys go to the
     float64 pass with all anchors.  Either way kappa is the float64 argmax."""
     rng = np.random.default_rng(n)
