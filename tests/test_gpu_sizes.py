@@ -1,5 +1,5 @@
 """Sizes at the borders of the kernels' splits: tile edges, remainders, and both
-sides of every rule that picks a variant by size, against float64."""
+sides of the rules that pick a variant by size, against float64."""
 import math
 import os
 
@@ -30,11 +30,12 @@ def randn(seed, *shape, dtype=torch.float32):
 # (pairs, queries, compact keys, shift of z).  256-wide Cholesky panels with 64-wide
 # blocks and 16-wide tile columns; 48 pairs of t = 1024 are past the rules for few
 # strips (256 of 64 rows), few block inverses (64), and few rows of the
-# 128-column solves (512 chunks).  A shift of 40 puts every pivot below 2^-96.
+# 128-column solves (512 chunks); 100 pairs of t = 1025 update three chunks of 64
+# per workgroup in the one-rhs solves.  A shift of 40 puts every pivot below 2^-96.
 FITS = [(1, 16, 1, 0), (2, 63, 15, 0), (2, 200, 64, 0), (2, 300, 65, 0), (1, 600, 255, 0), (1, 600, 256, 0),
-        (2, 700, 257, 0), (1, 1100, 513, 0), (1, 300, 100, 40), (48, 1300, 1024, 0)]
-# pairs for most of the CUs, whose 128-column solves take a workgroup per pair
-MANY_PAIRS = [(256, 40, 1), (122, 300, 65), (254, 700, 257), (162, 2200, 2049)]
+        (2, 700, 257, 0), (1, 1100, 513, 0), (1, 300, 100, 40), (48, 1300, 1024, 0), (100, 1300, 1025, 0)]
+# pairs whose 128-column solves are left-looking, and one short of them
+MANY_PAIRS = [(256, 40, 1), (122, 300, 65), (254, 700, 257), (162, 2200, 2049), (64, 700, 513), (66, 700, 513)]
 
 
 @pytest.mark.parametrize("B,n,t,shift", FITS)
@@ -144,15 +145,17 @@ def test_merge_chunks():
             (1, 12, 64))
 
 
+@pytest.mark.parametrize("B,n", [(2, 130), (33, 130), (129, 130)])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("T", [1, 63, 64, 65, 129, 1000])
-def test_rowstats_sizes(T, dtype):
-    """Few query tiles: key halves inside a workgroup, for fp32 a wave per key range.  z and m to
-    fp32 sums; bf16 inputs round the probabilities of Y's product to 2^-8."""
-    print(f"rowstats {dtype} T={T}", flush=True)
-    K, V, Q = (randn(i, 2, k, 128, dtype=DT[dtype]) for i, k in ((7, T), (8, T), (9, 130)))
+def test_rowstats_sizes(T, dtype, B, n):
+    """Up to 128 tiles of 256 queries (fp32: 64 of 128): key halves inside a workgroup (a wave per
+    key range); more: whole tiles of keys per wave.  z and m to fp32 sums; bf16 inputs round the
+    probabilities of Y's product to 2^-8."""
+    print(f"rowstats {dtype} T={T} B={B} n={n}", flush=True)
+    K, V, Q = (randn(i, B, k, 128, dtype=DT[dtype]) for i, k in ((7, T), (8, T), (9, n)))
     z, m, Y = A().rowstats(K, V, Q, scale=S128)
-    for b in range(2):
+    for b in (0, B - 1):
         L = Q[b].double() @ K[b].double().T * S128
         zr = L.amax(dim=1)
         E = torch.exp(L - zr[:, None])
@@ -176,9 +179,9 @@ def test_rowstats_alone_and_in_a_batch(T):
         assert float((Y1[0] - Y[b]).abs().max()) <= 2 * T * 2.0 ** -24 * float(V[b].float().abs().max())
 
 
-@pytest.mark.parametrize("B,T", [(1, 1), (1, 15), (2, 17), (3, 1000), (9, 4099)])
+@pytest.mark.parametrize("B,T", [(1, 1), (1, 15), (2, 17), (3, 1000), (9, 4099), (9, 8001)])
 def test_score_f32_sizes(B, T):
-    """16 or 64 tokens per step.  The bound is that of sums of 256 and 64 fp32 terms in any order."""
+    """16 or 64 tokens per step, one step or four.  The bound is that of sums of 256 and 64 fp32 terms in any order."""
     print(f"score f32 B={B} T={T}", flush=True)
     K, V = randn(10, B, T, 128), randn(11, B, T, 128)
     W1, b1, w2, b2 = randn(12, B, 64, 256) / 16, randn(13, B, 64), randn(14, B, 64) / 8, randn(15, B)
@@ -202,7 +205,7 @@ def test_group_sort_segments(t):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("n", [1, 127, 128, 129, 257, 520])
+@pytest.mark.parametrize("n", [1, 127, 128, 129, 257, 520, 1921, 2600])
 def test_assignment_query_ranges(n, dtype):
     """Anchors in close pairs, so that keys are refined and decided in float64, over query
     counts on both sides of the ranges' tiles; kappa is the float64 argmax."""
