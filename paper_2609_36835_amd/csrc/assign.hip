@@ -361,8 +361,6 @@ __device__ inline CandA cand_a(const uint64_t *p1, const uint64_t *p2, const uin
   return c;
 }
 
-// Queue key j for the float64 pass with its k surviving candidates, which sit
-// at pool offset off (off = -1, k = t: every anchor).
 // Queue key j for the float64 pass with k candidates starting at pool offset
 // off (off < 0: all t anchors).  More than kPassDSplit pool candidates are
 // split over consecutive entries; the capacity dcap covers the largest split

@@ -295,9 +295,10 @@ __device__ __forceinline__ void sub_column(float (&a)[16], float col, float l) {
   for (int q = C + 1; q < 16; ++q) a[q] = fmaf(-v[q], l, a[q]);
 }
 
-// sqrt(p) and its reciprocal from the hardware's estimate r0 of 1 / sqrt(p) with one
-// residual each: the root correctly rounded, the reciprocal too but for a root
-// whose significand is all ones.  TINY scales p below 2^-96 by 2^64 first, whose
+// sqrt(p) and the root's reciprocal from the hardware's estimate r0 of 1 / sqrt(p) with
+// one residual each, both faithful: over every significand of two binades and every
+// r0 within one unit of the rounded value (2^24 x 3), the root is one unit off the
+// correctly rounded one 5 times and the reciprocal 64 times, never more.  TINY scales p below 2^-96 by 2^64 first, whose
 // residuals would underflow.
 constexpr float kTinyPivot = 0x1p-96f;
 template <bool TINY>
@@ -634,13 +635,13 @@ __global__ void __launch_bounds__(4 * ROWS) __attribute__((amdgpu_waves_per_eu(1
 k_chol_strip16(float *__restrict__ Gw, int64_t ld, int K0, const float *__restrict__ dinv, f16 *__restrict__ Lp,
                const int32_t *__restrict__ shift, const int32_t *__restrict__ info) {
   extern __shared__ __attribute__((aligned(16))) char strip16_smem[];
-  f16 *sTh = reinterpret_cast<f16 *>(strip16_smem);        // [128][256] hi
-  f16 *sTl = sTh + ROWS * 256;                         // [128][256] lo
-  f16 *sBh = sTl + ROWS * 256;                         // [64][64] hi
+  f16 *sTh = reinterpret_cast<f16 *>(strip16_smem);        // [ROWS][256] hi
+  f16 *sTl = sTh + ROWS * 256;                               // [ROWS][256] lo
+  f16 *sBh = sTl + ROWS * 256;                               // [64][64] hi
   f16 *sBl = sBh + kNB * kNB;                                // [64][64] lo
   float *sBs = reinterpret_cast<float *>(sBl + kNB * kNB);   // [64] scales that take a product with B's rows to its units
-  int32_t *sSh = reinterpret_cast<int32_t *>(sBs + kNB);     // [128] row shifts of the strip
-  int32_t *sShC = sSh + ROWS;                          // [256] shifts of the panel's columns
+  int32_t *sSh = reinterpret_cast<int32_t *>(sBs + kNB);     // [ROWS] row shifts of the strip
+  int32_t *sShC = sSh + ROWS;                                // [256] shifts of the panel's columns
   constexpr int kThreads = 4 * ROWS, kB = kNB * kNB / 4 / kThreads;   // quads of B per thread
   const int b = blockIdx.y;
   if (info[b] != 0) return;   // uniform over the workgroup
@@ -734,7 +735,7 @@ k_chol_strip16(float *__restrict__ Gw, int64_t ld, int K0, const float *__restri
     }
     return acc;
   };
-  {  // the strip, 128 rows x 64 groups of 4, scaled by s_r s_c 2^-14 and split
+  {  // the strip, ROWS rows x 64 groups of 4, scaled by s_r s_c 2^-14 and split
     f32x4 v[ROWS * 64 / kThreads];
 #pragma unroll
     for (int i = 0; i < ROWS * 64 / kThreads; ++i) {
@@ -759,7 +760,7 @@ k_chol_strip16(float *__restrict__ Gw, int64_t ld, int K0, const float *__restri
   }
   split_b(0);
   // block kb (final after its panel step): planes and L = (hi + lo) / s_r of
-  // all 128 rows, four columns per thread-group, issued while later steps run
+  // all ROWS rows, four columns per thread-group, issued while later steps run
   f16 *hib = Lp + (size_t)b * 2 * ld * ld, *lob = hib + (size_t)ld * ld;
   auto write_block = [&](int kb) {
 #pragma unroll
@@ -1937,8 +1938,6 @@ __global__ void k_nnls_zero(int32_t *__restrict__ red) {
   if (threadIdx.x < 2) red[threadIdx.x] = 0;
 }
 
-// Free list of every unsettled pair: idx[k] = the k-th free key (ascending),
-// pos[r] = its slot or -1, nf = |F|; red = {max nf, unsettled pairs}.
 // Free and bound lists of every unsettled pair: idx[k] = the k-th free key,
 // bidx[k] = the k-th bound key (both ascending), pos[r] = the free slot of r or
 // -1; nf = |F|, nb = t - |F|; red = {max nf, unsettled pairs}.

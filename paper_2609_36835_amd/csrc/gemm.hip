@@ -66,10 +66,9 @@ hipError_t launch_gram(int dtype, const void *X, float *G, float *Gc, int P, int
 }
 
 // out[r][c] = sum_k A[r][k] B[c][k] (minus lam X) for 128 columns c, split bf16
-// operands.  With fewer 256-row tiles than CUs, 64-row tiles and four stages:
-// a tile's 128 slabs of 32 are then bound by their loads, which three slabs in
-// flight cover (223 -> 89 us at 8 pairs, t =
-// 1638, n = 4096).
+// operands.  With fewer 256-row tiles than CUs, 64-row tiles and four stages: a
+// tile's 128 slabs of 32 are then bound by their loads, which three slabs in flight
+// cover (223 -> 89 us at 8 pairs, t = 1638, n = 4096).
 static hipError_t gemm_cols128(const BigShape &g, const bf16 *A, const bf16 *B, float *out, const float *X,
                                const float *lam, hipStream_t s) {
   const int64_t pair = (int64_t)g.M * kHeadDim;

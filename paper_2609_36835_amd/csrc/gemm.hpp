@@ -298,9 +298,9 @@ struct EpiValueResid {
 };
 
 // SMALL: 64 x 64 tiles where 128 x 128 ones are fewer than a quarter of the CUs
-// (fp32 at t = 102, n = 256: Phi_C, Gram and residual
-// products 29.4, 24.6 and 24.0 us with 128 x 128 tiles, 11.3, 9.6 and 10.1 us so); not for EpiArgmax, whose partials are
-// per 128 rows.
+// (fp32 at t = 102, n = 256: Phi_C, Gram and residual products 29.4, 24.6 and 24.0
+// us with 128 x 128 tiles, 11.3, 9.6 and 10.1 us so); not for EpiArgmax, whose
+// partials are per 128 rows.
 template <typename T, int NA, int NB, bool SMALL = false, class Epi>
 hipError_t launch_gemm(const GemmShape &g, const T *A, const T *B, const Epi &epi, hipStream_t s) {
   const int64_t tiles = gemm_tiles(g, kGBM);
