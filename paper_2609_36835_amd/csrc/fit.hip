@@ -2115,16 +2115,17 @@ hipError_t launch_cholesky_factor(float *Gw, const float *Gc, int B, int t, int6
   hipLaunchKernelGGL(k_chol_scales, dim3((unsigned)((ld + 255) / 256), B), dim3(256), 0, s, Gw, ld, shift, sinv,
                      st.info);
   auto strip = [&](auto kern, int rows, int K0) {
-    const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             (int)strip16_lds(rows));
-    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)((ld - K0 - kOuter) / rows), B), dim3(4 * rows), strip16_lds(rows), s, Gw,
                        ld, K0, dinv, Lp, shift, st.info);
     return hipGetLastError();
   };
-  const hipError_t ed = hipFuncSetAttribute((const void *)k_chol_diag256, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                            (int)kDiag256Lds);
-  if (ed != hipSuccess) return ed;
+  auto set_lds = [](const void *kern, size_t bytes) {
+    return hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  };
+  hipError_t ea = set_lds((const void *)k_chol_diag256, kDiag256Lds);
+  if (ea == hipSuccess) ea = set_lds((const void *)k_chol_strip16<64>, strip16_lds(64));
+  if (ea == hipSuccess) ea = set_lds((const void *)k_chol_strip16<128>, strip16_lds(128));
+  if (ea != hipSuccess) return ea;
   for (int K0 = 0; K0 < ld; K0 += kOuter) {
     const int K1 = (int)(K0 + kOuter < ld ? K0 + kOuter : ld);
     if (K0 > 0) {
