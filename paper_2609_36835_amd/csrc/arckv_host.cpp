@@ -39,7 +39,7 @@ static int64_t chunked_count(int64_t T, int64_t t, int64_t chunk_len) {
   return total;
 }
 hipError_t launch_rowstats(int dtype, const void *K, const void *V, const void *Q, float *z, float *m, float *Y,
-                           int B, int T, int n, float scale, hipStream_t s);
+                           int B, int all, int T, int n, float scale, hipStream_t s);
 hipError_t launch_profiles(int dtype, const void *Q, const void *K, const float *zmerge, const int32_t *anchors,
                            int t, void *Et, float *phi, int B, int T, int n, int64_t Tp, int64_t np_, float scale,
                            hipStream_t s);
@@ -718,7 +718,7 @@ arckv_status arckv_rowstats(const arckv_problem *prob, const void *K, const void
   CHECK(check_problem(prob));
   if (!K || !V || !Q_ref || !z || !m || !Y) return ARCKV_ERR_INVALID_ARG;
   if (!aligned(K, 16) || !aligned(V, 16) || !aligned(Q_ref, 16) || !aligned(Y, 16)) return ARCKV_ERR_INVALID_ARG;
-  STAGE(ST_ROWSTATS, launch_rowstats(prob->dtype, K, V, Q_ref, z, m, Y, prob->B, prob->T, prob->n,
+  STAGE(ST_ROWSTATS, launch_rowstats(prob->dtype, K, V, Q_ref, z, m, Y, prob->B, prob->B, prob->T, prob->n,
                                      eff_scale(prob), stream));
   return ARCKV_OK;
 }
@@ -771,7 +771,7 @@ static arckv_status fit_rowstats(const Ctx &c, const void *K, const void *V, con
   if (!K || !V || !aligned(K, 16) || !aligned(V, 16)) return ARCKV_ERR_INVALID_ARG;
   float *zw = c.pers<float>(c.pl.z), *mw = c.pers<float>(c.pl.m), *Yw = c.pers<float>(c.pl.Y);
   hipStream_t stream = c.stream;
-  STAGE(ST_ROWSTATS, launch_rowstats(c.d.dtype, K, V, Q_ref, zw, mw, Yw, c.d.B, c.d.T, c.d.n, c.scale, stream));
+  STAGE(ST_ROWSTATS, launch_rowstats(c.d.dtype, K, V, Q_ref, zw, mw, Yw, c.d.B, c.d.B, c.d.T, c.d.n, c.scale, stream));
   if (z) *z = zw;
   if (m) *m = mw;
   if (Y) *Y = Yw;
@@ -889,7 +889,7 @@ static arckv_status compact_impl(const arckv_problem *prob, const void *K, const
     STAGE(ST_SCORE, launch_score(d.dtype, K, V, ix->W1, ix->b1, ix->w2, ix->b2, c.pers<float>(c.pl.scores), d.B, d.T,
                                  stream));
   STAGE(ST_SELECT, launch_select_ex(scores, d.B, d.T, t_nominal, nullptr, p->select_chunk, t, anchors, stream));
-  STAGE(ST_ROWSTATS, launch_rowstats(d.dtype, K, V, Q_ref, z, m, Y, d.B, d.T, d.n, c.scale, stream));
+  STAGE(ST_ROWSTATS, launch_rowstats(d.dtype, K, V, Q_ref, z, m, Y, d.B, d.B, d.T, d.n, c.scale, stream));
   STAGE(ST_ZMAX, launch_zmax(z, d.B, d.n, zmax, stream));
   for (int b0 = 0; b0 < d.B; b0 += (int)P) {
     const int Pc = (int)(d.B - b0 < P ? d.B - b0 : P);
@@ -1060,7 +1060,8 @@ arckv_status arckv_score_dsa(const arckv_problem *prob, const void *K, const voi
         return ARCKV_ERR_HIP;
     }
     STAGE(ST_DSA_VALUE, launch_rowstats(ARCKV_BF16, w0 + pl.ka, w0 + pl.va, w0 + pl.qa, (float *)(w0 + pl.za),
-                                        (float *)(w0 + pl.ma), (float *)(w0 + pl.c), Pc, (int)T, (int)n, sa, stream));
+                                        (float *)(w0 + pl.ma), (float *)(w0 + pl.c), Pc, (int)B, (int)T, (int)n, sa,
+                                        stream));
     {
       StageScope _sc(ST_DSA_PROJ, stream);
       if (launch_dsa_proj(Kc, Vc, false, mat(ix->L_k, 1024 * 128), mat(ix->L_v, 1024 * 128), Pc, (int)T, 8, true,

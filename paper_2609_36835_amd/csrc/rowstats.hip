@@ -529,11 +529,13 @@ __global__ void __launch_bounds__(512, 1) k_rowstats_bf16(const bf16 *__restrict
   }
 }
 
+// `all`: the pairs of the whole call, of which these B may be a chunk.  The forms sum
+// in different orders, and a pair's result must not depend on its chunk.
 hipError_t launch_rowstats(int dtype, const void *K, const void *V, const void *Q, float *z, float *m, float *Y,
-                           int B, int T, int n, float scale, hipStream_t s) {
+                           int B, int all, int T, int n, float scale, hipStream_t s) {
   if (dtype == ARCKV_BF16) {
     const int qtiles = (n + kRsQ - 1) / kRsQ;
-    if ((int64_t)qtiles * B <= 128) {
+    if ((int64_t)qtiles * all <= 128) {
       const int qt2 = (n + kRsQ / 2 - 1) / (kRsQ / 2);
       hipLaunchKernelGGL(k_rowstats_bf16<2>, dim3((unsigned)(qt2 * B)), dim3(512), 0, s, (const bf16 *)K,
                          (const bf16 *)V, (const bf16 *)Q, z, m, Y, T, n, scale, qt2);
@@ -544,7 +546,7 @@ hipError_t launch_rowstats(int dtype, const void *K, const void *V, const void *
     return hipGetLastError();
   }
   dim3 grid((n + 127) / 128, B);
-  if ((int64_t)grid.x * B <= kRsFewF32) {
+  if ((int64_t)grid.x * all <= kRsFewF32) {
     hipLaunchKernelGGL(k_rowstats_f32_few, dim3((n + 15) / 16, B), dim3(512), 0, s, (const float *)K,
                        (const float *)V, (const float *)Q, z, m, Y, T, n, scale);
     return hipGetLastError();

@@ -134,6 +134,19 @@ def test_mass_fit_chunks(B, n, t, mode):
                                       T=4 * t), B, (1, 10, 60))
 
 
+def test_dsa_chunks():
+    """The value head's row statistics go by the pairs of the call, not of the chunk."""
+    print("dsa chunks", flush=True)
+    B, T, n, dx = 136, 200, 64, 256
+    bf = lambda i, *sh: randn(i, B, *sh, dtype=torch.bfloat16)
+    K, V, Q = bf(44, T, 128), bf(45, T, 128), bf(46, n, 128)
+    p = {k: bf(47 + i, 1024, 128) / 11 for i, k in enumerate(("L_q", "L_k", "L_c", "L_v"))}
+    p.update({k: bf(51 + i, 128, 128) / 11 for i, k in enumerate(("U_q", "U_k", "U_v"))})
+    p.update(L_x=bf(54, 8, dx) / 16, b_x=0.1 * randn(55, B, 8))
+    X = bf(56, n, dx)
+    chunked(lambda pair_chunk: [A().score_dsa(K, V, Q, X, p, n, pair_chunk=pair_chunk)], B, (8, 64))
+
+
 def test_merge_chunks():
     """The anchors' norms are cut into query ranges by the pairs of the call, not of the chunk."""
     print("merge chunks", flush=True)
