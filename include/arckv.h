@@ -117,7 +117,8 @@ typedef struct {
                           * tenfold, as after a failed pivot (a ridge small next to the
                           * float32 rounding of a rank-deficient Gram, t > n, makes the
                           * steps diverge). */
-  int32_t pair_chunk;    /* pairs processed together by arckv_compact (0 = all B); sizes the workspace */
+  int32_t pair_chunk;    /* pairs processed together by arckv_compact (0 = all B); sizes the workspace,
+                          * results do not depend on it */
   int32_t select_chunk;  /* 0 = global top-t (default).  L > 0: when T > 10,000, anchors are the union of
                           * each L-position chunk's local top-t_c (Appendix A.3), so arckv_compact keeps
                           * arckv_select_count(T, t, L) anchors; merge and fits stay global. */

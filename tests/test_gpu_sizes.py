@@ -122,6 +122,21 @@ def test_value_fit_chunks(B, n, t, dtype):
     chunked(lambda **kw: A().fit_values(Q, Ck, beta, Y, A().default_params(**kw), scale=S128, T=4 * t), B, (1, 33, 65))
 
 
+def test_value_fit_bad_pairs_among_many():
+    """Pairs with non-finite inputs in a left-looking call: NaN values, and the others' bits stay."""
+    print("value fit bad pairs", flush=True)
+    B, n, t = 70, 700, 513
+    Q, Ck, Y, beta = randn(57, B, n, 128), randn(58, B, t, 128), randn(59, B, n, 128), 0.5 * randn(60, B, t)
+    good = A().fit_values(Q, Ck, beta, Y, scale=S128, T=4 * t)[0]
+    bad = [0, 33, B - 1]
+    for b in bad:
+        Y[b, 7, 5] = math.nan
+    Cv, info, _ = A().fit_values(Q, Ck, beta, Y, scale=S128, T=4 * t)
+    rest = [b for b in range(B) if b not in bad]
+    assert torch.all(info[bad] == -1) and torch.all(torch.isnan(Cv[bad]))
+    assert torch.all(info[rest] == 0) and torch.equal(Cv[rest], good[rest])
+
+
 @pytest.mark.parametrize("mode", [0, 1])
 @pytest.mark.parametrize("B,n,t", [(130, 520, 500), (66, 300, 250)])
 def test_mass_fit_chunks(B, n, t, mode):
